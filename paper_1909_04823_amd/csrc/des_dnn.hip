@@ -7,199 +7,472 @@
 // forms the gradient of its own field columns (dY W_s^T, which is the upstream gradient of the
 // pooled embeddings) and of its own weight rows (V_s dY).
 //
-// This is the one dense contraction of the path, so it runs on the matrix cores: fp32 MFMA
-// (v_mfma_f32_32x32x2f32, fp32 accumulate), 128x128 output tile per workgroup, four waves in a
-// 2x2 arrangement of 64x64, 16-deep k tiles staged in LDS k-major so both operands are read with
-// conflict-free 32-lane rows, next tile prefetched into registers during the MFMAs.
+// This is the one dense contraction of the path, so it runs on the matrix cores.  128x128 output tile per workgroup (64x64
+// where that leaves CUs idle), four waves in a 2x2 arrangement of 64x64 (32x32).  Two kernels:
 //
-// One kernel serves the three products through operand strides and a sliced k range:
+// k_gemm_f32, the forward product: the fp32 matrix instruction (32x32x2, 64 cycles), 32 products deep per LDS tile, the next
+// tile in registers meanwhile.  Bound by the matrix pipe.  The sum of an output element is one chain in ascending k whatever
+// the tile, so results do not depend on the tile size.  It keeps the fp32 chain because a ReLU follows it: with the split
+// (223 against 271 us at 16384 x 3200 x 256) a unit within 1e-8 of zero changes sides in one of six training steps at 4096 x 256
+// units, and its gradient with it.  A shard's fields are walked as one range (a field of 20 columns costs no padding).
+//
+// k_gemm_split, the two gradient products: fp32 accuracy from the bf16 instruction (32x32x16, 32 cycles).  Every operand
+// element is cut into three bf16 parts, a = hi + mid + lo, each the rounded rest of what the parts before it left (the cut is
+// exact: 3 x 8 significant bits), and a product is six bf16 products accumulated in fp32:
+//   hi*hi + hi*mid + mid*hi + hi*lo + lo*hi + mid*mid        (what is left out is below 2^-26 of a*b)
+// so 16 products of depth take 6 x 32 instead of 8 x 64 cycles.  Bound by the matrix pipe and, nearly as long, the vector
+// instructions of the cut (5.5 per element, once per element and tile, on the way into LDS): two LDS buffers of 16 products, so
+// that a wave cuts the next tile between the matrix instructions of the current one, and two tiles under way in registers.
+// 65536 x 12800 x 256: g_pool 3.81 -> 2.60 ms (165 TFLOP/s), dW 3.65 -> 2.55 ms; a library's plain bf16 product of 8192^3 reaches
+// 1.1 PFLOP/s here, one sixth of which is 183.  16384 x 3200 x 256: 248 -> 179 us, 233 -> 163 us.  Error against 64 bits, 2-norm:
+// 2.4e-7 where the fp32 instruction has 2.9e-7 (16384 x 3200 x 256), 2.6e-7 and 3.1e-7 (5003 x 540 x 300).
+//
+// Products through operand strides and a sliced k range:
 //   forward   C_s[B,H]   = sum over the shard's fields of pool[:, f, :] x W[f*D:(f+1)*D, :]
 //   g_pool    C[B,F*D]   = dY x W^T
 //   dW        C_z[F*D,H] = pool[z-th slice of samples]^T x dY[slice]   (split over samples, summed after)
+#include <type_traits>
 #include "des_internal.h"
 
 namespace des {
 namespace {
 
-constexpr int BM = 128, BN = 128, BK = 16;
-constexpr int LDA = BM + 4, LDB = BN + 4;    // LDS row pitches (floats)
-constexpr int kFlushTiles = 8;               // 128 products per first-level run
+constexpr int kRun = 128;                    // products per first-level run of a two-level sum
 constexpr long long kTwoLevelDepth = 1024;
+constexpr int kMinSlice = 16;                // samples a slice of dW has at least; slices are multiples of it
+constexpr int kForwardGroup = 32;           // row tiles of the forward product whose shards are done together
+constexpr int kXcds = 8;                     // dies; consecutive workgroups are handed to them in turn
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 struct GemmArgs {
   const float *A, *B;
   float *C;
-  long long a_rs, a_cs, b_rs, b_cs;   // element strides: A(m,k) = A[m*a_rs + k*a_cs], B(k,n) = B[k*b_rs + n*b_cs]
+  // element (x, k) of an operand, x the row of A or the column of B: P[x*xs + kpos*ks]; one of xs, ks is 1
+  uint32_t a_xs, a_ks, b_xs, b_ks;
   int M, N;
   long long c_rs;                     // C(m,n) = C[slice*c_slice + m*c_rs + n]
   long long c_slice;
-  // k range of slice z: blocks [base, base + blk_len) for base = k_begin + z*k_shift, += blk_stride, below k_limit
-  long long k_begin, k_shift, blk_len, blk_stride, k_limit;
+  // Slice z sums over the positions kpos of the blocks [base, base + blk_len) for base = z*k_shift, += blk_stride,
+  // below k_limit, at most k_max positions; the blocks are walked as one range, so a k tile may span several of them.
+  uint32_t k_shift, k_limit, k_max, blk_stride, blk_len;
+  int tiles_m, tiles_n, slices, m_group;
 };
 
 __device__ inline float4 ld4g(const float *p) { return *reinterpret_cast<const float4 *>(p); }
 
-// Loads the part of a 128 x 16 operand tile this thread stages: two float4 (eight floats).
-// kKContig: the k index is the contiguous one in memory (float4 along k), else the m/n index is.
-template <bool kKContig>
-__device__ inline void load_tile(const float *__restrict__ P, long long rs, long long cs, int mn0, int MN,
-                                 long long k0, long long kend, float4 (&r)[2]) {
-  // whole tile inside the operand (the same answer for every thread): plain 16-byte loads, no per-element guards
-  if (mn0 + BM <= MN && k0 + BK <= kend) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int idx = threadIdx.x + i * kBlock;
-      r[i] = kKContig ? ld4g(P + (long long)(mn0 + idx / 4) * rs + k0 + (idx % 4) * 4)
-                      : ld4g(P + (k0 + idx / 32) * cs + mn0 + (idx % 32) * 4);
-    }
-    return;
-  }
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int idx = threadIdx.x + i * kBlock;
-    float v[4] = {0.f, 0.f, 0.f, 0.f};
-    if (kKContig) {
-      const int mn = mn0 + idx / 4;
-      const long long k = k0 + (idx % 4) * 4;
-      if (mn < MN) {
-        const float *p = P + (long long)mn * rs + k;            // cs == 1
-        if (k + 3 < kend) { const float4 t = ld4g(p); v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w; }
-        else { for (int j = 0; j < 4; ++j) if (k + j < kend) v[j] = p[j]; }
-      }
-    } else {
-      const long long k = k0 + idx / 32;
-      const int mn = mn0 + (idx % 32) * 4;
-      if (k < kend) {
-        const float *p = P + k * cs + mn;                         // rs == 1
-        if (mn + 3 < MN) { const float4 t = ld4g(p); v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w; }
-        else { for (int j = 0; j < 4; ++j) if (mn + j < MN) v[j] = p[j]; }
-      }
-    }
-    r[i] = make_float4(v[0], v[1], v[2], v[3]);
-  }
+// Byte offset of 16-byte chunk `chunk` (eight bf16 along k) of row `row` in one plane of rows of 32 bytes.  The chunks of a row
+// change places from one group of four rows to the next and the rows of a group turn every second group, so that the operand
+// reads (one chunk of consecutive rows) and both kinds of stores spread over the banks.
+__device__ inline int lds_offset(int row, int chunk) {
+  return (((row & ~3) | ((row + (row >> 3)) & 3)) << 5) | ((chunk ^ ((row >> 2) & 1)) << 4);
 }
 
-// Writes the staged registers into the k-major LDS tile T[BK][LD].
-template <bool kKContig, int LD>
-__device__ inline void store_tile(float *__restrict__ T, const float4 (&r)[2]) {
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int idx = threadIdx.x + i * kBlock;
-    if (kKContig) {
-      const int mn = idx / 4, k = (idx % 4) * 4;
-      T[(k + 0) * LD + mn] = r[i].x;
-      T[(k + 1) * LD + mn] = r[i].y;
-      T[(k + 2) * LD + mn] = r[i].z;
-      T[(k + 3) * LD + mn] = r[i].w;
-    } else {
-      const int k = idx / 32, mn = (idx % 32) * 4;
-      *reinterpret_cast<float4 *>(&T[k * LD + mn]) = r[i];
-    }
-  }
+// What the cut cannot represent: `rest` collects in its low half bits of the last rest below bf16's smallest denormal
+// (operands under 2^-110); `nan` turns NaN at an infinity or NaN (or overflows at operands above 2^80).
+struct Odd {
+  uint32_t rest;
+  float nan;
+};
+
+// Two floats to their three bf16 parts, packed pairwise.
+__device__ inline void split2(float a0, float a1, uint32_t &hi, uint32_t &mid, uint32_t &lo, Odd &odd) {
+  hi = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){a0, a1}, bf16x2));
+  const float r0 = a0 - __uint_as_float(hi << 16), r1 = a1 - __uint_as_float(hi & 0xFFFF0000u);
+  mid = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){r0, r1}, bf16x2));
+  const float l0 = r0 - __uint_as_float(mid << 16), l1 = r1 - __uint_as_float(mid & 0xFFFF0000u);
+  lo = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){l0, l1}, bf16x2));
+  odd.rest |= __float_as_uint(l0) | __float_as_uint(l1);
+  odd.nan = __builtin_fmaf(l0, l1, odd.nan);
 }
 
-template <bool kAKContig, bool kBKContig, bool kTwoLevel>
-__global__ __launch_bounds__(kBlock) void k_gemm(const GemmArgs g) {
-  __shared__ __align__(16) float As[BK * LDA];
-  __shared__ __align__(16) float Bs[BK * LDB];
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  const int z = blockIdx.z;
-  // kTwoLevel (long contractions; the weight gradient sums over the whole batch): two-level fp32
-  // summation.  The matrix cores accumulate runs of kFlushTiles*BK products from zero and each run is
-  // then added into `total`, so small products are never added to a large running sum.  Short
-  // contractions keep the single accumulator and the registers that saves.
-  f32x16 acc[2][2], total[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) { acc[i][j][r] = 0.f; total[i][j][r] = 0.f; }
-  int run = 0;
+// The part of a T x BK operand tile that a thread stages, and its way there.
+// kKContig: k is contiguous in memory; BK/4 threads read a row's products side by side, each thread the same four products
+// of kUnits rows.  Else x is; a thread reads 4 rows x 4 products.
+// Rows past the operand's end repeat its last ones: they only reach outputs that are not stored.
+template <int T, int BK, bool kKContig>
+struct Operand {
+  static constexpr int kTotal = kKContig ? T * BK / 4 : T * BK / 16;    // units of the tile: float4s, 4x4 blocks
+  static constexpr int kUnits = kTotal > kBlock ? kTotal / kBlock : 1;  // per thread
+  static constexpr int kRowStep = T / kUnits;
+  static constexpr int kVecs = kKContig ? kUnits : 4;
+  static constexpr int kPitch = kKContig ? BK + 4 : T + 4;              // of the plain fp32 tile
+  static constexpr int kPlainFloats = (kKContig ? T : BK) * kPitch;
+  const float *row[kUnits];        // k contiguous: the unit's row; else the unit's four columns
+  uint32_t ks, last;               // stride of a position; last position that exists (of a float4 along k: its first)
+  uint32_t pos, in_blk;            // position of the thread's products, relative to the first block; offset inside the current one
+  int k_in, x0;
+  bool active;
 
-  const int lrow = lane & 31, lk = lane >> 5;     // MFMA operand: row/column within the 32-block, k within the pair
-  for (long long base = g.k_begin + (long long)z * g.k_shift; base < g.k_limit; base += g.blk_stride) {
-    const long long kend = min(base + g.blk_len, g.k_limit);
-    float4 ra[2], rb[2];
-    load_tile<kAKContig>(g.A, g.a_rs, g.a_cs, m0, g.M, base, kend, ra);
-    load_tile<kBKContig>(g.B, g.b_cs, g.b_rs, n0, g.N, base, kend, rb);   // for B the "row" index is n
-    for (long long k0 = base; k0 < kend; k0 += BK) {
-      __syncthreads();                              // previous tile fully consumed
-      store_tile<kAKContig, LDA>(As, ra);
-      store_tile<kBKContig, LDB>(Bs, rb);
-      __syncthreads();
-      if (k0 + BK < kend) {                         // prefetch the next tile while this one is multiplied
-        load_tile<kAKContig>(g.A, g.a_rs, g.a_cs, m0, g.M, k0 + BK, kend, ra);
-        load_tile<kBKContig>(g.B, g.b_cs, g.b_rs, n0, g.N, k0 + BK, kend, rb);
+  // `t`: which of the tile's units (threads past the last one stay idle).  klen > 0.
+  __device__ inline void start(const float *P, uint32_t xs, uint32_t ks_, int x_base, int X, int t, int klen, const GemmArgs &g) {
+    ks = ks_;
+    active = T == 128 || t < kTotal;               // the large tile keeps every thread busy
+    t %= kBlock;
+    if constexpr (kKContig) {
+      k_in = t % (BK / 4) * 4;
+      x0 = t / (BK / 4);
+#pragma unroll
+      for (int u = 0; u < kUnits; ++u) row[u] = P + (long long)min(x_base + x0 + u * kRowStep, X - 1) * xs;
+    } else {
+      constexpr int kPerWave = kWave / (BK / 4);   // a wave takes that many groups of four rows at all its products
+      k_in = t % kWave / kPerWave * 4;
+      x0 = (t / kWave * kPerWave + t % kPerWave) * 4;
+      row[0] = P + min(x_base + x0, X - 4);
+    }
+    const uint32_t k_last = klen - (kKContig ? 4 : 1);
+    last = k_last / g.blk_len * g.blk_stride + k_last % g.blk_len;
+    const uint32_t q = (uint32_t)k_in / g.blk_len;
+    in_blk = k_in - q * g.blk_len;
+    pos = q * g.blk_stride + in_blk;
+  }
+  // Requests the next tile into v and moves on by BK products = `whole` blocks and `rest`.  Whole float4s exist or do
+  // not: every extent that a float4 runs along is a multiple of four.  Past the last position it is read again (no
+  // branch around a load: the wait for it would be a wait for all of them); blank() then takes that out.
+  __device__ inline void load(float4 (&v)[kVecs], uint32_t whole, uint32_t rest, const GemmArgs &g) {
+    if (T == 128 || active) {
+#pragma unroll
+      for (int i = 0; i < kVecs; ++i) {
+        if constexpr (kKContig) v[i] = ld4g(row[i] + min(pos, last));
+        else v[i] = ld4g(row[0] + (unsigned long long)min(pos + i, last) * ks);
       }
-      // operands of step kk+2 are read from LDS before the MFMAs of step kk are issued
-      float a[2], b[2];
+    }
+    in_blk += rest;
+    pos += whole * g.blk_stride + rest;
+    if (in_blk >= g.blk_len) { in_blk -= g.blk_len; pos += g.blk_stride - g.blk_len; }
+  }
+  // zeros for the products of tile k0 that do not exist
+  __device__ inline void blank(float4 (&v)[kVecs], int k0, int klen) const {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) a[i] = As[lk * LDA + wm * 64 + i * 32 + lrow];
+    for (int i = 0; i < kVecs; ++i)
+      if (k0 + k_in + (kKContig ? 0 : i) >= klen) v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  // cuts the staged values into the three planes at `plane` (T rows each)
+  __device__ inline void store_split(const float4 (&v)[kVecs], char *plane, Odd &odd) const {
+    static_assert(BK == 16, "two chunks per row");
+    if (T != 128 && !active) return;
+    const float *f = reinterpret_cast<const float *>(v);
+    if constexpr (kKContig) {
 #pragma unroll
-      for (int j = 0; j < 2; ++j) b[j] = Bs[lk * LDB + wn * 64 + j * 32 + lrow];
+      for (int u = 0; u < kUnits; ++u) {
+        uint2 p[3];
+        split2(f[u * 4], f[u * 4 + 1], p[0].x, p[1].x, p[2].x, odd);
+        split2(f[u * 4 + 2], f[u * 4 + 3], p[0].y, p[1].y, p[2].y, odd);
+        const int at = lds_offset(x0 + u * kRowStep, k_in / 8) + (k_in & 4) * 2;
 #pragma unroll
-      for (int kk = 0; kk < BK; kk += 2) {
-        float an[2] = {0.f, 0.f}, bn[2] = {0.f, 0.f};
-        if (kk + 2 < BK) {
+        for (int q = 0; q < 3; ++q) *reinterpret_cast<uint2 *>(plane + q * (T * 32) + at) = p[q];
+      }
+    } else {
 #pragma unroll
-          for (int i = 0; i < 2; ++i) an[i] = As[(kk + 2 + lk) * LDA + wm * 64 + i * 32 + lrow];
+      for (int j = 0; j < 4; ++j) {                // transposed by picking registers
+        uint2 p[3];
+        split2(f[j], f[4 + j], p[0].x, p[1].x, p[2].x, odd);
+        split2(f[8 + j], f[12 + j], p[0].y, p[1].y, p[2].y, odd);
+        const int at = lds_offset(x0 + j, k_in / 8) + (k_in & 4) * 2;
 #pragma unroll
-          for (int j = 0; j < 2; ++j) bn[j] = Bs[(kk + 2 + lk) * LDB + wn * 64 + j * 32 + lrow];
+        for (int q = 0; q < 3; ++q) *reinterpret_cast<uint2 *>(plane + q * (T * 32) + at) = p[q];
+      }
+    }
+  }
+  // the staged values as they are, in memory order: rows along k, or along x
+  __device__ inline void store_plain(const float4 (&v)[kVecs], float *tile) const {
+    if (T != 128 && !active) return;
+    if constexpr (kKContig) {
+#pragma unroll
+      for (int u = 0; u < kUnits; ++u) *reinterpret_cast<float4 *>(tile + (x0 + u * kRowStep) * kPitch + k_in) = v[u];
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) *reinterpret_cast<float4 *>(tile + (k_in + i) * kPitch + x0) = v[i];
+    }
+  }
+  static __device__ inline float plain(const float *tile, int x, int k) {
+    return kKContig ? tile[x * kPitch + k] : tile[k * kPitch + x];
+  }
+};
+
+// One workgroup's place: output tile, slice and the slice's products.
+template <int T>
+struct Place {
+  int m0, n0, z, klen;
+  uint32_t first;                  // position of the slice's first product
+  bool ok;
+  __device__ inline explicit Place(const GemmArgs &g) {
+    // Every die takes a contiguous run of tiles.  They are numbered n first, then m inside a group of m_group tiles, then
+    // the slice, then the group: tiles that read the same rows of A follow each other, a slice's part of B is used by a
+    // whole group, and the slices of a group (in the forward product: the shards' columns of the same rows of A) are
+    // done together, before the next rows.
+    const uint32_t total = (uint32_t)g.tiles_m * g.tiles_n * g.slices, per_xcd = (total + kXcds - 1) / kXcds;
+    const uint32_t tile = blockIdx.x % kXcds * per_xcd + blockIdx.x / kXcds;
+    ok = tile < total;
+    const uint32_t per_group = (uint32_t)g.tiles_n * g.m_group * g.slices, group = tile / per_group;
+    const uint32_t in_group = min((uint32_t)g.m_group, g.tiles_m - group * g.m_group);
+    const uint32_t mz = (tile - group * per_group) / g.tiles_n;
+    n0 = (int)(tile - group * per_group - mz * g.tiles_n) * T;
+    z = (int)(mz / in_group);
+    m0 = (int)(group * g.m_group + mz % in_group) * T;
+    const unsigned long long at = (unsigned long long)z * g.k_shift;      // may lie past the end: a shard without a field
+    first = at < g.k_limit ? (uint32_t)at : g.k_limit;
+    const uint32_t avail = g.k_limit - first, blocks = avail / g.blk_stride, tail = avail - blocks * g.blk_stride;
+    klen = (int)min(blocks * g.blk_len + min(tail, g.blk_len), g.k_max);
+  }
+};
+
+// Sums of a wave: NB x NB blocks of 32x32.  kTwoLevel (long contractions; the weight gradient sums over the whole batch):
+// the matrix cores accumulate runs of kRun products from zero and each run is then added into `total`, so small
+// products are never added to a large running sum.  Short contractions keep the single accumulator and the registers
+// that saves.
+template <int NB, bool kTwoLevel>
+struct Sums {
+  f32x16 acc[NB][NB], total[NB][NB];
+  __device__ inline void clear() {
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { acc[i][j][r] = 0.f; total[i][j][r] = 0.f; }
+  }
+  __device__ inline void flush() {
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        total[i][j] += acc[i][j];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      }
+  }
+  // element r of a 32x32 block sits at row (r/4)*8 + (lane/32)*4 + r%4, column lane%32
+  __device__ inline void store(const GemmArgs &g, int z, int m_wave, int n_wave) {
+    const int lane = threadIdx.x & (kWave - 1);
+    float *C = g.C + (long long)z * g.c_slice;
+    if (kTwoLevel) flush();
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const int col = n_wave + j * 32 + (lane & 31);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int row = m_wave + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+          if (row < g.M && col < g.N) C[(long long)row * g.c_rs + col] = kTwoLevel ? total[i][j][r] : acc[i][j][r];
         }
-        __builtin_amdgcn_sched_barrier(0);       // keep the reads above the MFMAs: the scheduler would sink them to their use
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) { a[i] = an[i]; b[i] = bn[i]; }
       }
-      if (kTwoLevel && ++run == kFlushTiles) {
-        run = 0;
+  }
+};
+
+// The whole contraction of one tile with the fp32 instruction.
+constexpr int kPlainBK = 32;
+template <int T, bool kAKContig, bool kBKContig>
+constexpr int plain_floats() { return Operand<T, kPlainBK, kAKContig>::kPlainFloats + Operand<T, kPlainBK, kBKContig>::kPlainFloats; }
+
+template <int T, bool kAKContig, bool kBKContig, bool kTwoLevel>
+__device__ inline void multiply_f32(const GemmArgs &g, const Place<T> &at, float *lds, Sums<T / 64, kTwoLevel> &sums) {
+  constexpr int NB = T / 64, BK = kPlainBK;
+  using OpA = Operand<T, BK, kAKContig>;
+  using OpB = Operand<T, BK, kBKContig>;
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int xa = (wave >> 1) * (T / 2) + (lane & 31), xb = (wave & 1) * (T / 2) + (lane & 31), lk = lane >> 5;
+  const uint32_t whole = BK / g.blk_len, rest = BK - whole * g.blk_len;
+  const int klen = at.klen;
+  sums.clear();
+  if (klen == 0) return;
+  float *ta = lds, *tb = lds + OpA::kPlainFloats;
+  OpA oa;
+  OpB ob;
+  float4 va[OpA::kVecs], vb[OpB::kVecs];
+  oa.start(g.A + (unsigned long long)at.first * g.a_ks, g.a_xs, g.a_ks, at.m0, g.M, threadIdx.x, klen, g);
+  ob.start(g.B + (unsigned long long)at.first * g.b_ks, g.b_xs, g.b_ks, at.n0, g.N, threadIdx.x ^ (kBlock / 2), klen, g);
+  oa.load(va, whole, rest, g);
+  ob.load(vb, whole, rest, g);
+  int run = 0;
+  for (int k0 = 0; k0 < klen; k0 += BK) {
+    if (k0 + BK > klen) { oa.blank(va, k0, klen); ob.blank(vb, k0, klen); }
+    __syncthreads();                              // previous tile fully consumed
+    oa.store_plain(va, ta);
+    ob.store_plain(vb, tb);
+    __syncthreads();
+    oa.load(va, whole, rest, g);                  // the next tile travels while this one is multiplied
+    ob.load(vb, whole, rest, g);
+    // operands of step kk+2 are read from LDS before the matrix instructions of step kk are issued
+    float a[NB], b[NB];
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NB; ++i) { a[i] = OpA::plain(ta, xa + i * 32, lk); b[i] = OpB::plain(tb, xb + i * 32, lk); }
 #pragma unroll
-          for (int j = 0; j < 2; ++j) {
-            total[i][j] += acc[i][j];
+    for (int kk = 0; kk < BK; kk += 2) {
+      float an[NB], bn[NB];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-          }
+      for (int i = 0; i < NB; ++i) {
+        an[i] = bn[i] = 0.f;
+        if (kk + 2 < BK) { an[i] = OpA::plain(ta, xa + i * 32, kk + 2 + lk); bn[i] = OpB::plain(tb, xb + i * 32, kk + 2 + lk); }
       }
+      __builtin_amdgcn_sched_barrier(0);          // keep the reads above: the scheduler would sink them to their use
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) sums.acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], sums.acc[i][j], 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < NB; ++i) { a[i] = an[i]; b[i] = bn[i]; }
+    }
+    if (kTwoLevel && (run += BK) == kRun) { run = 0; sums.flush(); }
+  }
+}
+
+template <int T, bool kAKContig, bool kBKContig, bool kTwoLevel>
+__global__ __launch_bounds__(kBlock, 2) void k_gemm_f32(const GemmArgs g) {
+  __shared__ __align__(16) float lds[plain_floats<T, kAKContig, kBKContig>()];
+  const Place<T> at(g);
+  if (!at.ok) return;                             // uniform per workgroup
+  Sums<T / 64, kTwoLevel> sums;
+  multiply_f32<T, kAKContig, kBKContig, kTwoLevel>(g, at, lds, sums);
+  const int wave = threadIdx.x / kWave;
+  sums.store(g, at.z, at.m0 + (wave >> 1) * (T / 2), at.n0 + (wave & 1) * (T / 2));
+}
+
+// Staging of both operands' tiles as bf16 planes.  Where both need half of the threads or less, each thread stages one of the
+// two (no branch, and one set of registers).
+template <int T, int BK, bool kAKContig, bool kBKContig>
+struct SplitStage {
+  static constexpr int kOperandBytes = 3 * T * 32;
+  static constexpr bool kShared = !kAKContig && !kBKContig;
+  using OpA = Operand<T, BK, kAKContig>;
+  using OpB = Operand<T, BK, kBKContig>;
+  OpA oa;
+  OpB ob;
+  float4 va[2][OpA::kVecs], vb[2][OpB::kVecs];    // two tiles under way
+  char *to;
+  __device__ inline void start(const GemmArgs &g, const Place<T> &at, char *lds) {
+    const float *A = g.A + (unsigned long long)at.first * g.a_ks, *B = g.B + (unsigned long long)at.first * g.b_ks;
+    if constexpr (kShared) {
+      constexpr int n = Operand<T, BK, false>::kTotal;
+      const bool second = threadIdx.x / n == 1;   // threads past the second operand's units: idle
+      to = lds + (second ? kOperandBytes : 0);
+      oa.start(second ? B : A, 1, second ? g.b_ks : g.a_ks, second ? at.n0 : at.m0, second ? g.N : g.M,
+               second ? threadIdx.x - n : threadIdx.x, at.klen, g);
+    } else {
+      to = lds;
+      oa.start(A, g.a_xs, g.a_ks, at.m0, g.M, threadIdx.x, at.klen, g);
+      ob.start(B, g.b_xs, g.b_ks, at.n0, g.N, threadIdx.x ^ (kBlock / 2), at.klen, g);
     }
   }
+  template <int kSet>
+  __device__ inline void load(uint32_t whole, uint32_t rest, const GemmArgs &g) {
+    oa.load(va[kSet], whole, rest, g);
+    if constexpr (!kShared) ob.load(vb[kSet], whole, rest, g);
+  }
+  template <int kSet>
+  __device__ inline void blank(int k0, int klen) {
+    if (k0 + BK <= klen) return;                  // uniform
+    oa.blank(va[kSet], k0, klen);
+    if constexpr (!kShared) ob.blank(vb[kSet], k0, klen);
+  }
+  template <int kSet>
+  __device__ inline void store(int buf, Odd &odd) const {
+    oa.store_split(va[kSet], to + buf, odd);
+    if constexpr (!kShared) ob.store_split(vb[kSet], to + buf + kOperandBytes, odd);
+  }
+};
+
+template <int T, bool kAKContig, bool kBKContig, bool kTwoLevel>
+__global__ __launch_bounds__(kBlock, 2) void k_gemm_split(const GemmArgs g) {
+  constexpr int NB = T / 64, BK = 16;
+  constexpr int kPlane = T * 32, kBuffer = 6 * kPlane;      // bytes: one bf16 plane of one operand; both operands' planes
+  constexpr int kPlainBytes = plain_floats<T, kAKContig, kBKContig>() * 4;
+  __shared__ __align__(16) char lds[2 * kBuffer > kPlainBytes ? 2 * kBuffer : kPlainBytes];
+  const Place<T> at(g);
+  if (!at.ok) return;                             // uniform per workgroup
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int m_wave = (wave >> 1) * (T / 2), n_wave = (wave & 1) * (T / 2);
+  const int ra = lds_offset(m_wave + (lane & 31), lane >> 5), rb = 3 * kPlane + lds_offset(n_wave + (lane & 31), lane >> 5);
+  const uint32_t whole = BK / g.blk_len, rest = BK - whole * g.blk_len;
+  const int klen = at.klen;
+  Sums<NB, kTwoLevel> sums;
+  sums.clear();
+  Odd odd{0u, 0.f};
+  if (klen > 0) {
+    SplitStage<T, BK, kAKContig, kBKContig> stage;
+    stage.start(g, at, lds);
+    stage.template load<0>(whole, rest, g);
+    stage.template load<1>(whole, rest, g);
+    stage.template blank<0>(0, klen);
+    stage.template store<0>(0, odd);
+    stage.template load<0>(whole, rest, g);
+    int run = 0;
+    // multiplies the tile at k0 out of buffer kBuf, cuts the next one into the other buffer, requests the third one on
+    auto step = [&](auto buf_c, int k0) {
+      constexpr int kBuf = decltype(buf_c)::value, kNext = 1 - kBuf;
+      stage.template blank<kNext>(k0 + BK, klen);
+      __syncthreads();                            // the current tile is written, the other buffer fully read
+      bf16x8 a[3][NB], b[3][NB];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+      for (int q = 0; q < 3; ++q)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) total[i][j] += acc[i][j];
-  // accumulator element r of a 32x32 block sits at row (r/4)*8 + (lane/32)*4 + r%4, column lane%32
-  float *C = g.C + (long long)z * g.c_slice;
+        for (int i = 0; i < NB; ++i) {
+          a[q][i] = *reinterpret_cast<const bf16x8 *>(lds + kBuf * kBuffer + q * kPlane + i * 1024 + ra);
+          b[q][i] = *reinterpret_cast<const bf16x8 *>(lds + kBuf * kBuffer + q * kPlane + i * 1024 + rb);
+        }
+      stage.template store<kNext>(kNext * kBuffer, odd);
+      // smallest terms first
+      constexpr int qa[6] = {2, 0, 1, 1, 0, 0}, qb[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+      for (int p = 0; p < 6; ++p)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int col = n0 + wn * 64 + j * 32 + lrow;
+        for (int i = 0; i < NB; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = m0 + wm * 64 + i * 32 + (r >> 2) * 8 + lk * 4 + (r & 3);
-        if (row < g.M && col < g.N) C[(long long)row * g.c_rs + col] = total[i][j][r];
-      }
+          for (int j = 0; j < NB; ++j)
+            sums.acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[qa[p]][i], b[qb[p]][j], sums.acc[i][j], 0, 0, 0);
+      stage.template load<kNext>(whole, rest, g);
+      if (kTwoLevel && (run += BK) == kRun) { run = 0; sums.flush(); }
+    };
+    for (int k0 = 0; k0 < klen; k0 += 2 * BK) {
+      step(std::integral_constant<int, 0>{}, k0);
+      if (k0 + BK < klen) step(std::integral_constant<int, 1>{}, k0 + BK);
     }
+  }
+  // An infinity or NaN (times a zero part it would make a NaN of what should stay infinite), or an operand too small for
+  // three bf16 parts: the tile is computed again with the fp32 instruction.
+  if (__syncthreads_or((odd.rest & 0xFFFFu) != 0 || !(fabsf(odd.nan) <= 3.4028235e38f)))
+    multiply_f32<T, kAKContig, kBKContig, kTwoLevel>(g, at, reinterpret_cast<float *>(lds), sums);
+  sums.store(g, at.z, at.m0 + m_wave, at.n0 + n_wave);
+}
+
+inline long long tiles_of(long long n, int T) { return (n + T - 1) / T; }
+
+// Tile edge.  The large tile reads and cuts each operand element half as often; the small one gives four times as many
+// workgroups and less padding.  Measured, large / small tile:
+//   split, 16384 x 3200 x 256: 172 / 242 us (g_pool), 159 / 313 us (dW); 5003 x 540 x 300, 200 and 240 large tiles: 24.1 / 26.5 us
+//   and 24.0 / 26.6 us; 4096 x 416 x 256, 128 large tiles: 34.9 / 32.6 us for the two g_pool of a model step
+//   fp32 (results do not depend on the choice), 16384 x 3200 x 256: 271 / 281 us; 5003 x 540 x 300 with 7 shards, where the
+//   large tile multiplies 21 % more padding: 43 / 34 us
+template <bool kSplit>
+inline int tile_edge(long long M, long long N, long long slices) {
+  const long long large = tiles_of(M, 128) * tiles_of(N, 128) * slices, small = tiles_of(M, 64) * tiles_of(N, 64) * slices;
+  if (kSplit) return large >= 192 ? 128 : 64;
+  return large >= 384 && large * 40 <= small * 11 ? 128 : 64;    // at most 10 % more area
 }
 
 // `depth`: products summed per output element of one slice; above kTwoLevelDepth the two-level kernel runs.
-template <bool kAKContig, bool kBKContig>
-des_status_t launch(const GemmArgs &g, int slices, long long depth, int kid, hipStream_t s) {
-  const dim3 grid((unsigned)((g.N + BN - 1) / BN), (unsigned)((g.M + BM - 1) / BM), (unsigned)slices);
+template <bool kSplit, bool kAKContig, bool kBKContig>
+des_status_t launch(GemmArgs g, int slices, long long depth, int kid, hipStream_t s) {
+  const int T = tile_edge<kSplit>(g.M, g.N, slices);
+  g.tiles_m = (int)tiles_of(g.M, T); g.tiles_n = (int)tiles_of(g.N, T); g.slices = slices;
+  if (g.m_group <= 0 || g.m_group > g.tiles_m) g.m_group = g.tiles_m;
+  const long long total = (long long)g.tiles_m * g.tiles_n * slices;
+  if (total >= 2147483647ll) return DES_ERR_INVALID_ARG;
+  const dim3 grid((unsigned)((total + kXcds - 1) / kXcds * kXcds)), block(kBlock);
+  const bool two = depth > kTwoLevelDepth;
   ProfScope ps(kid, s);
-  if (depth > kTwoLevelDepth)
-    hipLaunchKernelGGL((k_gemm<kAKContig, kBKContig, true>), grid, dim3(kBlock), 0, s, g);
-  else
-    hipLaunchKernelGGL((k_gemm<kAKContig, kBKContig, false>), grid, dim3(kBlock), 0, s, g);
+#define DES_GEMM(EDGE, TWO)                                                                                         \
+  do {                                                                                                              \
+    if constexpr (kSplit) hipLaunchKernelGGL((k_gemm_split<EDGE, kAKContig, kBKContig, TWO>), grid, block, 0, s, g); \
+    else hipLaunchKernelGGL((k_gemm_f32<EDGE, kAKContig, kBKContig, TWO>), grid, block, 0, s, g);                    \
+  } while (0)
+  if (T == 128) { if (two) DES_GEMM(128, true); else DES_GEMM(128, false); }
+  else          { if (two) DES_GEMM(64, true);  else DES_GEMM(64, false); }
+#undef DES_GEMM
   return hipGetLastError() == hipSuccess ? DES_OK : DES_ERR_DEVICE;
 }
 
@@ -220,12 +493,13 @@ des_status_t des_dnn_partial_forward(const float *pool, const float *W, int64_t 
   if (B >= 2147483647ll || (int64_t)F * D >= 2147483647ll || !al16(pool) || !al16(W) || !al16(Y_partial))
     return DES_ERR_INVALID_ARG;
   GemmArgs g;
-  g.A = pool; g.a_rs = (long long)F * D; g.a_cs = 1;
-  g.B = W; g.b_rs = H; g.b_cs = 1;
+  g.A = pool; g.a_xs = (uint32_t)F * D; g.a_ks = 1;
+  g.B = W; g.b_xs = 1; g.b_ks = H;
   g.C = Y_partial; g.M = (int)B; g.N = H; g.c_rs = H; g.c_slice = (long long)B * H;
   // shard s: fields s, s+K, ... = k blocks of length D starting at s*D, K*D apart
-  g.k_begin = 0; g.k_shift = D; g.blk_len = D; g.blk_stride = (long long)K * D; g.k_limit = (long long)F * D;
-  return launch<true, false>(g, K, (long long)((F + K - 1) / K) * D, KID_DNN_FORWARD, (hipStream_t)stream);
+  g.m_group = kForwardGroup;
+  g.k_shift = g.blk_len = D; g.blk_stride = (uint32_t)(K < F ? K : F) * D; g.k_limit = g.k_max = (uint32_t)F * D;
+  return launch<false, true, false>(g, K, (long long)((F + K - 1) / K) * D, KID_DNN_FORWARD, (hipStream_t)stream);
 }
 
 des_status_t des_dnn_backward_bytes(int64_t B, int32_t F, int32_t D, int32_t H, size_t *workspace_bytes) {
@@ -248,37 +522,39 @@ des_status_t des_dnn_backward(const float *pool, const float *W, const float *dY
   const long long FD = (long long)F * D;
   if (g_pool) {                                   // g_pool[B, F*D] = dY[B,H] x W^T: B(k=h, n=j) = W[j*H + h]
     GemmArgs g;
-    g.A = dY; g.a_rs = H; g.a_cs = 1;
-    g.B = W; g.b_rs = 1; g.b_cs = H;
+    g.A = dY; g.a_xs = H; g.a_ks = 1;
+    g.B = W; g.b_xs = H; g.b_ks = 1;
     g.C = g_pool; g.M = (int)B; g.N = (int)FD; g.c_rs = FD; g.c_slice = 0;
-    g.k_begin = 0; g.k_shift = 0; g.blk_len = H; g.blk_stride = (1ll << 40); g.k_limit = H;
-    des_status_t st = launch<true, true>(g, 1, H, KID_DNN_GPOOL, s);
+    g.m_group = 0;
+    g.k_shift = 0; g.blk_len = g.blk_stride = g.k_limit = g.k_max = H;
+    des_status_t st = launch<true, true, true>(g, 1, H, KID_DNN_GPOOL, s);
     if (st != DES_OK) return st;
   }
   if (dW) {                                       // dW[F*D, H] = pool^T x dY, split over slices of samples
-    const long long tiles = ((FD + BM - 1) / BM) * ((H + BN - 1) / BN);
+    const long long tiles = tiles_of(FD, 128) * tiles_of(H, 128);
     // Slices of samples: enough workgroups to fill the chip, chosen so that the last round of resident
-    // workgroups (two per CU for the two-level kernel, 256 CUs) is as full as possible; fewer slices win ties
-    // (less partial-sum traffic).  At most 16 slices, at least BK samples each.
+    // workgroups (two per CU, 256 CUs) is as full as possible; fewer slices win ties
+    // (less partial-sum traffic).  At most 16 slices, at least kMinSlice samples each.
     int Z = 1;
     {
       const long long per_round = 2 * 256;
       double best = -1.0;
-      for (int z = 1; z <= 16 && (long long)z * BK <= (B > BK ? B : BK); ++z) {
+      for (int z = 1; z <= 16 && (long long)z * kMinSlice <= (B > kMinSlice ? B : kMinSlice); ++z) {
         const long long blocks = tiles * z, rounds = (blocks + per_round - 1) / per_round;
         const double fill = (double)blocks / (double)(rounds * per_round);
         if (fill > best + 0.02) { best = fill; Z = z; }
       }
     }
-    long long chunk = ((B + Z - 1) / Z + BK - 1) / BK * BK;
+    long long chunk = ((B + Z - 1) / Z + kMinSlice - 1) / kMinSlice * kMinSlice;
     Z = (int)((B + chunk - 1) / chunk);
     if (Z > 1 && (!workspace || workspace_bytes < (size_t)Z * FD * H * sizeof(float))) return DES_ERR_WORKSPACE;
     GemmArgs g;
-    g.A = pool; g.a_rs = 1; g.a_cs = FD;          // A(m=j, k=b) = pool[b*FD + j]
-    g.B = dY; g.b_rs = H; g.b_cs = 1;
+    g.A = pool; g.a_xs = 1; g.a_ks = (uint32_t)FD;          // A(m=j, k=b) = pool[b*FD + j]
+    g.B = dY; g.b_xs = 1; g.b_ks = H;
     g.C = Z > 1 ? (float *)workspace : dW; g.M = (int)FD; g.N = H; g.c_rs = H; g.c_slice = FD * H;
-    g.k_begin = 0; g.k_shift = chunk; g.blk_len = chunk; g.blk_stride = (1ll << 40); g.k_limit = B;
-    des_status_t st = launch<false, false>(g, Z, chunk, KID_DNN_DW, s);
+    g.m_group = 0;
+    g.k_shift = g.k_max = (uint32_t)chunk; g.blk_len = g.blk_stride = 1u << 31; g.k_limit = (uint32_t)B;
+    des_status_t st = launch<true, false, false>(g, Z, chunk, KID_DNN_DW, s);
     if (st != DES_OK) return st;
     if (Z > 1) return des_aggregate_partials((const float *)workspace, Z, FD * H, dW, stream);
   }

@@ -80,3 +80,60 @@ def test_dnn_layer_argument_checks(des):
     # empty batch: nothing launched, nothing written
     out = des.dnn_partial_forward(torch.zeros((0, 2, 4), device="cuda"), W, 2)
     assert out.shape == (2, 0, 8)
+
+
+def _gradients(des, torch, pool, W, dY):
+    B, F, D = pool.shape
+    g_pool = torch.full((B, F, D), float("nan"), dtype=torch.float32, device="cuda")
+    dW = torch.full(W.shape, float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.empty(des.dnn_backward_bytes(B, F, D, W.shape[1]), dtype=torch.uint8, device="cuda")
+    des.dnn_backward(dev(pool, torch), dev(W, torch), dev(dY, torch), g_pool, dW, ws)
+    torch.cuda.synchronize()
+    return g_pool.cpu().numpy().reshape(B, F * D), dW.cpu().numpy()
+
+
+# both tile sizes, ragged in every dimension; fields that are not a multiple of the k tile, several fields per k tile
+@pytest.mark.parametrize("B,F,D,H,K", [(12801, 8, 100, 128, 3), (1601, 9, 20, 388, 7), (65, 33, 4, 68, 2), (4097, 3, 12, 36, 5)])
+def test_dnn_products_at_tile_edges(des, B, F, D, H, K):
+    import torch
+    pool, W, dY = synth.dnn_layer_inputs(B + F, B, F, D, H)
+    x, w, g = pool.reshape(B, F * D).astype(np.float64), W.astype(np.float64), dY.astype(np.float64)
+    Y = des.dnn_partial_forward(dev(pool, torch), dev(W, torch), K).cpu().numpy()
+    for s in range(K):
+        cols = np.concatenate([np.arange(f * D, (f + 1) * D) for f in range(s, F, K)]) if s < F else np.zeros(0, int)
+        assert_close(Y[s], x[:, cols] @ w[cols], f"Y_partial shard {s}")
+    g_pool, dW = _gradients(des, torch, pool, W, dY)
+    assert_close(g_pool, g @ w.T, "g_pool")
+    assert_close(dW, x.T @ g, "dW")
+
+
+@pytest.mark.parametrize("B,F,D,H", [(300, 7, 8, 200), (12801, 8, 100, 128)])     # small and large tiles
+def test_dnn_gradients_of_infinities_nans_and_extreme_magnitudes(des, B, F, D, H):
+    """Infinities and NaN reach exactly the outputs that plain fp32 arithmetic sends them to; operands so small that bf16
+    parts cannot hold them, and so large that their leading part would round up to infinity, lose nothing."""
+    import torch
+    pool, W, dY = synth.dnn_layer_inputs(B + 1, B, F, D, H)
+    pool.reshape(B, -1)[5, 3] = np.inf
+    dY[7, 2] = -np.inf
+    dY[B - 1, H - 1] = np.nan
+    W[1, 1] = np.inf
+    x, w, g = pool.reshape(B, F * D).astype(np.float64), W.astype(np.float64), dY.astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        refs = g @ w.T, x.T @ g
+    for got, ref, what in zip(_gradients(des, torch, pool, W, dY), refs, ("g_pool", "dW")):
+        fin = np.isfinite(ref)
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[~fin & ~np.isnan(ref)], ref[~fin & ~np.isnan(ref)]), what
+        assert_close(got[fin], ref[fin], what)
+    # a power of two on one operand and its inverse on the other leave every product as it is
+    pool, W, dY = synth.dnn_layer_inputs(B + 2, B, F, D, H)
+    up, down = np.float32(2.0 ** 112), np.float32(2.0 ** -112)
+    x, w, g = pool.reshape(B, F * D).astype(np.float64), W.astype(np.float64), dY.astype(np.float64)
+    g_pool, _ = _gradients(des, torch, pool, W * up, dY * down)
+    assert_close(g_pool, g @ w.T, "g_pool, dY tiny")
+    _, dW = _gradients(des, torch, pool * up, W, dY * down)
+    assert_close(dW, x.T @ g, "dW, dY tiny")
+    W[0, 0] = np.float32(3.4e38)
+    g_pool, _ = _gradients(des, torch, pool, W, dY * np.float32(1e-3))
+    ref = (g * 1e-3) @ W.astype(np.float64).T
+    assert np.isfinite(g_pool).all()
+    assert np.all(np.abs(g_pool - ref) <= np.maximum(1e-5 * np.abs(ref), 1e-6))
