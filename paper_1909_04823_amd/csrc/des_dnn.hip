@@ -24,7 +24,9 @@
 // instructions of the cut (5.5 per element, once per element and tile, on the way into LDS): two LDS buffers of 16 products, so
 // that a wave cuts the next tile between the matrix instructions of the current one, and two tiles under way in registers.
 // 65536 x 12800 x 256: g_pool 3.81 -> 2.60 ms (165 TFLOP/s), dW 3.65 -> 2.55 ms; a library's plain bf16 product of 8192^3 reaches
-// 1.1 PFLOP/s here, one sixth of which is 183.  16384 x 3200 x 256: 248 -> 179 us, 233 -> 163 us.  Error against 64 bits, 2-norm:
+// 1.1 PFLOP/s here, one sixth of which is 183.  The bf16 instruction drops the bits of its sum that do not fit, towards minus
+// infinity; over many runs that adds up (a mean of -3e-7 of the results' root mean square at 124623 samples), so every second run
+// of kRun products is accumulated with the opposite sign.  16384 x 3200 x 256: 248 -> 179 us, 233 -> 163 us.  Error against 64 bits, 2-norm:
 // 2.4e-7 where the fp32 instruction has 2.9e-7 (16384 x 3200 x 256), 2.6e-7 and 3.1e-7 (5003 x 540 x 300).
 //
 // Products through operand strides and a sliced k range:
@@ -150,11 +152,17 @@ struct Operand {
     for (int i = 0; i < kVecs; ++i)
       if (k0 + k_in + (kKContig ? 0 : i) >= klen) v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
-  // cuts the staged values into the three planes at `plane` (T rows each)
-  __device__ inline void store_split(const float4 (&v)[kVecs], char *plane, Odd &odd) const {
+  // cuts the staged values into the three planes at `plane` (T rows each), their signs flipped if `flip` is the sign bit
+  template <bool kFlip>
+  __device__ inline void store_split(const float4 (&v)[kVecs], char *plane, uint32_t flip, Odd &odd) const {
     static_assert(BK == 16, "two chunks per row");
     if (T != 128 && !active) return;
-    const float *f = reinterpret_cast<const float *>(v);
+    float f[kVecs * 4];
+#pragma unroll
+    for (int i = 0; i < kVecs * 4; ++i) {
+      const float x = reinterpret_cast<const float *>(v)[i];
+      f[i] = kFlip ? __uint_as_float(__float_as_uint(x) ^ flip) : x;
+    }
     if constexpr (kKContig) {
 #pragma unroll
       for (int u = 0; u < kUnits; ++u) {
@@ -244,6 +252,17 @@ struct Sums {
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
       }
+  }
+  __device__ inline void negate() {
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) acc[i][j] = -acc[i][j];
+  }
+  // End of a run of a sum whose every second run is accumulated with the opposite sign (`odd`: this was one).
+  __device__ inline void turn(bool odd) {
+    if (!kTwoLevel || odd) negate();               // the next run, or the total, wants the other sign
+    if (kTwoLevel) flush();
   }
   // element r of a 32x32 block sits at row (r/4)*8 + (lane/32)*4 + r%4, column lane%32
   __device__ inline void store(const GemmArgs &g, int z, int m_wave, int n_wave) {
@@ -344,16 +363,19 @@ struct SplitStage {
   OpB ob;
   float4 va[2][OpA::kVecs], vb[2][OpB::kVecs];    // two tiles under way
   char *to;
+  uint32_t flips;                                 // the sign bit for threads that stage A
   __device__ inline void start(const GemmArgs &g, const Place<T> &at, char *lds) {
     const float *A = g.A + (unsigned long long)at.first * g.a_ks, *B = g.B + (unsigned long long)at.first * g.b_ks;
     if constexpr (kShared) {
       constexpr int n = Operand<T, BK, false>::kTotal;
       const bool second = threadIdx.x / n == 1;   // threads past the second operand's units: idle
       to = lds + (second ? kOperandBytes : 0);
+      flips = second ? 0u : 0x80000000u;
       oa.start(second ? B : A, 1, second ? g.b_ks : g.a_ks, second ? at.n0 : at.m0, second ? g.N : g.M,
                second ? threadIdx.x - n : threadIdx.x, at.klen, g);
     } else {
       to = lds;
+      flips = 0x80000000u;
       oa.start(A, g.a_xs, g.a_ks, at.m0, g.M, threadIdx.x, at.klen, g);
       ob.start(B, g.b_xs, g.b_ks, at.n0, g.N, threadIdx.x ^ (kBlock / 2), at.klen, g);
     }
@@ -369,10 +391,11 @@ struct SplitStage {
     oa.blank(va[kSet], k0, klen);
     if constexpr (!kShared) ob.blank(vb[kSet], k0, klen);
   }
+  // k0: the tile's first product; A is negated in every second run
   template <int kSet>
-  __device__ inline void store(int buf, Odd &odd) const {
-    oa.store_split(va[kSet], to + buf, odd);
-    if constexpr (!kShared) ob.store_split(vb[kSet], to + buf + kOperandBytes, odd);
+  __device__ inline void store(int buf, int k0, Odd &odd) const {
+    oa.template store_split<true>(va[kSet], to + buf, k0 / kRun & 1 ? flips : 0u, odd);
+    if constexpr (!kShared) ob.template store_split<false>(vb[kSet], to + buf + kOperandBytes, 0u, odd);
   }
 };
 
@@ -398,9 +421,8 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_split(const GemmArgs g) {
     stage.template load<0>(whole, rest, g);
     stage.template load<1>(whole, rest, g);
     stage.template blank<0>(0, klen);
-    stage.template store<0>(0, odd);
+    stage.template store<0>(0, 0, odd);
     stage.template load<0>(whole, rest, g);
-    int run = 0;
     // multiplies the tile at k0 out of buffer kBuf, cuts the next one into the other buffer, requests the third one on
     auto step = [&](auto buf_c, int k0) {
       constexpr int kBuf = decltype(buf_c)::value, kNext = 1 - kBuf;
@@ -414,7 +436,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_split(const GemmArgs g) {
           a[q][i] = *reinterpret_cast<const bf16x8 *>(lds + kBuf * kBuffer + q * kPlane + i * 1024 + ra);
           b[q][i] = *reinterpret_cast<const bf16x8 *>(lds + kBuf * kBuffer + q * kPlane + i * 1024 + rb);
         }
-      stage.template store<kNext>(kNext * kBuffer, odd);
+      stage.template store<kNext>(kNext * kBuffer, k0 + BK, odd);
       // smallest terms first
       constexpr int qa[6] = {2, 0, 1, 1, 0, 0}, qb[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
@@ -425,12 +447,15 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_split(const GemmArgs g) {
           for (int j = 0; j < NB; ++j)
             sums.acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[qa[p]][i], b[qb[p]][j], sums.acc[i][j], 0, 0, 0);
       stage.template load<kNext>(whole, rest, g);
-      if (kTwoLevel && (run += BK) == kRun) { run = 0; sums.flush(); }
+      if ((k0 + BK) % kRun == 0) sums.turn((k0 / kRun & 1) != 0);
     };
     for (int k0 = 0; k0 < klen; k0 += 2 * BK) {
       step(std::integral_constant<int, 0>{}, k0);
       if (k0 + BK < klen) step(std::integral_constant<int, 1>{}, k0 + BK);
     }
+    // the run the loop ended in, if it is not complete; a complete one has been turned
+    const int tiles = (klen + BK - 1) / BK;
+    if (tiles % (kRun / BK) != 0 ? tiles / (kRun / BK) & 1 : !kTwoLevel && (tiles / (kRun / BK) & 1)) sums.negate();
   }
   // An infinity or NaN (times a zero part it would make a NaN of what should stay infinite), or an operand too small for
   // three bf16 parts: the tile is computed again with the fp32 instruction.

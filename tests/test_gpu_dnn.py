@@ -137,3 +137,13 @@ def test_dnn_gradients_of_infinities_nans_and_extreme_magnitudes(des, B, F, D, H
     ref = (g * 1e-3) @ W.astype(np.float64).T
     assert np.isfinite(g_pool).all()
     assert np.all(np.abs(g_pool - ref) <= np.maximum(1e-5 * np.abs(ref), 1e-6))
+
+
+def test_dnn_weight_gradient_has_no_drift(des):
+    """The matrix instruction's rounding towards minus infinity must not pile up over a long sum: the mean error over 4096 sums of
+    2504 products per slice (uncorrected -3e-7 of the results' root mean square, its standard error 4e-9) stays below 3e-8."""
+    import torch
+    pool, W, dY = synth.dnn_layer_inputs(3, 40003, 4, 16, 64)
+    _, dW = _gradients(des, torch, pool, W, dY)
+    ref = pool.reshape(40003, 64).astype(np.float64).T @ dY.astype(np.float64)
+    assert abs((dW - ref).mean()) < 3e-8 * np.sqrt((ref * ref).mean())
