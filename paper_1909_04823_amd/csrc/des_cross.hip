@@ -275,21 +275,24 @@ __device__ inline double bias_prefix(const float *__restrict__ bias, int64_t d, 
   return c;
 }
 
-// kappa[k] = <c_k, u_k>; one workgroup per k.
-__global__ __launch_bounds__(kBlock) void k_cross_net_kappa(const float *__restrict__ U, const float *__restrict__ bias,
-                                                             int64_t d, double *__restrict__ kappa) {
-  __shared__ double red[kBlock];
+// kappa[k] = <c_k, u_k>; one large workgroup per k (a single pass over d waits on little but its own loads).
+constexpr int kKappaBlock = 1024;
+__global__ __launch_bounds__(kKappaBlock) void k_cross_net_kappa(const float *__restrict__ U, const float *__restrict__ bias,
+                                                                  int64_t d, double *__restrict__ kappa) {
+  __shared__ double red[kKappaBlock / kWave];
   const int k = blockIdx.x;
   double acc = 0.0;
-#pragma unroll 8
-  for (int64_t j = threadIdx.x; j < d; j += kBlock) acc += bias_prefix(bias, d, k, j) * (double)U[(int64_t)k * d + j];
-  red[threadIdx.x] = acc;
+#pragma unroll 4
+  for (int64_t j = threadIdx.x; j < d; j += kKappaBlock) acc += bias_prefix(bias, d, k, j) * (double)U[(int64_t)k * d + j];
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o, kWave);
+  if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = acc;
   __syncthreads();
-  for (int h = kBlock / 2; h > 0; h >>= 1) {
-    if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-    __syncthreads();
+  if (threadIdx.x == 0) {
+    double a = 0.0;
+    for (int w = 0; w < kKappaBlock / kWave; ++w) a += red[w];
+    kappa[k] = a;
   }
-  if (threadIdx.x == 0) kappa[k] = red[0];
 }
 
 // gamma[b,0] = 1, gamma[b,l+1] = gamma[b,l] + s_l[b], c[b] = gamma[b,n] t[b,n] + kappa[n]; one thread per sample.
@@ -351,19 +354,6 @@ __global__ __launch_bounds__(kBlock) void k_cross_net_beta(const float *__restri
   }
 }
 
-// Gsum[k] = sum over the workgroups' partials: one wave per k, lane i adds the partials i, i+64, ... in order,
-// an xor tree adds the lanes.
-__global__ __launch_bounds__(kWave) void k_cross_net_gsum(const double *__restrict__ Gpart, int64_t nblk, int m,
-                                                           double *__restrict__ Gsum) {
-  const int k = blockIdx.x;
-  double a = 0.0;
-#pragma unroll 4
-  for (int64_t i = threadIdx.x; i < nblk; i += kWave) a += Gpart[i * m + k];
-#pragma unroll
-  for (int o = kWave / 2; o > 0; o >>= 1) a += __shfl_xor(a, o, kWave);
-  if (threadIdx.x == 0) Gsum[k] = a;
-}
-
 // The pass over x0 of the backward: g_x0[b,j] (+)= sum_k beta[b,k] U[k,j] and the slice's part of
 // S[k,j] = sum_b beta[b,k] x0[b,j].  grid (blocks of 256 float4 columns, slices); partial[slice][k][:].
 template <int M, bool kAccumulate>
@@ -413,24 +403,55 @@ __global__ __launch_bounds__(kBlock) void k_cross_net_grad(const float *__restri
   }
 }
 
+// Sum of the workgroups' partials of G_k, the same in every thread: thread i adds the partials i, i + kBlock, ... in order, the
+// waves' xor trees and then the waves are added.
+__device__ inline double net_gsum(const double *__restrict__ Gpart, int64_t nblk, int m, int k, double *red) {
+  double a = 0.0;
+  for (int64_t i = threadIdx.x; i < nblk; i += kBlock) a += Gpart[i * m + k];
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) a += __shfl_xor(a, o, kWave);
+  __syncthreads();                                       // `red` is free again
+  if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = a;
+  __syncthreads();
+  return (red[0] + red[1]) + (red[2] + red[3]);
+}
+
 // dU[k,j] = sum over the slices of S + c_k[j] G_k;  dbias[l,j] = U[n,j] G_n + sum_{l'>l} U[l',j] G_l'.
+// grid (blocks of 64 columns, m + 1): block row k < m makes dU[k], the last one dbias.  Lane = column; the four waves take the
+// slices w, w+4, ... and their sums are added in wave order.  (One thread per column over all slices and vectors took 59 us
+// at 256 slices of 3 x 3200 columns: thirteen workgroups, one load at a time; this takes 6.)
 __global__ __launch_bounds__(kBlock) void k_cross_net_final(const double *__restrict__ partial, int slices,
-                                                             const double *__restrict__ Gsum, const float *__restrict__ U,
-                                                             const float *__restrict__ bias, int64_t d, int n,
-                                                             float *__restrict__ dU, float *__restrict__ dbias) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= d) return;
-  const int m = n + 1;
-  for (int k = 0; k < m; ++k) {
+                                                             const double *__restrict__ Gpart, int64_t nblk,
+                                                             const float *__restrict__ U, const float *__restrict__ bias,
+                                                             int64_t d, int n, float *__restrict__ dU,
+                                                             float *__restrict__ dbias) {
+  __shared__ double red[kBlock];
+  __shared__ double gred[kBlock / kWave];
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, m = n + 1;
+  const int64_t j = (int64_t)blockIdx.x * kWave + lane;
+  if ((int)blockIdx.y < m) {
+    const int k = blockIdx.y;
+    const double G = net_gsum(Gpart, nblk, m, k, gred);
     double a = 0.0;
+    if (j < d) {
 #pragma unroll 8
-    for (int sl = 0; sl < slices; ++sl) a += partial[((int64_t)sl * m + k) * d + j];
-    dU[(int64_t)k * d + j] = (float)(a + bias_prefix(bias, d, k, j) * Gsum[k]);
+      for (int sl = wave; sl < slices; sl += kBlock / kWave) a += partial[((int64_t)sl * m + k) * d + j];
+    }
+    red[threadIdx.x] = a;
+    __syncthreads();
+    if (wave == 0 && j < d) {
+      a = (red[lane] + red[lane + kWave]) + (red[lane + 2 * kWave] + red[lane + 3 * kWave]);
+      dU[(int64_t)k * d + j] = (float)(a + bias_prefix(bias, d, k, j) * G);
+    }
+    return;
   }
-  double tail = (double)U[(int64_t)n * d + j] * Gsum[n];      // u_n G_n + sum over the layers above l
-  for (int l = n - 1; l >= 0; --l) {
-    dbias[(int64_t)l * d + j] = (float)tail;
-    tail += (double)U[(int64_t)l * d + j] * Gsum[l];
+  double tail = 0.0;                                      // u_n G_n + sum over the layers above l
+  for (int l = n; l >= 1; --l) {
+    const double G = net_gsum(Gpart, nblk, m, l, gred);
+    if (wave == 0 && j < d) {
+      tail += (double)U[(int64_t)l * d + j] * G;
+      dbias[(int64_t)(l - 1) * d + j] = (float)tail;
+    }
   }
 }
 
@@ -556,7 +577,7 @@ des_status_t des_cross_partial_backward(const float *xl, const float *w, const f
 }
 
 // ---- whole cross network ----
-struct NetLayout { size_t kappa, gsum, beta, gpart, partial, total; int slices; int64_t nblk; };
+struct NetLayout { size_t kappa, beta, gpart, partial, total; int slices; int64_t nblk; };
 static NetLayout net_layout(int64_t B, int64_t d, int n) {
   const int m = n + 1;
   const int64_t rows = B > 0 ? B : 1;
@@ -566,7 +587,6 @@ static NetLayout net_layout(int64_t B, int64_t d, int n) {
   L.nblk = (rows + kBlock - 1) / kBlock;
   L.slices = cross_slices(rows, d);
   L.kappa = take(kCrossNetMax * sizeof(double));
-  L.gsum = take(kCrossNetMax * sizeof(double));
   L.beta = take((size_t)rows * m * sizeof(float));
   L.gpart = take((size_t)L.nblk * m * sizeof(double));
   L.partial = take((size_t)L.slices * m * (size_t)d * sizeof(double));
@@ -613,7 +633,7 @@ des_status_t des_cross_net_forward(const float *t, const float *U, const float *
   hipStream_t s = (hipStream_t)stream;
   double *kappa = (double *)((char *)workspace + L.kappa);
   ProfScope ps(KID_CROSS_APPLY, s);
-  hipLaunchKernelGGL(k_cross_net_kappa, dim3(n_layers + 1), dim3(kBlock), 0, s, U, bias, d, kappa);
+  hipLaunchKernelGGL(k_cross_net_kappa, dim3(n_layers + 1), dim3(kKappaBlock), 0, s, U, bias, d, kappa);
   hipLaunchKernelGGL(k_cross_net_scalars, dim3(blocks_for(B, 1 << 30)), dim3(kBlock), 0, s, t, kappa, B, n_layers, gamma, c);
   return hipGetLastError() == hipSuccess ? DES_OK : DES_ERR_DEVICE;
 }
@@ -629,19 +649,18 @@ des_status_t des_cross_net_backward(const float *x0, const float *U, const float
   hipStream_t s = (hipStream_t)stream;
   char *ws = (char *)workspace;
   float *beta = (float *)(ws + L.beta);
-  double *gpart = (double *)(ws + L.gpart), *gsum = (double *)(ws + L.gsum), *partial = (double *)(ws + L.partial);
+  double *gpart = (double *)(ws + L.gpart), *partial = (double *)(ws + L.partial);
   const int m = n_layers + 1;
   const int64_t d4 = d / 4;
+  const dim3 final_grid((unsigned)((d + kWave - 1) / kWave), (unsigned)(m + (n_layers > 0 ? 1 : 0)));
   ProfScope ps(KID_CROSS_GRAD, s);
   if (B == 0) {                                          // empty batch: every sum is zero
-    hipLaunchKernelGGL(k_cross_net_gsum, dim3(m), dim3(kWave), 0, s, gpart, (int64_t)0, m, gsum);
-    hipLaunchKernelGGL(k_cross_net_final, dim3(blocks_for(d, 1 << 20)), dim3(kBlock), 0, s, partial, 0, gsum, U, bias, d,
-                       n_layers, dU, dbias);
+    hipLaunchKernelGGL(k_cross_net_final, final_grid, dim3(kBlock), 0, s, partial, 0, gpart, (int64_t)0, U, bias, d, n_layers,
+                       dU, dbias);
     return hipGetLastError() == hipSuccess ? DES_OK : DES_ERR_DEVICE;
   }
   if (!x0 || !t || !gamma || !g || !g_x0 || !aligned16(x0) || !aligned16(U) || !aligned16(g_x0)) return DES_ERR_INVALID_ARG;
   hipLaunchKernelGGL(k_cross_net_beta, dim3((unsigned)L.nblk), dim3(kBlock), 0, s, t, gamma, g, B, n_layers, beta, gpart);
-  hipLaunchKernelGGL(k_cross_net_gsum, dim3(m), dim3(kWave), 0, s, gpart, L.nblk, m, gsum);
   const int64_t rows_per_slice = (B + L.slices - 1) / L.slices;
   const dim3 grid((unsigned)((d4 + kBlock - 1) / kBlock), (unsigned)L.slices);
 #define DES_NET_GRAD(M)                                                                                                  \
@@ -658,8 +677,8 @@ des_status_t des_cross_net_backward(const float *x0, const float *U, const float
     DES_NET_GRAD(5); DES_NET_GRAD(6); DES_NET_GRAD(7); DES_NET_GRAD(8);
   }
 #undef DES_NET_GRAD
-  hipLaunchKernelGGL(k_cross_net_final, dim3(blocks_for(d, 1 << 20)), dim3(kBlock), 0, s, partial, L.slices, gsum, U, bias,
-                     d, n_layers, dU, dbias);
+  hipLaunchKernelGGL(k_cross_net_final, final_grid, dim3(kBlock), 0, s, partial, L.slices, gpart, L.nblk, U, bias, d, n_layers,
+                     dU, dbias);
   return hipGetLastError() == hipSuccess ? DES_OK : DES_ERR_DEVICE;
 }
 
