@@ -326,6 +326,198 @@ __global__ __launch_bounds__(kBlock) void k_chunk_owner(const BwdArgs a) {
   }
 }
 
+// Steps (1)-(3) and the split of long segments for a batch of up to kSmallSort entries, all in the LDS of one workgroup: such a
+// batch is bound by launches (14 of them at 2560 entries, about 3.5 us each), not by work.  The sort is the same stable
+// radix sort, eight bits a pass.
+constexpr int kSmallSort = 4096;
+constexpr int64_t kSmallBags = 65536;                // bags whose offsets one workgroup walks
+constexpr int kSmallBlock = 1024;
+constexpr int kSmallWaves = kSmallBlock / kWave;
+constexpr int kSmallItems = kSmallSort / kSmallBlock;
+constexpr int kSmallBits = 8;
+
+// Exclusive scan over the workgroup's threads under `op` (sum or maximum, identity 0); total over all of them.
+template <typename Op>
+__device__ inline uint32_t small_excl_scan(uint32_t v, uint32_t *lds, uint32_t &total, Op op) {
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  uint32_t inc = v;
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const uint32_t o = __shfl_up(inc, off, kWave);
+    if (lane >= off) inc = op(inc, o);
+  }
+  uint32_t ex = __shfl_up(inc, 1, kWave);
+  if (lane == 0) ex = 0;
+  if (lane == kWave - 1) lds[wave] = inc;
+  __syncthreads();
+  uint32_t base = 0, tot = 0;
+#pragma unroll
+  for (int w = 0; w < kSmallWaves; ++w) {
+    const uint32_t x = lds[w];
+    if (w < wave) base = op(base, x);
+    tot = op(tot, x);
+  }
+  __syncthreads();
+  total = tot;
+  return op(base, ex);
+}
+
+template <bool kHasVals>
+__global__ __launch_bounds__(kSmallBlock) void k_sort_small(const BwdArgs a, uint32_t *__restrict__ pay_out, int bits) {
+  __shared__ uint32_t skey[kSmallSort + 1], spay[kSmallSort];
+  __shared__ uint32_t cnt[kSmallWaves][1 << kSmallBits];
+  __shared__ uint32_t scan_lds[kSmallWaves];
+  __shared__ uint32_t n_long, n_chunks, n_multi;
+  const int n = (int)a.n;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const auto sum = [](uint32_t x, uint32_t y) { return x + y; };
+  const auto largest = [](uint32_t x, uint32_t y) { return x > y ? x : y; };
+  uint32_t total;
+  if (tid == 0) n_long = n_chunks = n_multi = 0;
+
+  // (1) every bag that has entries leaves its number (plus one) at its first entry; the largest one up to an entry is its bag
+  for (int i = tid; i < kSmallSort; i += kSmallBlock) spay[i] = 0;
+  __syncthreads();
+  for (int b = tid; b < (int)a.nbags; b += kSmallBlock) {
+    const int e0 = a.offsets[b], e1 = a.offsets[b + 1];
+    if (e0 < e1) spay[e0] = (uint32_t)b + 1u;
+  }
+  __syncthreads();
+  {
+    uint32_t bag[kSmallItems], run = 0;
+#pragma unroll
+    for (int j = 0; j < kSmallItems; ++j) { run = largest(run, spay[tid * kSmallItems + j]); bag[j] = run; }
+    const uint32_t before = small_excl_scan(run, scan_lds, total, largest);
+#pragma unroll
+    for (int j = 0; j < kSmallItems; ++j) {
+      const int e = tid * kSmallItems + j;
+      bag[j] = largest(bag[j], before) - 1u;
+      if (e < n) {
+        const int r = a.rows[e];
+        skey[e] = r >= 0 ? (uint32_t)r : a.missing;
+        spay[e] = kHasVals ? (uint32_t)e : bag[j];
+        if (kHasVals) a.bag_of[e] = (int32_t)bag[j];
+      }
+    }
+  }
+
+  // (2) a wave owns kSmallItems * 64 consecutive items and walks them in rounds of 64
+  const unsigned long long lane_lt = (1ull << lane) - 1ull;
+  const int npass = (bits + kSmallBits - 1) / kSmallBits, per = (bits + npass - 1) / npass;
+  for (int p = 0; p < npass; ++p) {
+    const int shift = p * per, b = min(per, bits - shift);
+    const uint32_t radix = 1u << b, mask = radix - 1u;
+    for (int i = tid; i < kSmallWaves << kSmallBits; i += kSmallBlock) (&cnt[0][0])[i] = 0;
+    __syncthreads();                                 // the items are in place, the counters clear
+    uint32_t key[kSmallItems], pay[kSmallItems], rank[kSmallItems];
+#pragma unroll
+    for (int r = 0; r < kSmallItems; ++r) {
+      const int i = (wave * kSmallItems + r) * kWave + lane;
+      const bool live = i < n;
+      key[r] = live ? skey[i] : 0u;
+      pay[r] = live ? spay[i] : 0u;
+      const uint32_t d = (key[r] >> shift) & mask;
+      unsigned long long peers = __ballot(live);
+      for (int bit = 0; bit < b; ++bit) {
+        const bool one = (d >> bit) & 1u;
+        const unsigned long long bal = __ballot(one);
+        peers &= one ? bal : ~bal;
+      }
+      const uint32_t earlier = (uint32_t)__popcll(peers & lane_lt);
+      uint32_t prev = 0;
+      if (live) prev = cnt[wave][d];
+      __builtin_amdgcn_wave_barrier();               // every lane has read its counter before the group leaders write
+      if (live && earlier == 0) cnt[wave][d] = prev + (uint32_t)__popcll(peers);
+      __builtin_amdgcn_wave_barrier();
+      rank[r] = prev + earlier;
+    }
+    __syncthreads();
+    uint32_t of_digit = 0;                           // thread d: the digit's items; its counters become starts inside the digit
+    if (tid < (int)radix) {
+#pragma unroll
+      for (int w = 0; w < kSmallWaves; ++w) {
+        const uint32_t c = cnt[w][tid];
+        cnt[w][tid] = of_digit;
+        of_digit += c;
+      }
+    }
+    const uint32_t start = small_excl_scan(of_digit, scan_lds, total, sum);
+    if (tid < (int)radix) {
+#pragma unroll
+      for (int w = 0; w < kSmallWaves; ++w) cnt[w][tid] += start;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kSmallItems; ++r) {
+      const int i = (wave * kSmallItems + r) * kWave + lane;
+      if (i < n) {
+        const uint32_t at = cnt[wave][(key[r] >> shift) & mask] + rank[r];
+        skey[at] = key[r];
+        spay[at] = pay[r];
+      }
+    }
+    __syncthreads();
+  }
+
+  // (3) segment heads, in the order of the items
+  for (int i = tid; i < n; i += kSmallBlock) pay_out[i] = spay[i];
+  uint32_t key[kSmallItems], heads = 0;
+  const int i0 = tid * kSmallItems;
+  uint32_t prev = i0 > 0 && i0 <= n ? skey[i0 - 1] : 0xFFFFFFFFu;
+  const uint32_t first_prev = prev;
+#pragma unroll
+  for (int j = 0; j < kSmallItems; ++j) {
+    key[j] = i0 + j < n ? skey[i0 + j] : a.missing;
+    heads += (key[j] != a.missing && (i0 + j == 0 || key[j] != prev)) ? 1u : 0u;
+    prev = key[j];
+  }
+  uint32_t U;
+  uint32_t u = small_excl_scan(heads, scan_lds, U, sum);   // ends with a barrier: every key is in registers, skey may go
+  prev = first_prev;
+#pragma unroll
+  for (int j = 0; j < kSmallItems; ++j) {
+    const int i = i0 + j;
+    if (i < n) {
+      if (key[j] != a.missing && (i == 0 || key[j] != prev)) {
+        a.uniq_rows[u] = (int32_t)key[j];
+        a.first_pay[u] = spay[i];
+        a.seg_off[u] = i;
+        skey[u] = (uint32_t)i;                       // and for the split below
+        ++u;
+      }
+      // end of the last segment: first entry without a row, or the end of the array
+      const bool end_here = key[j] == a.missing && (i == 0 || prev != a.missing), end_after = i == n - 1 && key[j] != a.missing;
+      if (end_here || end_after) {
+        const int end = end_here ? i : n;
+        a.seg_off[U] = end;
+        skey[U] = (uint32_t)end;
+      }
+      prev = key[j];
+    }
+  }
+  __syncthreads();
+
+  // long segments and their chunks; their order is irrelevant to the results
+  for (uint32_t v = tid; v < U; v += kSmallBlock) {
+    const uint32_t len = skey[v + 1] - skey[v];
+    if (len <= (uint32_t)kShortMax) continue;
+    const uint32_t nch = (len + kChunk - 1) / kChunk;
+    const uint32_t j = atomicAdd(&n_long, 1u), c0 = atomicAdd(&n_chunks, nch);
+    a.long_seg[j] = (int32_t)v;
+    a.long_c0[j] = c0;
+    if (nch > 1) a.multi_seg[atomicAdd(&n_multi, 1u)] = (int32_t)j;
+    for (uint32_t c = 0; c < nch; ++c) a.chunk_owner[c0 + c] = (int32_t)j;
+  }
+  static_assert(kSmallSort / kChunk <= kMidFan, "no segment here has enough chunks for pre-summed groups");
+  __syncthreads();
+  if (tid == 0) {
+    heads_bookkeeping(a, U);
+    a.ctrl->n_long = n_long;
+    a.ctrl->n_chunks = n_chunks;
+    a.ctrl->n_multi = n_multi;
+  }
+}
+
 // Gradient sums of the sorted entries [i0, i1) seen by the lane holding columns 4*sub..4*sub+3:
 //   s1 = sum x*(g_fm[b]*A_sum[b,:] + g_pool[bag,:]),  s2 = sum x*x*g_fm[b],  gw = sum x*g_lr[b]
 // Accumulated in double: the first Adagrad step divides the merged gradient by |G| + eps, so a
@@ -861,6 +1053,14 @@ int sort_stage(des_table *t, BwdArgs &a, const Layout &L, hipStream_t s) {
   char *ws = t->ws;
   const int64_t n = a.n;
   uint32_t *key_a = (uint32_t *)(ws + L.key_a), *pay_a = (uint32_t *)(ws + L.pay_a);
+  const int bits = bits_for((uint64_t)t->cfg.capacity_rows);
+  if (n <= kSmallSort && a.nbags <= kSmallBags) {
+    ProfScope ps(KID_SORT_SCATTER, s);
+    a.pay_sorted = pay_a;
+    if (a.vals) hipLaunchKernelGGL(k_sort_small<true>, dim3(1), dim3(kSmallBlock), 0, s, a, pay_a, bits);
+    else hipLaunchKernelGGL(k_sort_small<false>, dim3(1), dim3(kSmallBlock), 0, s, a, pay_a, bits);
+    return 0;
+  }
   {
     ProfScope ps(KID_EXPAND, s);
     const dim3 grid(blocks_for(a.nbags, 1 << 20)), block(kBlock);     // one workgroup per kBlock bags
@@ -868,7 +1068,8 @@ int sort_stage(des_table *t, BwdArgs &a, const Layout &L, hipStream_t s) {
     else hipLaunchKernelGGL(k_expand<false>, grid, block, 0, s, a, key_a, pay_a);
   }
   SortBuffers sb{key_a, (uint32_t *)(ws + L.key_b), pay_a, (uint32_t *)(ws + L.pay_b)};
-  const int side = radix_sort_u32_pairs(sb, n, bits_for((uint64_t)t->cfg.capacity_rows), ws + L.sort_scratch, s);
+  const int side = radix_sort_u32_pairs(sb, n, bits, ws + L.sort_scratch,
+                                        (uint32_t *)(ws + L.uniq_rows), s);
   a.key_sorted = (uint32_t *)(ws + (side ? L.key_b : L.key_a));
   a.pay_sorted = (uint32_t *)(ws + (side ? L.pay_b : L.pay_a));
   {
@@ -887,7 +1088,8 @@ int sort_stage(des_table *t, BwdArgs &a, const Layout &L, hipStream_t s) {
     ProfScope ps(KID_CLASSIFY, s);
     hipLaunchKernelGGL(k_classify, dim3((unsigned)((n + kHeadTile - 1) / kHeadTile)), dim3(kBlock), 0, s, a);
     const int64_t max_long = n / (kShortMax + 1) + 1;
-    hipLaunchKernelGGL(k_chunk_owner, dim3((unsigned)(max_long < 65536 ? max_long : 65536)), dim3(kBlock), 0, s, a);
+    // at most eight workgroups per CU: 65536 of them, nearly all without a segment, took 17 us to start and end
+    hipLaunchKernelGGL(k_chunk_owner, dim3((unsigned)(max_long < 2048 ? max_long : 2048)), dim3(kBlock), 0, s, a);
   }
   return side;
 }

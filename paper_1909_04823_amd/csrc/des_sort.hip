@@ -15,6 +15,8 @@ constexpr int kSortTile = kBlock * kSortItems;
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kMaxDigitBits = 9;                    // widest radix digit of one pass
 constexpr int kMaxRadix = 1 << kMaxDigitBits;
+constexpr int kFewItemsBits = 6;                    // widest digit for fewer than kSortTotals items, whose callers have 256 bytes of `totals`
+static_assert(kMaxRadix <= kSortTotals && (1 << kFewItemsBits) * 4 <= 256, "the totals of a digit fit");
 
 template <typename T>
 __device__ inline T wave_inclusive_scan(T v) {
@@ -140,47 +142,105 @@ void exclusive_scan(T *data, int64_t n, T *total_out, void *scratch, hipStream_t
 // Radix sort.  One workgroup owns a tile of kSortTile consecutive items; wave w owns the w-th
 // quarter of the tile and walks it in rounds of 64, so "wave, round, lane" is item order.
 
-// Digit counts of kHistTiles consecutive tiles per workgroup: all keys of the workgroup are requested before the
-// first is counted, and the counts of one digit leave as one contiguous run of kHistTiles values.  Pays once
-// there are enough tiles to fill the chip with such workgroups (0.84 -> 0.74 ms over four passes of 1.05e8
-// keys; a loss at 8e6 keys, which keep one tile per workgroup).
-constexpr int kHistManyTiles = 8192;
-template <typename KeyT, int kHistTiles>
-__global__ __launch_bounds__(kBlock) void k_radix_hist(const KeyT *__restrict__ keys, int64_t n,
-                                                        const long long *__restrict__ n_dev, int shift, int bits,
-                                                        uint32_t *__restrict__ hist, int nblocks) {
-  __shared__ uint32_t cnt[kHistTiles][kMaxRadix];
-  const int64_t n_eff = n_dev ? (int64_t)min((long long)n, *n_dev) : n;
+// Digit counts of one tile per workgroup, one row of `hist`, written here and read by the scatter pass side by side.
+// Neighbouring lanes count into kCopies different counters of a digit: a hot row (18 % of a skewed batch) brings ten
+// equal digits per wave, and LDS adds to equal addresses run one after the other.  Three passes over 8.2e6 keys, Zipf(1.2):
+// 73 -> 36 us with four copies (82 with counts in one row per digit); 1.05e8 keys, half of them uniform: 516 -> 341 us.
+constexpr int kCopies = 4;
+template <typename KeyT>
+__global__ __launch_bounds__(kBlock) void k_radix_hist(const KeyT *__restrict__ keys, int64_t n, int shift, int bits,
+                                                        uint32_t *__restrict__ hist) {
+  __shared__ uint4 cnt[kMaxRadix];
+  static_assert(kCopies == 4, "one uint4 per digit");
   const int radix = 1 << bits;
-  const int blk0 = blockIdx.x * kHistTiles;
-  const uint32_t mask = (1u << bits) - 1u;
-  KeyT key[kHistTiles][kSortItems];
+  const uint32_t mask = (1u << bits) - 1u, copy = threadIdx.x % kCopies;
+  const int64_t base = (int64_t)blockIdx.x * kSortTile;
+  KeyT key[kSortItems];
   // the keys are requested before the counters are cleared, so that the barrier is passed while they travel
 #pragma unroll
-  for (int j = 0; j < kHistTiles; ++j) {
-    const int64_t base = (int64_t)(blk0 + j) * kSortTile;
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
-      const int64_t idx = base + (int64_t)i * kBlock + threadIdx.x;
-      key[j][i] = idx < n_eff ? keys[idx] : (KeyT)0;
-    }
+  for (int i = 0; i < kSortItems; ++i) {
+    const int64_t idx = base + (int64_t)i * kBlock + threadIdx.x;
+    key[i] = idx < n ? keys[idx] : (KeyT)0;
   }
-  for (int i = threadIdx.x; i < kHistTiles * kMaxRadix; i += kBlock) (&cnt[0][0])[i] = 0;
+  for (int d = threadIdx.x; d < radix; d += kBlock) cnt[d] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
+  uint32_t *counters = reinterpret_cast<uint32_t *>(cnt);
 #pragma unroll
-  for (int j = 0; j < kHistTiles; ++j) {
-    const int64_t base = (int64_t)(blk0 + j) * kSortTile;
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
-      const int64_t idx = base + (int64_t)i * kBlock + threadIdx.x;
-      if (idx < n_eff) atomicAdd(&cnt[j][(uint32_t)(key[j][i] >> shift) & mask], 1u);
-    }
+  for (int i = 0; i < kSortItems; ++i) {
+    const int64_t idx = base + (int64_t)i * kBlock + threadIdx.x;
+    if (idx < n) atomicAdd(&counters[((uint32_t)(key[i] >> shift) & mask) * kCopies + copy], 1u);
   }
   __syncthreads();
-  const int tiles = min(kHistTiles, nblocks - blk0);
-  for (int i = threadIdx.x; i < radix * kHistTiles; i += kBlock) {
-    const int d = i / kHistTiles, j = i % kHistTiles;
-    if (j < tiles) hist[(size_t)d * nblocks + blk0 + j] = cnt[j][d];
+  for (int d = threadIdx.x; d < radix; d += kBlock) {
+    const uint4 c = cnt[d];
+    hist[(size_t)blockIdx.x * radix + d] = (c.x + c.y) + (c.z + c.w);
+  }
+}
+
+// Turns the counts into each tile's offset inside its digit (exclusive sum over the tiles before it, in place) and leaves the
+// digits' totals.  A workgroup takes kScanDigits digits of one stretch of kScanStretch tiles; its kScanGroups groups of as
+// many lanes take consecutive runs of tiles, twice: once for their sums, which a wave per digit scans, once to write the
+// offsets.  With several stretches k_radix_stretch has left the stretches' sums.
+constexpr int kScanDigits = 16;
+constexpr int kScanBlock = 1024;
+constexpr int kScanGroups = kScanBlock / kScanDigits;
+constexpr int kScanFlight = 16;                        // rows a thread requests together
+constexpr int kScanStretch = kScanGroups * kScanFlight;
+
+__device__ inline uint32_t scan_load(const uint32_t *p, int lo, int hi, int radix, uint32_t (&v)[kScanFlight]) {
+  uint32_t sum = 0;
+#pragma unroll
+  for (int j = 0; j < kScanFlight; ++j) v[j] = lo + j < hi ? p[(size_t)(lo + j) * radix] : 0u;
+#pragma unroll
+  for (int j = 0; j < kScanFlight; ++j) sum += v[j];
+  return sum;
+}
+
+// sums of the stretches: grid (digit groups, stretches)
+__global__ __launch_bounds__(kScanBlock) void k_radix_stretch(const uint32_t *__restrict__ hist, int nblocks, int radix,
+                                                               uint32_t *__restrict__ stretch_sums) {
+  __shared__ uint32_t total[kScanDigits];
+  const int col = threadIdx.x % kScanDigits, grp = threadIdx.x / kScanDigits, d = blockIdx.x * kScanDigits + col;
+  if (threadIdx.x < kScanDigits) total[threadIdx.x] = 0;
+  __syncthreads();
+  const int lo = blockIdx.y * kScanStretch + grp * kScanFlight;
+  uint32_t v[kScanFlight];
+  if (d < radix) atomicAdd(&total[col], scan_load(hist + d, lo, nblocks, radix, v));
+  __syncthreads();
+  if (grp == 0 && d < radix) stretch_sums[(size_t)blockIdx.y * radix + d] = total[col];
+}
+
+__global__ __launch_bounds__(kScanBlock) void k_radix_scan(uint32_t *__restrict__ hist, int nblocks, int radix,
+                                                            const uint32_t *__restrict__ stretch_sums,
+                                                            uint32_t *__restrict__ totals) {
+  __shared__ uint32_t sums[kScanDigits][kScanGroups + 1];
+  static_assert(kScanGroups == kWave && kScanDigits == kScanBlock / kWave, "one wave scans one digit's groups");
+  const int col = threadIdx.x % kScanDigits, grp = threadIdx.x / kScanDigits, d = blockIdx.x * kScanDigits + col;
+  const bool live = d < radix;
+  uint32_t *p = hist + (live ? d : 0);
+  const int lo = blockIdx.y * kScanStretch + grp * kScanFlight;
+  uint32_t v[kScanFlight];
+  sums[col][grp] = scan_load(p, lo, nblocks, radix, v);
+  __syncthreads();
+  {
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, dw = blockIdx.x * kScanDigits + wave;
+    uint32_t before = 0;                               // the digit's items in earlier stretches
+    if (dw < radix)
+      for (int st = lane; st < (int)blockIdx.y; st += kWave) before += stretch_sums[(size_t)st * radix + dw];
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) before += __shfl_xor(before, o, kWave);
+    const uint32_t mine = sums[wave][lane], inc = wave_inclusive_scan(mine) + before;
+    __builtin_amdgcn_wave_barrier();
+    sums[wave][lane] = inc - mine;
+    if (lane == kWave - 1 && dw < radix && blockIdx.y == gridDim.y - 1) totals[dw] = inc;
+  }
+  __syncthreads();
+  uint32_t run = sums[col][grp];
+  if (!live) return;
+#pragma unroll
+  for (int j = 0; j < kScanFlight; ++j) {
+    if (lo + j < nblocks) p[(size_t)(lo + j) * radix] = run;
+    run += v[j];
   }
 }
 
@@ -193,19 +253,18 @@ template <typename KeyT, bool kHasPayload>
 __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KeyT *__restrict__ keys_in,
                                                            const uint32_t *__restrict__ pay_in,
                                                            KeyT *__restrict__ keys_out, uint32_t *__restrict__ pay_out,
-                                                           int64_t n, const long long *__restrict__ n_dev, int shift,
-                                                           int bits, const uint32_t *__restrict__ offsets, int nblocks) {
+                                                           int64_t n, int shift, int bits,
+                                                           const uint32_t *__restrict__ offsets,
+                                                           const uint32_t *__restrict__ totals) {
   __shared__ uint32_t cnt[kWavesPerBlock][kMaxRadix];   // per wave and digit: count, then start inside the digit's run
   __shared__ uint32_t dig_base[kMaxRadix];              // first sorted index of the digit inside the tile
   __shared__ uint32_t gofs[kMaxRadix];                  // where the tile's run of the digit starts in the output
-  __shared__ uint32_t scan_lds[kWavesPerBlock];
+  __shared__ unsigned long long scan_lds[kWavesPerBlock];
   __shared__ KeyT skey[kSortTile];                      // the sorted keys; afterwards reused for the payloads
   static_assert(sizeof(KeyT) >= sizeof(uint32_t), "payloads are staged in the key buffer");
-  const int64_t n_eff = n_dev ? (int64_t)min((long long)n, *n_dev) : n;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int64_t tile = (int64_t)blockIdx.x * kSortTile;
-  if (tile >= n_eff) return;                         // uniform per workgroup
-  const int tile_n = (int)min((int64_t)kSortTile, n_eff - tile);
+  const int tile_n = (int)min((int64_t)kSortTile, n - tile);
   const int radix = 1 << bits;
   const uint32_t mask = (1u << bits) - 1u;
   const unsigned long long lane_lt = (1ull << lane) - 1ull;
@@ -217,21 +276,30 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KeyT *__restrict
 #pragma unroll
   for (int r = 0; r < kSortItems; ++r) {
     const int64_t idx = wbase + r * kWave + lane;
-    const bool live = idx < n_eff;
+    const bool live = idx < n;
     key[r] = live ? keys_in[idx] : (KeyT)0;
     if (kHasPayload) pay[r] = live ? pay_in[idx] : 0u;
   }
-  for (int d = threadIdx.x; d < radix; d += kBlock) {
+  // two digits per thread (kMaxRadix <= 2 * kBlock): the tile's offset inside the digit and the digit's total
+  static_assert(kMaxRadix <= 2 * kBlock, "two digits per thread");
+  uint32_t in_digit[2] = {0u, 0u};
+  unsigned long long tot[2] = {0ull, 0ull};
 #pragma unroll
-    for (int w = 0; w < kWavesPerBlock; ++w) cnt[w][d] = 0;
-    gofs[d] = offsets[(size_t)d * nblocks + blockIdx.x];
+  for (int j = 0; j < 2; ++j) {
+    const int d = threadIdx.x * 2 + j;
+    if (d < radix) {
+      in_digit[j] = offsets[(size_t)blockIdx.x * radix + d];
+      tot[j] = (unsigned long long)totals[d] << 32;
+#pragma unroll
+      for (int w = 0; w < kWavesPerBlock; ++w) cnt[w][d] = 0;
+    }
   }
   __syncthreads();
 
 #pragma unroll
   for (int r = 0; r < kSortItems; ++r) {
     const int64_t idx = wbase + r * kWave + lane;
-    const bool live = idx < n_eff;
+    const bool live = idx < n;
     const uint32_t d = (uint32_t)(key[r] >> shift) & mask;
     // lanes of this wave holding the same digit
     unsigned long long peers = __ballot(live);
@@ -251,10 +319,8 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KeyT *__restrict
     rank[r] = prev + before;
   }
   __syncthreads();
-  // per digit: exclusive prefix over the waves; then exclusive prefix of the digit totals over the digits
-  // (two digits per thread: kMaxRadix <= 2 * kBlock)
-  static_assert(kMaxRadix <= 2 * kBlock, "two digits per thread");
-  uint32_t tot[2] = {0u, 0u};
+  // per digit: exclusive prefix over the waves; then one exclusive prefix over the digits of both the tile's counts (low
+  // half) and the array's (high half): where the digit starts in the tile and where in the output
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int d = threadIdx.x * 2 + j;
@@ -266,20 +332,27 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KeyT *__restrict
         cnt[w][d] = run;
         run += c;
       }
-      tot[j] = run;
+      tot[j] += run;
     }
   }
-  uint32_t total;
-  const uint32_t ex = block_exclusive_scan<uint32_t>(tot[0] + tot[1], scan_lds, total);
-  if (threadIdx.x * 2 < radix) dig_base[threadIdx.x * 2] = ex;
-  if (threadIdx.x * 2 + 1 < radix) dig_base[threadIdx.x * 2 + 1] = ex + tot[0];
+  unsigned long long total;
+  unsigned long long ex = block_exclusive_scan<unsigned long long>(tot[0] + tot[1], scan_lds, total);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int d = threadIdx.x * 2 + j;
+    if (d < radix) {
+      dig_base[d] = (uint32_t)ex;
+      gofs[d] = (uint32_t)(ex >> 32) + in_digit[j];
+    }
+    ex += tot[j];
+  }
   __syncthreads();
   uint32_t li[kSortItems];
 #pragma unroll
   for (int r = 0; r < kSortItems; ++r) {
     const int64_t idx = wbase + r * kWave + lane;
     li[r] = 0;
-    if (idx < n_eff) {
+    if (idx < n) {
       const uint32_t d = (uint32_t)(key[r] >> shift) & mask;
       li[r] = dig_base[d] + cnt[wave][d] + rank[r];
       skey[li[r]] = key[r];
@@ -305,7 +378,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KeyT *__restrict
     __syncthreads();                                   // all keys read before the buffer is overwritten
 #pragma unroll
     for (int r = 0; r < kSortItems; ++r)
-      if (wbase + r * kWave + lane < n_eff) spay[li[r]] = pay[r];
+      if (wbase + r * kWave + lane < n) spay[li[r]] = pay[r];
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kOut; ++j) {
@@ -318,13 +391,15 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KeyT *__restrict
 inline int64_t sort_blocks(int64_t n) { return (n + kSortTile - 1) / kSortTile; }
 
 template <typename KeyT, bool kHasPayload>
-int radix_sort(SortBuffers buf, int64_t n, const long long *n_dev, int bits, void *scratch, hipStream_t s,
-               int kid_hist, int kid_scan, int kid_scatter) {
+int radix_sort(SortBuffers buf, int64_t n, int bits, void *scratch, uint32_t *totals, hipStream_t s, int kid_hist, int kid_scan,
+               int kid_scatter) {
   if (n <= 0 || bits <= 0) return 0;
   const int nblocks = (int)sort_blocks(n);
   uint32_t *hist = (uint32_t *)scratch;
-  void *scan_scratch = (char *)scratch + align_up((size_t)kMaxRadix * nblocks * sizeof(uint32_t), 256);
-  const int npass = (bits + kMaxDigitBits - 1) / kMaxDigitBits;
+  // the sums of all stretches but the last, behind `hist` (see sort_scratch_bytes)
+  uint32_t *stretch_sums = (uint32_t *)((char *)scratch + align_up((size_t)kMaxRadix * nblocks * sizeof(uint32_t), 256));
+  const int widest = n >= kSortTotals ? kMaxDigitBits : kFewItemsBits;
+  const int npass = (bits + widest - 1) / widest;
   const int per = (bits + npass - 1) / npass;
   KeyT *kin = (KeyT *)buf.keys_a, *kout = (KeyT *)buf.keys_b;
   uint32_t *pin = buf.pay_a, *pout = buf.pay_b;
@@ -334,20 +409,19 @@ int radix_sort(SortBuffers buf, int64_t n, const long long *n_dev, int bits, voi
     const int b = (bits - shift) < per ? (bits - shift) : per;
     {
       ProfScope ps(kid_hist, s);
-      if (nblocks >= kHistManyTiles)
-        hipLaunchKernelGGL((k_radix_hist<KeyT, 4>), dim3((nblocks + 3) / 4), dim3(kBlock), 0, s, kin, n, n_dev, shift, b, hist,
-                           nblocks);
-      else
-        hipLaunchKernelGGL((k_radix_hist<KeyT, 1>), dim3(nblocks), dim3(kBlock), 0, s, kin, n, n_dev, shift, b, hist, nblocks);
+      hipLaunchKernelGGL(k_radix_hist<KeyT>, dim3(nblocks), dim3(kBlock), 0, s, kin, n, shift, b, hist);
     }
     {
       ProfScope ps(kid_scan, s);
-      exclusive_scan<uint32_t>(hist, (int64_t)(1 << b) * nblocks, nullptr, scan_scratch, s);
+      const dim3 grid(((1 << b) + kScanDigits - 1) / kScanDigits, (nblocks + kScanStretch - 1) / kScanStretch);
+      if (grid.y > 1)
+        hipLaunchKernelGGL(k_radix_stretch, dim3(grid.x, grid.y - 1), dim3(kScanBlock), 0, s, hist, nblocks, 1 << b, stretch_sums);
+      hipLaunchKernelGGL(k_radix_scan, grid, dim3(kScanBlock), 0, s, hist, nblocks, 1 << b, stretch_sums, totals);
     }
     {
       ProfScope ps(kid_scatter, s);
       hipLaunchKernelGGL((k_radix_scatter<KeyT, kHasPayload>), dim3(nblocks), dim3(kBlock), 0, s, kin, pin, kout, pout,
-                         n, n_dev, shift, b, hist, nblocks);
+                         n, shift, b, hist, totals);
     }
     KeyT *tk = kin; kin = kout; kout = tk;
     uint32_t *tp = pin; pin = pout; pout = tp;
@@ -363,8 +437,12 @@ size_t scan_scratch_bytes(int64_t n) {
   return align_up((size_t)(nb + 1) * sizeof(unsigned long long), 256);
 }
 
+// One row of counts per tile, then either the sums of the stretches (kMaxRadix values per kScanStretch tiles, the last
+// stretch left out: less than two bytes per tile) or the scratch of a device-wide scan, which the callers run after the sort.
 size_t sort_scratch_bytes(int64_t n) {
   const int64_t nblocks = sort_blocks(n > 0 ? n : 1);
+  static_assert(kMaxRadix * sizeof(uint32_t) * kScanTile <= kMaxRadix * sizeof(unsigned long long) * kScanStretch,
+                "a stretch's row of sums fits where its tiles' counts would have their scan scratch");
   return align_up((size_t)kMaxRadix * nblocks * sizeof(uint32_t), 256) + scan_scratch_bytes(kMaxRadix * nblocks);
 }
 
@@ -377,8 +455,8 @@ void exclusive_scan_u64(unsigned long long *data, int64_t n, unsigned long long 
   exclusive_scan<unsigned long long>(data, n, total_out, scratch, s);
 }
 
-int radix_sort_u32_pairs(SortBuffers buf, int64_t n, int bits, void *scratch, hipStream_t s) {
-  return radix_sort<uint32_t, true>(buf, n, nullptr, bits, scratch, s, KID_SORT_HIST, KID_SORT_SCAN, KID_SORT_SCATTER);
+int radix_sort_u32_pairs(SortBuffers buf, int64_t n, int bits, void *scratch, uint32_t *totals, hipStream_t s) {
+  return radix_sort<uint32_t, true>(buf, n, bits, scratch, totals, s, KID_SORT_HIST, KID_SORT_SCAN, KID_SORT_SCATTER);
 }
 
 }  // namespace des

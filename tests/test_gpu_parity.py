@@ -790,3 +790,40 @@ def test_merge_rows_of_more_than_64_chunks(oracle, des, D, with_vals):
         p.check_weights("giant segments adagrad")
     finally:
         p.close()
+
+
+# ------------------------------------------------- one-workgroup sort and its neighbours ---------
+@pytest.mark.parametrize("n,B,F,capacity,vals", [
+    (1, 1, 1, 1, False), (33, 3, 5, 300, True), (513, 40, 3, 1 << 16, False), (4095, 7, 9, 20000, True),
+    (4096, 512, 8, 1 << 22, False),            # the largest batch of the one-workgroup sort
+    (4096, 65536, 1, 5000, True),              # ... with the most bags, nearly all empty
+    (4097, 512, 8, 1 << 22, False),            # one entry more: two tiles
+    (300, 65537, 1, 5000, False),              # one bag more, and fewer entries than a digit has values
+])
+def test_row_sort_at_its_size_limits(oracle, des, n, B, F, capacity, vals):
+    """Merged order, counts and updates of small batches: empty bags first, last and in runs, one row that holds a third of
+    the entries (long segments, several chunks), IDs without a row."""
+    rng = np.random.default_rng(n + B)
+    D = 8
+    p = Pair(oracle, des, D, capacity, 3, 0, des.OPT_ADAGRAD, seed=5, max_n=max(n, 64))
+    try:
+        import torch
+        known = synth.scramble64(np.arange(1, min(capacity, 3000) + 1, dtype=np.uint64))
+        p.ot.insert(known)
+        for lo in range(0, known.size, p.gt.max_n):                          # the workspace is no larger than the batch needs
+            p.gt.insert(dev(known[lo:lo + p.gt.max_n], torch))
+        pick = rng.integers(0, known.size, n)
+        pick[rng.random(n) < 0.33] = 0
+        keys = known[pick]
+        keys[rng.random(n) < 0.1] = np.uint64(12345)                        # not in the table
+        cuts = np.sort(rng.integers(0, n + 1, B * F - 1)) if B * F > 1 else np.zeros(0, np.int64)
+        cuts[: cuts.size // 8] = 0
+        cuts[cuts.size - cuts.size // 8:] = n
+        offsets = np.concatenate([[0], np.sort(cuts), [n]]).astype(np.int32)
+        batch = synth.Batch(B, F, keys, offsets, rng.uniform(0.5, 2, n).astype(np.float32) if vals else None)
+        p.find(batch, insert=False)
+        g = lambda *s: (rng.standard_normal(s) / 64).astype(np.float32)
+        p.backward(batch, g(B), g(B), g(B, D), g(B, F, D))
+        p.check_weights("after update")
+    finally:
+        p.close()
