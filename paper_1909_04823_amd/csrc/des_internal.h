@@ -31,6 +31,7 @@ struct Ctrl {
   int pad[4];
   unsigned long long first_bad;   // verdict word of des_batch_validate
   long long n_multi;       // long segments of more than one chunk
+  unsigned long long first_dropped;   // of the running compaction
   long long n_groups;      // groups of chunk partials that are pre-summed for the segments of very many chunks
 };
 static_assert(sizeof(Ctrl) <= 256, "control block must fit its reserved 256 bytes");

@@ -186,3 +186,30 @@ def test_compact_keep_all_and_keep_none(des):
     again = t.find(keys[:100], des.MISS_INSERT)
     assert torch.equal(again, torch.arange(100, dtype=torch.int32, device="cuda")) and t.size() == 100
     t.close()
+
+
+@pytest.mark.parametrize("dropped", [[0], [19999], [5000], [5000, 19999], list(range(15000, 20000)), list(range(4096, 8192)), [0, 19999],
+                                     list(range(1, 20000))])
+def test_compact_moves_only_rows_behind_the_first_drop(des, dropped):
+    """Drops at either end, a hole of one chunk, a tail, all but the first row: every array and every lookup afterwards."""
+    import torch
+    n, D = 20000, 8
+    t = des.Table(D, n, 2, init_seed=3, max_n=1 << 15, state_arrays=(1, 2))
+    keys = torch.arange(1, n + 1, dtype=torch.int64, device="cuda") * 7919
+    t.insert(keys)
+    names = ("emb", "w", "acc_emb", "acc_w", "acc2_w", "row_keys")
+    for i, name in enumerate(names[2:5]):
+        getattr(t, name).copy_(torch.rand(getattr(t, name).shape, generator=torch.Generator().manual_seed(i)))
+    aux = torch.arange(n, dtype=torch.int32, device="cuda")
+    before = {name: getattr(t, name)[:n].clone() for name in names}
+    keep = torch.ones(n, dtype=torch.uint8, device="cuda")
+    keep[torch.tensor(dropped, device="cuda")] = 0
+    sel = torch.nonzero(keep).flatten()
+    assert t.compact(keep, torch.empty(4096 * D * 4, dtype=torch.uint8, device="cuda"), aux=aux) == sel.numel() == t.size()
+    for name in names:
+        assert torch.equal(getattr(t, name)[:sel.numel()], before[name][sel]), name
+    assert torch.equal(aux[:sel.numel()], sel.int())
+    want = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    want[sel] = torch.arange(sel.numel(), dtype=torch.int32, device="cuda")
+    assert torch.equal(t.find(keys, des.MISS_ZERO), want) and t.status() == 0
+    t.close()
