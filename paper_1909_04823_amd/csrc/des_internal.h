@@ -32,6 +32,7 @@ struct Ctrl {
   unsigned long long first_bad;   // verdict word of des_batch_validate
   long long n_multi;       // long segments of more than one chunk
   unsigned long long first_dropped;   // of the running compaction
+  long long base_rows;     // rows in use before the running insert
   long long n_groups;      // groups of chunk partials that are pre-summed for the segments of very many chunks
 };
 static_assert(sizeof(Ctrl) <= 256, "control block must fit its reserved 256 bytes");
@@ -46,7 +47,7 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // ---- per-kernel timing (process-wide collector) ----------------------------------------
 enum KernelId {
-  KID_PROBE = 0, KID_ASSIGN, KID_PATCH, KID_INIT_ROWS,
+  KID_PROBE = 0, KID_ASSIGN, KID_FINISH_ROWS,
   KID_FORWARD, KID_POOL_DENSE, KID_AGGREGATE, KID_FM_FINALIZE,
   KID_EXPAND, KID_SORT_HIST, KID_SORT_SCAN, KID_SORT_SCATTER,
   KID_HEADS, KID_CLASSIFY, KID_SHORT_UPDATE, KID_LONG_PARTIAL, KID_LONG_FINAL, KID_EXPORT,

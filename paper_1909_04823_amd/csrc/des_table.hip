@@ -23,6 +23,9 @@ namespace {
 
 constexpr int kFlagItems = 8;                       // entries per thread in the numbering kernels
 constexpr int kFlagTile = kBlock * kFlagItems;
+constexpr uint32_t kPendingBit = 0x80000000u;       // in a tile's count: the tile has entries whose row is not known yet
+constexpr int kSmallInsert = 4096;                  // up to this many entries one workgroup numbers the new rows
+constexpr int kSmallInsertBlock = 1024;
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int64_t kSelfPrefixTiles = 4096;          // up to this many tiles the numbering kernel sums the tile counts itself
 
@@ -39,78 +42,68 @@ __device__ inline Slot load_slot(const Slot *p) {
 
 // Pass A.  rows[e] = row (>= 0), kRowAbsent, or kRowPending for keys claimed in this call; for
 // pending entries slot_of[e] remembers the slot so later passes need not probe again.
-// A probe is one dependent chain (key -> hash -> slot), so every thread works on kProbeKeys keys at a time: all their
-// keys are requested, then all their first slots, and only then is each chain resolved (later slots of a collision
-// chain one by one; they mostly sit in the line already fetched).  That multiplies the random lines in flight.
-constexpr int kProbeKeys = 4;
+// A probe is one dependent chain (key -> hash -> slot -> perhaps the next slots, mostly of the line already fetched), and what
+// counts is how many chains are under way: one key per thread at full occupancy.  Four keys per thread, their first slots
+// requested together but their chains resolved in turn, need fewer threads and were slower (67 % load, Zipf-free lookups of
+// 6e3 / 1e6 / 1.6e7 keys in 4e6 rows: 10.1 / 38.5 / 377 against 7.1 / 27.9 / 316 us; 1e8 in 3e8 rows: 3.12 against 3.08 ms).
+// An inserting wave also leaves a bit per entry that is pending: the passes after it skip the tiles that have none.
 template <bool kInsert>
 __global__ __launch_bounds__(kBlock) void k_probe(Slot *__restrict__ slots, uint64_t slot_mask,
                                                    const uint64_t *__restrict__ keys, int64_t n,
                                                    int32_t *__restrict__ rows, Ctrl *__restrict__ ctrl,
-                                                   uint32_t *__restrict__ slot_of) {
+                                                   uint32_t *__restrict__ slot_of,
+                                                   unsigned long long *__restrict__ pending_bits) {
   // after a sticky error the table no longer grows: the call degrades to a pure lookup, so
   // rows[] is still fully written with valid rows or kRowAbsent
   const bool can_insert = kInsert && ctrl->status == 0;
-  const int64_t tile_stride = (int64_t)gridDim.x * kBlock * kProbeKeys;
-  for (int64_t tile = (int64_t)blockIdx.x * kBlock * kProbeKeys; tile < n; tile += tile_stride) {
-    uint64_t key[kProbeKeys], idx[kProbeKeys];
-    Slot first[kProbeKeys];
-#pragma unroll
-    for (int i = 0; i < kProbeKeys; ++i) {
-      const int64_t e = tile + (int64_t)i * kBlock + threadIdx.x;
-      key[i] = e < n ? keys[e] : kEmptyKey;
-    }
-#pragma unroll
-    for (int i = 0; i < kProbeKeys; ++i) {
-      idx[i] = mix64(key[i]) & slot_mask;
-      first[i].key = kEmptyKey; first[i].row = kRowAbsent; first[i].first = 0u;
-      if (key[i] != kEmptyKey) first[i] = load_slot(&slots[idx[i]]);
-    }
-#pragma unroll
-    for (int i = 0; i < kProbeKeys; ++i) {
-      const int64_t e = tile + (int64_t)i * kBlock + threadIdx.x;
-      if (e >= n) continue;
+  const int64_t stride = (int64_t)gridDim.x * kBlock;
+  for (int64_t tile = (int64_t)blockIdx.x * kBlock; tile < n; tile += stride) {
+    const int64_t e = tile + threadIdx.x;
+    bool pending = false;
+    if (e < n) {
+      const uint64_t k = keys[e];
       int32_t out = kRowAbsent;
-      if (key[i] == kEmptyKey) {                     // the reserved key is nobody's ID: absent, counted, nothing else is held up
+      if (k == kEmptyKey) {                          // the reserved key is nobody's ID: absent, counted, nothing else is held up
         atomicAdd(&ctrl->bad_keys, 1);
-        rows[e] = out;
-        continue;
-      }
-      const uint64_t k = key[i];
-      uint64_t at = idx[i];
-      Slot s = first[i];
-      bool done = false, pending = false;
-      for (uint64_t probe = 0; probe <= slot_mask && !done; ++probe) {
-        if (probe > 0) s = load_slot(&slots[at]);
-        if (s.key == k) {
-          // a negative row under a key is a claim of the running call, or the leftover of a
-          // call that failed: only a call that can insert resolves it
-          if (s.row >= 0) out = s.row; else pending = can_insert;
-          done = true;
-        } else if (s.key == kEmptyKey) {
-          if (!can_insert) {
+      } else {
+        uint64_t at = mix64(k) & slot_mask;
+        bool done = false;
+        for (uint64_t probe = 0; probe <= slot_mask && !done; ++probe) {
+          const Slot s = load_slot(&slots[at]);
+          if (s.key == k) {
+            // a negative row under a key is a claim of the running call, or the leftover of a
+            // call that failed: only a call that can insert resolves it
+            if (s.row >= 0) out = s.row; else pending = can_insert;
             done = true;
-          } else {
-            const unsigned long long old =
-                atomicCAS(reinterpret_cast<unsigned long long *>(&slots[at].key), kEmptyKey, k);
-            if (old == kEmptyKey || old == k) {   // claimed here, or by another entry of the same key
-              pending = true;
+          } else if (s.key == kEmptyKey) {
+            if (!can_insert) {
               done = true;
             } else {
-              at = (at + 1) & slot_mask;          // lost the slot to a different key
+              const unsigned long long old =
+                  atomicCAS(reinterpret_cast<unsigned long long *>(&slots[at].key), kEmptyKey, k);
+              if (old == kEmptyKey || old == k) {   // claimed here, or by another entry of the same key
+                pending = true;
+                done = true;
+              } else {
+                at = (at + 1) & slot_mask;          // lost the slot to a different key
+              }
             }
+          } else {
+            at = (at + 1) & slot_mask;
           }
-        } else {
-          at = (at + 1) & slot_mask;
+        }
+        if (!done) set_status(ctrl, DES_ERR_FULL);     // every slot visited
+        if (pending) {
+          atomicMin(&slots[at].first, (uint32_t)e);
+          slot_of[e] = (uint32_t)at;
+          out = kRowPending;
         }
       }
-      if (!done) set_status(ctrl, DES_ERR_FULL);     // every slot visited
-      if (pending) {
-        atomicMin(&slots[at].first, (uint32_t)e);
-        slot_of[e] = (uint32_t)at;
-        out = kRowPending;
-      }
       rows[e] = out;
+    }
+    if (kInsert && pending_bits) {                   // 64 consecutive entries per wave
+      const unsigned long long bits = __ballot(pending);
+      if ((threadIdx.x & (kWave - 1)) == 0 && e < n) pending_bits[e / kWave] = bits;
     }
   }
 }
@@ -163,11 +156,20 @@ __device__ inline void load_flag_rows(const int32_t *__restrict__ rows, int64_t 
   }
 }
 
-// Pass B1: per tile, how many entries open a new row.
+// Pass B1: per tile, how many entries open a new row (beside the tile's pending bit).  The first workgroup also notes the row
+// count of the table, which the passes after it number from: the last of them may then move it on.
 __global__ __launch_bounds__(kBlock) void k_new_count(const Slot *__restrict__ slots, const int32_t *__restrict__ rows,
                                                        const uint32_t *__restrict__ slot_of, int64_t n,
-                                                       uint32_t *__restrict__ tile_sums) {
+                                                       const unsigned long long *__restrict__ pending_bits,
+                                                       uint32_t *__restrict__ tile_sums, Ctrl *__restrict__ ctrl) {
   __shared__ uint32_t lds[kWavesPerBlock];
+  if (blockIdx.x == 0 && threadIdx.x == 0) ctrl->base_rows = ctrl->n_rows;
+  const int64_t word = (int64_t)blockIdx.x * (kFlagTile / kWave) + threadIdx.x;
+  const bool some = threadIdx.x < kFlagTile / kWave && word * kWave < n && pending_bits[word] != 0;
+  if (!__syncthreads_or(some)) {
+    if (threadIdx.x == 0) tile_sums[blockIdx.x] = 0;
+    return;
+  }
   const int64_t base = (int64_t)blockIdx.x * kFlagTile + (int64_t)threadIdx.x * kFlagItems;
   uint32_t cnt = 0;
   int32_t r[kFlagItems];
@@ -177,7 +179,7 @@ __global__ __launch_bounds__(kBlock) void k_new_count(const Slot *__restrict__ s
     if (base + i < n && opens_row(slots, r[i], slot_of, base + i)) ++cnt;
   uint32_t total;
   block_excl_scan_u32(cnt, lds, total);
-  if (threadIdx.x == 0) tile_sums[blockIdx.x] = total;
+  if (threadIdx.x == 0) tile_sums[blockIdx.x] = kPendingBit | total;
 }
 
 // Pass B2: one workgroup turns the tile counts into tile offsets, publishes the number of new
@@ -190,20 +192,22 @@ __global__ __launch_bounds__(kBlock) void k_new_sums(uint32_t *__restrict__ tile
     const int64_t i = base + threadIdx.x;
     const uint32_t v = i < nb ? tile_sums[i] : 0u;
     uint32_t total;
-    const uint32_t ex = block_excl_scan_u32(v, lds, total);
-    if (i < nb) tile_sums[i] = carry + ex;
+    const uint32_t ex = block_excl_scan_u32(v & ~kPendingBit, lds, total);
+    if (i < nb) tile_sums[i] = (carry + ex) | (v & kPendingBit);
     carry += total;
   }
   if (threadIdx.x == 0) {
     ctrl->n_new = carry;
-    if (ctrl->n_rows + (long long)carry > capacity) set_status(ctrl, DES_ERR_FULL);
+    if (ctrl->base_rows + (long long)carry > capacity) set_status(ctrl, DES_ERR_FULL);
+    else if (ctrl->status == 0) ctrl->n_rows = ctrl->base_rows + (long long)carry;
   }
 }
 
 // Pass B3: number the new rows in entry order; the slot learns its row.
 // kSelfPrefix: tile_sums still holds the tiles' counts; every workgroup adds up all of them itself (few tiles:
 // cheaper than a launch that does it once), which gives it the rows before its tile, the number of new rows and the
-// capacity verdict, the same in every workgroup.  The first workgroup publishes the latter two.
+// capacity verdict, the same in every workgroup.  The first workgroup publishes the latter two and makes the new rows part
+// of the table (nothing of the call reads the row count from here on, only the one noted before).
 template <bool kSelfPrefix>
 __global__ __launch_bounds__(kBlock) void k_new_assign(Slot *__restrict__ slots, const int32_t *__restrict__ rows,
                                                         const uint32_t *__restrict__ slot_of,
@@ -216,24 +220,26 @@ __global__ __launch_bounds__(kBlock) void k_new_assign(Slot *__restrict__ slots,
   if (kSelfPrefix) {
     uint32_t before = 0, rest = 0;
     for (uint32_t i = threadIdx.x; i < gridDim.x; i += kBlock) {
-      const uint32_t v = tile_sums[i];
+      const uint32_t v = tile_sums[i] & ~kPendingBit;
       if (i < blockIdx.x) before += v; else rest += v;
     }
     uint32_t rest_total;
     block_excl_scan_u32(before, lds, tile_base);
     block_excl_scan_u32(rest, lds, rest_total);
     const long long n_new = (long long)tile_base + rest_total;
-    const bool full = ctrl->n_rows + n_new > capacity;            // n_rows does not change before the commit
+    const bool full = ctrl->base_rows + n_new > capacity;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
       ctrl->n_new = n_new;
       if (full) set_status(ctrl, DES_ERR_FULL);
+      else if (ctrl->status == 0) ctrl->n_rows = ctrl->base_rows + n_new;
     }
     if (full || ctrl->status != 0) return;            // uniform over the grid: a status set earlier, or by a peer just now
   } else {
     if (ctrl->status != 0) return;                    // uniform: includes "would exceed the capacity"
-    tile_base = tile_sums[blockIdx.x];
+    tile_base = tile_sums[blockIdx.x] & ~kPendingBit;
   }
-  const long long n_rows = ctrl->n_rows;
+  if (!(tile_sums[blockIdx.x] & kPendingBit)) return;  // uniform
+  const long long n_rows = ctrl->base_rows;
   const int64_t base = (int64_t)blockIdx.x * kFlagTile + (int64_t)threadIdx.x * kFlagItems;
   bool flag[kFlagItems];
   uint32_t cnt = 0;
@@ -259,91 +265,141 @@ __global__ __launch_bounds__(kBlock) void k_new_assign(Slot *__restrict__ slots,
   }
 }
 
-// Rows created by this call get initialiser weights and zero optimizer state.
-// One thread per group of four columns; the group with index D/4 holds the LR weight.
-__global__ __launch_bounds__(kBlock) void k_init_rows(const Ctrl *__restrict__ ctrl, int D, uint64_t seed,
-                                                       float width, const uint64_t *__restrict__ row_keys,
-                                                       float *__restrict__ emb, float *__restrict__ w,
-                                                       float *__restrict__ acc_emb, float *__restrict__ acc_w,
-                                                       float *__restrict__ acc2_emb, float *__restrict__ acc2_w,
-                                                       int64_t capacity) {
+// Passes B and D for a batch of up to kSmallInsert entries, in one workgroup: counts, numbers, checks the capacity, tells the
+// slots, moves the row count on and patches the entries.  Three launches of about 4 us in one.
+__global__ __launch_bounds__(kSmallInsertBlock) void k_new_small(Slot *__restrict__ slots, int32_t *__restrict__ rows,
+                                                                  const uint32_t *__restrict__ slot_of,
+                                                                  const uint64_t *__restrict__ keys, int n,
+                                                                  Ctrl *__restrict__ ctrl, uint64_t *__restrict__ row_keys,
+                                                                  int32_t *__restrict__ first_idx, int64_t capacity) {
+  constexpr int kItems = kSmallInsert / kSmallInsertBlock, kWaves = kSmallInsertBlock / kWave;
+  __shared__ uint32_t lds[kWaves];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, base = threadIdx.x * kItems;
+  const int status = ctrl->status;
+  const long long n_rows = ctrl->n_rows;
+  int32_t r[kItems];
+  uint32_t cnt = 0;
+  bool flag[kItems];
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) {
+    r[i] = base + i < n ? rows[base + i] : kRowAbsent;
+    flag[i] = opens_row(slots, r[i], slot_of, base + i);
+    cnt += flag[i] ? 1u : 0u;
+  }
+  const uint32_t inc = wave_incl_scan_u32(cnt);
+  if (lane == kWave - 1) lds[wave] = inc;
+  __syncthreads();                                    // also: everybody has read the control block
+  uint32_t rank = inc - cnt, total = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    const uint32_t x = lds[w];
+    if (w < wave) rank += x;
+    total += x;
+  }
+  const bool full = n_rows + (long long)total > capacity;
+  if (threadIdx.x == 0) {
+    ctrl->base_rows = n_rows;
+    ctrl->n_new = total;
+    if (full) set_status(ctrl, DES_ERR_FULL);
+    else if (status == 0) ctrl->n_rows = n_rows + (long long)total;
+  }
+  if (!full && status == 0) {
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+      if (flag[i]) {
+        const long long row = n_rows + rank;
+        slots[slot_of[base + i]].row = (int32_t)row;
+        row_keys[row] = keys[base + i];
+        first_idx[rank] = base + i;
+        ++rank;
+      }
+    }
+  }
+  __syncthreads();                                    // the slots know their rows
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) {
+    if (r[i] != kRowPending) continue;
+    const int32_t row = __hip_atomic_load(&slots[slot_of[base + i]].row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    rows[base + i] = row >= 0 ? row : kRowAbsent;     // negative only after a failed call
+  }
+}
+
+// Last pass.  Entries that saw a pending key read the row from the slot they remembered (kPatch; tiles without such
+// entries are skipped).  Rows created by this call get initialiser weights, or (kValues) the values of their first
+// occurrence, and zero optimizer state: one thread per group of four columns, or per column; the last group holds
+// the LR weight.
+struct NewRowArgs {
+  int D;
+  uint64_t seed;
+  float width;
+  const uint64_t *row_keys;
+  const float *values;
+  const int32_t *first_idx;
+  float *emb, *w, *acc_emb, *acc_w, *acc2_emb, *acc2_w;
+  int64_t capacity;
+};
+
+template <bool kPatch, bool kValues>
+__global__ __launch_bounds__(kBlock) void k_finish(const Slot *__restrict__ slots, int64_t n, int32_t *__restrict__ rows,
+                                                    const uint32_t *__restrict__ slot_of,
+                                                    const uint32_t *__restrict__ tile_sums,
+                                                    const Ctrl *__restrict__ ctrl, const NewRowArgs a) {
+  if (kPatch) {
+    const int64_t nb = (n + kFlagTile - 1) / kFlagTile;
+    for (int64_t t = blockIdx.x; t < nb; t += gridDim.x) {
+      if (!(tile_sums[t] & kPendingBit)) continue;    // uniform
+      int32_t r[kFlagItems];
+      const int64_t base = t * kFlagTile + threadIdx.x;
+#pragma unroll
+      for (int i = 0; i < kFlagItems; ++i) r[i] = base + i * kBlock < n ? rows[base + i * kBlock] : kRowAbsent;
+#pragma unroll
+      for (int i = 0; i < kFlagItems; ++i) {
+        if (r[i] != kRowPending) continue;
+        const int32_t row = slots[slot_of[base + i * kBlock]].row;
+        rows[base + i * kBlock] = row >= 0 ? row : kRowAbsent;     // negative only after a failed call
+      }
+    }
+  }
   if (ctrl->status != 0) return;
-  const long long n_new = ctrl->n_new, n_rows = ctrl->n_rows;
-  if (n_rows + n_new > capacity) return;
-  const int groups = D / 4 + 1;
-  const int64_t total = n_new * groups;
+  const long long n_new = ctrl->n_new, n_rows = ctrl->base_rows;
+  if (n_rows + n_new > a.capacity) return;
+  const int D = a.D, per_row = kValues ? D + 1 : D / 4 + 1;
+  const int64_t total = n_new * per_row;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) {
-    const int64_t row = n_rows + i / groups;
-    const int g = (int)(i % groups);
-    const uint64_t key = row_keys[row];
-    if (g < D / 4) {
+    const int64_t j = i / per_row, row = n_rows + j;
+    const int c = (int)(i % per_row);
+    if (kValues) {
+      const float val = a.values[(int64_t)a.first_idx[j] * per_row + c];
+      if (c < D) {
+        a.emb[row * D + c] = val;
+        if (a.acc_emb) a.acc_emb[row * D + c] = 0.f;
+        if (a.acc2_emb) a.acc2_emb[row * D + c] = 0.f;
+      } else {
+        a.w[row] = val;
+        if (a.acc_w) a.acc_w[row] = 0.f;
+        if (a.acc2_w) a.acc2_w[row] = 0.f;
+      }
+      continue;
+    }
+    const uint64_t key = a.row_keys[row];
+    if (c < D / 4) {
       float v[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const uint64_t h = mix64(key ^ mix64(seed + (uint64_t)(g * 4 + k)));
+        const uint64_t h = mix64(key ^ mix64(a.seed + (uint64_t)(c * 4 + k)));
         const float u = (float)(h >> 40) * (1.0f / 16777216.0f);
-        v[k] = __fmul_rn(__fsub_rn(u, 0.5f), width);
+        v[k] = __fmul_rn(__fsub_rn(u, 0.5f), a.width);
       }
-      *reinterpret_cast<float4 *>(&emb[row * D + g * 4]) = make_float4(v[0], v[1], v[2], v[3]);
-      if (acc_emb) *reinterpret_cast<float4 *>(&acc_emb[row * D + g * 4]) = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (acc2_emb) *reinterpret_cast<float4 *>(&acc2_emb[row * D + g * 4]) = make_float4(0.f, 0.f, 0.f, 0.f);
+      *reinterpret_cast<float4 *>(&a.emb[row * D + c * 4]) = make_float4(v[0], v[1], v[2], v[3]);
+      if (a.acc_emb) *reinterpret_cast<float4 *>(&a.acc_emb[row * D + c * 4]) = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (a.acc2_emb) *reinterpret_cast<float4 *>(&a.acc2_emb[row * D + c * 4]) = make_float4(0.f, 0.f, 0.f, 0.f);
     } else {
-      const uint64_t h = mix64(key ^ mix64(seed + (uint64_t)D));
+      const uint64_t h = mix64(key ^ mix64(a.seed + (uint64_t)D));
       const float u = (float)(h >> 40) * (1.0f / 16777216.0f);
-      w[row] = __fmul_rn(__fsub_rn(u, 0.5f), width);
-      if (acc_w) acc_w[row] = 0.f;
-      if (acc2_w) acc2_w[row] = 0.f;
-    }
-  }
-}
-
-// Pass D.  Entries that saw a pending key read the row from the slot they remembered.
-// It is also the last kernel of an insert, so its first thread makes the new rows part of the table (no kernel of
-// the call reads the row count after this one was launched).
-__global__ __launch_bounds__(kBlock) void k_patch(const Slot *__restrict__ slots, int64_t n,
-                                                   int32_t *__restrict__ rows, const uint32_t *__restrict__ slot_of,
-                                                   Ctrl *__restrict__ ctrl, int64_t capacity) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
-    if (rows[e] != kRowPending) continue;
-    const int32_t row = slots[slot_of[e]].row;
-    rows[e] = row >= 0 ? row : kRowAbsent;         // negative only after a failed call
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    if (ctrl->status == 0 && ctrl->n_rows + ctrl->n_new <= capacity) ctrl->n_rows += ctrl->n_new;
-    ctrl->n_new = 0;
-  }
-}
-
-// Pass E (host values given): new row j copies the values of its first occurrence.
-__global__ __launch_bounds__(kBlock) void k_copy_values(const Ctrl *__restrict__ ctrl, int D,
-                                                         const float *__restrict__ values,
-                                                         const int32_t *__restrict__ first_idx,
-                                                         float *__restrict__ emb, float *__restrict__ w,
-                                                         float *__restrict__ acc_emb, float *__restrict__ acc_w,
-                                                         float *__restrict__ acc2_emb, float *__restrict__ acc2_w,
-                                                         int64_t capacity) {
-  if (ctrl->status != 0) return;
-  const long long n_new = ctrl->n_new, n_rows = ctrl->n_rows;
-  if (n_rows + n_new > capacity) return;
-  const int cols = D + 1;
-  const int64_t total = n_new * cols;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) {
-    const int64_t j = i / cols;
-    const int c = (int)(i % cols);
-    const int64_t row = n_rows + j;
-    const int32_t src = first_idx[j];
-    const float val = values[(int64_t)src * cols + c];
-    if (c < D) {
-      emb[row * D + c] = val;
-      if (acc_emb) acc_emb[row * D + c] = 0.f;
-      if (acc2_emb) acc2_emb[row * D + c] = 0.f;
-    } else {
-      w[row] = val;
-      if (acc_w) acc_w[row] = 0.f;
-      if (acc2_w) acc2_w[row] = 0.f;
+      a.w[row] = __fmul_rn(__fsub_rn(u, 0.5f), a.width);
+      if (a.acc_w) a.acc_w[row] = 0.f;
+      if (a.acc2_w) a.acc2_w[row] = 0.f;
     }
   }
 }
@@ -354,7 +410,7 @@ __global__ __launch_bounds__(kBlock) void k_fill_u64x2(uint4 *__restrict__ p, in
 }
 
 __global__ void k_zero_ctrl(Ctrl *ctrl) {
-  ctrl->n_rows = 0; ctrl->n_new = 0; ctrl->n_uniq = 0; ctrl->n_long = 0; ctrl->n_chunks = 0; ctrl->status = 0;
+  ctrl->n_rows = 0; ctrl->base_rows = 0; ctrl->n_new = 0; ctrl->n_uniq = 0; ctrl->n_long = 0; ctrl->n_chunks = 0; ctrl->status = 0;
   ctrl->n_multi = 0; ctrl->n_groups = 0; ctrl->bad_keys = 0;
 }
 
@@ -517,7 +573,7 @@ std::mutex g_prof_mutex;
 std::vector<ProfRec> g_prof;
 thread_local hipEvent_t g_open[KID_COUNT];
 const char *kKernelNames[KID_COUNT] = {
-    "table_probe", "table_number_new_rows", "table_patch_rows", "table_init_rows",
+    "table_probe", "table_number_new_rows", "table_finish_rows",
     "forward_gather_pool", "forward_pool_dense", "aggregate_partials", "fm_finalize",
     "backward_expand", "sort_histogram", "sort_scan", "sort_scatter",
     "backward_segment_heads", "backward_classify", "backward_short_update", "backward_long_partial",
@@ -666,12 +722,11 @@ static des_status_t insert_impl(des_table_t *t, const uint64_t *keys, int64_t n,
   t->prep.valid = false;
   if (n == 0) return DES_OK;
   if (insert && insert_ws_bytes(n) > t->ws_bytes) return DES_ERR_WORKSPACE;
-  const uint64_t mask = t->n_slots - 1;
   if (!insert) {
     if (!rows_out) return DES_ERR_INVALID_ARG;
     ProfScope ps(KID_PROBE, s);
-    hipLaunchKernelGGL(k_probe<false>, dim3(grid_for(n, kBlock * kProbeKeys)), dim3(kBlock), 0, s, t->slots, mask, keys, n, rows_out,
-                       t->ctrl, (uint32_t *)nullptr);
+    hipLaunchKernelGGL(k_probe<false>, dim3(grid_for(n)), dim3(kBlock), 0, s, t->slots, t->n_slots - 1, keys, n, rows_out,
+                       t->ctrl, (uint32_t *)nullptr, (unsigned long long *)nullptr);
     return hipGetLastError() == hipSuccess ? DES_OK : DES_ERR_DEVICE;
   }
   const size_t m = (size_t)n;
@@ -680,39 +735,46 @@ static des_status_t insert_impl(des_table_t *t, const uint64_t *keys, int64_t n,
   uint32_t *slot_of = (uint32_t *)p; p += align_up(m * 4, 256);
   int32_t *first_idx = (int32_t *)p; p += align_up(m * 4, 256);
   uint32_t *tile_sums = (uint32_t *)p;
+  unsigned long long *pending_bits = (unsigned long long *)first_idx;   // until k_new_assign lists the first occurrences there
   int32_t *rows = rows_out ? rows_out : tmp_rows;
   const des_table_config_t &c = t->cfg;
   const int64_t nb = (n + kFlagTile - 1) / kFlagTile;
+  const bool small = n <= kSmallInsert;
   {
     ProfScope ps(KID_PROBE, s);
-    hipLaunchKernelGGL(k_probe<true>, dim3(grid_for(n, kBlock * kProbeKeys)), dim3(kBlock), 0, s, t->slots, mask, keys, n, rows, t->ctrl,
-                       slot_of);
+    hipLaunchKernelGGL(k_probe<true>, dim3(grid_for(n)), dim3(kBlock), 0, s, t->slots, t->n_slots - 1, keys, n, rows, t->ctrl,
+                       slot_of, small ? (unsigned long long *)nullptr : pending_bits);
   }
   {
     ProfScope ps(KID_ASSIGN, s);
-    hipLaunchKernelGGL(k_new_count, dim3((unsigned)nb), dim3(kBlock), 0, s, t->slots, rows, slot_of, n, tile_sums);
-    if (nb > kSelfPrefixTiles) {
-      hipLaunchKernelGGL(k_new_sums, dim3(1), dim3(kBlock), 0, s, tile_sums, nb, t->ctrl, c.capacity_rows);
-      hipLaunchKernelGGL(k_new_assign<false>, dim3((unsigned)nb), dim3(kBlock), 0, s, t->slots, rows, slot_of, keys, n,
-                         tile_sums, t->ctrl, c.row_keys, first_idx, c.capacity_rows);
+    if (small) {
+      hipLaunchKernelGGL(k_new_small, dim3(1), dim3(kSmallInsertBlock), 0, s, t->slots, rows, slot_of, keys, (int)n, t->ctrl,
+                         c.row_keys, first_idx, c.capacity_rows);
     } else {
-      hipLaunchKernelGGL(k_new_assign<true>, dim3((unsigned)nb), dim3(kBlock), 0, s, t->slots, rows, slot_of, keys, n,
-                         tile_sums, t->ctrl, c.row_keys, first_idx, c.capacity_rows);
+      hipLaunchKernelGGL(k_new_count, dim3((unsigned)nb), dim3(kBlock), 0, s, t->slots, rows, slot_of, n, pending_bits, tile_sums,
+                         t->ctrl);
+      if (nb > kSelfPrefixTiles) {
+        hipLaunchKernelGGL(k_new_sums, dim3(1), dim3(kBlock), 0, s, tile_sums, nb, t->ctrl, c.capacity_rows);
+        hipLaunchKernelGGL(k_new_assign<false>, dim3((unsigned)nb), dim3(kBlock), 0, s, t->slots, rows, slot_of, keys, n,
+                           tile_sums, t->ctrl, c.row_keys, first_idx, c.capacity_rows);
+      } else {
+        hipLaunchKernelGGL(k_new_assign<true>, dim3((unsigned)nb), dim3(kBlock), 0, s, t->slots, rows, slot_of, keys, n,
+                           tile_sums, t->ctrl, c.row_keys, first_idx, c.capacity_rows);
+      }
     }
   }
   {
-    ProfScope ps(KID_INIT_ROWS, s);
-    if (values)
-      hipLaunchKernelGGL(k_copy_values, dim3(grid_for(n * (c.dim + 1), kBlock, 2048)), dim3(kBlock), 0, s, t->ctrl,
-                         c.dim, values, first_idx, c.emb, c.w, c.acc_emb, c.acc_w, c.acc2_emb, c.acc2_w, c.capacity_rows);
-    else
-      hipLaunchKernelGGL(k_init_rows, dim3(grid_for(n * (c.dim / 4 + 1), kBlock, 2048)), dim3(kBlock), 0, s, t->ctrl,
-                         c.dim, c.init_seed, t->init_width, c.row_keys, c.emb, c.w, c.acc_emb, c.acc_w,
-                         c.acc2_emb, c.acc2_w, c.capacity_rows);
-  }
-  {
-    ProfScope ps(KID_PATCH, s);
-    hipLaunchKernelGGL(k_patch, dim3(grid_for(n)), dim3(kBlock), 0, s, t->slots, n, rows, slot_of, t->ctrl, c.capacity_rows);
+    ProfScope ps(KID_FINISH_ROWS, s);
+    NewRowArgs a;
+    a.D = c.dim; a.seed = c.init_seed; a.width = t->init_width; a.row_keys = c.row_keys; a.values = values;
+    a.first_idx = first_idx; a.emb = c.emb; a.w = c.w; a.acc_emb = c.acc_emb; a.acc_w = c.acc_w;
+    a.acc2_emb = c.acc2_emb; a.acc2_w = c.acc2_w; a.capacity = c.capacity_rows;
+    const dim3 grid(grid_for(n * (values ? c.dim + 1 : c.dim / 4 + 1), kBlock, 2048)), block(kBlock);
+#define DES_FINISH(PATCH, VALUES) \
+  hipLaunchKernelGGL((k_finish<PATCH, VALUES>), grid, block, 0, s, t->slots, n, rows, slot_of, tile_sums, t->ctrl, a)
+    if (small) { if (values) DES_FINISH(false, true); else DES_FINISH(false, false); }
+    else       { if (values) DES_FINISH(true, true);  else DES_FINISH(true, false); }
+#undef DES_FINISH
   }
   return hipGetLastError() == hipSuccess ? DES_OK : DES_ERR_DEVICE;
 }

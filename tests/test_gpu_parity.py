@@ -827,3 +827,50 @@ def test_row_sort_at_its_size_limits(oracle, des, n, B, F, capacity, vals):
         p.check_weights("after update")
     finally:
         p.close()
+
+
+@pytest.mark.parametrize("n", [1, 63, 65, 1025, 4096, 4097, 6145, 300000])     # one workgroup numbers up to 4096 entries
+@pytest.mark.parametrize("with_values", [False, True])
+def test_insert_numbers_new_rows_at_its_size_limits(oracle, des, n, with_values):
+    """Calls of new, known and repeated IDs against the sequential loop, then one that does not fit: it inserts nothing, known IDs
+    are still found, and after the status is cleared a smaller call goes on where the table stood."""
+    import torch
+    rng = np.random.default_rng(n)
+    D = 4
+    pool = synth.scramble64(np.arange(1, 4 * n + 16, dtype=np.uint64))
+    first = rng.permutation(2 * n)[:n]                                          # all distinct
+    second = np.where(rng.random(n) < 0.5, first[rng.integers(0, n, n)], rng.integers(0, 2 * n, n))
+    capacity = len(set(first) | set(second)) + 3
+    p = Pair(oracle, des, D, capacity, 2, 0, des.OPT_ADAGRAD, seed=9, max_n=max(n, 64))
+    try:
+        known = {}
+        for ids in (first, second, second):
+            vals = rng.standard_normal((n, D + 1)).astype(np.float32) if with_values else None
+            rows_o = p.ot.insert(pool[ids], vals)
+            rows_g = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+            p.gt.insert(dev(pool[ids], torch), dev(vals, torch), rows_g)
+            for i in ids:
+                known.setdefault(int(i), len(known))
+            torch.cuda.synchronize()
+            assert_equal(rows_g.cpu().numpy(), rows_o, "rows")
+            assert_equal(rows_o, np.array([known[int(i)] for i in ids], np.int32), "rows of the sequential loop")
+            p.check_table("after insert")
+            p.check_weights("after insert", exact=True)
+        if n < 5:
+            return
+        new = np.arange(2 * n, 3 * n)                                           # n new IDs, three places left
+        mixed = np.where(rng.random(n) < 0.5, new, first)
+        if (mixed >= 2 * n).sum() <= 3:
+            return
+        rows_g = p.gt.find(dev(pool[mixed], torch), des.MISS_INSERT)
+        assert p.gt.status() == des.ERR_FULL and p.gt.size() == len(known)
+        assert_equal(rows_g.cpu().numpy(), np.array([known.get(int(i), -1) for i in mixed], np.int32), "rows of the call that does not fit")
+        p.gt.clear_status()
+        few = np.concatenate([new[:3], first[: min(n, 64) - 3], new[:1]])
+        rows_g = p.gt.find(dev(pool[few], torch), des.MISS_INSERT)
+        for i in few:
+            known.setdefault(int(i), len(known))
+        assert p.gt.status() == 0 and p.gt.size() == len(known) == capacity
+        assert_equal(rows_g.cpu().numpy(), np.array([known[int(i)] for i in few], np.int32), "rows after the status is cleared")
+    finally:
+        p.close()
