@@ -59,48 +59,49 @@ __global__ __launch_bounds__(kBlock) void k_probe(Slot *__restrict__ slots, uint
   const int64_t stride = (int64_t)gridDim.x * kBlock;
   for (int64_t tile = (int64_t)blockIdx.x * kBlock; tile < n; tile += stride) {
     const int64_t e = tile + threadIdx.x;
+    const uint64_t k = e < n ? keys[e] : kEmptyKey;
+    uint64_t at = mix64(k) & slot_mask;
+    Slot s;
+    s.key = kEmptyKey; s.row = kRowAbsent; s.first = 0u;
+    if (k != kEmptyKey) s = load_slot(&slots[at]);   // requested before the walk: inside it the wave's lanes part company
+    int32_t out = kRowAbsent;
     bool pending = false;
-    if (e < n) {
-      const uint64_t k = keys[e];
-      int32_t out = kRowAbsent;
-      if (k == kEmptyKey) {                          // the reserved key is nobody's ID: absent, counted, nothing else is held up
-        atomicAdd(&ctrl->bad_keys, 1);
-      } else {
-        uint64_t at = mix64(k) & slot_mask;
-        bool done = false;
-        for (uint64_t probe = 0; probe <= slot_mask && !done; ++probe) {
-          const Slot s = load_slot(&slots[at]);
-          if (s.key == k) {
-            // a negative row under a key is a claim of the running call, or the leftover of a
-            // call that failed: only a call that can insert resolves it
-            if (s.row >= 0) out = s.row; else pending = can_insert;
+    if (k != kEmptyKey) {
+      bool done = false;
+      for (uint64_t probe = 0; probe <= slot_mask && !done; ++probe) {
+        if (probe > 0) s = load_slot(&slots[at]);
+        if (s.key == k) {
+          // a negative row under a key is a claim of the running call, or the leftover of a
+          // call that failed: only a call that can insert resolves it
+          if (s.row >= 0) out = s.row; else pending = can_insert;
+          done = true;
+        } else if (s.key == kEmptyKey) {
+          if (!can_insert) {
             done = true;
-          } else if (s.key == kEmptyKey) {
-            if (!can_insert) {
+          } else {
+            const unsigned long long old =
+                atomicCAS(reinterpret_cast<unsigned long long *>(&slots[at].key), kEmptyKey, k);
+            if (old == kEmptyKey || old == k) {   // claimed here, or by another entry of the same key
+              pending = true;
               done = true;
             } else {
-              const unsigned long long old =
-                  atomicCAS(reinterpret_cast<unsigned long long *>(&slots[at].key), kEmptyKey, k);
-              if (old == kEmptyKey || old == k) {   // claimed here, or by another entry of the same key
-                pending = true;
-                done = true;
-              } else {
-                at = (at + 1) & slot_mask;          // lost the slot to a different key
-              }
+              at = (at + 1) & slot_mask;          // lost the slot to a different key
             }
-          } else {
-            at = (at + 1) & slot_mask;
           }
-        }
-        if (!done) set_status(ctrl, DES_ERR_FULL);     // every slot visited
-        if (pending) {
-          atomicMin(&slots[at].first, (uint32_t)e);
-          slot_of[e] = (uint32_t)at;
-          out = kRowPending;
+        } else {
+          at = (at + 1) & slot_mask;
         }
       }
-      rows[e] = out;
+      if (!done) set_status(ctrl, DES_ERR_FULL);     // every slot visited
+      if (pending) {
+        atomicMin(&slots[at].first, (uint32_t)e);
+        slot_of[e] = (uint32_t)at;
+        out = kRowPending;
+      }
+    } else if (e < n) {
+      atomicAdd(&ctrl->bad_keys, 1);                 // the reserved key is nobody's ID: absent, counted, nothing else is held up
     }
+    if (e < n) rows[e] = out;
     if (kInsert && pending_bits) {                   // 64 consecutive entries per wave
       const unsigned long long bits = __ballot(pending);
       if ((threadIdx.x & (kWave - 1)) == 0 && e < n) pending_bits[e / kWave] = bits;
