@@ -874,3 +874,21 @@ def test_insert_numbers_new_rows_at_its_size_limits(oracle, des, n, with_values)
         assert_equal(rows_g.cpu().numpy(), np.array([known[int(i)] for i in few], np.int32), "rows after the status is cleared")
     finally:
         p.close()
+
+
+@pytest.mark.parametrize("B,F,D,K", [(1, 1, 4, 1), (1, 100, 32, 5), (3, 17, 64, 8), (200, 33, 8, 3), (513, 26, 16, 8), (2049, 5, 128, 2)])
+@pytest.mark.parametrize("policy", [0, 1])
+def test_forward_of_small_batches_spread_over_several_waves(oracle, des, B, F, D, K, policy):
+    """One, two and four waves per sample, samples with fewer bags than lane groups, empty bags, values."""
+    rng = np.random.default_rng(B + F)
+    p = Pair(oracle, des, D, 4000, K, policy, des.OPT_SGD, seed=2, max_n=1 << 17)
+    try:
+        lens = rng.poisson(2.5, B * F)
+        offsets = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        n = int(offsets[-1])
+        keys = synth.scramble64(rng.integers(1, 3000, n).astype(np.uint64))
+        batch = synth.Batch(B, F, keys, offsets, rng.uniform(0.25, 2, n).astype(np.float32) if K > 4 else None)
+        p.find(batch, insert=True)
+        p.forward(batch)
+    finally:
+        p.close()
