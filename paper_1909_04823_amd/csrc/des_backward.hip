@@ -1035,7 +1035,7 @@ Layout layout_for(int D, int64_t n) {
   L.group_seg = take(max_groups * 4); L.group_c = take(max_groups * 4);
   L.chunk_owner = take(max_chunks * 4);
   L.partials = take(max_chunks * (size_t)(D + 4) * 8);
-  L.sort_scratch = take(sort_scratch_bytes(n));
+  L.sort_scratch = take(sort_scratch_bytes(n));       // right behind the partials, see sort_stage
   L.total = o;
   return L;
 }
@@ -1068,8 +1068,10 @@ int sort_stage(des_table *t, BwdArgs &a, const Layout &L, hipStream_t s) {
     else hipLaunchKernelGGL(k_expand<false>, grid, block, 0, s, a, key_a, pay_a);
   }
   SortBuffers sb{key_a, (uint32_t *)(ws + L.key_b), pay_a, (uint32_t *)(ws + L.pay_b)};
-  const int side = radix_sort_u32_pairs(sb, n, bits, ws + L.sort_scratch,
-                                        (uint32_t *)(ws + L.uniq_rows), s);
+  // what the later steps fill serves as scratch here: the unique rows for the digits' totals, the chunk sums, with the sort
+  // scratch right behind them, for the finer tile counts of a small batch (2 bytes per entry; the chunk sums alone are
+  // 8*(D+4)*(1/33 + 1/512) >= 2.06 bytes per entry)
+  const int side = radix_sort_u32_pairs(sb, n, bits, ws + L.sort_scratch, ws + L.partials, (uint32_t *)(ws + L.uniq_rows), s);
   a.key_sorted = (uint32_t *)(ws + (side ? L.key_b : L.key_a));
   a.pay_sorted = (uint32_t *)(ws + (side ? L.pay_b : L.pay_a));
   {

@@ -75,10 +75,14 @@ void exclusive_scan_u64(unsigned long long *data, int64_t n, unsigned long long 
                         void *scratch, hipStream_t s);
 
 // Stable LSD radix sort of (32-bit key, 32-bit payload) pairs on the low `bits` bits of the key.
-// Returns 0 if the sorted data is in the *_a buffers, 1 if in *_b.  totals: scratch of min(n, kSortTotals) values, at least 256 bytes.
+// Returns 0 if the sorted data is in the *_a buffers, 1 if in *_b.  scratch: sort_scratch_bytes(n); up to kFewSort items
+// few_scratch is used instead, few_sort_scratch_bytes(n).  totals: min(n, kSortTotals) values, at least 256 bytes.
 constexpr int kSortTotals = 512;
+constexpr int64_t kFewSort = 1 << 20;
+size_t few_sort_scratch_bytes(int64_t n);
 struct SortBuffers { void *keys_a, *keys_b; uint32_t *pay_a, *pay_b; };
-int radix_sort_u32_pairs(SortBuffers buf, int64_t n, int bits, void *scratch, uint32_t *totals, hipStream_t s);
+int radix_sort_u32_pairs(SortBuffers buf, int64_t n, int bits, void *scratch, void *few_scratch, uint32_t *totals,
+                         hipStream_t s);
 
 }  // namespace des
 

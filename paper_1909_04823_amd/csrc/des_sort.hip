@@ -12,6 +12,8 @@ constexpr int kScanItems = 8;                       // items per thread in the s
 constexpr int kScanTile = kBlock * kScanItems;
 constexpr int kSortItems = 16;                      // items per thread in the sort kernels
 constexpr int kSortTile = kBlock * kSortItems;
+constexpr int kFewSortItems = 4;                    // ... of a batch of up to kFewSort items
+constexpr int kFewSortTile = kBlock * kFewSortItems;
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kMaxDigitBits = 9;                    // widest radix digit of one pass
 constexpr int kMaxRadix = 1 << kMaxDigitBits;
@@ -139,26 +141,28 @@ void exclusive_scan(T *data, int64_t n, T *total_out, void *scratch, hipStream_t
 }
 
 // ---------------------------------------------------------------------------------------
-// Radix sort.  One workgroup owns a tile of kSortTile consecutive items; wave w owns the w-th
-// quarter of the tile and walks it in rounds of 64, so "wave, round, lane" is item order.
+// Radix sort.  One workgroup owns a tile of kBlock * kItems consecutive items; wave w owns the w-th
+// quarter of the tile and walks it in rounds of 64, so "wave, round, lane" is item order.  Large tiles write longer runs; up to
+// kFewSort items they would leave a CU one workgroup or none, whose sixteen rounds nobody overlaps (three passes over
+// 1.0e6 / 3.7e5 items, the scatter kernels alone: 49 -> 32 / 45 -> 25 us).
 
 // Digit counts of one tile per workgroup, one row of `hist`, written here and read by the scatter pass side by side.
 // Neighbouring lanes count into kCopies different counters of a digit: a hot row (18 % of a skewed batch) brings ten
 // equal digits per wave, and LDS adds to equal addresses run one after the other.  Three passes over 8.2e6 keys, Zipf(1.2):
 // 73 -> 36 us with four copies (82 with counts in one row per digit); 1.05e8 keys, half of them uniform: 516 -> 341 us.
 constexpr int kCopies = 4;
-template <typename KeyT>
+template <typename KeyT, int kItems>
 __global__ __launch_bounds__(kBlock) void k_radix_hist(const KeyT *__restrict__ keys, int64_t n, int shift, int bits,
                                                         uint32_t *__restrict__ hist) {
   __shared__ uint4 cnt[kMaxRadix];
   static_assert(kCopies == 4, "one uint4 per digit");
   const int radix = 1 << bits;
   const uint32_t mask = (1u << bits) - 1u, copy = threadIdx.x % kCopies;
-  const int64_t base = (int64_t)blockIdx.x * kSortTile;
-  KeyT key[kSortItems];
+  const int64_t base = (int64_t)blockIdx.x * (kBlock * kItems);
+  KeyT key[kItems];
   // the keys are requested before the counters are cleared, so that the barrier is passed while they travel
 #pragma unroll
-  for (int i = 0; i < kSortItems; ++i) {
+  for (int i = 0; i < kItems; ++i) {
     const int64_t idx = base + (int64_t)i * kBlock + threadIdx.x;
     key[i] = idx < n ? keys[idx] : (KeyT)0;
   }
@@ -166,7 +170,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_hist(const KeyT *__restrict__ 
   __syncthreads();
   uint32_t *counters = reinterpret_cast<uint32_t *>(cnt);
 #pragma unroll
-  for (int i = 0; i < kSortItems; ++i) {
+  for (int i = 0; i < kItems; ++i) {
     const int64_t idx = base + (int64_t)i * kBlock + threadIdx.x;
     if (idx < n) atomicAdd(&counters[((uint32_t)(key[i] >> shift) & mask) * kCopies + copy], 1u);
   }
@@ -249,32 +253,33 @@ __global__ __launch_bounds__(kScanBlock) void k_radix_scan(uint32_t *__restrict_
 // lower lanes of its round, which is item order, so the pass is stable); then consecutive threads
 // write consecutive sorted items, so the items of one digit leave as one contiguous run instead of
 // one 4-byte store per lane.
-template <typename KeyT, bool kHasPayload>
+template <typename KeyT, bool kHasPayload, int kItems>
 __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KeyT *__restrict__ keys_in,
                                                            const uint32_t *__restrict__ pay_in,
                                                            KeyT *__restrict__ keys_out, uint32_t *__restrict__ pay_out,
                                                            int64_t n, int shift, int bits,
                                                            const uint32_t *__restrict__ offsets,
                                                            const uint32_t *__restrict__ totals) {
+  constexpr int kTile = kBlock * kItems;
   __shared__ uint32_t cnt[kWavesPerBlock][kMaxRadix];   // per wave and digit: count, then start inside the digit's run
   __shared__ uint32_t dig_base[kMaxRadix];              // first sorted index of the digit inside the tile
   __shared__ uint32_t gofs[kMaxRadix];                  // where the tile's run of the digit starts in the output
   __shared__ unsigned long long scan_lds[kWavesPerBlock];
-  __shared__ KeyT skey[kSortTile];                      // the sorted keys; afterwards reused for the payloads
+  __shared__ KeyT skey[kTile];                      // the sorted keys; afterwards reused for the payloads
   static_assert(sizeof(KeyT) >= sizeof(uint32_t), "payloads are staged in the key buffer");
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const int64_t tile = (int64_t)blockIdx.x * kSortTile;
-  const int tile_n = (int)min((int64_t)kSortTile, n - tile);
+  const int64_t tile = (int64_t)blockIdx.x * kTile;
+  const int tile_n = (int)min((int64_t)kTile, n - tile);
   const int radix = 1 << bits;
   const uint32_t mask = (1u << bits) - 1u;
   const unsigned long long lane_lt = (1ull << lane) - 1ull;
-  const int64_t wbase = tile + (int64_t)wave * (kSortItems * kWave);
-  KeyT key[kSortItems];
-  uint32_t pay[kSortItems];
-  uint32_t rank[kSortItems];
+  const int64_t wbase = tile + (int64_t)wave * (kItems * kWave);
+  KeyT key[kItems];
+  uint32_t pay[kItems];
+  uint32_t rank[kItems];
   // the tile's items are requested first, so that their latency overlaps the fetch of the run offsets
 #pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
+  for (int r = 0; r < kItems; ++r) {
     const int64_t idx = wbase + r * kWave + lane;
     const bool live = idx < n;
     key[r] = live ? keys_in[idx] : (KeyT)0;
@@ -297,7 +302,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KeyT *__restrict
   __syncthreads();
 
 #pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
+  for (int r = 0; r < kItems; ++r) {
     const int64_t idx = wbase + r * kWave + lane;
     const bool live = idx < n;
     const uint32_t d = (uint32_t)(key[r] >> shift) & mask;
@@ -347,9 +352,9 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KeyT *__restrict
     ex += tot[j];
   }
   __syncthreads();
-  uint32_t li[kSortItems];
+  uint32_t li[kItems];
 #pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
+  for (int r = 0; r < kItems; ++r) {
     const int64_t idx = wbase + r * kWave + lane;
     li[r] = 0;
     if (idx < n) {
@@ -360,7 +365,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KeyT *__restrict
   }
   __syncthreads();
   // keys out; every thread remembers where its sorted items went, for the payloads that follow
-  constexpr int kOut = kSortTile / kBlock;
+  constexpr int kOut = kTile / kBlock;
   uint32_t pos[kOut];
 #pragma unroll
   for (int j = 0; j < kOut; ++j) {
@@ -377,7 +382,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KeyT *__restrict
     uint32_t *spay = reinterpret_cast<uint32_t *>(skey);
     __syncthreads();                                   // all keys read before the buffer is overwritten
 #pragma unroll
-    for (int r = 0; r < kSortItems; ++r)
+    for (int r = 0; r < kItems; ++r)
       if (wbase + r * kWave + lane < n) spay[li[r]] = pay[r];
     __syncthreads();
 #pragma unroll
@@ -390,14 +395,11 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KeyT *__restrict
 
 inline int64_t sort_blocks(int64_t n) { return (n + kSortTile - 1) / kSortTile; }
 
-template <typename KeyT, bool kHasPayload>
-int radix_sort(SortBuffers buf, int64_t n, int bits, void *scratch, uint32_t *totals, hipStream_t s, int kid_hist, int kid_scan,
-               int kid_scatter) {
+template <typename KeyT, bool kHasPayload, int kItems>
+int radix_sort(SortBuffers buf, int64_t n, int bits, uint32_t *hist, uint32_t *stretch_sums, uint32_t *totals, hipStream_t s,
+               int kid_hist, int kid_scan, int kid_scatter) {
   if (n <= 0 || bits <= 0) return 0;
-  const int nblocks = (int)sort_blocks(n);
-  uint32_t *hist = (uint32_t *)scratch;
-  // the sums of all stretches but the last, behind `hist` (see sort_scratch_bytes)
-  uint32_t *stretch_sums = (uint32_t *)((char *)scratch + align_up((size_t)kMaxRadix * nblocks * sizeof(uint32_t), 256));
+  const int nblocks = (int)((n + kBlock * kItems - 1) / (kBlock * kItems));
   const int widest = n >= kSortTotals ? kMaxDigitBits : kFewItemsBits;
   const int npass = (bits + widest - 1) / widest;
   const int per = (bits + npass - 1) / npass;
@@ -409,7 +411,7 @@ int radix_sort(SortBuffers buf, int64_t n, int bits, void *scratch, uint32_t *to
     const int b = (bits - shift) < per ? (bits - shift) : per;
     {
       ProfScope ps(kid_hist, s);
-      hipLaunchKernelGGL(k_radix_hist<KeyT>, dim3(nblocks), dim3(kBlock), 0, s, kin, n, shift, b, hist);
+      hipLaunchKernelGGL((k_radix_hist<KeyT, kItems>), dim3(nblocks), dim3(kBlock), 0, s, kin, n, shift, b, hist);
     }
     {
       ProfScope ps(kid_scan, s);
@@ -420,7 +422,7 @@ int radix_sort(SortBuffers buf, int64_t n, int bits, void *scratch, uint32_t *to
     }
     {
       ProfScope ps(kid_scatter, s);
-      hipLaunchKernelGGL((k_radix_scatter<KeyT, kHasPayload>), dim3(nblocks), dim3(kBlock), 0, s, kin, pin, kout, pout,
+      hipLaunchKernelGGL((k_radix_scatter<KeyT, kHasPayload, kItems>), dim3(nblocks), dim3(kBlock), 0, s, kin, pin, kout, pout,
                          n, shift, b, hist, totals);
     }
     KeyT *tk = kin; kin = kout; kout = tk;
@@ -455,8 +457,20 @@ void exclusive_scan_u64(unsigned long long *data, int64_t n, unsigned long long 
   exclusive_scan<unsigned long long>(data, n, total_out, scratch, s);
 }
 
-int radix_sort_u32_pairs(SortBuffers buf, int64_t n, int bits, void *scratch, uint32_t *totals, hipStream_t s) {
-  return radix_sort<uint32_t, true>(buf, n, bits, scratch, totals, s, KID_SORT_HIST, KID_SORT_SCAN, KID_SORT_SCATTER);
+size_t few_sort_scratch_bytes(int64_t n) {
+  return (size_t)kMaxRadix * sizeof(uint32_t) * (size_t)((n + kFewSortTile - 1) / kFewSortTile);
+}
+
+int radix_sort_u32_pairs(SortBuffers buf, int64_t n, int bits, void *scratch, void *few_scratch, uint32_t *totals,
+                         hipStream_t s) {
+  static_assert(kFewSort <= (int64_t)kScanStretch * kFewSortTile, "one stretch: no sums of stretches");
+  if (n <= kFewSort)
+    return radix_sort<uint32_t, true, kFewSortItems>(buf, n, bits, (uint32_t *)few_scratch, nullptr, totals, s, KID_SORT_HIST,
+                                                     KID_SORT_SCAN, KID_SORT_SCATTER);
+  // the sums of all stretches but the last lie behind the counts (see sort_scratch_bytes)
+  uint32_t *stretch_sums = (uint32_t *)((char *)scratch + align_up((size_t)kMaxRadix * sort_blocks(n) * sizeof(uint32_t), 256));
+  return radix_sort<uint32_t, true, kSortItems>(buf, n, bits, (uint32_t *)scratch, stretch_sums, totals, s, KID_SORT_HIST,
+                                                KID_SORT_SCAN, KID_SORT_SCATTER);
 }
 
 }  // namespace des

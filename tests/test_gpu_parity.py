@@ -799,12 +799,14 @@ def test_merge_rows_of_more_than_64_chunks(oracle, des, D, with_vals):
     (4096, 65536, 1, 5000, True),              # ... with the most bags, nearly all empty
     (4097, 512, 8, 1 << 22, False),            # one entry more: two tiles
     (300, 65537, 1, 5000, False),              # one bag more, and fewer entries than a digit has values
+    (1 << 20, 3000, 4, 70000, False),          # the last batch with the finer tiles, whose counts lie among the later steps' arrays
+    ((1 << 20) + 1, 3000, 4, 70000, True),
 ])
 def test_row_sort_at_its_size_limits(oracle, des, n, B, F, capacity, vals):
     """Merged order, counts and updates of small batches: empty bags first, last and in runs, one row that holds a third of
     the entries (long segments, several chunks), IDs without a row."""
     rng = np.random.default_rng(n + B)
-    D = 8
+    D = 4 if n > 100000 else 8                                              # 4: the least scratch per entry
     p = Pair(oracle, des, D, capacity, 3, 0, des.OPT_ADAGRAD, seed=5, max_n=max(n, 64))
     try:
         import torch
