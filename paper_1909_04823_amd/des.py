@@ -149,7 +149,9 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    """The current device's current stream.  Asked of the runtime directly: building a torch.cuda.Stream object for it takes
+    2.7 us, a third of a call (0.2 us this way): lookup, forward pass and aggregation of 48 samples 23 -> 17 us."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 class Batch:
