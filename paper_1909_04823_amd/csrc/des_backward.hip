@@ -762,12 +762,16 @@ __device__ inline void add_entry(const BwdArgs &a, uint32_t p, int sub, Acc &acc
 // The kernel waits on memory for most of its time, so a fifth wave per SIMD is worth more than registers: it is
 // compiled for five (96 vector registers; at the 120 it would take by itself four fit), and gathers two entries'
 // gradient rows at a time instead of four, which is what lets it fit almost without spilling.  Measured at the large
-// table: 18.2 -> 16.5 ms; six waves (80 registers, 68 bytes of spill) lose that again.
+// table: 18.2 -> 16.5 ms; six waves (80 registers, 68 bytes of spill) lose that again.  The second state array's registers do
+// not fit in 96 (6 to 10 spilled), so those variants are compiled for four waves: D = 32, Adam, 4.8e5 / 1.9e6 / 7.7e6 entries
+// 50.7 -> 45.4, 101 -> 90, 245 -> 224 us.  Up to D = 16 they also have room for four entries at a time: FTRL with
+// Adagrad, D = 16, same sizes: 54.7 -> 45.5, 110 -> 87, 270 -> 217 us (two at a time: 48.7, 90, 232; at D = 32 four lose).
 // kSecond: an optimizer with a second state array (Adam, FTRL) may be in use.
 template <int D, bool kHasVals, bool kSecond>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5, 5))) void k_short_update(const BwdArgs a) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kSecond ? 4 : 5, kSecond ? 4 : 5))) void k_short_update(
+    const BwdArgs a) {
   constexpr int G = D / 4;
-  constexpr int U = 2;
+  constexpr int U = kSecond && (D == 8 || D == 16) ? 4 : 2;
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int sub = (int)(gid % G);
   const int64_t ngroups = (int64_t)gridDim.x * blockDim.x / G;
@@ -823,7 +827,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5, 5))) 
     } else {
       const RowState st = load_row<D, kSecond>(a, row, sub);
       add_entry<D, kHasVals>(a, p0, sub, acc);
-      reduce_entries<D, kHasVals, 2>(a, i0 + 1, i1, sub, acc);
+      reduce_entries<D, kHasVals, U>(a, i0 + 1, i1, sub, acc);
       apply_row<D, kSecond>(a, u, row, sub, st, acc);
     }
   }
@@ -831,7 +835,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5, 5))) 
 
 // (4b) one wave per chunk of a long segment: the chunk is split evenly over the wave's lane
 // groups, the groups' sums are combined with cross-lane shuffles, and the wave writes
-// partials[c] = (s1[D], s2, gw, 0, 0) in double -- or, when the segment has no other chunk (33 .. 512
+// partials[c] = (s1[D], s2, gw, 0, 0) in double -- or, when the segment has no other chunk (33 .. 512 or 128
 // entries, most long segments), updates the row at once
 template <int D, bool kHasVals>
 __global__ __launch_bounds__(kBlock) void k_long_partial(const BwdArgs a) {
