@@ -7,7 +7,7 @@
 // Steps: (1) expand the CSR batch to (row, bag) pairs, (2) stable radix sort by row, (3) mark
 // segment heads and compact them (ascending row order), (4) one lane group per segment of up to
 // kShortMax entries reduces its entries in registers and updates the row in the same kernel; longer
-// segments are cut into chunks of kChunk entries, one wave each: a segment that is a single chunk
+// segments are cut into chunks of 512 or 128 entries, one wave each: a segment that is a single chunk
 // is updated by that wave, the others are combined and updated by one workgroup per segment.
 // Steps (1)-(3) need the batch and its rows only and can be issued ahead of the gradients
 // (des_backward_prepare).
@@ -22,7 +22,14 @@ namespace des {
 namespace {
 
 constexpr int kShortMax = 32;              // segments up to this many entries are reduced by one lane group
-constexpr int kChunk = 512;                // entries per chunk of a longer segment (one wave per chunk)
+// Entries per chunk of a longer segment (one wave per chunk), as a power of two.  A wave reads its chunk in dependent steps of 4
+// entries per lane group; a smaller batch has too few chunks of 512 to fill the chip, so those steps are all that is
+// waited for.  k_long_partial, 512 -> 128, D = 64: 4.8e5 entries 50 -> 20 us, 1.9e6 58 -> 42, 3.8e6 84 -> 79, 7.7e6
+// 179 -> 174, where k_long_final takes the gain back (17 -> 22).  64 or 256 are no better at 3.7e5.  (No batch has more chunks than n/33: a segment of L > 32 entries
+// has at most ceil(L/128) <= L/33 of them.)
+constexpr int kChunkShift = 9, kFewChunkShift = 7;
+constexpr int64_t kFewEntries = 1 << 22;
+inline int chunk_shift_for(int64_t n) { return n <= kFewEntries ? kFewChunkShift : kChunkShift; }
 constexpr int kMidFan = 64;                // chunk partials that one wave pre-sums for segments of more chunks than this
 constexpr int kShortGrid = 65536;          // most workgroups of the short-segment kernel (it strides over the segments)
 constexpr int kHeadItems = 8;
@@ -53,10 +60,12 @@ struct BwdArgs {
   uint32_t *head_sums;
   int32_t *long_seg;    // segment index of long segment j
   uint32_t *long_c0;    // first chunk of long segment j
+  // (the next three lie in the sorted keys, which nothing reads once the segments are cut)
   int32_t *multi_seg;   // long segment indices j of the segments with more than one chunk
   int32_t *group_seg;   // long segment index j of pre-summed group i (segments of more than kMidFan chunks)
   uint32_t *group_c;    // first chunk of that group
   int32_t *chunk_owner; // long segment index of chunk c
+  int chunk_shift;      // log2 of the entries per chunk
   double *partials;     // [chunks][D+4]
   // optimizer (opt_emb == DES_OPT_NONE: merge only)
   int opt_emb, opt_w;
@@ -70,6 +79,8 @@ struct BwdArgs {
   float *merged_out;
   int64_t *n_uniq_out;
 };
+
+__device__ inline int chunks_of(const BwdArgs &a, int len) { return (len + (1 << a.chunk_shift) - 1) >> a.chunk_shift; }
 
 __device__ inline float4 ld4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
 __device__ inline void st4(float *p, float4 v) { *reinterpret_cast<float4 *>(p) = v; }
@@ -278,7 +289,7 @@ __global__ __launch_bounds__(kBlock) void k_classify(const BwdArgs a) {
 #pragma unroll
   for (int i = 0; i < kHeadItems; ++i) {
     if (len[i] > kShortMax) {
-      const uint32_t nch = (uint32_t)((len[i] + kChunk - 1) / kChunk);
+      const uint32_t nch = (uint32_t)chunks_of(a, len[i]);
       ++nl; nc += nch;
       if (nch > 1) ++nm;
       if (nch > kMidFan) ng += (nch + kMidFan - 1) / kMidFan;
@@ -303,7 +314,7 @@ __global__ __launch_bounds__(kBlock) void k_classify(const BwdArgs a) {
 #pragma unroll
   for (int i = 0; i < kHeadItems; ++i) {
     if (len[i] > kShortMax) {
-      const uint32_t nch = (uint32_t)((len[i] + kChunk - 1) / kChunk);
+      const uint32_t nch = (uint32_t)chunks_of(a, len[i]);
       a.long_seg[j] = (int32_t)(tile0 + i);
       a.long_c0[j] = c0;
       if (nch > 1) a.multi_seg[jm++] = (int32_t)j;           // what the per-segment combine has to visit
@@ -320,7 +331,7 @@ __global__ __launch_bounds__(kBlock) void k_chunk_owner(const BwdArgs a) {
   const long long NL = a.ctrl->n_long;
   for (int64_t j = blockIdx.x; j < NL; j += gridDim.x) {
     const int u = a.long_seg[j];
-    const int nch = (a.seg_off[u + 1] - a.seg_off[u] + kChunk - 1) / kChunk;
+    const int nch = chunks_of(a, a.seg_off[u + 1] - a.seg_off[u]);
     const uint32_t c0 = a.long_c0[j];
     for (int i = threadIdx.x; i < nch; i += blockDim.x) a.chunk_owner[c0 + i] = (int32_t)j;
   }
@@ -501,14 +512,14 @@ __global__ __launch_bounds__(kSmallBlock) void k_sort_small(const BwdArgs a, uin
   for (uint32_t v = tid; v < U; v += kSmallBlock) {
     const uint32_t len = skey[v + 1] - skey[v];
     if (len <= (uint32_t)kShortMax) continue;
-    const uint32_t nch = (len + kChunk - 1) / kChunk;
+    const uint32_t nch = (uint32_t)chunks_of(a, (int)len);
     const uint32_t j = atomicAdd(&n_long, 1u), c0 = atomicAdd(&n_chunks, nch);
     a.long_seg[j] = (int32_t)v;
     a.long_c0[j] = c0;
     if (nch > 1) a.multi_seg[atomicAdd(&n_multi, 1u)] = (int32_t)j;
     for (uint32_t c = 0; c < nch; ++c) a.chunk_owner[c0 + c] = (int32_t)j;
   }
-  static_assert(kSmallSort / kChunk <= kMidFan, "no segment here has enough chunks for pre-summed groups");
+  static_assert((kSmallSort >> kFewChunkShift) <= kMidFan, "no segment here has enough chunks for pre-summed groups");
   __syncthreads();
   if (tid == 0) {
     heads_bookkeeping(a, U);
@@ -847,8 +858,8 @@ __global__ __launch_bounds__(kBlock) void k_long_partial(const BwdArgs a) {
   const int g = lane / G, sub = lane % G;
   const int j = a.chunk_owner[c];
   const int u = a.long_seg[j];
-  const int c_lo = a.seg_off[u] + (int)(c - a.long_c0[j]) * kChunk;
-  const int c_hi = min(c_lo + kChunk, a.seg_off[u + 1]);
+  const int c_lo = a.seg_off[u] + ((int)(c - a.long_c0[j]) << a.chunk_shift);
+  const int c_hi = min(c_lo + (1 << a.chunk_shift), a.seg_off[u + 1]);
   const int per = (c_hi - c_lo + NG - 1) / NG;
   const int i0 = min(c_lo + g * per, c_hi), i1 = min(i0 + per, c_hi);
   Acc acc = acc_zero();
@@ -861,7 +872,7 @@ __global__ __launch_bounds__(kBlock) void k_long_partial(const BwdArgs a) {
     acc.gw += __shfl_xor(acc.gw, m, kWave);
   }
   if (g == 0) {
-    if (a.seg_off[u + 1] - a.seg_off[u] <= kChunk) {
+    if (a.seg_off[u + 1] - a.seg_off[u] <= (1 << a.chunk_shift)) {
       // the segment is this one chunk: the wave holds its whole sum and updates the row itself
       const int row = a.uniq_rows[u];
       apply_row<D>(a, u, row, sub, load_row<D>(a, row, sub), acc);
@@ -887,7 +898,7 @@ __global__ __launch_bounds__(kBlock) void k_long_mid(const BwdArgs a) {
   if (gi >= a.ctrl->n_groups) return;                         // uniform per wave
   const int j = a.group_seg[gi];
   const int u = a.long_seg[j];
-  const int nch = (a.seg_off[u + 1] - a.seg_off[u] + kChunk - 1) / kChunk;
+  const int nch = chunks_of(a, a.seg_off[u + 1] - a.seg_off[u]);
   const int64_t c = a.group_c[gi];
   const int rel = (int)(c - a.long_c0[j]);
   const int cnt = min(kMidFan, nch - rel);
@@ -929,7 +940,7 @@ __global__ __launch_bounds__(kBlock) void k_long_final(const BwdArgs a) {
   for (int64_t jj = blockIdx.x; jj < NM; jj += gridDim.x) {
     const int j = a.multi_seg[jj];
     const int u = a.long_seg[j];
-    const int nch = (a.seg_off[u + 1] - a.seg_off[u] + kChunk - 1) / kChunk;
+    const int nch = chunks_of(a, a.seg_off[u + 1] - a.seg_off[u]);
     const double *p0 = a.partials + (int64_t)a.long_c0[j] * (D + 4);
     const int step = nch > kMidFan ? kMidFan : 1;      // k_long_mid left one sum per kMidFan chunks
     Acc acc = acc_zero();
@@ -992,7 +1003,7 @@ template <int D, bool kHasVals>
 void launch_update(const BwdArgs &a, hipStream_t s) {
   constexpr int G = D / 4;
   const int64_t max_long = a.n / (kShortMax + 1) + 1;
-  const int64_t max_chunks = a.n / kChunk + max_long + 1;
+  const int64_t max_chunks = (a.n >> a.chunk_shift) + max_long + 1;
   {
     ProfScope ps(KID_SHORT_UPDATE, s);
     const bool second = a.opt_emb == DES_OPT_ADAM || a.opt_w == DES_OPT_ADAM || a.opt_w == DES_OPT_FTRL;
@@ -1006,8 +1017,9 @@ void launch_update(const BwdArgs &a, hipStream_t s) {
   }
   {
     ProfScope ps(KID_LONG_FINAL, s);
-    const int64_t max_multi = a.n / (kChunk + 1) + 1, max_groups = 3 * (a.n / ((int64_t)kChunk * kMidFan)) + 4;
-    if (a.n > (int64_t)kChunk * kMidFan)          // a smaller batch cannot hold a segment of that many chunks
+    const int64_t chunk = 1ll << a.chunk_shift, max_multi = a.n / (chunk + 1) + 1;
+    const int64_t max_groups = 3 * (a.n / (chunk * kMidFan)) + 4;   // sum of ceil(chunks / kMidFan) over those segments
+    if (a.n > chunk * kMidFan)          // a smaller batch cannot hold a segment of that many chunks
       hipLaunchKernelGGL(k_long_mid<D>, dim3(blocks_for(max_groups * kWave)), dim3(kBlock), 0, s, a);
     hipLaunchKernelGGL(k_long_final<D>, dim3((unsigned)(max_multi < 8192 ? max_multi : 8192)), dim3(kBlock), 0, s, a);
   }
@@ -1019,13 +1031,12 @@ void launch_update_v(const BwdArgs &a, hipStream_t s) {
 }
 
 struct Layout {
-  size_t key_a, key_b, pay_a, pay_b, bag_of, seg_off, uniq_rows, first_pay, head_sums, long_seg, long_c0, multi_seg, group_seg,
-      group_c, chunk_owner, partials, sort_scratch, total;
+  size_t key_a, key_b, pay_a, pay_b, bag_of, seg_off, uniq_rows, first_pay, head_sums, long_seg, long_c0, chunk_owner, partials, sort_scratch, total;
 };
 
 Layout layout_for(int D, int64_t n) {
   const size_t m = (size_t)(n > 0 ? n : 1);
-  const size_t max_long = m / (kShortMax + 1) + 1, max_chunks = m / kChunk + max_long + 1;
+  const size_t max_long = m / (kShortMax + 1) + 1, max_chunks = (m >> kChunkShift) + max_long + 1;
   Layout L;
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o += align_up(bytes, 256); return at; };
@@ -1034,9 +1045,6 @@ Layout layout_for(int D, int64_t n) {
   L.seg_off = take((m + 1) * 4); L.uniq_rows = take(m * 4); L.first_pay = take(m * 4);
   L.head_sums = take(((m + kHeadTile - 1) / kHeadTile + 1) * 4);
   L.long_seg = take(max_long * 4); L.long_c0 = take(max_long * 4);
-  L.multi_seg = take((m / (kChunk + 1) + 1) * 4);
-  const size_t max_groups = 3 * (m / ((size_t)kChunk * kMidFan)) + 4;   // sum of ceil(chunks / kMidFan) over those segments
-  L.group_seg = take(max_groups * 4); L.group_c = take(max_groups * 4);
   L.chunk_owner = take(max_chunks * 4);
   L.partials = take(max_chunks * (size_t)(D + 4) * 8);
   L.sort_scratch = take(sort_scratch_bytes(n));       // right behind the partials, see sort_stage
@@ -1053,6 +1061,15 @@ int bits_for(uint64_t max_value) {
 // Row-sorting half of the backward pass: CSR -> (row, bag) pairs, sort by row, segment heads, split into
 // short and long segments.  Needs the batch and its rows only, not the gradients.  Returns which sort
 // buffer holds the sorted pairs.
+// The sorted keys' buffer, and in it the lists that the split of long segments leaves once the keys have served: up to n/129
+// segments of several chunks, and 3n/8192 + 4 groups in batches of more than 8192 entries.
+void set_sorted_keys(BwdArgs &a, uint32_t *keys) {
+  a.key_sorted = keys;
+  a.multi_seg = (int32_t *)keys;
+  a.group_seg = (int32_t *)(keys + a.n / 2);
+  a.group_c = keys + a.n / 4 * 3;
+}
+
 int sort_stage(des_table *t, BwdArgs &a, const Layout &L, hipStream_t s) {
   char *ws = t->ws;
   const int64_t n = a.n;
@@ -1061,6 +1078,7 @@ int sort_stage(des_table *t, BwdArgs &a, const Layout &L, hipStream_t s) {
   if (n <= kSmallSort && a.nbags <= kSmallBags) {
     ProfScope ps(KID_SORT_SCATTER, s);
     a.pay_sorted = pay_a;
+    set_sorted_keys(a, key_a);
     if (a.vals) hipLaunchKernelGGL(k_sort_small<true>, dim3(1), dim3(kSmallBlock), 0, s, a, pay_a, bits);
     else hipLaunchKernelGGL(k_sort_small<false>, dim3(1), dim3(kSmallBlock), 0, s, a, pay_a, bits);
     return 0;
@@ -1076,7 +1094,7 @@ int sort_stage(des_table *t, BwdArgs &a, const Layout &L, hipStream_t s) {
   // scratch right behind them, for the finer tile counts of a small batch (2 bytes per entry; the chunk sums alone are
   // 8*(D+4)*(1/33 + 1/512) >= 2.06 bytes per entry)
   const int side = radix_sort_u32_pairs(sb, n, bits, ws + L.sort_scratch, ws + L.partials, (uint32_t *)(ws + L.uniq_rows), s);
-  a.key_sorted = (uint32_t *)(ws + (side ? L.key_b : L.key_a));
+  set_sorted_keys(a, (uint32_t *)(ws + (side ? L.key_b : L.key_a)));
   a.pay_sorted = (uint32_t *)(ws + (side ? L.pay_b : L.pay_a));
   {
     ProfScope ps(KID_HEADS, s);
@@ -1114,8 +1132,7 @@ void batch_args(des_table *t, const des_batch_t *b, const int32_t *rows, const L
   a.first_pay = (uint32_t *)(ws + L.first_pay);
   a.head_sums = (uint32_t *)(ws + L.head_sums);
   a.long_seg = (int32_t *)(ws + L.long_seg); a.long_c0 = (uint32_t *)(ws + L.long_c0);
-  a.multi_seg = (int32_t *)(ws + L.multi_seg);
-  a.group_seg = (int32_t *)(ws + L.group_seg); a.group_c = (uint32_t *)(ws + L.group_c);
+  a.chunk_shift = chunk_shift_for(b->nnz);
   a.chunk_owner = (int32_t *)(ws + L.chunk_owner); a.partials = (double *)(ws + L.partials);
 }
 
@@ -1164,7 +1181,7 @@ des_status_t backward_launch(des_table *t, const des_batch_t *b, const int32_t *
   a.uniq_rows_out = io->uniq_rows_out; a.uniq_keys_out = io->uniq_keys_out; a.counts_out = io->counts_out;
   a.merged_out = io->merged_out; a.n_uniq_out = io->n_uniq_out;
   if (prepared) {
-    a.key_sorted = (uint32_t *)(ws + (t->prep.side ? L.key_b : L.key_a));
+    set_sorted_keys(a, (uint32_t *)(ws + (t->prep.side ? L.key_b : L.key_a)));
     a.pay_sorted = (uint32_t *)(ws + (t->prep.side ? L.pay_b : L.pay_a));
     if (io->n_uniq_out) hipLaunchKernelGGL(k_report_n_uniq, dim3(1), dim3(1), 0, s, t->ctrl, io->n_uniq_out);
   } else {

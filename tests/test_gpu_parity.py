@@ -792,6 +792,45 @@ def test_merge_rows_of_more_than_64_chunks(oracle, des, D, with_vals):
         p.close()
 
 
+@pytest.mark.parametrize("n,D,lens,with_vals", [
+    (4096, 16, [32, 33, 127, 128, 129, 256, 257, 1025], True),                  # the one-workgroup sort
+    (4097, 8, [33, 128, 129, 3001], False),                                    # one entry more
+    (60001, 32, [128, 129, 8191, 8192, 8193, 24577], True),                    # 64 chunks of 128, one more, 193
+    (1 << 22, 4, [129, 512, 513, 8193, 32769, 1000001], False),                # the last size with chunks of 128
+    ((1 << 22) + 1, 4, [129, 512, 513, 8193, 32769, 1000001], False),          # the first with chunks of 512
+])
+def test_merge_chunk_length_limits(oracle, des, n, D, lens, with_vals):
+    """Rows whose occurrences sit on the boundaries of the chunks, next to rows of a few entries: merged sums and counts, then Adam
+    with FTRL."""
+    import torch
+    rng = np.random.default_rng(n)
+    few = rng.integers(len(lens), len(lens) + max(n // 8, 64), n - sum(lens))
+    ids = np.concatenate([np.repeat(np.arange(len(lens)), lens), few])
+    keys = synth.scramble64(ids[rng.permutation(n)].astype(np.uint64) + np.uint64(1))
+    B, F, K = 4096, 3, 4
+    cuts = np.sort(rng.integers(0, n + 1, size=B * F - 1))
+    offsets = np.concatenate([[0], cuts, [n]]).astype(np.int32)
+    vals = rng.uniform(0.25, 2.0, n).astype(np.float32) if with_vals else None
+    batch = synth.Batch(B, F, keys, offsets, vals)
+    capacity = np.unique(ids).size + 3
+    p = Pair(oracle, des, D, capacity, K, 0, des.OPT_NONE, seed=5, init_scale=0.1, max_n=n, state_arrays=(2, 2))
+    try:
+        rows = p.find(batch, insert=True)
+        P = p.ot.partial_forward(B, F, batch.keys, batch.offsets, rows, K, 0, batch.vals, pool=False)
+        A_sum = oracle.aggregate(P["P_sum"]).astype(np.float32)
+        g_lr = (1e-3 * rng.standard_normal(B)).astype(np.float32)
+        g_fm = (1e-4 * rng.standard_normal(B)).astype(np.float32)
+        g_pool = (1e-3 * rng.standard_normal((B, F, D))).astype(np.float32)
+        ref = p.backward(batch, g_lr, g_fm, A_sum, g_pool, opt=des.OPT_NONE)
+        assert set(lens) <= set(ref["counts"].tolist()) and int(ref["counts"].sum()) == n
+        p.backward(batch, g_lr, g_fm, A_sum, g_pool, optimizer=dict(
+            opt_emb=des.OPT_ADAM, opt_w=des.OPT_FTRL, lr=0.01, eps=1e-8, beta1=0.9, beta2=0.999, step=1, ftrl_alpha=0.05,
+            ftrl_beta=1.0, ftrl_l1=1e-4, ftrl_l2=0.1))
+        p.check_weights("adam with ftrl")
+    finally:
+        p.close()
+
+
 # ------------------------------------------------- one-workgroup sort and its neighbours ---------
 @pytest.mark.parametrize("n,B,F,capacity,vals", [
     (1, 1, 1, 1, False), (33, 3, 5, 300, True), (513, 40, 3, 1 << 16, False), (4095, 7, 9, 20000, True),
