@@ -73,22 +73,15 @@ __device__ inline int lds_offset(int row, int chunk) {
   return (((row & ~3) | ((row + (row >> 3)) & 3)) << 5) | ((chunk ^ ((row >> 2) & 1)) << 4);
 }
 
-// What the cut cannot represent: `rest` collects in its low half bits of the last rest below bf16's smallest denormal
-// (operands under 2^-110); `nan` turns NaN at an infinity or NaN (or overflows at operands above 2^80).
-struct Odd {
-  uint32_t rest;
-  float nan;
-};
-
-// Two floats to their three bf16 parts, packed pairwise.
-__device__ inline void split2(float a0, float a1, uint32_t &hi, uint32_t &mid, uint32_t &lo, Odd &odd) {
+// Two floats to their three bf16 parts, packed pairwise.  What the cut cannot represent shows in the low half of `odd`: bits
+// of the last rest below bf16's smallest denormal (operands under 2^-110).
+__device__ inline void split2(float a0, float a1, uint32_t &hi, uint32_t &mid, uint32_t &lo, uint32_t &odd) {
   hi = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){a0, a1}, bf16x2));
   const float r0 = a0 - __uint_as_float(hi << 16), r1 = a1 - __uint_as_float(hi & 0xFFFF0000u);
   mid = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){r0, r1}, bf16x2));
   const float l0 = r0 - __uint_as_float(mid << 16), l1 = r1 - __uint_as_float(mid & 0xFFFF0000u);
   lo = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){l0, l1}, bf16x2));
-  odd.rest |= __float_as_uint(l0) | __float_as_uint(l1);
-  odd.nan = __builtin_fmaf(l0, l1, odd.nan);
+  odd |= __float_as_uint(l0) | __float_as_uint(l1);
 }
 
 // The part of a T x BK operand tile that a thread stages, and its way there.
@@ -154,7 +147,7 @@ struct Operand {
   }
   // cuts the staged values into the three planes at `plane` (T rows each), their signs flipped if `flip` is the sign bit
   template <bool kFlip>
-  __device__ inline void store_split(const float4 (&v)[kVecs], char *plane, uint32_t flip, Odd &odd) const {
+  __device__ inline void store_split(const float4 (&v)[kVecs], char *plane, uint32_t flip, uint32_t &odd) const {
     static_assert(BK == 16, "two chunks per row");
     if (T != 128 && !active) return;
     float f[kVecs * 4];
@@ -264,11 +257,22 @@ struct Sums {
     if (!kTwoLevel || odd) negate();               // the next run, or the total, wants the other sign
     if (kTwoLevel) flush();
   }
+  // The finished sum; flush() first if there are two levels.
+  __device__ inline float value(int i, int j, int r) const { return kTwoLevel ? total[i][j][r] : acc[i][j][r]; }
+  __device__ inline bool finite() const {
+    float any = 0.f;                               // times zero: NaN for an infinity or NaN, else zero
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) any = __builtin_fmaf(value(i, j, r), 0.f, any);
+    return any == 0.f;
+  }
   // element r of a 32x32 block sits at row (r/4)*8 + (lane/32)*4 + r%4, column lane%32
-  __device__ inline void store(const GemmArgs &g, int z, int m_wave, int n_wave) {
+  __device__ inline void store(const GemmArgs &g, int z, int m_wave, int n_wave) const {
     const int lane = threadIdx.x & (kWave - 1);
     float *C = g.C + (long long)z * g.c_slice;
-    if (kTwoLevel) flush();
 #pragma unroll
     for (int i = 0; i < NB; ++i)
 #pragma unroll
@@ -277,7 +281,7 @@ struct Sums {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int row = m_wave + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-          if (row < g.M && col < g.N) C[(long long)row * g.c_rs + col] = kTwoLevel ? total[i][j][r] : acc[i][j][r];
+          if (row < g.M && col < g.N) C[(long long)row * g.c_rs + col] = value(i, j, r);
         }
       }
   }
@@ -338,6 +342,7 @@ __device__ inline void multiply_f32(const GemmArgs &g, const Place<T> &at, float
     }
     if (kTwoLevel && (run += BK) == kRun) { run = 0; sums.flush(); }
   }
+  if (kTwoLevel) sums.flush();
 }
 
 template <int T, bool kAKContig, bool kBKContig, bool kTwoLevel>
@@ -393,7 +398,7 @@ struct SplitStage {
   }
   // k0: the tile's first product; A is negated in every second run
   template <int kSet>
-  __device__ inline void store(int buf, int k0, Odd &odd) const {
+  __device__ inline void store(int buf, int k0, uint32_t &odd) const {
     oa.template store_split<true>(va[kSet], to + buf, k0 / kRun & 1 ? flips : 0u, odd);
     if constexpr (!kShared) ob.template store_split<false>(vb[kSet], to + buf + kOperandBytes, 0u, odd);
   }
@@ -414,7 +419,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_split(const GemmArgs g) {
   const int klen = at.klen;
   Sums<NB, kTwoLevel> sums;
   sums.clear();
-  Odd odd{0u, 0.f};
+  uint32_t odd = 0;
   if (klen > 0) {
     SplitStage<T, BK, kAKContig, kBKContig> stage;
     stage.start(g, at, lds);
@@ -456,10 +461,12 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_split(const GemmArgs g) {
     // the run the loop ended in, if it is not complete; a complete one has been turned
     const int tiles = (klen + BK - 1) / BK;
     if (tiles % (kRun / BK) != 0 ? tiles / (kRun / BK) & 1 : !kTwoLevel && (tiles / (kRun / BK) & 1)) sums.negate();
+    if (kTwoLevel) sums.flush();
   }
-  // An infinity or NaN (times a zero part it would make a NaN of what should stay infinite), or an operand too small for
-  // three bf16 parts: the tile is computed again with the fp32 instruction.
-  if (__syncthreads_or((odd.rest & 0xFFFFu) != 0 || !(fabsf(odd.nan) <= 3.4028235e38f)))
+  // An infinity or NaN among the operands (times a zero part it makes a NaN of what should stay infinite), a product or sum past
+  // fp32's range (its parts' products can be infinities of both signs, a NaN again): either leaves a sum that is not
+  // finite.  Then, or if an operand was too small for three bf16 parts, the tile is computed again with the fp32 instruction.
+  if (__syncthreads_or((odd & 0xFFFFu) != 0 || !sums.finite()))
     multiply_f32<T, kAKContig, kBKContig, kTwoLevel>(g, at, reinterpret_cast<float *>(lds), sums);
   sums.store(g, at.z, at.m0 + m_wave, at.n0 + n_wave);
 }

@@ -139,6 +139,28 @@ def test_dnn_gradients_of_infinities_nans_and_extreme_magnitudes(des, B, F, D, H
     assert np.all(np.abs(g_pool - ref) <= np.maximum(1e-5 * np.abs(ref), 1e-6))
 
 
+@pytest.mark.parametrize("B,F,D,H", [(300, 7, 8, 200), (12801, 8, 100, 128)])     # small and large tiles
+def test_dnn_gradients_that_overflow_are_infinite(des, B, F, D, H):
+    """A product beyond fp32's range, and a sum of finite products that leaves it, make an infinity of the sign that fp32
+    arithmetic gives; no NaN, and the other outputs keep their values."""
+    import torch
+    pool, W, dY = synth.dnn_layer_inputs(B + 3, B, F, D, H)
+    dY[7, 5], dY[9, 6] = 1.37 * 2.0 ** 70, 1.37 * 2.0 ** 100
+    W[3, 5], W[4, 6] = 1.21 * 2.0 ** 70, -1.21 * 2.0 ** 60
+    pool.reshape(B, -1)[7, 2], pool.reshape(B, -1)[9, 1] = 1.43 * 2.0 ** 79, -1.11 * 2.0 ** 75
+    dY[200, :], W[-1, :] = 2.0 ** 63, 2.0 ** 64           # each product 2^127, their sum past the range (in a tile of its own)
+    x, w, g = pool.reshape(B, F * D).astype(np.float64), W.astype(np.float64), dY.astype(np.float64)
+    with np.errstate(over="ignore"):
+        refs = (g @ w.T).astype(np.float32), (x.T @ g).astype(np.float32)
+    assert np.isinf(refs[0]).sum() >= 3 and np.isinf(refs[1]).sum() >= 2
+    for got, ref, what in zip(_gradients(des, torch, pool, W, dY), refs, ("g_pool", "dW")):
+        fin = np.isfinite(ref)
+        assert np.array_equal(got[~fin], ref[~fin]), what
+        # 2^-21 of the sum of the magnitudes: a chain of up to 12801 products, each huge element met by ordinary ones
+        mag = (np.abs(g) @ np.abs(w.T)) if what == "g_pool" else (np.abs(x.T) @ np.abs(g))
+        assert np.all(np.abs(got[fin].astype(np.float64) - ref[fin]) <= 2.0 ** -21 * mag[fin]), what
+
+
 def test_dnn_weight_gradient_has_no_drift(des):
     """The matrix instruction's rounding towards minus infinity must not pile up over a long sum: the mean error over 4096 sums of
     2504 products per slice (uncorrected -3e-7 of the results' root mean square, its standard error 4e-9) stays below 3e-8."""
