@@ -246,11 +246,11 @@ struct Sums {
         for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
       }
   }
-  __device__ inline void negate() {
+  __device__ inline void negate() {                // a sum of zeros stays +0
 #pragma unroll
     for (int i = 0; i < NB; ++i)
 #pragma unroll
-      for (int j = 0; j < NB; ++j) acc[i][j] = -acc[i][j];
+      for (int j = 0; j < NB; ++j) acc[i][j] = 0.f - acc[i][j];
   }
   // End of a run of a sum whose every second run is accumulated with the opposite sign (`odd`: this was one).
   __device__ inline void turn(bool odd) {

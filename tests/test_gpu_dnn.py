@@ -161,6 +161,15 @@ def test_dnn_gradients_that_overflow_are_infinite(des, B, F, D, H):
         assert np.all(np.abs(got[fin].astype(np.float64) - ref[fin]) <= 2.0 ** -21 * mag[fin]), what
 
 
+@pytest.mark.parametrize("H", [64, 128, 200, 256, 300, 400, 1100])     # one run of 128 products, odd and even numbers of them
+def test_dnn_gradients_of_zeros_are_plus_zero(des, H):
+    import torch
+    pool, W, dY = synth.dnn_layer_inputs(H, 300, 7, 8, H)
+    dY[:] = 0
+    for got, what in zip(_gradients(des, torch, pool, W, dY), ("g_pool", "dW")):
+        assert not got.view(np.int32).any(), what
+
+
 def test_dnn_weight_gradient_has_no_drift(des):
     """The matrix instruction's rounding towards minus infinity must not pile up over a long sum: the mean error over 4096 sums of
     2504 products per slice (uncorrected -3e-7 of the results' root mean square, its standard error 4e-9) stays below 3e-8."""
