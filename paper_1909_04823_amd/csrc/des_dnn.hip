@@ -26,7 +26,10 @@
 // 65536 x 12800 x 256: g_pool 3.81 -> 2.60 ms (165 TFLOP/s), dW 3.65 -> 2.55 ms; a library's plain bf16 product of 8192^3 reaches
 // 1.1 PFLOP/s here, one sixth of which is 183.  The bf16 instruction drops the bits of its sum that do not fit, towards minus
 // infinity; over many runs that adds up (a mean of -3e-7 of the results' root mean square at 124623 samples), so every second run
-// of kRun products is accumulated with the opposite sign.  16384 x 3200 x 256: 248 -> 179 us, 233 -> 163 us.  Error against 64 bits, 2-norm:
+// of kRun products is accumulated with the opposite sign.  A single run, or a last one without a partner, keeps its part: tiles and
+// slices begin with alternating signs, so that it has both signs in what a row of the table adds up over the samples and in
+// a slice sum (mean error / root mean square, all beginning with plus and so: g_pool of 128 hidden units, 4096 samples,
+// -9.4e-9 and -2e-11; dW of 2048 samples -2.9e-8 and 3e-10.  Signs by rows instead of tiles cost g_pool 4 %).  16384 x 3200 x 256: 248 -> 179 us, 233 -> 163 us.  Error against 64 bits, 2-norm:
 // 2.4e-7 where the fp32 instruction has 2.9e-7 (16384 x 3200 x 256), 2.6e-7 and 3.1e-7 (5003 x 540 x 300).
 //
 // Products through operand strides and a sliced k range:
@@ -198,6 +201,7 @@ struct Operand {
 template <int T>
 struct Place {
   int m0, n0, z, klen;
+  int sign;                        // 1: the split product's first run is accumulated with the opposite sign
   uint32_t first;                  // position of the slice's first product
   bool ok;
   __device__ inline explicit Place(const GemmArgs &g) {
@@ -214,6 +218,7 @@ struct Place {
     n0 = (int)(tile - group * per_group - mz * g.tiles_n) * T;
     z = (int)(mz / in_group);
     m0 = (int)(group * g.m_group + mz % in_group) * T;
+    sign = (m0 / T ^ n0 / T ^ z) & 1;
     const unsigned long long at = (unsigned long long)z * g.k_shift;      // may lie past the end: a shard without a field
     first = at < g.k_limit ? (uint32_t)at : g.k_limit;
     const uint32_t avail = g.k_limit - first, blocks = avail / g.blk_stride, tail = avail - blocks * g.blk_stride;
@@ -235,6 +240,12 @@ struct Sums {
       for (int j = 0; j < NB; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) { acc[i][j][r] = 0.f; total[i][j][r] = 0.f; }
+  }
+  __device__ inline void negate_total() {
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) total[i][j] = 0.f - total[i][j];
   }
   __device__ inline void flush() {
 #pragma unroll
@@ -369,8 +380,10 @@ struct SplitStage {
   float4 va[2][OpA::kVecs], vb[2][OpB::kVecs];    // two tiles under way
   char *to;
   uint32_t flips;                                 // the sign bit for threads that stage A
+  int sign;
   __device__ inline void start(const GemmArgs &g, const Place<T> &at, char *lds) {
     const float *A = g.A + (unsigned long long)at.first * g.a_ks, *B = g.B + (unsigned long long)at.first * g.b_ks;
+    sign = at.sign;
     if constexpr (kShared) {
       constexpr int n = Operand<T, BK, false>::kTotal;
       const bool second = threadIdx.x / n == 1;   // threads past the second operand's units: idle
@@ -396,10 +409,10 @@ struct SplitStage {
     oa.blank(va[kSet], k0, klen);
     if constexpr (!kShared) ob.blank(vb[kSet], k0, klen);
   }
-  // k0: the tile's first product; A is negated in every second run
+  // k0: the tile's first product; A is negated in every second run, in the first one if `sign` is 1
   template <int kSet>
   __device__ inline void store(int buf, int k0, uint32_t &odd) const {
-    oa.template store_split<true>(va[kSet], to + buf, k0 / kRun & 1 ? flips : 0u, odd);
+    oa.template store_split<true>(va[kSet], to + buf, (k0 / kRun ^ sign) & 1 ? flips : 0u, odd);
     if constexpr (!kShared) ob.template store_split<false>(vb[kSet], to + buf + kOperandBytes, 0u, odd);
   }
 };
@@ -458,10 +471,16 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_split(const GemmArgs g) {
       step(std::integral_constant<int, 0>{}, k0);
       if (k0 + BK < klen) step(std::integral_constant<int, 1>{}, k0 + BK);
     }
-    // the run the loop ended in, if it is not complete; a complete one has been turned
+    // the run the loop ended in, if it is not complete (a complete one has been turned), and the sign of the whole
     const int tiles = (klen + BK - 1) / BK;
-    if (tiles % (kRun / BK) != 0 ? tiles / (kRun / BK) & 1 : !kTwoLevel && (tiles / (kRun / BK) & 1)) sums.negate();
-    if (kTwoLevel) sums.flush();
+    const bool odd_run = (tiles % (kRun / BK) != 0 || !kTwoLevel) && (tiles / (kRun / BK) & 1);
+    if (kTwoLevel) {
+      if (odd_run) sums.negate();
+      sums.flush();
+      if (at.sign) sums.negate_total();
+    } else if (odd_run != (at.sign != 0)) {
+      sums.negate();
+    }
   }
   // An infinity or NaN among the operands (times a zero part it makes a NaN of what should stay infinite), a product or sum past
   // fp32's range (its parts' products can be infinities of both signs, a NaN again): either leaves a sum that is not

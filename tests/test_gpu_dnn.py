@@ -170,6 +170,19 @@ def test_dnn_gradients_of_zeros_are_plus_zero(des, H):
         assert not got.view(np.int32).any(), what
 
 
+@pytest.mark.parametrize("B,F,D,H", [(4096, 26, 16, 64), (4096, 26, 16, 128), (4096, 26, 16, 300), (4096, 26, 16, 1100),   # g_pool: 1, 1, 3, 9 runs
+                                     (2048, 26, 16, 256), (300, 26, 16, 256)])   # dW: slices of one or two runs
+def test_dnn_gradients_have_no_mean_error(des, B, F, D, H):
+    """Also where the number of runs is odd.  The mean of n independent errors of the size `err` is within 6 err / sqrt(n); with the
+    instruction's rounding towards minus infinity left in, it is up to 100 times err / sqrt(n) here."""
+    import torch
+    pool, W, dY = synth.dnn_layer_inputs(B + H, B, F, D, H)
+    x, w, g = pool.reshape(B, F * D).astype(np.float64), W.astype(np.float64), dY.astype(np.float64)
+    for got, ref, what in zip(_gradients(des, torch, pool, W, dY), (g @ w.T, x.T @ g), ("g_pool", "dW")):
+        err = got - ref
+        assert abs(err.mean()) <= 6 * np.sqrt((err * err).mean() / err.size), what
+
+
 def test_dnn_weight_gradient_has_no_drift(des):
     """The matrix instruction's rounding towards minus infinity must not pile up over a long sum: the mean error over 4096 sums of
     2504 products per slice (uncorrected -3e-7 of the results' root mean square, its standard error 4e-9) stays below 3e-8."""
