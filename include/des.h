@@ -230,7 +230,7 @@ des_status_t des_fm_finalize(const float *A_sum, const float *A_sq, int64_t B, i
  *     Y_partial[s,b,h] = sum over fields f of shard s, d < D of  pool[b,f,d] * W[f*D+d, h].
  * des_aggregate_partials(Y_partial, K, B*H) then gives the layer output.  A shard with no field
  * (K > F) writes zeros.  fp32 in and out; products accumulate in fp32 on the matrix cores in
- * ascending k; a contraction deeper than 1024 products is summed in runs of 128 products that are
+ * ascending k; a contraction deeper than 1024 products is summed in runs of up to 128 products that are
  * then added up (two-level fp32 summation), which keeps a sum over a whole batch within the
  * 1e-5 / 1e-6 bound of the rest of the library.
  * pool, W, Y_partial: device, 16-byte aligned, row-major as written; Y_partial [K,B,H] is owned by

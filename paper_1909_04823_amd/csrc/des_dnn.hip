@@ -11,8 +11,8 @@
 // where that leaves CUs idle), four waves in a 2x2 arrangement of 64x64 (32x32).  Two kernels:
 //
 // k_gemm_f32, the forward product: the fp32 matrix instruction (32x32x2, 64 cycles), 32 products deep per LDS tile, the next
-// tile in registers meanwhile.  Bound by the matrix pipe.  The sum of an output element is one chain in ascending k whatever
-// the tile, so results do not depend on the tile size.  It keeps the fp32 chain because a ReLU follows it: with the split
+// tile in registers meanwhile.  Bound by the matrix pipe.  The sum of an output element is one chain in ascending k (above 1024
+// products: of chains of forward_run products) whatever the tile, so results do not depend on the tile size.  It keeps the fp32 chain because a ReLU follows it: with the split
 // (223 against 271 us at 16384 x 3200 x 256) a unit within 1e-8 of zero changes sides in one of six training steps at 4096 x 256
 // units, and its gradient with it.  A shard's fields are walked as one range (a field of 20 columns costs no padding).
 //
@@ -65,6 +65,7 @@ struct GemmArgs {
   // below k_limit, at most k_max positions; the blocks are walked as one range, so a k tile may span several of them.
   uint32_t k_shift, k_limit, k_max, blk_stride, blk_len;
   int tiles_m, tiles_n, slices, m_group;
+  int run;                            // products per first-level run of a two-level sum with the fp32 instruction
 };
 
 __device__ inline float4 ld4g(const float *p) { return *reinterpret_cast<const float4 *>(p); }
@@ -351,7 +352,7 @@ __device__ inline void multiply_f32(const GemmArgs &g, const Place<T> &at, float
 #pragma unroll
       for (int i = 0; i < NB; ++i) { a[i] = an[i]; b[i] = bn[i]; }
     }
-    if (kTwoLevel && (run += BK) == kRun) { run = 0; sums.flush(); }
+    if (kTwoLevel && (run += BK) == g.run) { run = 0; sums.flush(); }
   }
   if (kTwoLevel) sums.flush();
 }
@@ -505,6 +506,15 @@ inline int tile_edge(long long M, long long N, long long slices) {
   return large >= 384 && large * 40 <= small * 11 ? 128 : 64;    // at most 10 % more area
 }
 
+// Runs of the forward product's two-level sums: as many products as eight 16-deep tiles hold that never span two fields, in whole
+// k tiles, so 128 only where the fields fill such tiles.  (Runs of 128 for every D: error against 64 bits, 2-norm, at F x D =
+// 300 x 4 / 200 x 8 / 100 x 20 / 50 x 36 2.1e-7 / 2.1e-7 / 2.2e-7 / 2.2e-7; so
+// 1.5e-7 / 1.7e-7 / 1.8e-7 / 1.9e-7, in the same time.)
+inline int forward_run(int D) {
+  const int run = 8 * D / ((D + 15) / 16) / kPlainBK * kPlainBK;
+  return run < kPlainBK ? kPlainBK : run;
+}
+
 // `depth`: products summed per output element of one slice; above kTwoLevelDepth the two-level kernel runs.
 template <bool kSplit, bool kAKContig, bool kBKContig>
 des_status_t launch(GemmArgs g, int slices, long long depth, int kid, hipStream_t s) {
@@ -549,6 +559,7 @@ des_status_t des_dnn_partial_forward(const float *pool, const float *W, int64_t 
   g.C = Y_partial; g.M = (int)B; g.N = H; g.c_rs = H; g.c_slice = (long long)B * H;
   // shard s: fields s, s+K, ... = k blocks of length D starting at s*D, K*D apart
   g.m_group = kForwardGroup;
+  g.run = forward_run(D);
   g.k_shift = g.blk_len = D; g.blk_stride = (uint32_t)(K < F ? K : F) * D; g.k_limit = g.k_max = (uint32_t)F * D;
   return launch<false, true, false>(g, K, (long long)((F + K - 1) / K) * D, KID_DNN_FORWARD, (hipStream_t)stream);
 }
@@ -577,6 +588,7 @@ des_status_t des_dnn_backward(const float *pool, const float *W, const float *dY
     g.B = W; g.b_xs = H; g.b_ks = 1;
     g.C = g_pool; g.M = (int)B; g.N = (int)FD; g.c_rs = FD; g.c_slice = 0;
     g.m_group = 0;
+    g.run = kRun;
     g.k_shift = 0; g.blk_len = g.blk_stride = g.k_limit = g.k_max = H;
     des_status_t st = launch<true, true, true>(g, 1, H, KID_DNN_GPOOL, s);
     if (st != DES_OK) return st;
@@ -604,6 +616,7 @@ des_status_t des_dnn_backward(const float *pool, const float *W, const float *dY
     g.B = dY; g.b_xs = 1; g.b_ks = H;
     g.C = Z > 1 ? (float *)workspace : dW; g.M = (int)FD; g.N = H; g.c_rs = H; g.c_slice = FD * H;
     g.m_group = 0;
+    g.run = kRun;
     g.k_shift = g.k_max = (uint32_t)chunk; g.blk_len = g.blk_stride = 1u << 31; g.k_limit = (uint32_t)B;
     des_status_t st = launch<true, false, false>(g, Z, chunk, KID_DNN_DW, s);
     if (st != DES_OK) return st;

@@ -82,6 +82,18 @@ def test_dnn_layer_argument_checks(des):
     assert out.shape == (2, 0, 8)
 
 
+@pytest.mark.parametrize("F,D,bound", [(300, 4, 1.6e-7), (200, 8, 1.8e-7), (150, 12, 2.0e-7), (100, 16, 2.2e-7), (100, 20, 1.93e-7), (50, 36, 2.0e-7)])
+def test_dnn_forward_sums_deep_shards_in_short_runs(des, F, D, bound):
+    """A sum of more than 1024 products is taken in runs of at most 8 * D / ceil(D/16) products, 128 where D fills 16-deep tiles: its
+    2-norm error, which grows with the run's length, stays within 4 % of what a chain of that length leaves (1.54, 1.73, 1.94,
+    2.14, 1.87 and 1.95 e-7 on inputs of this kind)."""
+    import torch
+    pool, W, _ = synth.dnn_layer_inputs(F, 4096, F, D, 128)
+    Y = des.dnn_partial_forward(dev(pool, torch), dev(W, torch), 1).cpu().numpy()[0]
+    ref = pool.reshape(4096, F * D).astype(np.float64) @ W.astype(np.float64)
+    assert np.linalg.norm(Y - ref) <= bound * np.linalg.norm(ref)
+
+
 def _gradients(des, torch, pool, W, dY):
     B, F, D = pool.shape
     g_pool = torch.full((B, F, D), float("nan"), dtype=torch.float32, device="cuda")
