@@ -173,6 +173,19 @@ def test_dnn_gradients_that_overflow_are_infinite(des, B, F, D, H):
         assert np.all(np.abs(got[fin].astype(np.float64) - ref[fin]) <= 2.0 ** -21 * mag[fin]), what
 
 
+@pytest.mark.parametrize("B", [1, 2, 3])
+def test_dnn_weight_gradient_of_a_few_samples(des, B):
+    """One product is rounded once, to nearest; the sum of two or three loses no more than fp32 arithmetic does (2-norm errors 3.1e-8
+    and 3.6e-8, 3 % added)."""
+    import torch
+    pool, W, dY = synth.dnn_layer_inputs(B, B, 26, 16, 256)
+    _, dW = _gradients(des, torch, pool, W, dY)
+    ref = pool.reshape(B, 416).astype(np.float64).T @ dY.astype(np.float64)
+    if B == 1:
+        assert np.array_equal(dW, ref.astype(np.float32))
+    assert np.linalg.norm(dW - ref) <= {1: 2.6e-8, 2: 3.2e-8, 3: 3.7e-8}[B] * np.linalg.norm(ref)
+
+
 @pytest.mark.parametrize("H", [64, 128, 200, 256, 300, 400, 1100])     # one run of 128 products, odd and even numbers of them
 def test_dnn_gradients_of_zeros_are_plus_zero(des, H):
     import torch
