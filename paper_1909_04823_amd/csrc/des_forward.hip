@@ -19,6 +19,7 @@
 // Accumulation is in double, inputs and outputs are fp32: a sample's sum of several hundred
 // signed terms cancels, and fp32 accumulation alone would exceed the 1e-5 relative bound
 // against an exact reference.
+#include <type_traits>
 #include "des_internal.h"
 
 namespace des {
@@ -35,7 +36,8 @@ struct FwdArgs {
   float *P_lr, *P_sum, *P_sq, *pool;
   int64_t B;
   int F, K, policy;
-  int acc_doubles;      // LDS doubles per sample for the accumulators
+  int acc_doubles;      // LDS doubles of one set of a sample's accumulators
+  int sets;             // sets per sample: 1, which its waves share, or one for each of them
   int lds_per_sample;   // LDS doubles per sample in total (accumulators + staged offsets)
   int wps;              // waves per sample: 1, 2 or 4
 };
@@ -82,8 +84,9 @@ __global__ __launch_bounds__(kBlock) void k_forward(const FwdArgs a) {
   // LDS: one 16-byte metadata slot per thread, then per sample the accumulators and offsets
   int4 *meta = reinterpret_cast<int4 *>(lds) + wave * kWave;
   constexpr int P = D + 2;                                // row pitch: D columns, sum of squares, LR sum
-  double *sum = lds + 2 * kBlock + (size_t)local * a.lds_per_sample;   // [K][P]
-  int *offs = reinterpret_cast<int *>(sum + a.acc_doubles);   // [F+1]
+  double *sums = lds + 2 * kBlock + (size_t)local * a.lds_per_sample;  // [sets][K][P]
+  double *sum = a.sets > 1 ? sums + wis * a.acc_doubles : sums;        // the one this wave adds to
+  int *offs = reinterpret_cast<int *>(sums + a.sets * a.acc_doubles);  // [F+1]
   const int64_t b = (int64_t)blockIdx.x * (kBlock / kWave / wps) + local;
   const bool active = b < a.B;
   const bool need_fm = a.P_sum != nullptr, need_lr = a.P_lr != nullptr, need_pool = a.pool != nullptr;
@@ -91,7 +94,7 @@ __global__ __launch_bounds__(kBlock) void k_forward(const FwdArgs a) {
   constexpr bool by_key = kByKey;
   const int tis = wis * kWave + lane, nts = wps * kWave;  // thread in sample, threads per sample
 
-  for (int i = tis; i < a.acc_doubles; i += nts) sum[i] = 0.0;
+  for (int i = tis; i < a.sets * a.acc_doubles; i += nts) sums[i] = 0.0;
   if (active)
     for (int i = tis; i <= F; i += nts) offs[i] = a.offsets[b * F + i];
   __syncthreads();
@@ -241,17 +244,30 @@ __global__ __launch_bounds__(kBlock) void k_forward(const FwdArgs a) {
   __syncthreads();
 
   if (active) {
-    if (need_fm) {
-      for (int idx = tis * 4; idx < K * D; idx += nts * 4) {
-        const int s = idx / D, d = idx % D;                 // d = 4*sub: columns d..d+3 sit at k*G + sub
-        const double *row = sum + s * P + d / 4;
-        st4(a.P_sum + ((int64_t)s * a.B + b) * D + d,
-            make_float4((float)row[0], (float)row[G], (float)row[2 * G], (float)row[3 * G]));
+    const auto write = [&](auto sets_c) {
+      constexpr int kSets = decltype(sets_c)::value;
+      const auto total = [&](int i) {
+        double v[kSets];
+#pragma unroll
+        for (int w = 0; w < kSets; ++w) v[w] = sums[w * a.acc_doubles + i];
+#pragma unroll
+        for (int w = 1; w < kSets; ++w) v[0] += v[w];
+        return (float)v[0];
+      };
+      if (need_fm) {
+        for (int idx = tis * 4; idx < K * D; idx += nts * 4) {
+          const int s = idx / D, d = idx % D;               // d = 4*sub: columns d..d+3 sit at k*G + sub
+          const int at = s * P + d / 4;
+          st4(a.P_sum + ((int64_t)s * a.B + b) * D + d, make_float4(total(at), total(at + G), total(at + 2 * G), total(at + 3 * G)));
+        }
+        for (int s = tis; s < K; s += nts) a.P_sq[(int64_t)s * a.B + b] = total(s * P + D);
       }
-      for (int s = tis; s < K; s += nts) a.P_sq[(int64_t)s * a.B + b] = (float)sum[s * P + D];
-    }
-    if (need_lr)
-      for (int s = tis; s < K; s += nts) a.P_lr[(int64_t)s * a.B + b] = (float)sum[s * P + D + 1];
+      if (need_lr)
+        for (int s = tis; s < K; s += nts) a.P_lr[(int64_t)s * a.B + b] = total(s * P + D + 1);
+    };
+    if (a.sets == 1) write(std::integral_constant<int, 1>{});
+    else if (a.sets == 2) write(std::integral_constant<int, 2>{});
+    else write(std::integral_constant<int, 4>{});
   }
 }
 
@@ -301,7 +317,7 @@ FwdArgs make_args(des_table *t, const des_batch_t *b, const int32_t *rows) {
   a.keys = b->keys; a.offsets = b->offsets; a.vals = b->vals; a.rows = rows;
   a.P_lr = a.P_sum = a.P_sq = a.pool = nullptr;
   a.B = b->B; a.F = b->F; a.K = t->cfg.num_shards; a.policy = t->cfg.shard_policy;
-  a.acc_doubles = 0; a.lds_per_sample = 0; a.wps = 1;
+  a.acc_doubles = 0; a.sets = 1; a.lds_per_sample = 0; a.wps = 1;
   return a;
 }
 
@@ -320,7 +336,6 @@ des_status_t forward_launch(des_table *t, const des_batch_t *b, const int32_t *r
   const int64_t per_sample = acc_doubles + ((int64_t)b->F + 2) / 2;
   if (per_sample * 8 + 16 * kBlock > 65536) return DES_ERR_INVALID_ARG;   // K*(dim+2) doubles + F+1 ints + 4 KB must fit 64 KB of LDS
   a.acc_doubles = (int)acc_doubles;
-  a.lds_per_sample = (int)per_sample;
   int wps = 1;
   while (wps < 4 && (kBlock / kWave / wps) * per_sample * 8 > 40 * 1024) wps *= 2;
   const int64_t entries_per_sample = b->nnz / (b->B > 0 ? b->B : 1);
@@ -329,11 +344,17 @@ des_status_t forward_launch(des_table *t, const des_batch_t *b, const int32_t *r
   // them (a wave takes 64/(D/4) bags at a time; what a lane group walks one after the other is all that is waited for).
   // 48 x 26 bags of 16 columns: 10.9 -> 7.6 us, 100 / 1000 / 2000 x 100 bags of 32: 36.9 / 43.4 / 48.1 -> 14.5 / 22.9 / 35.5;
   // from 512 workgroups on there is nothing more to gain (37.3 at 1024 or 2048).
+  // One wave adds to a sample's accumulators in program order.  Where several take its place, each has a set of its own and the
+  // sets are added in the order of the waves, so that sums do not depend on scheduling there either; a workgroup needs no more
+  // LDS for it than with four samples of one wave each.
+  const int without = wps;
   while (wps < 4 && (b->B * wps + 3) / 4 < kFillGroups && b->F > wps * (kWave * 4 / D)) wps *= 2;
   a.wps = wps;
+  a.sets = without == 1 ? wps : 1;
+  a.lds_per_sample = (int)((a.sets - 1) * acc_doubles + per_sample);
   const int spb = kBlock / kWave / wps;
   const dim3 grid((unsigned)((b->B + spb - 1) / spb)), block(kBlock);
-  const size_t shmem = 16 * (size_t)kBlock + (size_t)per_sample * 8 * spb;
+  const size_t shmem = 16 * (size_t)kBlock + (size_t)a.lds_per_sample * 8 * spb;
   const bool by_key = a.policy == DES_SHARD_KEY_HASH;
   ProfScope ps(KID_FORWARD, s);
   switch (D) {

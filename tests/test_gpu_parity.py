@@ -933,3 +933,35 @@ def test_forward_of_small_batches_spread_over_several_waves(oracle, des, B, F, D
         p.forward(batch)
     finally:
         p.close()
+
+
+@pytest.mark.parametrize("policy", [0, 1])
+@pytest.mark.parametrize("F", [16, 32])                  # two and four waves per sample
+def test_forward_of_small_batches_adds_in_the_order_of_the_waves(des, F, policy):
+    """Four waves: terms of 2^60, 1, -2^60 and 1, one in a bag of each, the first behind 300 zero entries.  Added in the order of the
+    waves they give 1, in the order in which the waves reach them 0.  Two waves: 2^60, 300 zeros and 1 beside -2^60 give 0,
+    and 1 in the order of arrival (by key; by field a bag is summed before it is added)."""
+    import torch
+    D, B = 32, 3
+    t = des.Table(D, 16, 1, shard_policy=policy, max_n=4096)
+    try:
+        key = synth.scramble64(np.arange(1, 2, dtype=np.uint64))
+        t.insert(dev(key, torch), dev(np.ones((1, D + 1), np.float32), torch))
+        bags = [[] for _ in range(F)]
+        if F == 32:
+            bags[0], bags[8], bags[16], bags[24] = [0.0] * 300 + [2.0 ** 60], [1.0], [-2.0 ** 60], [1.0]
+        else:
+            bags[0], bags[8] = [2.0 ** 60] + [0.0] * 300 + [1.0], [-2.0 ** 60]
+        lens = np.tile([len(b) for b in bags], B)
+        offsets = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        vals = np.tile(np.concatenate([np.array(b, np.float32) for b in bags]), B).astype(np.float32)
+        batch = des.Batch(B, F, dev(np.repeat(key, vals.size), torch), dev(offsets, torch), dev(vals, torch))
+        rows = t.find(batch.keys, des.MISS_ZERO)
+        want = 1.0 if F == 32 else 0.0
+        for _ in range(5):
+            P_lr, P_sum, P_sq = (torch.full(s, float("nan"), device="cuda") for s in ((1, B), (1, B, D), (1, B)))
+            t.partial_forward(batch, rows, P_lr, P_sum, P_sq)
+            torch.cuda.synchronize()
+            assert (P_sum == want).all() and (P_lr == want).all()
+    finally:
+        t.close()
