@@ -78,3 +78,16 @@ def test_header_is_plain_c_and_cxx(tmp_path):
     cpp = tmp_path / "use.cpp"
     cpp.write_text(c.read_text())
     subprocess.check_call(["g++", "-std=c++17", "-Wall", "-Wextra", "-Werror", "-fsyntax-only", "-I", inc, str(cpp)])
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_binding_takes_its_stream_the_public_way_where_the_private_one_is_missing(monkeypatch, missing):
+    import types
+    import torch
+    from paper_1909_04823_amd import des
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 5 + device)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    assert des._stream() == 5
+    monkeypatch.delattr(torch._C, missing)
+    assert des._stream() == 77
