@@ -31,7 +31,6 @@ struct Ctrl {
   int pad[4];
   unsigned long long first_bad;   // verdict word of des_batch_validate
   long long n_multi;       // long segments of more than one chunk
-  unsigned long long first_dropped;   // of the running compaction
   long long base_rows;     // rows in use before the running insert
   long long n_groups;      // groups of chunk partials that are pre-summed for the segments of very many chunks
 };

@@ -213,3 +213,26 @@ def test_compact_moves_only_rows_behind_the_first_drop(des, dropped):
     want[sel] = torch.arange(sel.numel(), dtype=torch.int32, device="cuda")
     assert torch.equal(t.find(keys, des.MISS_ZERO), want) and t.status() == 0
     t.close()
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 4095, 4096, 4097, 70000])
+def test_compact_finds_the_first_drop_anywhere(des, n):
+    """One dropped row, then that one and every third row behind it: at each place around the powers of 64 by which the first drop is
+    looked for, and at both ends."""
+    import torch
+    D = 4
+    t = des.Table(D, n, 1, init_seed=3, max_n=max(n, 4096))
+    staging = torch.empty(4096 * D * 4, dtype=torch.uint8, device="cuda")
+    base = torch.arange(1, n + 1, dtype=torch.int64, device="cuda") * 7919
+    for at in sorted({a for a in (0, 1, 31, 62, 63, 64, 65, 1023, 1024, 4094, 4095, 4096, 4097, n // 2, n - 2, n - 1) if 0 <= a < n}):
+        for step in (n, 3):
+            t.insert(base)
+            assert t.size() == n and t.status() == 0
+            keys = t.row_keys[:n].clone()
+            keep = torch.ones(n, dtype=torch.uint8, device="cuda")
+            keep[at::step] = 0
+            want = keys[keep.bool()]
+            assert t.compact(keep, staging) == want.numel() == t.size(), (at, step)
+            assert torch.equal(t.row_keys[:want.numel()], want), (at, step)
+            assert torch.equal(t.find(want, des.MISS_ZERO), torch.arange(want.numel(), dtype=torch.int32, device="cuda")), (at, step)
+    t.close()
