@@ -45,7 +45,8 @@ namespace {
 constexpr int kRun = 128;                    // products per first-level run of a two-level sum
 constexpr long long kTwoLevelDepth = 1024;
 constexpr int kMinSlice = 16;                // samples a slice of dW has at least; slices are multiples of it
-constexpr int kForwardGroup = 32;           // row tiles of the forward product whose shards are done together
+constexpr int kForwardGroup = 16;           // row tiles of the forward product whose shards are done together
+constexpr int kShallowDepth = 64;           // products of the largest shard up to which the forward product is bound by its writes
 constexpr int kXcds = 8;                     // dies; consecutive workgroups are handed to them in turn
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -65,6 +66,8 @@ struct GemmArgs {
   // below k_limit, at most k_max positions; the blocks are walked as one range, so a k tile may span several of them.
   uint32_t k_shift, k_limit, k_max, blk_stride, blk_len;
   int tiles_m, tiles_n, slices, m_group;
+  bool in_turn = false;               // the dies take the n tiles of one row tile and slice each, in turn; else each an eighth of all tiles
+  uint32_t die_run = 0;               // tiles in succession that a die takes, accordingly
   int run;                            // products per first-level run of a two-level sum with the fp32 instruction
 };
 
@@ -98,8 +101,6 @@ struct Operand {
   static constexpr int kUnits = kTotal > kBlock ? kTotal / kBlock : 1;  // per thread
   static constexpr int kRowStep = T / kUnits;
   static constexpr int kVecs = kKContig ? kUnits : 4;
-  static constexpr int kPitch = kKContig ? BK + 4 : T + 4;              // of the plain fp32 tile
-  static constexpr int kPlainFloats = (kKContig ? T : BK) * kPitch;
   const float *row[kUnits];        // k contiguous: the unit's row; else the unit's four columns
   uint32_t ks, last;               // stride of a position; last position that exists (of a float4 along k: its first)
   uint32_t pos, in_blk;            // position of the thread's products, relative to the first block; offset inside the current one
@@ -182,20 +183,62 @@ struct Operand {
       }
     }
   }
-  // the staged values as they are, in memory order: rows along k, or along x
-  __device__ inline void store_plain(const float4 (&v)[kVecs], float *tile) const {
-    if (T != 128 && !active) return;
+};
+
+// The same for the fp32 instruction: the part of a T x BK tile that a thread stages as it is, in memory order.  k contiguous: as
+// above; else a thread reads a few successive products (1, 2 or 4, never of two blocks) of four neighbouring rows.
+template <int T, int BK, bool kKContig>
+struct Plain {
+  static constexpr int kVecs = T * BK / 4 / kBlock;
+  static constexpr int kRowStep = T / kVecs;
+  static constexpr int kPitch = kKContig ? BK + 4 : T + 4;
+  static constexpr int kFloats = (kKContig ? T : BK) * kPitch;
+  const float *row[kKContig ? kVecs : 1];
+  uint32_t ks, last, pos, in_blk;
+  int k_in, x0;
+
+  __device__ inline void start(const float *P, uint32_t xs, uint32_t ks_, int x_base, int X, int klen, const GemmArgs &g) {
+    static_assert(4 % kVecs == 0 || kKContig, "a block is a multiple of four products");
+    const int t = threadIdx.x;
+    ks = ks_;
     if constexpr (kKContig) {
+      k_in = t % (BK / 4) * 4;
+      x0 = t / (BK / 4);
 #pragma unroll
-      for (int u = 0; u < kUnits; ++u) *reinterpret_cast<float4 *>(tile + (x0 + u * kRowStep) * kPitch + k_in) = v[u];
+      for (int u = 0; u < kVecs; ++u) row[u] = P + (long long)min(x_base + x0 + u * kRowStep, X - 1) * xs;
     } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) *reinterpret_cast<float4 *>(tile + (k_in + i) * kPitch + x0) = v[i];
+      k_in = t / (T / 4) * kVecs;
+      x0 = t % (T / 4) * 4;
+      row[0] = P + min(x_base + x0, X - 4);
     }
+    const uint32_t k_last = klen - (kKContig ? 4 : 1);
+    last = k_last / g.blk_len * g.blk_stride + k_last % g.blk_len;
+    const uint32_t q = (uint32_t)k_in / g.blk_len;
+    in_blk = k_in - q * g.blk_len;
+    pos = q * g.blk_stride + in_blk;
   }
-  static __device__ inline float plain(const float *tile, int x, int k) {
-    return kKContig ? tile[x * kPitch + k] : tile[k * kPitch + x];
+  __device__ inline void load(float4 (&v)[kVecs], uint32_t whole, uint32_t rest, const GemmArgs &g) {
+#pragma unroll
+    for (int i = 0; i < kVecs; ++i) {
+      if constexpr (kKContig) v[i] = ld4g(row[i] + min(pos, last));
+      else v[i] = ld4g(row[0] + (unsigned long long)min(pos + i, last) * ks);
+    }
+    in_blk += rest;
+    pos += whole * g.blk_stride + rest;
+    if (in_blk >= g.blk_len) { in_blk -= g.blk_len; pos += g.blk_stride - g.blk_len; }
   }
+  // zeros for the products of tile k0 that do not exist
+  __device__ inline void blank(float4 (&v)[kVecs], int k0, int klen) const {
+#pragma unroll
+    for (int i = 0; i < kVecs; ++i)
+      if (k0 + k_in + (kKContig ? 0 : i) >= klen) v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  __device__ inline void store(const float4 (&v)[kVecs], float *tile) const {
+#pragma unroll
+    for (int i = 0; i < kVecs; ++i)
+      *reinterpret_cast<float4 *>(tile + (kKContig ? (x0 + i * kRowStep) * kPitch + k_in : (k_in + i) * kPitch + x0)) = v[i];
+  }
+  static __device__ inline float at(const float *tile, int x, int k) { return kKContig ? tile[x * kPitch + k] : tile[k * kPitch + x]; }
 };
 
 // One workgroup's place: output tile, slice and the slice's products.
@@ -205,13 +248,17 @@ struct Place {
   int sign;                        // 1: the split product's first run is accumulated with the opposite sign
   uint32_t first;                  // position of the slice's first product
   bool ok;
-  __device__ inline explicit Place(const GemmArgs &g) {
-    // Every die takes a contiguous run of tiles.  They are numbered n first, then m inside a group of m_group tiles, then
+  // kInTurn: g.in_turn may be set (the division tells in short products)
+  template <bool kInTurn>
+  __device__ inline Place(const GemmArgs &g, std::integral_constant<bool, kInTurn>) {
+    // Every die takes contiguous runs of tiles.  They are numbered n first, then m inside a group of m_group tiles, then
     // the slice, then the group: tiles that read the same rows of A follow each other, a slice's part of B is used by a
     // whole group, and the slices of a group (in the forward product: the shards' columns of the same rows of A) are
     // done together, before the next rows.
-    const uint32_t total = (uint32_t)g.tiles_m * g.tiles_n * g.slices, per_xcd = (total + kXcds - 1) / kXcds;
-    const uint32_t tile = blockIdx.x % kXcds * per_xcd + blockIdx.x / kXcds;
+    const uint32_t total = (uint32_t)g.tiles_m * g.tiles_n * g.slices, turn = blockIdx.x / kXcds;
+    uint32_t round = 0;
+    if (kInTurn && g.in_turn) round = turn / g.die_run;
+    const uint32_t tile = (round * kXcds + blockIdx.x % kXcds) * g.die_run + (turn - round * g.die_run);
     ok = tile < total;
     const uint32_t per_group = (uint32_t)g.tiles_n * g.m_group * g.slices, group = tile / per_group;
     const uint32_t in_group = min((uint32_t)g.m_group, g.tiles_m - group * g.m_group);
@@ -300,49 +347,52 @@ struct Sums {
 };
 
 // The whole contraction of one tile with the fp32 instruction.
-constexpr int kPlainBK = 32;
-template <int T, bool kAKContig, bool kBKContig>
-constexpr int plain_floats() { return Operand<T, kPlainBK, kAKContig>::kPlainFloats + Operand<T, kPlainBK, kBKContig>::kPlainFloats; }
+constexpr int kPlainBK = 32;                      // ... of two-level sums and small tiles; see launch()
+template <int T, int BK, bool kAKContig, bool kBKContig>
+constexpr int plain_floats() { return Plain<T, BK, kAKContig>::kFloats + Plain<T, BK, kBKContig>::kFloats; }
 
-template <int T, bool kAKContig, bool kBKContig, bool kTwoLevel>
+template <int T, int BK, bool kAKContig, bool kBKContig, bool kTwoLevel>
 __device__ inline void multiply_f32(const GemmArgs &g, const Place<T> &at, float *lds, Sums<T / 64, kTwoLevel> &sums) {
-  constexpr int NB = T / 64, BK = kPlainBK;
-  using OpA = Operand<T, BK, kAKContig>;
-  using OpB = Operand<T, BK, kBKContig>;
+  constexpr int NB = T / 64;
+  using OpA = Plain<T, BK, kAKContig>;
+  using OpB = Plain<T, BK, kBKContig>;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int xa = (wave >> 1) * (T / 2) + (lane & 31), xb = (wave & 1) * (T / 2) + (lane & 31), lk = lane >> 5;
   const uint32_t whole = BK / g.blk_len, rest = BK - whole * g.blk_len;
   const int klen = at.klen;
   sums.clear();
   if (klen == 0) return;
-  float *ta = lds, *tb = lds + OpA::kPlainFloats;
+  float *ta = lds, *tb = lds + OpA::kFloats;
   OpA oa;
   OpB ob;
   float4 va[OpA::kVecs], vb[OpB::kVecs];
-  oa.start(g.A + (unsigned long long)at.first * g.a_ks, g.a_xs, g.a_ks, at.m0, g.M, threadIdx.x, klen, g);
-  ob.start(g.B + (unsigned long long)at.first * g.b_ks, g.b_xs, g.b_ks, at.n0, g.N, threadIdx.x ^ (kBlock / 2), klen, g);
+  oa.start(g.A + (unsigned long long)at.first * g.a_ks, g.a_xs, g.a_ks, at.m0, g.M, klen, g);
+  ob.start(g.B + (unsigned long long)at.first * g.b_ks, g.b_xs, g.b_ks, at.n0, g.N, klen, g);
   oa.load(va, whole, rest, g);
   ob.load(vb, whole, rest, g);
   int run = 0;
   for (int k0 = 0; k0 < klen; k0 += BK) {
     if (k0 + BK > klen) { oa.blank(va, k0, klen); ob.blank(vb, k0, klen); }
     __syncthreads();                              // previous tile fully consumed
-    oa.store_plain(va, ta);
-    ob.store_plain(vb, tb);
+    oa.store(va, ta);
+    ob.store(vb, tb);
     __syncthreads();
-    oa.load(va, whole, rest, g);                  // the next tile travels while this one is multiplied
-    ob.load(vb, whole, rest, g);
+    if (k0 + BK < klen) {                         // the next tile travels while this one is multiplied
+      oa.load(va, whole, rest, g);
+      ob.load(vb, whole, rest, g);
+    }
     // operands of step kk+2 are read from LDS before the matrix instructions of step kk are issued
     float a[NB], b[NB];
 #pragma unroll
-    for (int i = 0; i < NB; ++i) { a[i] = OpA::plain(ta, xa + i * 32, lk); b[i] = OpB::plain(tb, xb + i * 32, lk); }
+    for (int i = 0; i < NB; ++i) { a[i] = OpA::at(ta, xa + i * 32, lk); b[i] = OpB::at(tb, xb + i * 32, lk); }
 #pragma unroll
     for (int kk = 0; kk < BK; kk += 2) {
+      if (kk == 16 && k0 + 16 >= klen) break;     // uniform: nothing but padding from here on
       float an[NB], bn[NB];
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
         an[i] = bn[i] = 0.f;
-        if (kk + 2 < BK) { an[i] = OpA::plain(ta, xa + i * 32, kk + 2 + lk); bn[i] = OpB::plain(tb, xb + i * 32, kk + 2 + lk); }
+        if (kk + 2 < BK) { an[i] = OpA::at(ta, xa + i * 32, kk + 2 + lk); bn[i] = OpB::at(tb, xb + i * 32, kk + 2 + lk); }
       }
       __builtin_amdgcn_sched_barrier(0);          // keep the reads above: the scheduler would sink them to their use
 #pragma unroll
@@ -357,13 +407,13 @@ __device__ inline void multiply_f32(const GemmArgs &g, const Place<T> &at, float
   if (kTwoLevel) sums.flush();
 }
 
-template <int T, bool kAKContig, bool kBKContig, bool kTwoLevel>
+template <int T, int BK, bool kAKContig, bool kBKContig, bool kTwoLevel>
 __global__ __launch_bounds__(kBlock, 2) void k_gemm_f32(const GemmArgs g) {
-  __shared__ __align__(16) float lds[plain_floats<T, kAKContig, kBKContig>()];
-  const Place<T> at(g);
+  __shared__ __align__(16) float lds[plain_floats<T, BK, kAKContig, kBKContig>()];
+  const Place<T> at(g, std::true_type{});
   if (!at.ok) return;                             // uniform per workgroup
   Sums<T / 64, kTwoLevel> sums;
-  multiply_f32<T, kAKContig, kBKContig, kTwoLevel>(g, at, lds, sums);
+  multiply_f32<T, BK, kAKContig, kBKContig, kTwoLevel>(g, at, lds, sums);
   const int wave = threadIdx.x / kWave;
   sums.store(g, at.z, at.m0 + (wave >> 1) * (T / 2), at.n0 + (wave & 1) * (T / 2));
 }
@@ -380,11 +430,9 @@ struct SplitStage {
   OpB ob;
   float4 va[2][OpA::kVecs], vb[2][OpB::kVecs];    // two tiles under way
   char *to;
-  uint32_t flips;                                 // the sign bit for threads that stage A
-  int sign;
+  uint32_t flips, flip;                           // the sign bit for threads that stage A; what the current run flips
   __device__ inline void start(const GemmArgs &g, const Place<T> &at, char *lds) {
     const float *A = g.A + (unsigned long long)at.first * g.a_ks, *B = g.B + (unsigned long long)at.first * g.b_ks;
-    sign = at.sign;
     if constexpr (kShared) {
       constexpr int n = Operand<T, BK, false>::kTotal;
       const bool second = threadIdx.x / n == 1;   // threads past the second operand's units: idle
@@ -398,6 +446,7 @@ struct SplitStage {
       oa.start(A, g.a_xs, g.a_ks, at.m0, g.M, threadIdx.x, at.klen, g);
       ob.start(B, g.b_xs, g.b_ks, at.n0, g.N, threadIdx.x ^ (kBlock / 2), at.klen, g);
     }
+    flip = at.sign ? 0u : flips;                  // the first run turns it
   }
   template <int kSet>
   __device__ inline void load(uint32_t whole, uint32_t rest, const GemmArgs &g) {
@@ -410,10 +459,11 @@ struct SplitStage {
     oa.blank(va[kSet], k0, klen);
     if constexpr (!kShared) ob.blank(vb[kSet], k0, klen);
   }
-  // k0: the tile's first product; A is negated in every second run, in the first one if `sign` is 1
+  // k0: the tile's first product, in order; A is negated in every second run, in the first one if at.sign is 1
   template <int kSet>
-  __device__ inline void store(int buf, int k0, uint32_t &odd) const {
-    oa.template store_split<true>(va[kSet], to + buf, (k0 / kRun ^ sign) & 1 ? flips : 0u, odd);
+  __device__ inline void store(int buf, int k0, uint32_t &odd) {
+    if (k0 % kRun == 0) flip ^= flips;            // uniform
+    oa.template store_split<true>(va[kSet], to + buf, flip, odd);
     if constexpr (!kShared) ob.template store_split<false>(vb[kSet], to + buf + kOperandBytes, 0u, odd);
   }
 };
@@ -422,9 +472,9 @@ template <int T, bool kAKContig, bool kBKContig, bool kTwoLevel>
 __global__ __launch_bounds__(kBlock, 2) void k_gemm_split(const GemmArgs g) {
   constexpr int NB = T / 64, BK = 16;
   constexpr int kPlane = T * 32, kBuffer = 6 * kPlane;      // bytes: one bf16 plane of one operand; both operands' planes
-  constexpr int kPlainBytes = plain_floats<T, kAKContig, kBKContig>() * 4;
+  constexpr int kPlainBytes = plain_floats<T, kPlainBK, kAKContig, kBKContig>() * 4;
   __shared__ __align__(16) char lds[2 * kBuffer > kPlainBytes ? 2 * kBuffer : kPlainBytes];
-  const Place<T> at(g);
+  const Place<T> at(g, std::false_type{});
   if (!at.ok) return;                             // uniform per workgroup
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int m_wave = (wave >> 1) * (T / 2), n_wave = (wave & 1) * (T / 2);
@@ -487,7 +537,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_split(const GemmArgs g) {
   // fp32's range (its parts' products can be infinities of both signs, a NaN again): either leaves a sum that is not
   // finite.  Then, or if an operand was too small for three bf16 parts, the tile is computed again with the fp32 instruction.
   if (__syncthreads_or((odd & 0xFFFFu) != 0 || !sums.finite()))
-    multiply_f32<T, kAKContig, kBKContig, kTwoLevel>(g, at, reinterpret_cast<float *>(lds), sums);
+    multiply_f32<T, kPlainBK, kAKContig, kBKContig, kTwoLevel>(g, at, reinterpret_cast<float *>(lds), sums);
   sums.store(g, at.z, at.m0 + m_wave, at.n0 + n_wave);
 }
 
@@ -523,13 +573,20 @@ des_status_t launch(GemmArgs g, int slices, long long depth, int kid, hipStream_
   if (g.m_group <= 0 || g.m_group > g.tiles_m) g.m_group = g.tiles_m;
   const long long total = (long long)g.tiles_m * g.tiles_n * slices;
   if (total >= 2147483647ll) return DES_ERR_INVALID_ARG;
-  const dim3 grid((unsigned)((total + kXcds - 1) / kXcds * kXcds)), block(kBlock);
+  g.die_run = g.in_turn ? (uint32_t)g.tiles_n : (uint32_t)((total + kXcds - 1) / kXcds);
+  const long long round = (long long)kXcds * g.die_run;
+  const dim3 grid((unsigned)((total + round - 1) / round * round)), block(kBlock);
   const bool two = depth > kTwoLevelDepth;
   ProfScope ps(kid, s);
-#define DES_GEMM(EDGE, TWO)                                                                                         \
-  do {                                                                                                              \
-    if constexpr (kSplit) hipLaunchKernelGGL((k_gemm_split<EDGE, kAKContig, kBKContig, TWO>), grid, block, 0, s, g); \
-    else hipLaunchKernelGGL((k_gemm_f32<EDGE, kAKContig, kBKContig, TWO>), grid, block, 0, s, g);                    \
+  // k tiles of the fp32 product: 16 deep for large tiles of one level, so that four workgroups fit a CU (116 registers; 32 deep
+  // 137 and three; 65536 x 416 x 256: 118 / 142 us), and shards whose depth is no multiple of 32 have no half tile of padding
+  // (65536 x 26 x 16, 8 shards, 256 columns: 183 / 212 us).  Two-level sums do not fit more than two either way (16384 x 3200 x 256
+  // with one shard: 301 / 250 us), and small tiles, of which there are few, wait for their barriers (4096 x 256 x 128: 10.0 / 8.7 us).
+#define DES_GEMM(EDGE, TWO)                                                                                               \
+  do {                                                                                                                    \
+    constexpr int kBK = EDGE == 128 && !TWO ? 16 : kPlainBK;                                                              \
+    if constexpr (kSplit) hipLaunchKernelGGL((k_gemm_split<EDGE, kAKContig, kBKContig, TWO>), grid, block, 0, s, g);       \
+    else hipLaunchKernelGGL((k_gemm_f32<EDGE, kBK, kAKContig, kBKContig, TWO>), grid, block, 0, s, g);                     \
   } while (0)
   if (T == 128) { if (two) DES_GEMM(128, true); else DES_GEMM(128, false); }
   else          { if (two) DES_GEMM(64, true);  else DES_GEMM(64, false); }
@@ -558,10 +615,17 @@ des_status_t des_dnn_partial_forward(const float *pool, const float *W, int64_t 
   g.B = W; g.b_xs = 1; g.b_ks = H;
   g.C = Y_partial; g.M = (int)B; g.N = H; g.c_rs = H; g.c_slice = (long long)B * H;
   // shard s: fields s, s+K, ... = k blocks of length D starting at s*D, K*D apart
-  g.m_group = kForwardGroup;
+  const long long depth = (long long)((F + K - 1) / K) * D;        // of the largest shard
+  // Shallow shards, whose partials are most of the traffic, one shard after the other: with the shards of a group of rows done
+  // together the card writes K distant places at a time.  16384 x 60 x 16, 64 shards, 128 columns: 125 / 118 us.  Where the pooled rows
+  // are as large, their lines, which hold several shards' columns, are better read once: 131072 x 39 x 8, 8 shards, 64
+  // columns 116 / 139 us; and deep shards use all of W anew with every shard: 131072 x 200 x 64, 64 shards 7.72 / 7.89 ms.
+  const bool shallow = depth <= kShallowDepth && (long long)K * H >= 2ll * F * D;
+  g.m_group = shallow ? 0 : kForwardGroup;
+  g.in_turn = shallow;
   g.run = forward_run(D);
   g.k_shift = g.blk_len = D; g.blk_stride = (uint32_t)(K < F ? K : F) * D; g.k_limit = g.k_max = (uint32_t)F * D;
-  return launch<false, true, false>(g, K, (long long)((F + K - 1) / K) * D, KID_DNN_FORWARD, (hipStream_t)stream);
+  return launch<false, true, false>(g, K, depth, KID_DNN_FORWARD, (hipStream_t)stream);
 }
 
 des_status_t des_dnn_backward_bytes(int64_t B, int32_t F, int32_t D, int32_t H, size_t *workspace_bytes) {
