@@ -48,6 +48,7 @@ constexpr int kMinSlice = 16;                // samples a slice of dW has at lea
 constexpr int kForwardGroup = 16;           // row tiles of the forward product whose shards are done together
 constexpr int kShallowDepth = 64;           // products of the largest shard up to which the forward product is bound by its writes
 constexpr int kXcds = 8;                     // dies; consecutive workgroups are handed to them in turn
+constexpr uint32_t kGridRow = 1u << 23;      // workgroups per row of a grid; a launch takes fewer than 2^32 threads along x
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -255,10 +256,11 @@ struct Place {
     // the slice, then the group: tiles that read the same rows of A follow each other, a slice's part of B is used by a
     // whole group, and the slices of a group (in the forward product: the shards' columns of the same rows of A) are
     // done together, before the next rows.
-    const uint32_t total = (uint32_t)g.tiles_m * g.tiles_n * g.slices, turn = blockIdx.x / kXcds;
+    const uint32_t block = kInTurn ? blockIdx.y * kGridRow + blockIdx.x : blockIdx.x;
+    const uint32_t total = (uint32_t)g.tiles_m * g.tiles_n * g.slices, turn = block / kXcds;
     uint32_t round = 0;
     if (kInTurn && g.in_turn) round = turn / g.die_run;
-    const uint32_t tile = (round * kXcds + blockIdx.x % kXcds) * g.die_run + (turn - round * g.die_run);
+    const uint32_t tile = (round * kXcds + block % kXcds) * g.die_run + (turn - round * g.die_run);
     ok = tile < total;
     const uint32_t per_group = (uint32_t)g.tiles_n * g.m_group * g.slices, group = tile / per_group;
     const uint32_t in_group = min((uint32_t)g.m_group, g.tiles_m - group * g.m_group);
@@ -593,7 +595,12 @@ des_status_t launch(GemmArgs g, int slices, long long depth, int kid, hipStream_
   if (total >= 2147483647ll) return DES_ERR_INVALID_ARG;
   g.die_run = g.in_turn ? (uint32_t)g.tiles_n : (uint32_t)((total + kXcds - 1) / kXcds);
   const long long round = (long long)kXcds * g.die_run;
-  const dim3 grid((unsigned)((total + round - 1) / round * round)), block(kBlock);
+  const long long blocks = (total + round - 1) / round * round;
+  // A product whose operands and result fit the card has fewer than 2^23 large tiles; only the forward product, whose tiles
+  // are small where it has few columns and whose shards come on top, may need further rows.
+  if (kSplit && blocks > (long long)kGridRow) return DES_ERR_INVALID_ARG;
+  const dim3 grid((unsigned)(blocks < (long long)kGridRow ? blocks : kGridRow), (unsigned)((blocks + kGridRow - 1) / kGridRow));
+  const dim3 block(kBlock);
   const bool two = depth > kTwoLevelDepth;
   ProfScope ps(kid, s);
   // k tiles of the fp32 product: 16 deep for large tiles of one level, so that four workgroups fit a CU (116 registers; 32 deep

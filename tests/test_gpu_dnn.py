@@ -82,6 +82,22 @@ def test_dnn_layer_argument_checks(des):
     assert out.shape == (2, 0, 8)
 
 
+def test_dnn_forward_of_more_workgroups_than_a_row_of_the_grid(des):
+    """65537 row tiles times 256 shards, one of them with a field: 2^24 and some workgroups, more threads than a launch takes along one
+    dimension."""
+    import torch
+    B, K = 4194304 + 64, 256
+    pool, W, _ = synth.dnn_layer_inputs(1, B, 1, 4, 4)
+    Y = torch.full((K, B, 4), float("nan"), dtype=torch.float32, device="cuda")
+    des.dnn_partial_forward(dev(pool, torch), dev(W, torch), K, out=Y)
+    torch.cuda.synchronize()
+    assert_close(Y[0].cpu().numpy(), pool.reshape(B, 4).astype(np.float64) @ W.astype(np.float64), "Y_partial of the shard with a field")
+    for s in range(1, K):
+        assert not Y[s].any(), s
+    del Y
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("F,D,bound", [(300, 4, 1.6e-7), (200, 8, 1.8e-7), (150, 12, 2.0e-7), (100, 16, 2.2e-7), (100, 20, 1.93e-7), (50, 36, 2.0e-7)])
 def test_dnn_forward_sums_deep_shards_in_short_runs(des, F, D, bound):
     """A sum of more than 1024 products is taken in runs of at most 8 * D / ceil(D/16) products, 128 where D fills 16-deep tiles: its
