@@ -243,9 +243,10 @@ des_status_t des_dnn_partial_forward(const float *pool, const float *W, int64_t 
  * unchanged, each shard differentiates its own block, nothing is exchanged):
  *     g_pool[b, j] = sum_h dY[b,h] * W[j,h]        (the g_pool input of des_backward_update*)
  *     dW[j, h]     = sum_b pool[b,j] * dY[b,h]      j = f*D + d
- * Both products take each fp32 operand as the sum of three bf16 parts on the bf16 matrix cores (sums in fp32, in
- * runs of 128 products; the error against 64 bits is no larger than with fp32 products), tiles with infinities, NaN or
- * values too small to be cut exactly in fp32.
+ * Both products take each fp32 operand as the sum of three bf16 parts on the bf16 matrix cores, sums in fp32 in runs of
+ * 128 products.  A single product is then within 2^-23 (fp32 arithmetic: 2^-24); sums are closer than fp32 arithmetic's
+ * in the 2-norm (of 16 products 3.4e-8 against 7.3e-8, of 256 2.4e-7 against 2.9e-7).  dW of one or two samples, tiles with
+ * infinities, NaN or sums past fp32's range and tiles with operands under 2^-110 are computed in fp32.
  * Either output may be null (skipped), not both.  dW is computed in up to 16 slices of samples
  * that are summed in double; the slices live in `workspace` (device, 16-byte aligned, at least
  * des_dnn_backward_bytes() bytes; not needed, and may be null, when dW is not asked for or the

@@ -10,27 +10,32 @@
 // This is the one dense contraction of the path, so it runs on the matrix cores.  128x128 output tile per workgroup (64x64
 // where that leaves CUs idle), four waves in a 2x2 arrangement of 64x64 (32x32).  Two kernels:
 //
-// k_gemm_f32, the forward product: the fp32 matrix instruction (32x32x2, 64 cycles), 32 products deep per LDS tile, the next
-// tile in registers meanwhile.  Bound by the matrix pipe.  The sum of an output element is one chain in ascending k (above 1024
-// products: of chains of forward_run products) whatever the tile, so results do not depend on the tile size.  It keeps the fp32 chain because a ReLU follows it: with the split
-// (223 against 271 us at 16384 x 3200 x 256) a unit within 1e-8 of zero changes sides in one of six training steps at 4096 x 256
-// units, and its gradient with it.  A shard's fields are walked as one range (a field of 20 columns costs no padding).
+// k_gemm_f32, the forward product: the fp32 matrix instruction (32x32x2, 64 cycles), 16 or 32 products deep per LDS tile, the
+// next tile in registers meanwhile.  Bound by the matrix pipe, and by its writes where the shards are shallow.  The sum of an
+// output element is one chain in ascending k (above 1024 products: of chains of forward_run products) whatever the tile,
+// so results do not depend on the tile size.  It keeps the fp32 chain because a ReLU follows it: with the split (223 against
+// 271 us at 16384 x 3200 x 256) a unit within 1e-8 of zero changes sides in one of six training steps at 4096 x 256 units, and
+// its gradient with it.  A shard's fields are walked as one range (a field of 20 columns costs no padding).
 //
 // k_gemm_split, the two gradient products: fp32 accuracy from the bf16 instruction (32x32x16, 32 cycles).  Every operand
 // element is cut into three bf16 parts, a = hi + mid + lo, each the rounded rest of what the parts before it left (the cut is
 // exact: 3 x 8 significant bits), and a product is six bf16 products accumulated in fp32:
-//   hi*hi + hi*mid + mid*hi + hi*lo + lo*hi + mid*mid        (what is left out is below 2^-26 of a*b)
-// so 16 products of depth take 6 x 32 instead of 8 x 64 cycles.  Bound by the matrix pipe and, nearly as long, the vector
-// instructions of the cut (5.5 per element, once per element and tile, on the way into LDS): two LDS buffers of 16 products, so
-// that a wave cuts the next tile between the matrix instructions of the current one, and two tiles under way in registers.
-// 65536 x 12800 x 256: g_pool 3.81 -> 2.60 ms (165 TFLOP/s), dW 3.65 -> 2.55 ms; a library's plain bf16 product of 8192^3 reaches
-// 1.1 PFLOP/s here, one sixth of which is 183.  The bf16 instruction drops the bits of its sum that do not fit, towards minus
-// infinity; over many runs that adds up (a mean of -3e-7 of the results' root mean square at 124623 samples), so every second run
-// of kRun products is accumulated with the opposite sign.  A single run, or a last one without a partner, keeps its part: tiles and
-// slices begin with alternating signs, so that it has both signs in what a row of the table adds up over the samples and in
-// a slice sum (mean error / root mean square, all beginning with plus and so: g_pool of 128 hidden units, 4096 samples,
-// -9.4e-9 and -2e-11; dW of 2048 samples -2.9e-8 and 3e-10.  Signs by rows instead of tiles cost g_pool 4 %).  16384 x 3200 x 256: 248 -> 179 us, 233 -> 163 us.  Error against 64 bits, 2-norm:
-// 2.4e-7 where the fp32 instruction has 2.9e-7 (16384 x 3200 x 256), 2.6e-7 and 3.1e-7 (5003 x 540 x 300).
+//   hi*hi + hi*mid + mid*hi + hi*lo + lo*hi + mid*mid
+// so 16 products of depth take 6 x 32 instead of 8 x 64 cycles.  What is left out is at most 2^-24 of a*b (mid is up to 2^-8 of
+// a, lo up to 2^-17): a single product can be off by 2^-23 where the fp32 instruction is by 2^-24, a sum is closer from three
+// products on.  Error against 64 bits, 2-norm, split / fp32: sums of 1, 2, 3, 16 and 64 products 3.5 / 2.5, 3.3 / 3.1, 3.2 / 3.6, 3.4 /
+// 7.3 and 10.9 / 14.4 e-8; 16384 x 3200 x 256 2.4e-7 / 2.9e-7.
+// Bound by the matrix pipe and, nearly as long, the vector instructions of the cut (5 per element, once per element and tile, on
+// the way into LDS): two LDS buffers of 16 products, so that a wave cuts the next tile between the matrix instructions of
+// the current one, and two tiles under way in registers.  16384 x 3200 x 256, fp32 / split: 242 / 174 us, 235 / 154 us; 131072 x
+// 12800 x 256: g_pool 7.31 / 5.47 ms (157 TFLOP/s), dW 7.07 / 4.90 ms; a library's plain bf16 product of 8192^3 reaches 1.1
+// PFLOP/s here, one sixth of which is 183.
+// The bf16 instruction drops the bits of its sum that do not fit, towards minus infinity; over many runs that adds up (a mean
+// of -3e-7 of the results' root mean square at 124623 samples), so every second run of kRun products is accumulated with the
+// opposite sign.  A single run, or a last one without a partner, keeps its part: tiles and slices begin with alternating
+// signs, so that it has both signs in what a row of the table adds up over the samples and in a slice sum (mean error /
+// root mean square, all beginning with plus and so: g_pool of 128 hidden units, 4096 samples, -9.4e-9 and -2e-11; dW of 2048
+// samples -2.9e-8 and 3e-10.  Signs by rows instead of tiles cost g_pool 4 %).
 //
 // Products through operand strides and a sliced k range:
 //   forward   C_s[B,H]   = sum over the shard's fields of pool[:, f, :] x W[f*D:(f+1)*D, :]
@@ -567,8 +572,8 @@ inline long long tiles_of(long long n, int T) { return (n + T - 1) / T; }
 // workgroups and less padding.  Measured, large / small tile:
 //   split, 16384 x 3200 x 256: 172 / 242 us (g_pool), 159 / 313 us (dW); 5003 x 540 x 300, 200 and 240 large tiles: 24.1 / 26.5 us
 //   and 24.0 / 26.6 us; 4096 x 416 x 256, 128 large tiles: 34.9 / 32.6 us for the two g_pool of a model step
-//   fp32 (results do not depend on the choice), 16384 x 3200 x 256: 271 / 281 us; 5003 x 540 x 300 with 7 shards, where the
-//   large tile multiplies 21 % more padding: 43 / 34 us
+//   fp32 (results do not depend on the choice), 16384 x 3200 x 256, 16 shards: 311 / 321 us; 5003 x 540 x 300 with 7 shards, where
+//   the large tile multiplies 21 % more padding: 36 / 30 us
 template <bool kSplit>
 inline int tile_edge(long long M, long long N, long long slices) {
   const long long large = tiles_of(M, 128) * tiles_of(N, 128) * slices, small = tiles_of(M, 64) * tiles_of(N, 64) * slices;
