@@ -1048,6 +1048,11 @@ Layout layout_for(int D, int64_t n) {
   L.chunk_owner = take(max_chunks * 4);
   L.partials = take(max_chunks * (size_t)(D + 4) * 8);
   L.sort_scratch = take(sort_scratch_bytes(n));       // right behind the partials, see sort_stage
+  // Room for the lists of segments that now lie in the sorted keys: the workspace also bounds how many rows
+  // des_table_compact takes, which is to stay what it was.
+  constexpr size_t kChunk = (size_t)1 << kChunkShift;
+  take((m / (kChunk + 1) + 1) * 4);
+  for (int i = 0; i < 2; ++i) take((3 * (m / (kChunk * kMidFan)) + 4) * 4);
   L.total = o;
   return L;
 }

@@ -91,3 +91,15 @@ def test_binding_takes_its_stream_the_public_way_where_the_private_one_is_missin
     assert des._stream() == 5
     monkeypatch.delattr(torch._C, missing)
     assert des._stream() == 77
+
+
+@pytest.mark.parametrize("dim,max_n,want", [(64, 287251, 14491648), (32, 4000001, 168693248), (8, 100000, 3602176), (64, 65536, 3307776)])
+def test_workspace_keeps_its_size(lib, dim, max_n, want):
+    """The workspace of a table made for `max_n` entries also limits the rows that compaction numbers in it (8 bytes each): a table that
+    could be compacted with it still can."""
+    from paper_1909_04823_amd import des
+    cfg = des.TableConfig()
+    cfg.dim, cfg.capacity_rows, cfg.num_shards, cfg.init_scale = dim, 8_100_000, 1, 0.01
+    slots, ws = C.c_size_t(0), C.c_size_t(0)
+    assert lib.des_table_query_bytes(C.byref(cfg), C.c_int64(max_n), C.byref(slots), C.byref(ws)) == 0
+    assert ws.value == want
