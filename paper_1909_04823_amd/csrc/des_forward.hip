@@ -9,12 +9,20 @@
 // the chunk (row, key -> shard, value, bag found in the sample's offsets staged in LDS) and
 // publishes it in LDS, from where the group reads entry j with one broadcast read; the row
 // gathers of a chunk are issued back to back.  The running bag sum stays in registers (the
-// pooled output is written once per bag, already summed over shards).  The per-shard FM / LR
+// pooled output is written once per bag, at its last entry, already summed over shards).  The per-shard FM / LR
 // partials of the sample live in LDS ([K][D+2] doubles per sample: D columns, then the sum of
 // squares and the LR sum) and are updated with LDS atomics, because the entries of one shard are
-// scattered over all groups.  A lane owns columns 4*sub..4*sub+3 of a row but the LDS copy is
+// scattered over all groups; the two scalars of an entry by the lane that holds its metadata, once per chunk.
+// A lane owns columns 4*sub..4*sub+3 of a row but the LDS copy is
 // stored column-permuted (column 4*sub+k at k*G+sub) with a row pitch of D+2 doubles, so that the
 // 64 lanes of one atomic instruction spread over the LDS banks instead of piling onto a few.
+//
+// What bounds it: at D = 32 the LDS pipe (78 % busy, about 14 cycles per wave of double additions, a quarter of it bank
+// conflicts) and the vector ALU (62 %); at D = 64 dependent accesses beside them (57 % of the waves' time is waiting).
+// Vector memory operations complete in order and a wait can only be counted along straight code: with a gather under a
+// condition, or the bag's store between a batch's gathers and their uses, each was waited for alone.  Gathers without
+// conditions, all waited for at once ahead of the stores: 8.0e6 entries of 64 floats 694 -> 598 us, 1.05e8 of 64 7.50 -> 6.35 ms,
+// 8.2e6 of 32 236 -> 218 us.
 //
 // Accumulation is in double, inputs and outputs are fp32: a sample's sum of several hundred
 // signed terms cancels, and fp32 accumulation alone would exceed the 1e-5 relative bound
@@ -75,8 +83,7 @@ __global__ __launch_bounds__(kBlock) void k_forward(const FwdArgs a) {
   extern __shared__ __align__(16) double lds[];
   constexpr int G = D / 4;                 // lanes per row = entries per chunk
   constexpr int NG = kWave / G;            // lane groups per wave
-  constexpr int U = G >= 16 ? 8 : (G < 4 ? G : 4);   // row gathers in flight per lane (measured: 8 pays from D = 64 on)
-  constexpr int kLrLane = G > 1 ? 1 : 0;   // lane of a group that fetches and adds the LR weight
+  constexpr int U = G >= 8 ? 8 : G;        // row gathers in flight per lane (4 / 8: D = 64 625 -> 598 us, D = 32 with values 21.9 -> 21.4, without 218 -> 219)
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int g = lane / G, sub = lane % G;
   const int K = a.K, F = a.F, wps = a.wps;
@@ -90,8 +97,9 @@ __global__ __launch_bounds__(kBlock) void k_forward(const FwdArgs a) {
   const int64_t b = (int64_t)blockIdx.x * (kBlock / kWave / wps) + local;
   const bool active = b < a.B;
   const bool need_fm = a.P_sum != nullptr, need_lr = a.P_lr != nullptr, need_pool = a.pool != nullptr;
-  const bool need_v = need_fm || need_pool;
-  constexpr bool by_key = kByKey;
+  const bool hashed = kByKey && (need_fm || need_lr);
+  const int row_mask = need_fm || need_pool ? -1 : 0;     // first-order terms alone need no rows
+  const float *w_base = need_lr ? a.w : a.emb;
   const int tis = wis * kWave + lane, nts = wps * kWave;  // thread in sample, threads per sample
 
   for (int i = tis; i < a.sets * a.acc_doubles; i += nts) sums[i] = 0.0;
@@ -102,143 +110,132 @@ __global__ __launch_bounds__(kBlock) void k_forward(const FwdArgs a) {
   if (active) {
     const int gg = wis * NG + g, ngt = wps * NG;
     const int f0 = (int)(((int64_t)F * gg) / ngt), f1 = (int)(((int64_t)F * (gg + 1)) / ngt);
-    const int e0 = offs[f0], e1 = offs[f1];
-    int cur = f0;                                         // bag whose sum is being accumulated
+    const int first = offs[0];                            // the sample's entries start here
+    const int e0 = offs[f0] - first, e1 = offs[f1] - first;
+    const int32_t *rows = a.rows + first;
+    const uint64_t *keys = a.keys + first;
+    const float *vals = kHasVals ? a.vals + first : nullptr;
+    float *pool = a.pool + (b * F) * (int64_t)D;
+    if (need_pool)                                        // bags without entries; the others are stored at their last entry
+      for (int f = f0; f < f1; ++f)
+        if (offs[f] == offs[f + 1]) st4(pool + (f * D + sub * 4), make_float4(0.f, 0.f, 0.f, 0.f));
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    double bag_sq = 0.0, bag_lr = 0.0;                    // field partition: this lane's share of the bag's scalars
-    bool bag_dirty = false;
-    float *pool_row = need_pool ? a.pool + (b * F) * (int64_t)D + sub * 4 : nullptr;
-    // closes bag `cur`: pooled sum out; under the field partition also the bag's contribution to its shard
-    auto close_bag = [&]() {
-      if (need_pool)
-        st4(pool_row + (int64_t)cur * D, make_float4((float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3]));
-      if (!kByKey && bag_dirty) {
-        const int s = cur % K;
-        if (need_fm) {
-          double *dst = sum + s * P + sub;
-#pragma unroll
-          for (int k = 0; k < 4; ++k) atomicAdd(dst + k * G, acc[k]);
-          const double q = group_sum<G>(bag_sq);
-          if (sub == 0) atomicAdd(sum + s * P + D, q);
-        }
-        if (need_lr && sub == kLrLane) atomicAdd(sum + s * P + D + 1, bag_lr);
-        bag_sq = 0.0;
-        bag_lr = 0.0;
-        bag_dirty = false;
-      }
-      acc[0] = acc[1] = acc[2] = acc[3] = 0.0;
-    };
+    double bag_sq = 0.0;                                  // field partition: this lane's share of the bag's sum of squares
+    int cur = f0;                                         // bag of the entry before the chunk
 
     // metadata of entry e0 + sub of the first chunk; later chunks are fetched one chunk ahead
     int r_n = -1;
     uint64_t key_n = 0;
     float x_n = 1.f;
-    {
-      const int my = e0 + sub;
-      if (my < e1) {
-        r_n = a.rows[my];
-        if (by_key) key_n = a.keys[my];
-        if (kHasVals) x_n = a.vals[my];
-      }
+    if (e0 + sub < e1) {
+      r_n = rows[e0 + sub];
+      if (hashed) key_n = keys[e0 + sub];
+      if (kHasVals) x_n = vals[e0 + sub];
     }
     for (int e = e0; e < e1; e += G) {
       const int my = e + sub;
       const int r_l = r_n;
       const uint64_t key_l = key_n;
       const float x_l = x_n;
-      {                                                   // prefetch the next chunk's metadata
-        const int nx = my + G;
-        r_n = -1;
-        if (nx < e1) {
-          r_n = a.rows[nx];
-          if (by_key) key_n = a.keys[nx];
-          if (kHasVals) x_n = a.vals[nx];
-        }
+      r_n = -1;
+      if (my + G < e1) {                                  // the next chunk's metadata
+        r_n = rows[my + G];
+        if (hashed) key_n = keys[my + G];
+        if (kHasVals) x_n = vals[my + G];
       }
-      // bag of this lane's entry: the largest f with offs[f] <= my.  Entries are walked in order,
-      // so it is at or shortly after the bag of the last processed entry: a few linear steps,
-      // then a binary search for the rare long run of empty bags.
-      int bag_l = cur;
-      if (my < e1) {
-        int lo = cur;
+      // bag of this lane's entry: the largest f with offs[f] <= its index.  Entries are walked in order, so it is at
+      // or shortly after the bag of the last processed entry: up to four bags on in one step (offsets ascend), then a
+      // binary search for the rare long run of empty bags.
+      int lo = cur;
+      const int at = my + first;
+      {
+        int ahead = 0;
 #pragma unroll
-        for (int step = 0; step < 4; ++step)
-          if (offs[lo + 1] <= my) ++lo;
-        if (offs[lo + 1] <= my) {
+        for (int k = 1; k <= 4; ++k) ahead += offs[min(cur + k, f1)] <= at ? 1 : 0;
+        lo += ahead;
+        if (my < e1 && ahead == 4 && offs[lo + 1] <= at) {
           int hi = f1;
           ++lo;
           while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
-            if (offs[mid] <= my) lo = mid; else hi = mid;
+            if (offs[mid] <= at) lo = mid; else hi = mid;
           }
         }
-        bag_l = lo;
       }
-      const int sh_l = by_key ? (int)((uint32_t)(mix64(key_l) >> 32) % (uint32_t)K) : bag_l % K;
-      // publish (row, bag, shard, value) of this lane's entry; the group then reads entry j of the
-      // chunk from slot j with one broadcast LDS read.  Same wave, program order: no barrier needed.
-      meta[lane] = make_int4(r_l, bag_l, sh_l, __float_as_int(x_l));
+      const int bag_l = my < e1 ? lo : cur;
+      const int sh_l = !need_fm && !need_lr ? 0 : kByKey ? (int)((uint32_t)(mix64(key_l) >> 32) % (uint32_t)K) : bag_l % K;
+      // what the group needs of this lane's entry, read back with one broadcast LDS read per entry: row (0 if absent), its
+      // shard's accumulators (-1: absent), its bag's pooled row if it is the bag's last entry (-1: it is not), its value.
+      // Same wave, program order: no barrier needed.
+      const bool last_l = my < e1 && at + 1 == offs[bag_l + 1];
+      meta[lane] = make_int4(max(r_l, 0) & row_mask, r_l >= 0 ? sh_l * P : -1, last_l ? bag_l * D : -1, __float_as_int(x_l));
+      cur = __shfl(bag_l, lane - sub + min(G, e1 - e) - 1, kWave);
+      // The first-order weight of this lane's own entry: one gather per chunk for the whole group.
+      float w_l = w_base[max(r_l, 0)];
+      double q_l = 0.0;                                   // sum of squares of this lane's own entry
       const int cnt = min(G, e1 - e);
 #pragma unroll
       for (int j0 = 0; j0 < G; j0 += U) {
-        if (j0 < cnt) {
+        if (j0 == 0 || j0 < cnt) {
           int4 md[U];
           float4 v[U];
-          float wv[U];
+          // Every row is requested without a condition (an absent one reads row 0 and is left out below) and all of them,
+          // with what was requested before them, are waited for here: loads under a condition, or waits between the pooled
+          // stores, would be waited for one by one.
 #pragma unroll
           for (int i = 0; i < U; ++i) {
             md[i] = meta[g * G + j0 + i];
-            v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-            wv[i] = 0.f;
-            if (j0 + i < cnt && md[i].x >= 0) {
-              if (need_v) v[i] = ld4(a.emb + (int64_t)md[i].x * D + sub * 4);
-              if (need_lr && sub == kLrLane) wv[i] = a.w[md[i].x];
-            }
+            v[i] = ld4(a.emb + (int64_t)md[i].x * D + sub * 4);
+          }
+#pragma unroll
+          for (int i = 0; i < U; ++i) asm volatile("" : "+v"(v[i].x), "+v"(v[i].y), "+v"(v[i].z), "+v"(v[i].w));
+          if (j0 == 0) {
+            asm volatile("" : "+v"(w_l), "+v"(r_n));
+            if (hashed) asm volatile("" : "+v"(key_n));
+            if (kHasVals) asm volatile("" : "+v"(x_n));
           }
 #pragma unroll
           for (int i = 0; i < U; ++i) {
-            if (j0 + i < cnt) {
-              const int bag = md[i].y, s = md[i].z;
-              while (cur < bag) {                          // close finished (possibly empty) bags
-                close_bag();
-                ++cur;
-              }
-              if (md[i].x >= 0) {
-                const double xd = kHasVals ? (double)__int_as_float(md[i].w) : 1.0;
-                const double xv[4] = {kHasVals ? xd * (double)v[i].x : (double)v[i].x, kHasVals ? xd * (double)v[i].y : (double)v[i].y,
-                                      kHasVals ? xd * (double)v[i].z : (double)v[i].z, kHasVals ? xd * (double)v[i].w : (double)v[i].w};
+            if (md[i].y >= 0) {
+              const double xd = kHasVals ? (double)__int_as_float(md[i].w) : 1.0;
+              const double xv[4] = {kHasVals ? xd * (double)v[i].x : (double)v[i].x, kHasVals ? xd * (double)v[i].y : (double)v[i].y,
+                                    kHasVals ? xd * (double)v[i].z : (double)v[i].z, kHasVals ? xd * (double)v[i].w : (double)v[i].w};
 #pragma unroll
-                for (int k = 0; k < 4; ++k) acc[k] += xv[k];
+              for (int k = 0; k < 4; ++k) acc[k] += xv[k];
+              if (need_fm) {
+                const double p = xv[0] * xv[0] + xv[1] * xv[1] + xv[2] * xv[2] + xv[3] * xv[3];
                 if (!kByKey) {
-                  bag_sq += xv[0] * xv[0] + xv[1] * xv[1] + xv[2] * xv[2] + xv[3] * xv[3];
-                  bag_lr += xd * (double)wv[i];
-                  bag_dirty = true;
-                  continue;
-                }
-                double q = 0.0;
-                if (need_fm) {
-                  double *dst = sum + s * P + sub;
+                  bag_sq += p;
+                } else {
+                  double *dst = sum + md[i].y + sub;
 #pragma unroll
                   for (int k = 0; k < 4; ++k) atomicAdd(dst + k * G, xv[k]);
-                  q = group_sum<G>(xv[0] * xv[0] + xv[1] * xv[1] + xv[2] * xv[2] + xv[3] * xv[3]);
-                }
-                // one LDS instruction for both scalars: lane 0 adds the sum of squares, lane kLrLane
-                // the LR term (the same lane when a row is a single lane wide)
-                if (kLrLane == 0) {
-                  if (need_fm && sub == 0) atomicAdd(sum + s * P + D, q);
-                  if (need_lr && sub == 0) atomicAdd(sum + s * P + D + 1, xd * (double)wv[i]);
-                } else if ((sub == 0 && need_fm) || (sub == kLrLane && need_lr)) {
-                  atomicAdd(sum + s * P + D + sub, sub == 0 ? q : xd * (double)wv[i]);
+                  const double q = group_sum<G>(p);
+                  if (sub == j0 + i) q_l = q;
                 }
               }
+            }
+            if (md[i].z >= 0) {                            // the bag ends: pooled sum out, and to its shard under the field partition
+              if (need_pool) st4(pool + (md[i].z + sub * 4), make_float4((float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3]));
+              if (!kByKey && need_fm) {
+                const int s = (md[i].z / D) % K;
+                double *dst = sum + s * P + sub;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) atomicAdd(dst + k * G, acc[k]);
+                const double q = group_sum<G>(bag_sq);
+                if (sub == 0) atomicAdd(sum + s * P + D, q);
+                bag_sq = 0.0;
+              }
+              acc[0] = acc[1] = acc[2] = acc[3] = 0.0;
             }
           }
         }
       }
-    }
-    while (cur < f1) {                                    // last bag of the range and empty ones after it
-      close_bag();
-      ++cur;
+      if (r_l >= 0) {
+        double *dst = sum + sh_l * P + D;
+        if (kByKey && need_fm) atomicAdd(dst, q_l);
+        if (need_lr) atomicAdd(dst + 1, kHasVals ? (double)x_l * (double)w_l : (double)w_l);
+      }
     }
   }
   __syncthreads();
