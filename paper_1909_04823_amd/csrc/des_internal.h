@@ -42,6 +42,16 @@ __host__ __device__ inline uint64_t mix64(uint64_t z) {
   return z ^ (z >> 31);
 }
 
+// Work item of a workgroup such that each of the chip's eight dies takes one contiguous stretch of the items: consecutive
+// workgroup numbers go round the dies, each with an L2 of its own, so neighbouring items whose outputs share cache lines
+// would write parts of one line from several L2s.
+#ifdef __HIPCC__
+__device__ inline uint32_t die_contiguous(uint32_t block, uint32_t grid) {
+  const uint32_t whole = grid / 8, rest = grid % 8, die = block % 8;
+  return die * whole + (die < rest ? die : rest) + block / 8;
+}
+#endif
+
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // ---- per-kernel timing (process-wide collector) ----------------------------------------
