@@ -43,6 +43,8 @@ struct BwdArgs {
   const float *vals;
   const int32_t *rows;
   const float *g_lr, *g_fm, *A_sum, *g_pool;
+  struct Take { const float *base; uint32_t mask; };   // an upstream array, or (mask 0) the table's first row in its place
+  Take take_lr, take_fm, take_sum, take_pool;
   int64_t n;            // nnz
   int64_t nbags;
   int F;
@@ -539,32 +541,60 @@ struct Acc {
 };
 __device__ inline Acc acc_zero() { Acc r; r.v[0] = r.v[1] = r.v[2] = r.v[3] = 0.0; r.s2 = 0.0; r.gw = 0.0; return r; }
 
-// Adds the terms of up to U entries whose bags (and values) are already known: all their upstream
-// gradient rows are requested before the first is used.
+// Upstream gradients of one entry.  Each is requested whether the caller passed that array or not (BwdArgs::take; an absent one
+// reads the table's first row, and is then replaced by zeros): a load under a condition is waited for where the paths join,
+// one after the other.
+struct Upstream {
+  float4 gp, as;
+  float gf, gl;
+};
+template <int D, bool kStream = false>
+__device__ inline Upstream request_upstream(const BwdArgs &a, uint32_t bag, int sub) {
+  const uint32_t b = bag / (uint32_t)a.F;
+  const float *gp = a.take_pool.base + (int64_t)(bag & a.take_pool.mask) * D + sub * 4;
+  Upstream u;
+  u.gp = kStream ? ld4_stream(gp) : ld4(gp);
+  u.as = ld4(a.take_sum.base + (int64_t)(b & a.take_sum.mask) * D + sub * 4);
+  u.gf = a.take_fm.base[b & a.take_fm.mask];
+  u.gl = a.take_lr.base[b & a.take_lr.mask];
+  return u;
+}
+// Waits for what was requested.
+__device__ inline void arrive(Upstream &u) {
+  asm volatile("" : "+v"(u.gp.x), "+v"(u.gp.y), "+v"(u.gp.z), "+v"(u.gp.w), "+v"(u.as.x), "+v"(u.as.y), "+v"(u.as.z), "+v"(u.as.w),
+               "+v"(u.gf), "+v"(u.gl));
+}
+__device__ inline void drop_absent(const BwdArgs &a, Upstream &u) {
+  if (!a.g_pool) u.gp = f4zero();
+  if (!a.g_fm) { u.as = f4zero(); u.gf = 0.f; }
+  if (!a.g_lr) u.gl = 0.f;
+}
+__device__ inline void add_upstream(const Upstream &u, float x, Acc &acc) {
+  const double xd = (double)x;
+  const double xg = xd * (double)u.gf;
+  acc.v[0] += xd * (double)u.gp.x + xg * (double)u.as.x;
+  acc.v[1] += xd * (double)u.gp.y + xg * (double)u.as.y;
+  acc.v[2] += xd * (double)u.gp.z + xg * (double)u.as.z;
+  acc.v[3] += xd * (double)u.gp.w + xg * (double)u.as.w;
+  acc.s2 += xd * xg;
+  acc.gw += xd * (double)u.gl;
+}
+
+// Adds the terms of up to U entries whose bags (and values) are already known (a dead entry has some valid bag): all their
+// upstream gradient rows are requested before the first is used.
 template <int D, int U>
 __device__ inline void accumulate_batch(const BwdArgs &a, const uint32_t (&bag)[U], const bool (&live)[U],
                                         const float (&x)[U], int sub, Acc &acc) {
-  float gf[U], gl[U];
-  float4 gp[U], as[U];
+  Upstream u[U];
 #pragma unroll
-  for (int k = 0; k < U; ++k) {
-    const uint32_t b = bag[k] / (uint32_t)a.F;
-    gp[k] = (live[k] && a.g_pool) ? ld4(a.g_pool + (int64_t)bag[k] * D + sub * 4) : f4zero();
-    as[k] = (live[k] && a.g_fm) ? ld4(a.A_sum + (int64_t)b * D + sub * 4) : f4zero();
-    gf[k] = (live[k] && a.g_fm) ? a.g_fm[b] : 0.f;
-    gl[k] = (live[k] && a.g_lr) ? a.g_lr[b] : 0.f;
-  }
+  for (int k = 0; k < U; ++k) u[k] = request_upstream<D>(a, bag[k], sub);
+#pragma unroll
+  for (int k = 0; k < U; ++k) arrive(u[k]);
 #pragma unroll
   for (int k = 0; k < U; ++k) {
     if (!live[k]) continue;
-    const double xd = (double)x[k];
-    const double xg = xd * (double)gf[k];
-    acc.v[0] += xd * (double)gp[k].x + xg * (double)as[k].x;
-    acc.v[1] += xd * (double)gp[k].y + xg * (double)as[k].y;
-    acc.v[2] += xd * (double)gp[k].z + xg * (double)as[k].z;
-    acc.v[3] += xd * (double)gp[k].w + xg * (double)as[k].w;
-    acc.s2 += xd * xg;
-    acc.gw += xd * (double)gl[k];
+    drop_absent(a, u[k]);
+    add_upstream(u[k], x[k], acc);
   }
 }
 
@@ -744,38 +774,19 @@ __device__ inline void apply_row(const BwdArgs &a, int64_t u, int row, int sub, 
   }
 }
 
-// Terms of one entry with payload p (bag, or entry index when feature values are present).
-template <int D, bool kHasVals>
-__device__ inline void add_entry(const BwdArgs &a, uint32_t p, int sub, Acc &acc) {
-  float x = 1.f;
-  if (kHasVals) {
-    x = a.vals[p];
-    p = (uint32_t)a.bag_of[p];
-  }
-  const uint32_t b = p / (uint32_t)a.F;
-  const float4 gp = a.g_pool ? ld4_stream(a.g_pool + (int64_t)p * D + sub * 4) : f4zero();
-  const float4 as = a.g_fm ? ld4(a.A_sum + (int64_t)b * D + sub * 4) : f4zero();
-  const float gf = a.g_fm ? a.g_fm[b] : 0.f;
-  const float gl = a.g_lr ? a.g_lr[b] : 0.f;
-  const double xd = (double)x;
-  const double xg = xd * (double)gf;
-  acc.v[0] += xd * (double)gp.x + xg * (double)as.x;
-  acc.v[1] += xd * (double)gp.y + xg * (double)as.y;
-  acc.v[2] += xd * (double)gp.z + xg * (double)as.z;
-  acc.v[3] += xd * (double)gp.w + xg * (double)as.w;
-  acc.s2 += xd * xg;
-  acc.gw += xd * (double)gl;
-}
-
 // (4a) one lane group per segment; long segments are left to the chunked path.  The segment's
 // bounds, row and first payload arrive together; the row state and the first entry's upstream
 // gradients are then fetched together, so a one-entry segment costs two memory round trips.
-// The kernel waits on memory for most of its time, so a fifth wave per SIMD is worth more than registers: it is
-// compiled for five (96 vector registers; at the 120 it would take by itself four fit), and gathers two entries'
-// gradient rows at a time instead of four, which is what lets it fit almost without spilling.  Measured at the large
-// table: 18.2 -> 16.5 ms; six waves (80 registers, 68 bytes of spill) lose that again.  The second state array's registers do
-// not fit in 96 (6 to 10 spilled), so those variants are compiled for four waves: D = 32, Adam, 4.8e5 / 1.9e6 / 7.7e6 entries
-// 50.7 -> 45.4, 101 -> 90, 245 -> 224 us.  Up to D = 16 they also have room for four entries at a time: FTRL with
+// All gathers are unconditional and waited for once per step, ahead of the row's stores: with a condition around each (an
+// array the caller did not pass, an entry past the end) a step of two entries waited four times, and a segment's first
+// accesses behind the previous one's stores.  8.0e6 entries of 64 floats, 1.0e6 short segments 387 -> 341 us (their 1.6 GB at
+// 4.7 TB/s), 1.05e8 of 64 12.9 -> 11.5 ms, 8.2e6 of 32 128 -> 117 us, 3.7e5 of 32 with values and Adam 39.4 -> 28.5.
+// Compiled for five waves per SIMD (up to 88 of 96 vector registers), two entries at a time: with six 395 us and 12.1 ms
+// at those sizes, with four entries at a time 403 us and 13.1 ms, with four entries and four waves 341 us and 11.7 ms.
+// The second state array's registers do
+// not fit in 96, so those variants are compiled for four waves: D = 32, Adam, 4.8e5 / 1.9e6 / 7.7e6 entries
+// 50.7 -> 45.4, 101 -> 90, 245 -> 224 us (before the gathers were freed of conditions, as the next).  Up to D = 16 they also have
+// room for four entries at a time: FTRL with
 // Adagrad, D = 16, same sizes: 54.7 -> 45.5, 110 -> 87, 270 -> 217 us (two at a time: 48.7, 90, 232; at D = 32 four lose).
 // kSecond: an optimizer with a second state array (Adam, FTRL) may be in use.
 template <int D, bool kHasVals, bool kSecond>
@@ -804,21 +815,31 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kSecond 
     }
     const int len = i1 - i0;
     if (len > kShortMax) continue;
+    const int rest = i1 - 1;                               // the segment's last entry: what a dead lane or entry reads
+    // The payloads of the next G entries are fetched lane by lane in the same round trip as the row state and
+    // the first entry's gradients, so a segment of up to G+1 entries costs 2 + ceil((len-1)/U) round trips.
+    uint32_t mine = G >= U ? a.pay_sorted[min(i0 + 1 + sub, rest)] : 0u;
+    RowState st = load_row<D, kSecond>(a, row, sub);
+    float x0 = 1.f;
+    uint32_t bag0 = p0;
+    if (kHasVals) { x0 = a.vals[p0]; bag0 = (uint32_t)a.bag_of[p0]; }
     Acc acc = acc_zero();
+    {
+      Upstream first = request_upstream<D, true>(a, bag0, sub);
+      arrive(first);
+      // and for all that was requested before it, so that nothing below waits behind this segment's stores
+      asm volatile("" : "+v"(i0_n), "+v"(i1_n), "+v"(row_n), "+v"(p0_n), "+v"(mine));
+      drop_absent(a, first);
+      add_upstream(first, x0, acc);
+    }
     if (G >= U) {
-      // The payloads of the next G entries are fetched lane by lane in the same round trip as the row state and
-      // the first entry's gradients, so a segment of up to G+1 entries costs 2 + ceil((len-1)/U) round trips.
-      uint32_t mine = (1 + sub < len) ? a.pay_sorted[i0 + 1 + sub] : 0u;
       float myx = 1.f;
-      const RowState st = load_row<D, kSecond>(a, row, sub);
-      add_entry<D, kHasVals>(a, p0, sub, acc);
       const int glane = (int)(threadIdx.x & (kWave - 1)) - sub;       // first lane of this group in the wave
       for (int base = 1; base < len; base += G) {
-        if (base > 1) mine = (base + sub < len) ? a.pay_sorted[i0 + base + sub] : 0u;
+        if (base > 1) mine = a.pay_sorted[min(i0 + base + sub, rest)];
         if (kHasVals) {
-          const bool have = base + sub < len;
-          myx = have ? a.vals[mine] : 1.f;
-          mine = have ? (uint32_t)a.bag_of[mine] : 0u;
+          myx = a.vals[mine];
+          mine = (uint32_t)a.bag_of[mine];
         }
         const int cnt = min(G, len - base);
         for (int j0 = 0; j0 < cnt; j0 += U) {
@@ -834,13 +855,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kSecond 
           accumulate_batch<D, U>(a, bag, live, x, sub, acc);
         }
       }
-      apply_row<D, kSecond>(a, u, row, sub, st, acc);
     } else {
-      const RowState st = load_row<D, kSecond>(a, row, sub);
-      add_entry<D, kHasVals>(a, p0, sub, acc);
       reduce_entries<D, kHasVals, U>(a, i0 + 1, i1, sub, acc);
-      apply_row<D, kSecond>(a, u, row, sub, st, acc);
     }
+    apply_row<D, kSecond>(a, u, row, sub, st, acc);
   }
 }
 
@@ -1177,6 +1195,8 @@ des_status_t backward_launch(des_table *t, const des_batch_t *b, const int32_t *
   BwdArgs a;
   batch_args(t, b, rows, L, a);
   a.g_lr = io->g_lr; a.g_fm = io->g_fm; a.A_sum = io->A_sum; a.g_pool = io->g_pool;
+  const auto take = [&](const float *p) { return p ? BwdArgs::Take{p, ~0u} : BwdArgs::Take{a.emb, 0u}; };
+  a.take_lr = take(a.g_lr); a.take_fm = take(a.g_fm); a.take_sum = take(a.g_fm ? a.A_sum : nullptr); a.take_pool = take(a.g_pool);
   a.opt_emb = opt->opt_emb; a.opt_w = opt->opt_w; a.lr = opt->lr; a.eps = opt->eps;
   a.b1 = opt->beta1; a.b2 = opt->beta2;
   const double t_step = (double)(opt->step > 0 ? opt->step : 1);
