@@ -119,24 +119,189 @@ __global__ __launch_bounds__(kBlock) void k_compact_store(T *__restrict__ arr, i
   arr[(first + i) * upr + u] = staging[i * upr + u];
 }
 
-// The row count after a compaction, and for the host what it decides by: {rows kept, first dropped row (n if none)}.  The
-// rows before the first drop keep their numbers and every later one's is smaller, so one wave finds the first that changed by
-// halving in 64.  (With an atomic minimum over the flags instead, and a copy to the host of its own, evicting a random 5 % or
-// half of 4.0e6 rows took 1275 / 1020 us, so 1170 / 925.)
-__global__ __launch_bounds__(kWave) void k_take_rows(Ctrl *ctrl, const unsigned long long *__restrict__ new_row, int64_t n,
-                                                      long long *__restrict__ out) {
-  int64_t same = 0, moved = n + 1;                   // new_row[same] == same, and new_row[moved] < moved where it exists
-  while (moved - same > 1) {
-    const int64_t step = (moved - same + kWave - 1) / kWave, r = same + (int64_t)(threadIdx.x + 1) * step;
-    const unsigned long long after = __ballot(r >= moved || new_row[r] != (unsigned long long)r);
-    const int k = __ffsll(after) - 1;                // the last lane is always past the change
-    moved = min(moved, same + (int64_t)(k + 1) * step);
-    same += (int64_t)k * step;
+// Compaction, first look at the keep flags: rows kept per tile of kKeepTile rows, 16 flags per load where they are aligned.
+constexpr int kKeepTile = 2048;
+constexpr int kKeepItems = kKeepTile / kBlock;
+
+__device__ inline uint32_t load_keep(const uint8_t *__restrict__ keep, int64_t r0, int64_t n) {   // bit i: row r0 + i is kept
+  static_assert(kKeepItems == 8, "one 8-byte load per thread");
+  uint32_t bits = 0;
+  if (r0 + kKeepItems <= n && ((uintptr_t)keep & 7u) == 0) {
+    const uint2 v = *reinterpret_cast<const uint2 *>(keep + r0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if ((v.x >> (8 * i)) & 0xFFu) bits |= 1u << i;
+      if ((v.y >> (8 * i)) & 0xFFu) bits |= 16u << i;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < kKeepItems; ++i)
+      if (r0 + i < n && keep[r0 + i]) bits |= 1u << i;
   }
+  return bits;
+}
+
+// Sum of v over the workgroup's threads before this one (and over all of them).
+__device__ inline uint32_t block_sum_before(uint32_t v, uint32_t *lds, uint32_t &total) {
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, waves = blockDim.x / kWave;
+  uint32_t inc = v;
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const uint32_t o = __shfl_up(inc, off, kWave);
+    if (lane >= off) inc += o;
+  }
+  if (lane == kWave - 1) lds[wave] = inc;
+  __syncthreads();
+  uint32_t base = 0, tot = 0;
+  for (int w = 0; w < waves; ++w) {
+    const uint32_t x = lds[w];
+    if (w < wave) base += x;
+    tot += x;
+  }
+  __syncthreads();
+  total = tot;
+  return base + inc - v;
+}
+
+__global__ __launch_bounds__(kBlock) void k_keep_count(const uint8_t *__restrict__ keep, int64_t n, uint32_t *__restrict__ counts) {
+  __shared__ uint32_t lds[kBlock / kWave];
+  const int64_t r0 = (int64_t)blockIdx.x * kKeepTile + (int64_t)threadIdx.x * kKeepItems;
+  uint32_t total;
+  block_sum_before(__popc(load_keep(keep, r0, n)), lds, total);
+  if (threadIdx.x == 0) counts[blockIdx.x] = total;
+}
+
+// The slots are rebuilt in place, tile by tile: under linear probing a key lies between its home slot and the next empty one, so
+// the slots from one empty slot to the next hold the same keys whatever the order of insertion, and fewer keys need no others.
+// A tile's region runs from its first empty slot to the next tile's, here noted (kSlotTile if it has none) before any
+// region is changed.  One wave per tile; the first 64 slots nearly always answer.
+constexpr int kSlotTile = 1024;
+__global__ __launch_bounds__(kBlock) void k_slot_bounds(const Slot *__restrict__ slots, int64_t ntiles, uint32_t *__restrict__ first_empty) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int64_t t = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
+  if (t >= ntiles) return;                                    // uniform per wave
+  uint32_t at = kSlotTile;
+  for (int i = 0; i < kSlotTile; i += kWave) {
+    const unsigned long long empty = __ballot(slots[t * kSlotTile + i + lane].key == kEmptyKey);
+    if (empty) { at = (uint32_t)(i + __ffsll(empty) - 1); break; }
+  }
+  if (lane == 0) first_empty[t] = at;
+}
+
+// One workgroup: turns the tiles' counts into exclusive sums, sets the table's row count and leaves for the host what it decides
+// by: {rows kept, first dropped row (n if none), slot tiles without an empty slot}.
+constexpr int kTellBlock = 1024;
+__global__ __launch_bounds__(kTellBlock) void k_keep_tell(Ctrl *ctrl, const uint8_t *__restrict__ keep, int64_t n,
+                                                           uint32_t *__restrict__ counts, const uint32_t *__restrict__ first_empty,
+                                                           int64_t ntiles, long long *__restrict__ out) {
+  __shared__ uint32_t lds[kTellBlock / kWave];
+  __shared__ unsigned int first_tile, full_tiles;
+  __shared__ int first_row;
+  const int64_t nb = (n + kKeepTile - 1) / kKeepTile;
+  if (threadIdx.x == 0) { first_tile = 0xFFFFFFFFu; full_tiles = 0; first_row = kKeepTile; }
+  __syncthreads();
+  uint32_t carry = 0;                                         // rows are fewer than 2^31
+  for (int64_t base = 0; base < nb; base += kTellBlock) {
+    const int64_t i = base + threadIdx.x;
+    const uint32_t c = i < nb ? counts[i] : 0u;
+    uint32_t total;
+    const uint32_t before = block_sum_before(c, lds, total);
+    if (i < nb) {
+      counts[i] = carry + before;
+      if (c < (uint32_t)min((int64_t)kKeepTile, n - i * kKeepTile)) atomicMin(&first_tile, (unsigned int)i);
+    }
+    carry += total;
+  }
+  for (int64_t t = threadIdx.x; t < ntiles; t += kTellBlock)
+    if (first_empty[t] >= kSlotTile) atomicAdd(&full_tiles, 1u);
+  __syncthreads();
+  if (first_tile != 0xFFFFFFFFu) {                            // uniform
+    const int64_t r0 = (int64_t)first_tile * kKeepTile;
+    for (int i = threadIdx.x; i < kKeepTile; i += kTellBlock)
+      if (r0 + i < n && !keep[r0 + i]) atomicMin(&first_row, i);
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
-    out[0] = (long long)new_row[n];
-    out[1] = moved - 1;
-    ctrl->n_rows = (long long)new_row[n];
+    out[0] = (long long)carry;
+    out[1] = first_tile == 0xFFFFFFFFu ? n : (long long)first_tile * kKeepTile + first_row;
+    out[2] = (long long)full_tiles;
+    ctrl->n_rows = (long long)carry;
+  }
+}
+
+// Exclusive prefix sum of the keep flags, where rows move: new_row[n] is the number of kept rows.
+__global__ __launch_bounds__(kBlock) void k_keep_rows(const uint8_t *__restrict__ keep, int64_t n, const uint32_t *__restrict__ sums,
+                                                       unsigned long long *__restrict__ new_row) {
+  __shared__ uint32_t lds[kBlock / kWave];
+  const int64_t r0 = (int64_t)blockIdx.x * kKeepTile + (int64_t)threadIdx.x * kKeepItems;
+  const uint32_t bits = load_keep(keep, r0, n);
+  uint32_t total;
+  uint32_t run = sums[blockIdx.x] + block_sum_before(__popc(bits), lds, total);
+#pragma unroll
+  for (int i = 0; i < kKeepItems; ++i) {
+    if (r0 + i < n) new_row[r0 + i] = run;
+    run += (bits >> i) & 1u;
+    if (r0 + i == n - 1) new_row[n] = run;
+  }
+}
+
+// Rebuilds one tile's region in LDS (see k_slot_bounds): drops the keys whose rows go, renumbers the others.  Rows below `lo` keep
+// their number, later ones take new_row, or go if that is null.  Bound by reading and writing the slots once; clearing them and
+// claiming each kept key's slot by compare-and-swap took about 310 us for 4.0e6 rows in 8.4e6
+// slots; with the first look at the flags, which wrote and scanned 8 bytes a row, the whole call's kernels 440 -> 136 us.
+__global__ __launch_bounds__(kBlock) void k_rebuild_slots(Slot *__restrict__ slots, uint64_t n_slots, const uint32_t *__restrict__ first_empty,
+                                                           const uint8_t *__restrict__ keep,
+                                                           const unsigned long long *__restrict__ new_row, int64_t lo,
+                                                           Ctrl *__restrict__ ctrl) {
+  __shared__ unsigned long long keys[2 * kSlotTile];
+  __shared__ int32_t rows[2 * kSlotTile];
+  constexpr int kItems = 2 * kSlotTile / kBlock;
+  const uint64_t mask = n_slots - 1, t = blockIdx.x, ntiles = n_slots / kSlotTile;
+  const uint64_t start = t * kSlotTile + first_empty[t];
+  const int len = (int)((t + 1) * kSlotTile + first_empty[t + 1 < ntiles ? t + 1 : 0] - start);   // 1 .. 2 * kSlotTile - 1
+  unsigned long long key[kItems];
+  int32_t row[kItems];
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    const int i = j * kBlock + threadIdx.x;
+    key[j] = kEmptyKey;
+    row[j] = -1;
+    if (i < len) {
+      const Slot s = slots[(start + i) & mask];
+      key[j] = s.key;
+      row[j] = s.row;
+    }
+    keys[i] = kEmptyKey;
+    rows[i] = -1;
+  }
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    if (row[j] >= lo) row[j] = new_row && keep[row[j]] ? (int32_t)new_row[row[j]] : -1;
+    if (row[j] < 0) key[j] = kEmptyKey;                       // dropped, or a key that never got a row
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    if (key[j] == kEmptyKey) continue;
+    bool placed = false;
+    for (uint64_t at = ((mix64(key[j]) & mask) - start) & mask; at < (uint64_t)len; ++at) {
+      if (atomicCAS(&keys[at], (unsigned long long)kEmptyKey, key[j]) == kEmptyKey) {
+        rows[at] = row[j];
+        placed = true;
+        break;
+      }
+    }
+    if (!placed) atomicCAS(&ctrl->status, 0, (int)DES_ERR_FULL);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    const int i = j * kBlock + threadIdx.x;
+    if (i < len) {
+      Slot s;
+      s.key = keys[i]; s.row = rows[i]; s.first = 0xFFFFFFFFu;
+      slots[(start + i) & mask] = s;
+    }
   }
 }
 
@@ -282,10 +447,12 @@ des_status_t des_table_compact(des_table_t *t, const uint8_t *keep, uint32_t *au
   if (!t || ((uintptr_t)aux & 3u)) return DES_ERR_INVALID_ARG;
   const des_table_config_t &c = t->cfg;
   hipStream_t s = (hipStream_t)stream;
-  int64_t n = 0;
-  des_status_t st = des_table_size(t, &n);
-  if (st != DES_OK) return st;
-  if (blocking_status(t) != DES_OK) return DES_ERR_INVALID_ARG;
+  Ctrl ctrl;                                                // the row count and the status in one copy
+  if (hipStreamSynchronize(t->last_stream) != hipSuccess ||
+      hipMemcpy(&ctrl, t->ctrl, sizeof(ctrl), hipMemcpyDeviceToHost) != hipSuccess)
+    return DES_ERR_DEVICE;
+  const int64_t n = ctrl.n_rows;
+  if (ctrl.status != DES_OK) return DES_ERR_INVALID_ARG;
   if (n_rows_out) *n_rows_out = n;
   t->last_stream = s;
   t->prep.valid = false;
@@ -294,22 +461,29 @@ des_status_t des_table_compact(des_table_t *t, const uint8_t *keep, uint32_t *au
   if (!staging || ((uintptr_t)staging & 15u) || staging_bytes < (size_t)4096 * (size_t)c.dim * 4) return DES_ERR_WORKSPACE;
   const size_t flags_bytes = align_up((size_t)(n + 1) * 8, 256);
   if (t->ws_bytes < flags_bytes + scan_scratch_bytes(n + 1)) return DES_ERR_WORKSPACE;
+  // the new row numbers, then three words for the host, the tiles' counts and, if there is room, the bounds of the slot tiles
   unsigned long long *flags = (unsigned long long *)t->ws;
-  void *scan_scratch = t->ws + flags_bytes;
+  const unsigned nb = (unsigned)((n + kKeepTile - 1) / kKeepTile);
+  long long *words = (long long *)(t->ws + flags_bytes);
+  uint32_t *counts = (uint32_t *)(words + 4);
+  const size_t bounds_at = flags_bytes + align_up(sizeof(long long) * 4 + (size_t)nb * 4, 256);
+  static_assert(kKeepTile >= 2048, "the words and counts fit where the scratch of a scan of n + 1 values would lie");
+  static_assert(kSlotTile <= 1024, "whole tiles: a table has at least 1024 slots, a power of two");
+  const int64_t ntiles = t->ws_bytes >= bounds_at + t->n_slots / kSlotTile * 4 ? (int64_t)(t->n_slots / kSlotTile) : 0;
+  uint32_t *bounds = (uint32_t *)(t->ws + bounds_at);
   ProfScope ps(KID_MIGRATE, s);
-  // the scan's total lands behind its values: flags[n] is the number of kept rows
-  hipLaunchKernelGGL(k_keep_flags, dim3(blocks_for(n)), dim3(kBlock), 0, s, keep, n, flags);
-  exclusive_scan_u64(flags, n, flags + n, scan_scratch, s);
-  hipLaunchKernelGGL(k_take_rows, dim3(1), dim3(kWave), 0, s, t->ctrl, (const unsigned long long *)flags, n,
-                     (long long *)scan_scratch);               // the scan is done with it
-  long long told[2] = {0, 0};
-  if (hipMemcpyAsync(told, scan_scratch, sizeof(told), hipMemcpyDeviceToHost, s) != hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess)
+  hipLaunchKernelGGL(k_keep_count, dim3(nb), dim3(kBlock), 0, s, keep, n, counts);
+  if (ntiles)
+    hipLaunchKernelGGL(k_slot_bounds, dim3((unsigned)((ntiles * kWave + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, t->slots, ntiles, bounds);
+  hipLaunchKernelGGL(k_keep_tell, dim3(1), dim3(kTellBlock), 0, s, t->ctrl, keep, n, counts, (const uint32_t *)bounds, ntiles, words);
+  long long told[3] = {0, 0, 0};
+  if (hipMemcpyAsync(told, words, sizeof(told), hipMemcpyDeviceToHost, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
     return DES_ERR_DEVICE;
   const int64_t kept = told[0], lo = told[1];
   // As many kept rows as rows before the first drop: nothing moves.  Moving a row onto itself through the staging buffer costs
   // as much as any other move: 4.0e6 rows of 32 columns with their state in front of 1.2e6 dropped ones took 160 launches, 1.2 ms.
   const int64_t hi = kept > lo ? n : lo;
+  if (hi > lo) hipLaunchKernelGGL(k_keep_rows, dim3(nb), dim3(kBlock), 0, s, keep, n, (const uint32_t *)counts, flags);
   compact_array<float4>((float4 *)c.emb, c.dim / 4, keep, flags, lo, hi, staging, staging_bytes, s);
   compact_array<float4>((float4 *)c.acc_emb, c.dim / 4, keep, flags, lo, hi, staging, staging_bytes, s);
   compact_array<float4>((float4 *)c.acc2_emb, c.dim / 4, keep, flags, lo, hi, staging, staging_bytes, s);
@@ -318,15 +492,24 @@ des_status_t des_table_compact(des_table_t *t, const uint8_t *keep, uint32_t *au
   compact_array<uint32_t>((uint32_t *)c.acc2_w, 1, keep, flags, lo, hi, staging, staging_bytes, s);
   compact_array<uint32_t>(aux, 1, keep, flags, lo, hi, staging, staging_bytes, s);
   compact_array<unsigned long long>((unsigned long long *)c.row_keys, 1, keep, flags, lo, hi, staging, staging_bytes, s);
-  // the slots are rebuilt from the kept keys
-  hipLaunchKernelGGL(k_fill_slots, dim3(blocks_for((int64_t)t->n_slots, 1 << 16)), dim3(kBlock), 0, s, (uint4 *)t->slots,
-                     (int64_t)t->n_slots);
-  if (kept > 0)
-    hipLaunchKernelGGL(k_rehash, dim3(blocks_for(kept, 1 << 16)), dim3(kBlock), 0, s, t->slots, t->n_slots - 1,
-                       (const uint64_t *)c.row_keys, (int64_t)kept, t->ctrl);
-  if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) return DES_ERR_DEVICE;
+  // The slots: each tile by itself, unless one has no empty slot (a run of a thousand occupied ones) or the workspace has no
+  // room for the tiles' bounds; then from nothing, by the kept keys.
+  if (ntiles && told[2] == 0) {
+    hipLaunchKernelGGL(k_rebuild_slots, dim3((unsigned)ntiles), dim3(kBlock), 0, s, t->slots, t->n_slots, (const uint32_t *)bounds, keep,
+                       hi > lo ? (const unsigned long long *)flags : nullptr, lo, t->ctrl);
+  } else {
+    hipLaunchKernelGGL(k_fill_slots, dim3(blocks_for((int64_t)t->n_slots, 1 << 16)), dim3(kBlock), 0, s, (uint4 *)t->slots,
+                       (int64_t)t->n_slots);
+    if (kept > 0)
+      hipLaunchKernelGGL(k_rehash, dim3(blocks_for(kept, 1 << 16)), dim3(kBlock), 0, s, t->slots, t->n_slots - 1,
+                         (const uint64_t *)c.row_keys, (int64_t)kept, t->ctrl);
+  }
+  int status = 0;
+  if (hipGetLastError() != hipSuccess || hipMemcpyAsync(&status, &t->ctrl->status, sizeof(status), hipMemcpyDeviceToHost, s) != hipSuccess ||
+      hipStreamSynchronize(s) != hipSuccess)
+    return DES_ERR_DEVICE;
   if (n_rows_out) *n_rows_out = kept;
-  return blocking_status(t);
+  return (des_status_t)status;
 }
 
 des_status_t des_batch_validate(des_table_t *t, const des_batch_t *batch, const int32_t *rows, int64_t *first_bad,

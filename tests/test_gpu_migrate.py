@@ -236,3 +236,43 @@ def test_compact_finds_the_first_drop_anywhere(des, n):
             assert torch.equal(t.row_keys[:want.numel()], want), (at, step)
             assert torch.equal(t.find(want, des.MISS_ZERO), torch.arange(want.numel(), dtype=torch.int32, device="cuda")), (at, step)
     t.close()
+
+
+@pytest.mark.parametrize("capacity,n,home_lo,home_hi", [
+    (700, 700, 0, 1024),            # one slot tile, whose region is the whole table
+    (1535, 500, 1900, 2048),        # the last tile's region wraps round to the first
+    (1535, 1000, 900, 1100),        # a run across the tiles' border
+    (1535, 1500, 0, 400),           # a tile without an empty slot: rebuilt from nothing
+    (1535, 1200, 1900, 2048),       # ... around the end of the table
+    (20000, 20000, 0, 32768),
+])
+@pytest.mark.parametrize("keep_every", [0, 1, 2, 7])
+def test_compact_rebuilds_slot_tiles(des, capacity, n, home_lo, home_hi, keep_every):
+    """Slot tiles, their borders and runs that cover a whole tile: after dropping rows, every kept key is found under its new row, no
+    dropped one is, and newcomers fill the free slots."""
+    import torch
+    n_slots = 1024
+    while n_slots < capacity + capacity // 3 + 1:
+        n_slots *= 2
+    z = np.arange(1, 40 * n_slots, dtype=np.uint64)
+    h = (z ^ (z >> np.uint64(30))) * np.uint64(0xBF58476D1CE4E5B9)
+    h = (h ^ (h >> np.uint64(27))) * np.uint64(0x94D049BB133111EB)
+    home = (h ^ (h >> np.uint64(31))) & np.uint64(n_slots - 1)
+    pick = z[(home >= home_lo) & (home < home_hi)].astype(np.int64)
+    assert pick.shape[0] >= n
+    keys = torch.from_numpy(pick[:n]).cuda()
+    t = des.Table(4, capacity, 1, init_seed=3, max_n=1 << 15)
+    assert torch.equal(t.find(keys, des.MISS_INSERT), torch.arange(n, dtype=torch.int32, device="cuda"))
+    keep = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    if keep_every:
+        keep[::keep_every] = 1
+    sel = torch.nonzero(keep).flatten()
+    assert t.compact(keep, torch.empty(4096 * 16, dtype=torch.uint8, device="cuda")) == sel.numel() == t.size()
+    want = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    want[sel] = torch.arange(sel.numel(), dtype=torch.int32, device="cuda")
+    assert torch.equal(t.find(keys, des.MISS_ZERO), want) and t.status() == 0
+    gone = keys[~keep.bool()]
+    back = t.find(gone, des.MISS_INSERT)
+    assert torch.equal(back, torch.arange(sel.numel(), n, dtype=torch.int32, device="cuda"))
+    assert torch.equal(t.find(keys[sel], des.MISS_ZERO), want[sel]) and t.size() == n and t.status() == 0
+    t.close()
