@@ -2,12 +2,13 @@
 //   LR  M1 (Section 4.1, Eq. lr_m1), FM M1 and M2 (Section 4.2, Eq. fm_m1m2) and the per-field
 //   pooled embeddings (Section 4.3).
 //
-// Mapping: 1, 2 or 4 wave64s per sample.  A row of D floats is read by G = D/4 adjacent lanes
+// Mapping: 1, 2 or 4 wave64s per sample, or several samples of few fields per wave.  A row of D floats is read by G = D/4 adjacent lanes
 // as one 16-byte load each, so a wave holds 64/G "lane groups" that each fetch a different row
 // at the same time.  Every group owns a contiguous range of the sample's bags and walks its
 // entries in CSR order in chunks of G: lane i of the group loads the metadata of entry i of
 // the chunk (row, key -> shard, value, bag found in the sample's offsets staged in LDS) and
-// publishes it in LDS, from where the group reads entry j with one broadcast read; the row
+// publishes it in LDS, from where the group reads entry j with one broadcast read (groups inside a quad
+// of lanes exchange it by DPP instead); the row
 // gathers of a chunk are issued back to back.  The running bag sum stays in registers (the
 // pooled output is written once per bag, at its last entry, already summed over shards).  The per-shard FM / LR
 // partials of the sample live in LDS ([K][D+2] doubles per sample: D columns, then the sum of
@@ -23,6 +24,9 @@
 // condition, or the bag's store between a batch's gathers and their uses, each was waited for alone.  Gathers without
 // conditions, all waited for at once ahead of the stores: 8.0e6 entries of 64 floats 694 -> 598 us, 1.05e8 of 64 7.50 -> 6.35 ms,
 // 8.2e6 of 32 236 -> 218 us.
+// Registers: U gathers of four floats each.  Four waves per SIMD need 128 registers (without the bound 131 at D = 128 with values:
+// 91 -> 81 us for 8.1e5 entries); D = 32 without values fits six waves with four gathers in flight (8.2e6 entries 217 -> 207 us, with
+// the scalars' additions below).
 //
 // Accumulation is in double, inputs and outputs are fp32: a sample's sum of several hundred
 // signed terms cancels, and fp32 accumulation alone would exceed the 1e-5 relative bound
@@ -47,7 +51,7 @@ struct FwdArgs {
   int acc_doubles;      // LDS doubles of one set of a sample's accumulators
   int sets;             // sets per sample: 1, which its waves share, or one for each of them
   int lds_per_sample;   // LDS doubles per sample in total (accumulators + staged offsets)
-  int wps;              // waves per sample: 1, 2 or 4
+  int log_threads;      // log2 of the threads per sample: part of a wave (whole lane groups), or 1, 2 or 4 waves
 };
 
 __device__ inline float4 ld4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
@@ -74,33 +78,45 @@ __device__ inline double group_sum(double q) {
   return q;
 }
 
+// v of lane `src` of the caller's group of G = 1, 2 or 4 lanes (VALU, does not use the LDS pipe).
+template <int G>
+__device__ inline int group_lane(int v, int src) {
+  static_assert(G <= 4, "inside a quad");
+  if (G == 1) return v;
+  if (G == 2) return src == 0 ? __builtin_amdgcn_mov_dpp(v, 0xA0, 0xF, 0xF, true) : __builtin_amdgcn_mov_dpp(v, 0xF5, 0xF, 0xF, true);
+  if (src == 0) return __builtin_amdgcn_mov_dpp(v, 0x00, 0xF, 0xF, true);
+  if (src == 1) return __builtin_amdgcn_mov_dpp(v, 0x55, 0xF, 0xF, true);
+  if (src == 2) return __builtin_amdgcn_mov_dpp(v, 0xAA, 0xF, 0xF, true);
+  return __builtin_amdgcn_mov_dpp(v, 0xFF, 0xF, 0xF, true);
+}
+
 // kByKey: shard of an entry = hash of its ID (entries of a bag scatter over the shards: one LDS update per
 // entry).  Otherwise the field partition of Section 5: a bag belongs to shard f mod K as a whole, so its sums
 // are formed in registers and the shard's accumulators take one update per bag.
 // kHasVals: the batch carries feature values; without them every x is 1 and the products with x are left out.
 template <int D, bool kByKey, bool kHasVals>
-__global__ __launch_bounds__(kBlock) void k_forward(const FwdArgs a) {
+__global__ __launch_bounds__(kBlock, D == 32 && !kHasVals ? 6 : 4) void k_forward(const FwdArgs a) {
   extern __shared__ __align__(16) double lds[];
   constexpr int G = D / 4;                 // lanes per row = entries per chunk
-  constexpr int NG = kWave / G;            // lane groups per wave
-  constexpr int U = G >= 8 ? 8 : G;        // row gathers in flight per lane (4 / 8: D = 64 625 -> 598 us, D = 32 with values 21.9 -> 21.4, without 218 -> 219)
+  constexpr int U = G < 8 ? G : D == 32 && !kHasVals ? 4 : 8;         // row gathers in flight per lane (4 / 8: D = 64 625 -> 598 us, D = 32 with values 21.9 -> 21.4, without 218 -> 219)
+  constexpr bool kQuad = G <= 4;           // a group lies inside a quad: its lanes' metadata comes by DPP instead of through LDS
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int g = lane / G, sub = lane % G;
-  const int K = a.K, F = a.F, wps = a.wps;
-  const int local = wave / wps, wis = wave % wps;         // sample slot in the workgroup, wave in sample
+  const int K = a.K, F = a.F;
+  const int local = threadIdx.x >> a.log_threads;         // sample in the workgroup
+  const int nts = 1 << a.log_threads, tis = threadIdx.x & (nts - 1);   // threads per sample, thread in sample
   // LDS: one 16-byte metadata slot per thread, then per sample the accumulators and offsets
   int4 *meta = reinterpret_cast<int4 *>(lds) + wave * kWave;
   constexpr int P = D + 2;                                // row pitch: D columns, sum of squares, LR sum
   double *sums = lds + 2 * kBlock + (size_t)local * a.lds_per_sample;  // [sets][K][P]
-  double *sum = a.sets > 1 ? sums + wis * a.acc_doubles : sums;        // the one this wave adds to
+  double *sum = a.sets > 1 ? sums + tis / kWave * a.acc_doubles : sums;  // the one this wave adds to
   int *offs = reinterpret_cast<int *>(sums + a.sets * a.acc_doubles);  // [F+1]
-  const int64_t b = (int64_t)blockIdx.x * (kBlock / kWave / wps) + local;
+  const int64_t b = ((int64_t)blockIdx.x * kBlock >> a.log_threads) + local;
   const bool active = b < a.B;
   const bool need_fm = a.P_sum != nullptr, need_lr = a.P_lr != nullptr, need_pool = a.pool != nullptr;
   const bool hashed = kByKey && (need_fm || need_lr);
   const int row_mask = need_fm || need_pool ? -1 : 0;     // first-order terms alone need no rows
   const float *w_base = need_lr ? a.w : a.emb;
-  const int tis = wis * kWave + lane, nts = wps * kWave;  // thread in sample, threads per sample
 
   for (int i = tis; i < a.sets * a.acc_doubles; i += nts) sums[i] = 0.0;
   if (active)
@@ -108,7 +124,7 @@ __global__ __launch_bounds__(kBlock) void k_forward(const FwdArgs a) {
   __syncthreads();
 
   if (active) {
-    const int gg = wis * NG + g, ngt = wps * NG;
+    const int gg = tis / G, ngt = nts / G;
     const int f0 = (int)(((int64_t)F * gg) / ngt), f1 = (int)(((int64_t)F * (gg + 1)) / ngt);
     const int first = offs[0];                            // the sample's entries start here
     const int e0 = offs[f0] - first, e1 = offs[f1] - first;
@@ -121,7 +137,8 @@ __global__ __launch_bounds__(kBlock) void k_forward(const FwdArgs a) {
         if (offs[f] == offs[f + 1]) st4(pool + (f * D + sub * 4), make_float4(0.f, 0.f, 0.f, 0.f));
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     double bag_sq = 0.0;                                  // field partition: this lane's share of the bag's sum of squares
-    int cur = f0;                                         // bag of the entry before the chunk
+    int cur = f0;                                         // a bag that no entry to come lies before
+    int cur_end = offs[min(f0 + 1, F)];                   // kQuad: where it ends
 
     // metadata of entry e0 + sub of the first chunk; later chunks are fetched one chunk ahead
     int r_n = -1;
@@ -133,7 +150,7 @@ __global__ __launch_bounds__(kBlock) void k_forward(const FwdArgs a) {
       if (kHasVals) x_n = vals[e0 + sub];
     }
     for (int e = e0; e < e1; e += G) {
-      const int my = e + sub;
+      const int my = e + sub, at = my + first;
       const int r_l = r_n;
       const uint64_t key_l = key_n;
       const float x_l = x_n;
@@ -143,33 +160,47 @@ __global__ __launch_bounds__(kBlock) void k_forward(const FwdArgs a) {
         if (hashed) key_n = keys[my + G];
         if (kHasVals) x_n = vals[my + G];
       }
-      // bag of this lane's entry: the largest f with offs[f] <= its index.  Entries are walked in order, so it is at
-      // or shortly after the bag of the last processed entry: up to four bags on in one step (offsets ascend), then a
-      // binary search for the rare long run of empty bags.
-      int lo = cur;
-      const int at = my + first;
-      {
+      // Bag of this lane's entry: the largest f with offs[f] <= its index, and where that bag ends.  A lane of a small group comes
+      // back after few entries, mostly to the same bag or the next.  In larger groups the chunk starts at or shortly after the bag of
+      // the one before: up to four bags on in one step (offsets ascend), then a binary search for the rare long run of short or
+      // empty bags.
+      int lo = cur, end = 0x7FFFFFFF;
+      if (kQuad) {
+        end = cur_end;
+        if (my < e1 && end <= at)
+          do { ++lo; end = offs[lo + 1]; } while (end <= at);
+        cur_end = end;
+      } else {
         int ahead = 0;
 #pragma unroll
-        for (int k = 1; k <= 4; ++k) ahead += offs[min(cur + k, f1)] <= at ? 1 : 0;
+        for (int k = 1; k <= 4; ++k) {
+          const int o = offs[min(cur + k, f1)];
+          ahead += o <= at ? 1 : 0;
+          if (o > at) end = min(end, o);
+        }
         lo += ahead;
-        if (my < e1 && ahead == 4 && offs[lo + 1] <= at) {
-          int hi = f1;
-          ++lo;
-          while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (offs[mid] <= at) lo = mid; else hi = mid;
+        if (my < e1 && ahead == 4) {
+          if (offs[lo + 1] <= at) {
+            int hi = f1;
+            ++lo;
+            while (hi - lo > 1) {
+              const int mid = (lo + hi) >> 1;
+              if (offs[mid] <= at) lo = mid; else hi = mid;
+            }
           }
+          end = offs[lo + 1];
         }
       }
       const int bag_l = my < e1 ? lo : cur;
+      cur = kQuad ? bag_l : __shfl(bag_l, lane - sub + min(G, e1 - e) - 1, kWave);
       const int sh_l = !need_fm && !need_lr ? 0 : kByKey ? (int)((uint32_t)(mix64(key_l) >> 32) % (uint32_t)K) : bag_l % K;
-      // what the group needs of this lane's entry, read back with one broadcast LDS read per entry: row (0 if absent), its
-      // shard's accumulators (-1: absent), its bag's pooled row if it is the bag's last entry (-1: it is not), its value.
-      // Same wave, program order: no barrier needed.
-      const bool last_l = my < e1 && at + 1 == offs[bag_l + 1];
-      meta[lane] = make_int4(max(r_l, 0) & row_mask, r_l >= 0 ? sh_l * P : -1, last_l ? bag_l * D : -1, __float_as_int(x_l));
-      cur = __shfl(bag_l, lane - sub + min(G, e1 - e) - 1, kWave);
+      // what the group needs of this lane's entry: row (0 if absent), its shard's accumulators (-1: absent), its bag's pooled
+      // row if it is the bag's last entry (-1: it is not), its value
+      const int row_l = max(r_l, 0) & row_mask;
+      const int acc_l = r_l >= 0 ? sh_l * P : -1;
+      const int end_l = my < e1 && at + 1 == end ? bag_l * D : -1;
+      // read back with one broadcast LDS read per entry; same wave, program order: no barrier needed
+      if (!kQuad) meta[lane] = make_int4(row_l, acc_l, end_l, __float_as_int(x_l));
       // The first-order weight of this lane's own entry: one gather per chunk for the whole group.
       float w_l = w_base[max(r_l, 0)];
       double q_l = 0.0;                                   // sum of squares of this lane's own entry
@@ -184,7 +215,11 @@ __global__ __launch_bounds__(kBlock) void k_forward(const FwdArgs a) {
           // stores, would be waited for one by one.
 #pragma unroll
           for (int i = 0; i < U; ++i) {
-            md[i] = meta[g * G + j0 + i];
+            if constexpr (kQuad)
+              md[i] = make_int4(group_lane<G>(row_l, j0 + i), group_lane<G>(acc_l, j0 + i), group_lane<G>(end_l, j0 + i),
+                                kHasVals ? group_lane<G>(__float_as_int(x_l), j0 + i) : 0);
+            else
+              md[i] = meta[g * G + j0 + i];
             v[i] = ld4(a.emb + (int64_t)md[i].x * D + sub * 4);
           }
 #pragma unroll
@@ -233,8 +268,18 @@ __global__ __launch_bounds__(kBlock) void k_forward(const FwdArgs a) {
       }
       if (r_l >= 0) {
         double *dst = sum + sh_l * P + D;
-        if (kByKey && need_fm) atomicAdd(dst, q_l);
-        if (need_lr) atomicAdd(dst + 1, kHasVals ? (double)x_l * (double)w_l : (double)w_l);
+        const double l_l = kHasVals ? (double)x_l * (double)w_l : (double)w_l;
+        // half of the lanes the other way round: with few shards the lanes' addresses are equal (K = 2: 7.2e6 entries of 8 floats
+        // 149 -> 135 us, 6.9e6 of 16 207 -> 187)
+        if (kByKey && need_fm && need_lr) {
+          const bool odd = sub & 1;
+          atomicAdd(dst + (odd ? 1 : 0), odd ? l_l : q_l);
+          atomicAdd(dst + (odd ? 0 : 1), odd ? q_l : l_l);
+        } else if (kByKey && need_fm) {
+          atomicAdd(dst, q_l);
+        } else if (need_lr) {
+          atomicAdd(dst + 1, l_l);
+        }
       }
     }
   }
@@ -314,7 +359,7 @@ FwdArgs make_args(des_table *t, const des_batch_t *b, const int32_t *rows) {
   a.keys = b->keys; a.offsets = b->offsets; a.vals = b->vals; a.rows = rows;
   a.P_lr = a.P_sum = a.P_sq = a.pool = nullptr;
   a.B = b->B; a.F = b->F; a.K = t->cfg.num_shards; a.policy = t->cfg.shard_policy;
-  a.acc_doubles = 0; a.sets = 1; a.lds_per_sample = 0; a.wps = 1;
+  a.acc_doubles = 0; a.sets = 1; a.lds_per_sample = 0; a.log_threads = 6;
   return a;
 }
 
@@ -346,10 +391,16 @@ des_status_t forward_launch(des_table *t, const des_batch_t *b, const int32_t *r
   // LDS for it than with four samples of one wave each.
   const int without = wps;
   while (wps < 4 && (b->B * wps + 3) / 4 < kFillGroups && b->F > wps * (kWave * 4 / D)) wps *= 2;
-  a.wps = wps;
+  // Few fields: a wave's lane groups beyond the sample's bags would idle, so it takes several samples, as long as every bag has a
+  // group of its own and the chip stays full (D = 16: 73821 x 4 bags 85 -> 31 us; D = 4: 32762 x 2 51 -> 15 us).
+  int threads = kWave * wps;
+  while (threads <= kWave && b->F * (D / 4) <= threads / 2 && b->B * (threads / 2) / kBlock >= kFillGroups &&
+         kBlock / (threads / 2) * per_sample * 8 <= 40 * 1024)
+    threads /= 2;
+  a.log_threads = __builtin_ctz((unsigned)threads);
   a.sets = without == 1 ? wps : 1;
   a.lds_per_sample = (int)((a.sets - 1) * acc_doubles + per_sample);
-  const int spb = kBlock / kWave / wps;
+  const int spb = kBlock / threads;
   const dim3 grid((unsigned)((b->B + spb - 1) / spb)), block(kBlock);
   const size_t shmem = 16 * (size_t)kBlock + (size_t)a.lds_per_sample * 8 * spb;
   const bool by_key = a.policy == DES_SHARD_KEY_HASH;
