@@ -614,61 +614,13 @@ __device__ inline void load_batch_meta(const BwdArgs &a, int i, int i1, uint32_t
   }
 }
 
-// Per-sample values of the entry processed last by a lane group: entries of one row arrive in batch order, so a
-// row that occurs many times in one sample (the hot IDs of a skewed batch) brings runs of entries with the same
-// sample, which then reuse these instead of fetching them again.
-struct SampleRun {
-  uint32_t b;
-  float4 as;
-  float gf, gl;
-};
-
-// accumulate_batch for such runs: the A_sum row, g_fm and g_lr of an entry are fetched only if its sample differs
-// from the previous entry's.  Same values, same order of additions as accumulate_batch.
-template <int D, int U>
-__device__ inline void accumulate_batch_runs(const BwdArgs &a, const uint32_t (&bag)[U], const bool (&live)[U],
-                                             const float (&x)[U], int sub, Acc &acc, SampleRun &run) {
-  float gf[U], gl[U];
-  float4 gp[U], as[U];
-  uint32_t b[U];
-  bool same[U];
-  uint32_t prev = run.b;
-#pragma unroll
-  for (int k = 0; k < U; ++k) {
-    b[k] = bag[k] / (uint32_t)a.F;
-    same[k] = live[k] && b[k] == prev;
-    if (live[k]) prev = b[k];
-    gp[k] = (live[k] && a.g_pool) ? ld4(a.g_pool + (int64_t)bag[k] * D + sub * 4) : f4zero();
-    as[k] = (live[k] && !same[k] && a.g_fm) ? ld4(a.A_sum + (int64_t)b[k] * D + sub * 4) : f4zero();
-    gf[k] = (live[k] && !same[k] && a.g_fm) ? a.g_fm[b[k]] : 0.f;
-    gl[k] = (live[k] && !same[k] && a.g_lr) ? a.g_lr[b[k]] : 0.f;
-  }
-#pragma unroll
-  for (int k = 0; k < U; ++k) {
-    if (!live[k]) continue;
-    if (same[k]) { as[k] = run.as; gf[k] = run.gf; gl[k] = run.gl; }
-    run.b = b[k]; run.as = as[k]; run.gf = gf[k]; run.gl = gl[k];
-    const double xd = (double)x[k];
-    const double xg = xd * (double)gf[k];
-    acc.v[0] += xd * (double)gp[k].x + xg * (double)as[k].x;
-    acc.v[1] += xd * (double)gp[k].y + xg * (double)as[k].y;
-    acc.v[2] += xd * (double)gp[k].z + xg * (double)as[k].z;
-    acc.v[3] += xd * (double)gp[k].w + xg * (double)as[k].w;
-    acc.s2 += xd * xg;
-    acc.gw += xd * (double)gl[k];
-  }
-}
-
 // Sums over the sorted entries [i0, i1), U at a time; the payloads of the next U entries are requested
 // before the gradient rows of the current ones, so a batch costs one memory round trip, not two.
-// kRuns: reuse the per-sample values along runs of entries of one sample (long segments).
-template <int D, bool kHasVals, int U, bool kRuns = false>
+template <int D, bool kHasVals, int U>
 __device__ inline void reduce_entries(const BwdArgs &a, int i0, int i1, int sub, Acc &acc) {
   uint32_t nbag[U];
   bool nlive[U];
   float nx[U];
-  SampleRun run;
-  run.b = 0xFFFFFFFFu; run.as = f4zero(); run.gf = 0.f; run.gl = 0.f;
   if (i0 < i1) load_batch_meta<kHasVals, U>(a, i0, i1, nbag, nlive, nx);
   for (int i = i0; i < i1; i += U) {
     uint32_t bag[U];
@@ -677,8 +629,7 @@ __device__ inline void reduce_entries(const BwdArgs &a, int i0, int i1, int sub,
 #pragma unroll
     for (int k = 0; k < U; ++k) { bag[k] = nbag[k]; live[k] = nlive[k]; x[k] = nx[k]; }
     if (i + U < i1) load_batch_meta<kHasVals, U>(a, i + U, i1, nbag, nlive, nx);
-    if (kRuns) accumulate_batch_runs<D, U>(a, bag, live, x, sub, acc, run);
-    else accumulate_batch<D, U>(a, bag, live, x, sub, acc);
+    accumulate_batch<D, U>(a, bag, live, x, sub, acc);
   }
 }
 
@@ -862,40 +813,140 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kSecond 
   }
 }
 
-// (4b) one wave per chunk of a long segment: the chunk is split evenly over the wave's lane
-// groups, the groups' sums are combined with cross-lane shuffles, and the wave writes
+// Which chunk of its segment wave `c` takes, where the segment has the waves c0 .. c0 + nch - 1: the waves of one die (workgroups
+// go round the eight dies) take consecutive chunks.  A row's entries come in batch order, so a die then sees an eighth of the
+// samples of every row with eight workgroups or more, and that eighth of A_sum stays in its L2: 8.0e6 entries of 64 floats
+// 359 -> 346 us, 1.05e8 of 64 2.62 -> 2.51 ms, 8.2e6 of 32 150 -> 141 us.
+__device__ inline uint32_t chunk_of_wave(uint32_t c, uint32_t c0, uint32_t nch) {
+  constexpr uint32_t kDies = 8, kRound = kDies * kWavesPerBlock;
+  const auto before = [](uint32_t w, uint32_t die) {          // waves of the die below w
+    const int in = (int)(w % kRound) - (int)(die * kWavesPerBlock);
+    return w / kRound * kWavesPerBlock + (uint32_t)min(max(in, 0), kWavesPerBlock);
+  };
+  const uint32_t mine = c / kWavesPerBlock % kDies;
+  uint32_t k = before(c, mine) - before(c0, mine);
+  for (uint32_t die = 0; die < mine; ++die) k += before(c0 + nch, die) - before(c0, die);
+  return k;
+}
+
+// (4b) one wave per chunk of a long segment: the wave walks the chunk in batches, its lane groups take equal runs of a
+// batch, the groups' sums are combined with cross-lane shuffles, and the wave writes
 // partials[c] = (s1[D], s2, gw, 0, 0) in double -- or, when the segment has no other chunk (33 .. 512 or 128
-// entries, most long segments), updates the row at once
+// entries, most long segments), updates the row at once.
+// Bound by the gradient rows and A_sum rows that come through the fabric (2.7 GB at 7 TB/s for 8.0e6 entries of 64 floats); in
+// smaller batches by the round trips.  A lane loads, divides and adds up what an entry needs once (bag, sample, value, g_fm,
+// g_lr) and leaves the rest to read in LDS; no gather is under a condition, so a step of U entries is waited for once: 8.2e6
+// entries of 32 floats 165 -> 150 us, 3.7e5 of 32 with values 17.3 -> 14.4, 8.0e6 of 64 366 -> 359.  U = 2 / 8 (150 / 162,
+// 15.2 / 14.9, 358 / 365) and six waves per SIMD (169, 20.8, 380) are no better.
 template <int D, bool kHasVals>
-__global__ __launch_bounds__(kBlock) void k_long_partial(const BwdArgs a) {
+__global__ __launch_bounds__(kBlock, 5) void k_long_partial(const BwdArgs a) {
   constexpr int G = D / 4;
   constexpr int NG = kWave / G;
-  const int lane = threadIdx.x & (kWave - 1);
-  const int64_t c = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-  if (c >= a.ctrl->n_chunks) return;                          // uniform per wave
+  constexpr int U = 4;                                        // gradient rows in flight per lane
+  constexpr int kBatch = NG * (G > U ? G : U), kLoads = kBatch / kWave;
+  __shared__ uint2 l_bag[kWavesPerBlock][kBatch];             // (bag, sample) of a batch's entries
+  __shared__ float2 l_x[kWavesPerBlock][kBatch];              // their (value, value * g_fm) factors
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const uint32_t wave_no = blockIdx.x * kWavesPerBlock + wave;
+  if (wave_no >= a.ctrl->n_chunks) return;                    // uniform per wave
   const int g = lane / G, sub = lane % G;
-  const int j = a.chunk_owner[c];
+  const int j = a.chunk_owner[wave_no];
   const int u = a.long_seg[j];
-  const int c_lo = a.seg_off[u] + ((int)(c - a.long_c0[j]) << a.chunk_shift);
-  const int c_hi = min(c_lo + (1 << a.chunk_shift), a.seg_off[u + 1]);
-  const int per = (c_hi - c_lo + NG - 1) / NG;
-  const int i0 = min(c_lo + g * per, c_hi), i1 = min(i0 + per, c_hi);
+  const int seg_lo = a.seg_off[u], seg_hi = a.seg_off[u + 1];
+  const uint32_t c0 = a.long_c0[j], k_seg = chunk_of_wave(wave_no, c0, (uint32_t)chunks_of(a, seg_hi - seg_lo));
+  const int c_lo = seg_lo + (int)(k_seg << a.chunk_shift);
+  const int c_hi = min(c_lo + (1 << a.chunk_shift), seg_hi);
   Acc acc = acc_zero();
-  reduce_entries<D, kHasVals, 4, true>(a, i0, i1, sub, acc);
+  // payloads of the lane's entries of the first batch and of the one after (an index past the end reads the last entry)
+  uint32_t bag[kLoads], pay_n[kLoads];
+  float x[kLoads];
 #pragma unroll
-  for (int m = G; m < kWave; m <<= 1) {
+  for (int q = 0; q < kLoads; ++q) {
+    bag[q] = a.pay_sorted[min(c_lo + q * kWave + lane, c_hi - 1)];
+    pay_n[q] = a.pay_sorted[min(c_lo + kBatch + q * kWave + lane, c_hi - 1)];
+    x[q] = 1.f;
+  }
+  if (kHasVals) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) acc.v[k] += __shfl_xor(acc.v[k], m, kWave);
+    for (int q = 0; q < kLoads; ++q) { x[q] = a.vals[bag[q]]; bag[q] = (uint32_t)a.bag_of[bag[q]]; }
+  }
+  for (int base = c_lo; base < c_hi; base += kBatch) {
+    float gf[kLoads], gl[kLoads], xc[kLoads];
+#pragma unroll
+    for (int q = 0; q < kLoads; ++q) {
+      const uint32_t b = bag[q] / (uint32_t)a.F;
+      l_bag[wave][q * kWave + lane] = make_uint2(bag[q] & a.take_pool.mask, b & a.take_sum.mask);
+      gf[q] = a.take_fm.base[b & a.take_fm.mask];
+      gl[q] = a.take_lr.base[b & a.take_lr.mask];
+      xc[q] = x[q];
+    }
+    // the next batch's, and the payloads of the one after that
+#pragma unroll
+    for (int q = 0; q < kLoads; ++q) {
+      bag[q] = pay_n[q];
+      if (kHasVals) { x[q] = a.vals[pay_n[q]]; bag[q] = (uint32_t)a.bag_of[pay_n[q]]; }
+      pay_n[q] = a.pay_sorted[min(base + 2 * kBatch + q * kWave + lane, c_hi - 1)];
+    }
+    const int cnt = min(kBatch, c_hi - base), per = (cnt + NG - 1) / NG;
+    const int mine = g * per, upto = min(mine + per, cnt);    // this lane group's run of the batch
+    for (int k0 = 0; k0 < per; k0 += U) {
+      float4 gp[U], as[U];
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const uint2 id = l_bag[wave][min(mine + k0 + k, cnt - 1)];
+        gp[k] = ld4(a.take_pool.base + (int64_t)id.x * D + sub * 4);
+        as[k] = ld4(a.take_sum.base + (int64_t)id.y * D + sub * 4);
+      }
+#pragma unroll
+      for (int k = 0; k < U; ++k)
+        asm volatile("" : "+v"(gp[k].x), "+v"(gp[k].y), "+v"(gp[k].z), "+v"(gp[k].w), "+v"(as[k].x), "+v"(as[k].y), "+v"(as[k].z),
+                     "+v"(as[k].w));
+      if (k0 == 0) {                                          // the scalars of the lane's own entries came in the same round trip
+#pragma unroll
+        for (int q = 0; q < kLoads; ++q) {
+          if (!a.g_fm) gf[q] = 0.f;
+          if (!a.g_lr) gl[q] = 0.f;
+          if (q * kWave + lane < cnt) {
+            const double xd = (double)xc[q];
+            acc.s2 += xd * (xd * (double)gf[q]);
+            acc.gw += xd * (double)gl[q];
+          }
+          l_x[wave][q * kWave + lane] = make_float2(xc[q], gf[q]);
+        }
+      }
+      float2 f[U];
+#pragma unroll
+      for (int k = 0; k < U; ++k) f[k] = l_x[wave][min(mine + k0 + k, cnt - 1)];
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        if (mine + k0 + k >= upto) continue;
+        const double xd = kHasVals ? (double)f[k].x : 1.0;
+        const double xg = xd * (double)f[k].y;
+        if (!a.g_pool) gp[k] = f4zero();
+        if (!a.g_fm) as[k] = f4zero();
+        acc.v[0] += xd * (double)gp[k].x + xg * (double)as[k].x;
+        acc.v[1] += xd * (double)gp[k].y + xg * (double)as[k].y;
+        acc.v[2] += xd * (double)gp[k].z + xg * (double)as[k].z;
+        acc.v[3] += xd * (double)gp[k].w + xg * (double)as[k].w;
+      }
+    }
+    __builtin_amdgcn_wave_barrier();                          // every lane has read its entries before the next batch's are left
+  }
+#pragma unroll
+  for (int m = 1; m < kWave; m <<= 1) {
     acc.s2 += __shfl_xor(acc.s2, m, kWave);
     acc.gw += __shfl_xor(acc.gw, m, kWave);
+    if (m < G) continue;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) acc.v[k] += __shfl_xor(acc.v[k], m, kWave);
   }
   if (g == 0) {
-    if (a.seg_off[u + 1] - a.seg_off[u] <= (1 << a.chunk_shift)) {
+    if (seg_hi - seg_lo <= (1 << a.chunk_shift)) {
       // the segment is this one chunk: the wave holds its whole sum and updates the row itself
       const int row = a.uniq_rows[u];
       apply_row<D>(a, u, row, sub, load_row<D>(a, row, sub), acc);
     } else {
-      double *p = a.partials + c * (D + 4);
+      double *p = a.partials + (int64_t)(c0 + k_seg) * (D + 4);
       *reinterpret_cast<double2 *>(p + sub * 4) = make_double2(acc.v[0], acc.v[1]);
       *reinterpret_cast<double2 *>(p + sub * 4 + 2) = make_double2(acc.v[2], acc.v[3]);
       if (sub == 0) *reinterpret_cast<double2 *>(p + D) = make_double2(acc.s2, acc.gw);

@@ -831,6 +831,18 @@ def test_merge_chunk_length_limits(oracle, des, n, D, lens, with_vals):
         p.close()
 
 
+@pytest.mark.parametrize("n,D,lens,with_vals", [
+    (20011, 4, [33, 255, 256, 257, 1153, 5001], True),       # steps of 256 entries in chunks of 128
+    (20011, 8, [63, 64, 65, 127, 1025, 4999], True),         # of 128
+    (20011, 128, [33, 34, 63, 64, 65, 129, 6017], False),    # of 64 for two lane groups
+    (20011, 256, [33, 63, 64, 65, 191, 193, 4097], True),    # of 64 for one
+    ((1 << 22) + 3, 8, [511, 513, 16385, 17000, 2000003], True),   # chunks of 512 on all dies: 33, 34 and 3907 of them
+])
+def test_merge_walk_of_a_chunk(oracle, des, n, D, lens, with_vals):
+    """The same with segments on the boundaries of the steps in which a wave walks a chunk, and of whole rounds of the dies."""
+    test_merge_chunk_length_limits(oracle, des, n, D, lens, with_vals)
+
+
 # ------------------------------------------------- one-workgroup sort and its neighbours ---------
 @pytest.mark.parametrize("n,B,F,capacity,vals", [
     (1, 1, 1, 1, False), (33, 3, 5, 300, True), (513, 40, 3, 1 << 16, False), (4095, 7, 9, 20000, True),
