@@ -4,7 +4,7 @@
 // every shard's sub-operator, so the backward pass needs no exchange.  Section 5: the merged
 // gradient of a weight is applied locally and the table row is updated.
 //
-// Steps: (1) expand the CSR batch to (row, bag) pairs, (2) stable radix sort by row, (3) mark
+// Steps: (1, 2) stable radix sort of the CSR batch's (row, bag) pairs by row, (3) mark
 // segment heads and compact them (ascending row order), (4) one lane group per segment of up to
 // kShortMax entries reduces its entries in registers and updates the row in the same kernel; longer
 // segments are cut into chunks of 512 or 128 entries, one wave each: a segment that is a single chunk
@@ -97,10 +97,13 @@ __device__ inline void st4_stream(float *p, float4 v) {
   v4f r; r.x = v.x; r.y = v.y; r.z = v.z; r.w = v.w;
   __builtin_nontemporal_store(r, reinterpret_cast<v4f *>(p));
 }
+constexpr int64_t kBagsPerEntry = 4;
 __device__ inline float4 f4zero() { return make_float4(0.f, 0.f, 0.f, 0.f); }
 __device__ inline float4 f4add(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
 
-// (1) sort key = row (or `missing`), payload = bag (or entry index with vals).  A workgroup takes
+// (1) The first sorting pass takes rows and offsets as they are, as long as there are at most kBagsPerEntry bags per entry: its workgroups
+// walk the bags of a tile of entries (some 16 steps each at that ratio), which without a bound could be all of an almost empty
+// batch's.  Beyond that this kernel writes the pairs: sort key = row (or `missing`), payload = bag (or entry index with vals).  A workgroup takes
 // kBlock consecutive bags, i.e. one contiguous range of entries, stages their offsets in LDS and
 // walks the entries with consecutive threads (coalesced reads and writes); the bag of an entry
 // is found by binary search in the staged offsets.
@@ -1157,7 +1160,9 @@ int sort_stage(des_table *t, BwdArgs &a, const Layout &L, hipStream_t s) {
     else hipLaunchKernelGGL(k_sort_small<false>, dim3(1), dim3(kSmallBlock), 0, s, a, pay_a, bits);
     return 0;
   }
-  {
+  const SortCsr csr{a.rows, a.offsets, a.nbags, a.missing, (uint32_t *)(ws + L.first_pay), a.vals ? a.bag_of : nullptr};
+  const bool from_csr = a.nbags <= kBagsPerEntry * n;
+  if (!from_csr) {
     ProfScope ps(KID_EXPAND, s);
     const dim3 grid(blocks_for(a.nbags, 1 << 20)), block(kBlock);     // one workgroup per kBlock bags
     if (a.vals) hipLaunchKernelGGL(k_expand<true>, grid, block, 0, s, a, key_a, pay_a);
@@ -1167,7 +1172,8 @@ int sort_stage(des_table *t, BwdArgs &a, const Layout &L, hipStream_t s) {
   // what the later steps fill serves as scratch here: the unique rows for the digits' totals, the chunk sums, with the sort
   // scratch right behind them, for the finer tile counts of a small batch (2 bytes per entry; the chunk sums alone are
   // 8*(D+4)*(1/33 + 1/512) >= 2.06 bytes per entry)
-  const int side = radix_sort_u32_pairs(sb, n, bits, ws + L.sort_scratch, ws + L.partials, (uint32_t *)(ws + L.uniq_rows), s);
+  const int side = radix_sort_u32_pairs(sb, n, bits, ws + L.sort_scratch, ws + L.partials, (uint32_t *)(ws + L.uniq_rows),
+                                        from_csr ? &csr : nullptr, s);
   set_sorted_keys(a, (uint32_t *)(ws + (side ? L.key_b : L.key_a)));
   a.pay_sorted = (uint32_t *)(ws + (side ? L.pay_b : L.pay_a));
   {

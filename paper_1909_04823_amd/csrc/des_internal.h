@@ -90,8 +90,18 @@ constexpr int kSortTotals = 512;
 constexpr int64_t kFewSort = 1 << 20;
 size_t few_sort_scratch_bytes(int64_t n);
 struct SortBuffers { void *keys_a, *keys_b; uint32_t *pay_a, *pay_b; };
+// csr, if given, is what the first pass sorts instead of the *_a buffers, whose contents then do not matter: the entries of a CSR
+// batch.  Key = row (negative: `missing`), payload = bag, or, with bag_of, the entry's index, and bag_of[entry] = bag.
+struct SortCsr {
+  const int32_t *rows, *offsets;   // offsets[nbags + 1], ascending from 0 to n
+  int64_t nbags;
+  uint32_t missing;
+  uint32_t *tile_bag;              // scratch: csr_scratch_bytes(n)
+  int32_t *bag_of;
+};
+size_t csr_scratch_bytes(int64_t n);
 int radix_sort_u32_pairs(SortBuffers buf, int64_t n, int bits, void *scratch, void *few_scratch, uint32_t *totals,
-                         hipStream_t s);
+                         const SortCsr *csr, hipStream_t s);
 
 }  // namespace des
 

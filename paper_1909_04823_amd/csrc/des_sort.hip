@@ -2,6 +2,7 @@
 //
 // Both are plain multi-kernel primitives without inter-workgroup waiting: every kernel's
 // workgroups are independent, so every wave reaches its exit whatever the dispatch order.
+#include <type_traits>
 #include "des_internal.h"
 
 namespace des {
@@ -151,9 +152,12 @@ void exclusive_scan(T *data, int64_t n, T *total_out, void *scratch, hipStream_t
 // equal digits per wave, and LDS adds to equal addresses run one after the other.  Three passes over 8.2e6 keys, Zipf(1.2):
 // 73 -> 36 us with four copies (82 with counts in one row per digit); 1.05e8 keys, half of them uniform: 516 -> 341 us.
 constexpr int kCopies = 4;
-template <typename KeyT, int kItems>
+__device__ inline uint32_t csr_key(const SortCsr &csr, uint32_t row) { return (int32_t)row >= 0 ? row : csr.missing; }
+// kCsr: the keys are the rows of a CSR batch, and the workgroups also note the bag of every tile's first entry, each for a share of
+// the bags, and behind them the bag of the last entry.
+template <typename KeyT, int kItems, bool kCsr>
 __global__ __launch_bounds__(kBlock) void k_radix_hist(const KeyT *__restrict__ keys, int64_t n, int shift, int bits,
-                                                        uint32_t *__restrict__ hist) {
+                                                        uint32_t *__restrict__ hist, const SortCsr csr) {
   __shared__ uint4 cnt[kMaxRadix];
   static_assert(kCopies == 4, "one uint4 per digit");
   const int radix = 1 << bits;
@@ -164,7 +168,16 @@ __global__ __launch_bounds__(kBlock) void k_radix_hist(const KeyT *__restrict__ 
 #pragma unroll
   for (int i = 0; i < kItems; ++i) {
     const int64_t idx = base + (int64_t)i * kBlock + threadIdx.x;
-    key[i] = idx < n ? keys[idx] : (KeyT)0;
+    key[i] = idx < n ? (kCsr ? (KeyT)csr.rows[idx] : keys[idx]) : (KeyT)0;
+  }
+  if (kCsr) {
+    constexpr int kTile = kBlock * kItems;
+    const int64_t share = (csr.nbags + gridDim.x - 1) / gridDim.x, b1 = min(csr.nbags, (blockIdx.x + 1) * share);
+    for (int64_t b = blockIdx.x * share + threadIdx.x; b < b1; b += kBlock) {
+      const int64_t e0 = csr.offsets[b], e1 = csr.offsets[b + 1];
+      for (int64_t t = (e0 + kTile - 1) / kTile; t * kTile < min(e1, n); ++t) csr.tile_bag[t] = (uint32_t)b;
+      if (e0 < n && e1 >= n) csr.tile_bag[gridDim.x] = (uint32_t)b;
+    }
   }
   for (int d = threadIdx.x; d < radix; d += kBlock) cnt[d] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
@@ -172,6 +185,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_hist(const KeyT *__restrict__ 
 #pragma unroll
   for (int i = 0; i < kItems; ++i) {
     const int64_t idx = base + (int64_t)i * kBlock + threadIdx.x;
+    if (kCsr) key[i] = csr_key(csr, key[i]);
     if (idx < n) atomicAdd(&counters[((uint32_t)(key[i] >> shift) & mask) * kCopies + copy], 1u);
   }
   __syncthreads();
@@ -276,14 +290,22 @@ __device__ inline unsigned long long same_digit(uint32_t d, int bits, unsigned l
 // 8.2e6 121 -> 103; the tiles of up to kFewSort items all run at once, where it gives nothing: 29.8 and 32.1 us at 1.0e6).
 // kBits: width of the digit where it is known here, else 0 (unrolled ballots: 145 -> 121 us at 8.2e6, the passes of smaller
 // batches 32.6 -> 29.8 us at 1.0e6).
-template <typename KeyT, bool kHasPayload, int kItems, int kBits>
-__global__ __launch_bounds__(kBlock) void k_radix_scatter(const KeyT *__restrict__ keys_in,
+// kCsr (first pass over a CSR batch): an entry's bag is the one that the last bag start up to it belongs to.  The tile's starts are
+// marked in LDS, as a bit per entry and the bag's number where the sorted keys come later; a wave holds the words of bits, one
+// per lane, with the last start before each of them.  Without the pass that wrote (row, bag) pairs first the kernels up to here
+// take, at 3.7e5 / 1.0e6 / 8.2e6 / 1.05e8 entries, 33 -> 29, 48 -> 37, 169 -> 145 and 2204 -> 1863 us.  (Three waves per SIMD instead
+// of four, which spill 16 bytes: 46 against 43 us at 8.0e6.)
+template <typename KeyT, bool kHasPayload, int kItems, int kBits, bool kCsr>
+__global__ __launch_bounds__(kBlock, kItems == kSortItems ? 4 : 8) void k_radix_scatter(const KeyT *__restrict__ keys_in,
                                                            const uint32_t *__restrict__ pay_in,
                                                            KeyT *__restrict__ keys_out, uint32_t *__restrict__ pay_out,
                                                            int64_t n, int shift, int any_bits,
                                                            const uint32_t *__restrict__ offsets,
-                                                           const uint32_t *__restrict__ totals) {
+                                                           const uint32_t *__restrict__ totals, const SortCsr csr) {
   constexpr int kTile = kBlock * kItems;
+  constexpr int kWords = kTile / kWave;
+  static_assert(!kCsr || (kHasPayload && kWords <= kWave && kItems <= kWave), "a lane per word of starts");
+  __shared__ uint32_t starts[kCsr ? kWords * 2 : 1];    // bit per entry: a bag starts there
   __shared__ uint32_t cnt[kWavesPerBlock][kMaxRadix];   // per wave and digit: count, then start inside the digit's run
   __shared__ uint32_t dig_base[kMaxRadix];              // first sorted index of the digit inside the tile
   __shared__ uint32_t gofs[kMaxRadix];                  // where the tile's run of the digit starts in the output
@@ -307,9 +329,10 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KeyT *__restrict
   for (int r = 0; r < kItems; ++r) {
     const int64_t idx = wbase + r * kWave + lane;
     const bool live = idx < n;
-    key[r] = live ? keys_in[idx] : (KeyT)0;
-    if (kHasPayload) pay[r] = live ? pay_in[idx] : 0u;
+    key[r] = live ? (kCsr ? (KeyT)csr.rows[idx] : keys_in[idx]) : (KeyT)0;
+    if (kHasPayload && !kCsr) pay[r] = live ? pay_in[idx] : 0u;
   }
+  if (kCsr && threadIdx.x < kWords * 2) starts[threadIdx.x] = 0u;
   // two digits per thread (kMaxRadix <= 2 * kBlock): the tile's offset inside the digit and the digit's total
   static_assert(kMaxRadix <= 2 * kBlock, "two digits per thread");
   uint32_t in_digit[2] = {0u, 0u};
@@ -325,11 +348,25 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KeyT *__restrict
     }
   }
   __syncthreads();
+  uint32_t *bag_at = reinterpret_cast<uint32_t *>(skey);  // bag that starts at the entry
+  uint32_t first_bag = 0;                                // of the tile's first entry
+  if (kCsr) {
+    first_bag = csr.tile_bag[tile_no];
+    const uint32_t last_bag = min(csr.tile_bag[tile_no + 1], (uint32_t)csr.nbags - 1u);
+    for (uint32_t b = first_bag + 1 + threadIdx.x; b <= last_bag; b += kBlock) {
+      const int64_t at = csr.offsets[b] - tile;
+      if (at >= 0 && at < tile_n && csr.offsets[b + 1] - tile > at) {
+        atomicOr(&starts[at >> 5], 1u << (at & 31));
+        bag_at[at] = b;
+      }
+    }
+  }
 
 #pragma unroll
   for (int r = 0; r < kItems; ++r) {
     const int64_t idx = wbase + r * kWave + lane;
     const bool live = idx < n;
+    if (kCsr) key[r] = csr_key(csr, key[r]);
     const uint32_t d = (uint32_t)(key[r] >> shift) & mask;
     const unsigned long long peers = same_digit<kBits>(d, bits, __ballot(live));
     const uint32_t before = (uint32_t)__popcll(peers & lane_lt);
@@ -343,6 +380,34 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KeyT *__restrict
     rank[r] = prev + before;
   }
   __syncthreads();
+  if (kCsr) {                                           // done with the starts before the barriers ahead of the sorted keys
+    uint32_t lo = 0, hi = 0;
+    if (lane < kWords) { lo = starts[lane * 2]; hi = starts[lane * 2 + 1]; }
+    int last = hi ? lane * kWave + 63 - __clz(hi) : lo ? lane * kWave + 31 - __clz(lo) : -1;
+#pragma unroll
+    for (int off = 1; off < kWords; off <<= 1) {
+      const int o = __shfl_up(last, off, kWave);
+      if (lane >= off) last = max(last, o);
+    }
+    last = __shfl_up(last, 1, kWave);
+    if (lane == 0) last = -1;
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+      const int word = wave * kItems + r;
+      const unsigned long long bits_r = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane(hi, word) << 32) |
+                                        (uint32_t)__builtin_amdgcn_readlane(lo, word);
+      const unsigned long long upto = bits_r & (lane_lt | 1ull << lane);
+      const int before = __builtin_amdgcn_readlane(last, word);  // not in a branch: the lane read from has to be active
+      const int at = upto ? word * kWave + 63 - __clzll(upto) : before;
+      const uint32_t bag = at >= 0 ? bag_at[at] : first_bag;
+      const int64_t idx = wbase + r * kWave + lane;
+      pay[r] = bag;
+      if (csr.bag_of) {
+        pay[r] = (uint32_t)idx;
+        if (idx < n) csr.bag_of[idx] = (int32_t)bag;
+      }
+    }
+  }
   // per digit: exclusive prefix over the waves; then one exclusive prefix over the digits of both the tile's counts (low
   // half) and the array's (high half): where the digit starts in the tile and where in the output
 #pragma unroll
@@ -415,8 +480,8 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KeyT *__restrict
 inline int64_t sort_blocks(int64_t n) { return (n + kSortTile - 1) / kSortTile; }
 
 template <typename KeyT, bool kHasPayload, int kItems>
-int radix_sort(SortBuffers buf, int64_t n, int bits, uint32_t *hist, uint32_t *stretch_sums, uint32_t *totals, hipStream_t s,
-               int kid_hist, int kid_scan, int kid_scatter) {
+int radix_sort(SortBuffers buf, int64_t n, int bits, uint32_t *hist, uint32_t *stretch_sums, uint32_t *totals,
+               const SortCsr *csr, hipStream_t s, int kid_hist, int kid_scan, int kid_scatter) {
   if (n <= 0 || bits <= 0) return 0;
   const int nblocks = (int)((n + kBlock * kItems - 1) / (kBlock * kItems));
   const int widest = n >= kSortTotals ? kMaxDigitBits : kFewItemsBits;
@@ -428,9 +493,11 @@ int radix_sort(SortBuffers buf, int64_t n, int bits, uint32_t *hist, uint32_t *s
   for (int p = 0; p < npass; ++p) {
     const int shift = p * per;
     const int b = (bits - shift) < per ? (bits - shift) : per;
+    const bool from_csr = csr && p == 0;
     {
       ProfScope ps(kid_hist, s);
-      hipLaunchKernelGGL((k_radix_hist<KeyT, kItems>), dim3(nblocks), dim3(kBlock), 0, s, kin, n, shift, b, hist);
+      if (from_csr) hipLaunchKernelGGL((k_radix_hist<KeyT, kItems, true>), dim3(nblocks), dim3(kBlock), 0, s, kin, n, shift, b, hist, *csr);
+      else hipLaunchKernelGGL((k_radix_hist<KeyT, kItems, false>), dim3(nblocks), dim3(kBlock), 0, s, kin, n, shift, b, hist, SortCsr{});
     }
     {
       ProfScope ps(kid_scan, s);
@@ -442,12 +509,17 @@ int radix_sort(SortBuffers buf, int64_t n, int bits, uint32_t *hist, uint32_t *s
     {
       ProfScope ps(kid_scatter, s);
       const auto scatter = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(kBlock), 0, s, kin, pin, kout, pout, n, shift, b, hist, totals);
+        hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(kBlock), 0, s, kin, pin, kout, pout, n, shift, b, hist, totals,
+                           from_csr ? *csr : SortCsr{});
       };
-      if (b == 9) scatter(k_radix_scatter<KeyT, kHasPayload, kItems, 9>);
-      else if (b == 8) scatter(k_radix_scatter<KeyT, kHasPayload, kItems, 8>);
-      else if (b == 7) scatter(k_radix_scatter<KeyT, kHasPayload, kItems, 7>);
-      else scatter(k_radix_scatter<KeyT, kHasPayload, kItems, 0>);
+      const auto of_width = [&](auto first) {
+        constexpr bool kCsr = decltype(first)::value;
+        if (b == 9) scatter(k_radix_scatter<KeyT, kHasPayload, kItems, 9, kCsr>);
+        else if (b == 8) scatter(k_radix_scatter<KeyT, kHasPayload, kItems, 8, kCsr>);
+        else if (b == 7) scatter(k_radix_scatter<KeyT, kHasPayload, kItems, 7, kCsr>);
+        else scatter(k_radix_scatter<KeyT, kHasPayload, kItems, 0, kCsr>);
+      };
+      if (from_csr) of_width(std::true_type{}); else of_width(std::false_type{});
     }
     KeyT *tk = kin; kin = kout; kout = tk;
     uint32_t *tp = pin; pin = pout; pout = tp;
@@ -481,19 +553,21 @@ void exclusive_scan_u64(unsigned long long *data, int64_t n, unsigned long long 
   exclusive_scan<unsigned long long>(data, n, total_out, scratch, s);
 }
 
+size_t csr_scratch_bytes(int64_t n) { return (size_t)((n + kFewSortTile - 1) / kFewSortTile + 1) * sizeof(uint32_t); }
+
 size_t few_sort_scratch_bytes(int64_t n) {
   return (size_t)kMaxRadix * sizeof(uint32_t) * (size_t)((n + kFewSortTile - 1) / kFewSortTile);
 }
 
 int radix_sort_u32_pairs(SortBuffers buf, int64_t n, int bits, void *scratch, void *few_scratch, uint32_t *totals,
-                         hipStream_t s) {
+                         const SortCsr *csr, hipStream_t s) {
   static_assert(kFewSort <= (int64_t)kScanStretch * kFewSortTile, "one stretch: no sums of stretches");
   if (n <= kFewSort)
-    return radix_sort<uint32_t, true, kFewSortItems>(buf, n, bits, (uint32_t *)few_scratch, nullptr, totals, s, KID_SORT_HIST,
+    return radix_sort<uint32_t, true, kFewSortItems>(buf, n, bits, (uint32_t *)few_scratch, nullptr, totals, csr, s, KID_SORT_HIST,
                                                      KID_SORT_SCAN, KID_SORT_SCATTER);
   // the sums of all stretches but the last lie behind the counts (see sort_scratch_bytes)
   uint32_t *stretch_sums = (uint32_t *)((char *)scratch + align_up((size_t)kMaxRadix * sort_blocks(n) * sizeof(uint32_t), 256));
-  return radix_sort<uint32_t, true, kSortItems>(buf, n, bits, (uint32_t *)scratch, stretch_sums, totals, s, KID_SORT_HIST,
+  return radix_sort<uint32_t, true, kSortItems>(buf, n, bits, (uint32_t *)scratch, stretch_sums, totals, csr, s, KID_SORT_HIST,
                                                 KID_SORT_SCAN, KID_SORT_SCATTER);
 }
 

@@ -831,6 +831,37 @@ def test_merge_chunk_length_limits(oracle, des, n, D, lens, with_vals):
         p.close()
 
 
+@pytest.mark.parametrize("n,nbags,with_vals", [
+    (4097, 4, False),                       # bags over several tiles of 1024 entries, one entry in the last tile
+    (5120, 20480, True),                    # four bags per entry: the last ratio whose bags the sort finds itself
+    (5120, 20484, True),                    # one bag of every field more: pairs are written first
+    (1 << 20, 300000, True),                # the last size with tiles of 1024
+    ((1 << 20) + 1, 2000000, False),        # the first with tiles of 4096, most bags empty
+    ((1 << 20) + 4095, 64, True),           # bags over several of them
+])
+def test_merge_finds_the_bags(oracle, des, n, nbags, with_vals):
+    """Merged sums and counts where the bags' sizes differ most from the usual ones: empty ones and ones longer than a tile."""
+    import torch
+    rng = np.random.default_rng(nbags)
+    F, D = 4, 4
+    keys = synth.scramble64(rng.zipf(1.3, n).astype(np.uint64) % np.uint64(5000) + np.uint64(1))
+    cuts = np.sort(rng.integers(0, n + 1, size=nbags - 1))
+    cuts[:2], cuts[-1] = 0, n                               # empty ones at both ends
+    offsets = np.concatenate([[0], np.sort(cuts), [n]]).astype(np.int32)
+    vals = rng.uniform(0.25, 2.0, n).astype(np.float32) if with_vals else None
+    batch = synth.Batch(nbags // F, F, keys, offsets, vals)
+    p = Pair(oracle, des, D, 5003, 4, 0, des.OPT_NONE, seed=5, init_scale=0.1, max_n=n)
+    try:
+        p.find(batch, insert=True)
+        B = nbags // F
+        g_lr = (1e-3 * rng.standard_normal(B)).astype(np.float32)
+        g_pool = (1e-3 * rng.standard_normal((B, F, D))).astype(np.float32)
+        ref = p.backward(batch, g_lr, None, None, g_pool, opt=des.OPT_NONE)
+        assert int(ref["counts"].sum()) == n
+    finally:
+        p.close()
+
+
 @pytest.mark.parametrize("n,D,lens,with_vals", [
     (20011, 4, [33, 255, 256, 257, 1153, 5001], True),       # steps of 256 entries in chunks of 128
     (20011, 8, [63, 64, 65, 127, 1025, 4999], True),         # of 128
