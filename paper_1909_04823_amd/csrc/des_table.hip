@@ -56,6 +56,8 @@ __global__ __launch_bounds__(kBlock) void k_probe(Slot *__restrict__ slots, uint
   // after a sticky error the table no longer grows: the call degrades to a pure lookup, so
   // rows[] is still fully written with valid rows or kRowAbsent
   const bool can_insert = kInsert && ctrl->status == 0;
+  // the row count that the passes after this one number from: the last of them may then move it on
+  if (kInsert && blockIdx.x == 0 && threadIdx.x == 0) ctrl->base_rows = ctrl->n_rows;
   const int64_t stride = (int64_t)gridDim.x * kBlock;
   for (int64_t tile = (int64_t)blockIdx.x * kBlock; tile < n; tile += stride) {
     const int64_t e = tile + threadIdx.x;
@@ -102,7 +104,7 @@ __global__ __launch_bounds__(kBlock) void k_probe(Slot *__restrict__ slots, uint
       atomicAdd(&ctrl->bad_keys, 1);                 // the reserved key is nobody's ID: absent, counted, nothing else is held up
     }
     if (e < n) rows[e] = out;
-    if (kInsert && pending_bits) {                   // 64 consecutive entries per wave
+    if (kInsert) {                                   // 64 consecutive entries per wave
       const unsigned long long bits = __ballot(pending);
       if ((threadIdx.x & (kWave - 1)) == 0 && e < n) pending_bits[e / kWave] = bits;
     }
@@ -159,14 +161,12 @@ __device__ inline void load_flag_rows(const int32_t *__restrict__ rows, int64_t 
   }
 }
 
-// Pass B1: per tile, how many entries open a new row (beside the tile's pending bit).  The first workgroup also notes the row
-// count of the table, which the passes after it number from: the last of them may then move it on.
+// Pass B1: per tile, how many entries open a new row (beside the tile's pending bit).
 __global__ __launch_bounds__(kBlock) void k_new_count(const Slot *__restrict__ slots, int32_t *__restrict__ rows,
                                                        const uint32_t *__restrict__ slot_of, int64_t n,
                                                        const unsigned long long *__restrict__ pending_bits,
-                                                       uint32_t *__restrict__ tile_sums, Ctrl *__restrict__ ctrl) {
+                                                       uint32_t *__restrict__ tile_sums) {
   __shared__ uint32_t lds[kWavesPerBlock];
-  if (blockIdx.x == 0 && threadIdx.x == 0) ctrl->base_rows = ctrl->n_rows;
   const int64_t word = (int64_t)blockIdx.x * (kFlagTile / kWave) + threadIdx.x;
   const bool some = threadIdx.x < kFlagTile / kWave && word * kWave < n && pending_bits[word] != 0;
   if (!__syncthreads_or(some)) {
@@ -271,115 +271,33 @@ __global__ __launch_bounds__(kBlock) void k_new_assign(Slot *__restrict__ slots,
   }
 }
 
-// Passes B and D for a batch of up to kSmallInsert entries, in one workgroup: counts, numbers, checks the capacity, tells the
-// slots, moves the row count on and patches the entries.  Three launches of about 4 us in one.
-__global__ __launch_bounds__(kSmallInsertBlock) void k_new_small(Slot *__restrict__ slots, int32_t *__restrict__ rows,
-                                                                  const uint32_t *__restrict__ slot_of,
-                                                                  const uint64_t *__restrict__ keys, int n,
-                                                                  Ctrl *__restrict__ ctrl, uint64_t *__restrict__ row_keys,
-                                                                  int32_t *__restrict__ first_idx, int64_t capacity) {
-  constexpr int kItems = kSmallInsert / kSmallInsertBlock, kWaves = kSmallInsertBlock / kWave;
-  __shared__ uint32_t lds[kWaves];
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, base = threadIdx.x * kItems;
-  const int status = ctrl->status;
-  const long long n_rows = ctrl->n_rows;
-  int32_t r[kItems];
-  uint32_t cnt = 0;
-  bool flag[kItems];
-#pragma unroll
-  for (int i = 0; i < kItems; ++i) {
-    r[i] = base + i < n ? rows[base + i] : kRowAbsent;
-    flag[i] = opens_row(slots, r[i], slot_of, base + i);
-    cnt += flag[i] ? 1u : 0u;
-  }
-  const uint32_t inc = wave_incl_scan_u32(cnt);
-  if (lane == kWave - 1) lds[wave] = inc;
-  __syncthreads();                                    // also: everybody has read the control block
-  uint32_t rank = inc - cnt, total = 0;
-#pragma unroll
-  for (int w = 0; w < kWaves; ++w) {
-    const uint32_t x = lds[w];
-    if (w < wave) rank += x;
-    total += x;
-  }
-  const bool full = n_rows + (long long)total > capacity;
-  if (threadIdx.x == 0) {
-    ctrl->base_rows = n_rows;
-    ctrl->n_new = total;
-    if (full) set_status(ctrl, DES_ERR_FULL);
-    else if (status == 0) ctrl->n_rows = n_rows + (long long)total;
-  }
-  if (!full && status == 0) {
-#pragma unroll
-    for (int i = 0; i < kItems; ++i) {
-      if (flag[i]) {
-        const long long row = n_rows + rank;
-        slots[slot_of[base + i]].row = (int32_t)row;
-        row_keys[row] = keys[base + i];
-        first_idx[rank] = base + i;
-        ++rank;
-      }
-    }
-  }
-  __syncthreads();                                    // the slots know their rows
-#pragma unroll
-  for (int i = 0; i < kItems; ++i) {
-    if (r[i] != kRowPending) continue;
-    const int32_t row = __hip_atomic_load(&slots[slot_of[base + i]].row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    rows[base + i] = row >= 0 ? row : kRowAbsent;     // negative only after a failed call
-  }
-}
-
-// Last pass.  Entries that saw a pending key read the row from the slot they remembered (kPatch; tiles without such
-// entries are skipped).  Rows created by this call get initialiser weights, or (kValues) the values of their first
-// occurrence, and zero optimizer state: one thread per group of four columns, or per column, then one per row for the LR weight.
-// The initialiser is two hashes per column, of which the one that does not depend on the key is kept in LDS: the pass was bound by
-// hashing and by the division that turned a thread's number into row and column.  1.2e6 new rows of 32 columns with
-// Adagrad state: 119 -> 87 us.
 struct NewRowArgs {
   int D;
   uint64_t seed;
   float width;
+  const uint64_t *keys;                               // the batch's, or row_keys in their place: the new rows' (filled by an earlier launch)
   const uint64_t *row_keys;
   const float *values;
-  const int32_t *first_idx;
   float *emb, *w, *acc_emb, *acc_w, *acc2_emb, *acc2_w;
   int64_t capacity;
 };
 
-template <bool kPatch, bool kValues>
-__global__ __launch_bounds__(kBlock) void k_finish(const Slot *__restrict__ slots, int64_t n, int32_t *__restrict__ rows,
-                                                    const uint32_t *__restrict__ slot_of,
-                                                    const uint32_t *__restrict__ tile_sums,
-                                                    const Ctrl *__restrict__ ctrl, const NewRowArgs a) {
-  __shared__ uint64_t column_hash[kValues ? 1 : 256 + 1];
-  if (kPatch) {
-    const int64_t nb = (n + kFlagTile - 1) / kFlagTile;
-    for (int64_t t = blockIdx.x; t < nb; t += gridDim.x) {
-      if (!(tile_sums[t] & kPendingBit)) continue;    // uniform
-      int32_t r[kFlagItems];
-      const int64_t base = t * kFlagTile + threadIdx.x;
-#pragma unroll
-      for (int i = 0; i < kFlagItems; ++i) r[i] = base + i * kBlock < n ? rows[base + i * kBlock] : kRowAbsent;
-#pragma unroll
-      for (int i = 0; i < kFlagItems; ++i) {
-        if (r[i] > kRowPending) continue;             // neither pending nor kRowOpens
-        const int32_t row = slots[slot_of[base + i * kBlock]].row;
-        rows[base + i * kBlock] = row >= 0 ? row : kRowAbsent;     // negative only after a failed call
-      }
-    }
-  }
-  if (ctrl->status != 0) return;
-  const long long n_new = ctrl->n_new, n_rows = ctrl->base_rows;
-  if (n_rows + n_new > a.capacity) return;
+// Rows n_rows .. n_rows + n_new - 1 get initialiser weights, or (kValues) the values of their first occurrences, the entries first[j],
+// and zero optimizer state: one thread per group of four columns, or per column, then one per row for the LR weight.
+// The initialiser is two hashes per column, of which the one that does not depend on the key is kept in LDS: the pass was bound by
+// hashing and by the division that turned a thread's number into row and column.  1.2e6 new rows of 32 columns with
+// Adagrad state: 119 -> 87 us.
+template <bool kValues>
+__device__ inline void fill_new_rows(const NewRowArgs &a, long long n_rows, long long n_new, const int32_t *first,
+                                     uint64_t (&column_hash)[kValues ? 1 : 256 + 1]) {
   const int D = a.D;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x, thread = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (kValues) {
+  if constexpr (kValues) {
     const int per_row = D + 1;
     for (int64_t i = thread; i < n_new * per_row; i += stride) {
       const int64_t j = i / per_row, row = n_rows + j;
       const int c = (int)(i % per_row);
-      const float val = a.values[(int64_t)a.first_idx[j] * per_row + c];
+      const float val = a.values[(int64_t)first[j] * per_row + c];
       if (c < D) {
         a.emb[row * D + c] = val;
         if (a.acc_emb) a.acc_emb[row * D + c] = 0.f;
@@ -390,30 +308,135 @@ __global__ __launch_bounds__(kBlock) void k_finish(const Slot *__restrict__ slot
         if (a.acc2_w) a.acc2_w[row] = 0.f;
       }
     }
+  } else {
+    const auto initial = [&](uint64_t key, int c) {
+      const uint64_t h = mix64(key ^ column_hash[c]);
+      const float u = (float)(h >> 40) * (1.0f / 16777216.0f);
+      return __fmul_rn(__fsub_rn(u, 0.5f), a.width);
+    };
+    for (int c = threadIdx.x; c <= D; c += blockDim.x) column_hash[c] = mix64(a.seed + (uint64_t)c);
+    __syncthreads();
+    const int shift = 31 - __clz(D / 4);              // D is a power of two
+    for (int64_t i = thread; i < n_new << shift; i += stride) {
+      const int64_t j = i >> shift, row = n_rows + j;
+      const int c = (int)(i & (D / 4 - 1)) * 4;
+      const uint64_t key = a.row_keys ? a.row_keys[row] : a.keys[first[j]];
+      *reinterpret_cast<float4 *>(&a.emb[row * D + c]) = make_float4(initial(key, c), initial(key, c + 1), initial(key, c + 2), initial(key, c + 3));
+      if (a.acc_emb) *reinterpret_cast<float4 *>(&a.acc_emb[row * D + c]) = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (a.acc2_emb) *reinterpret_cast<float4 *>(&a.acc2_emb[row * D + c]) = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    for (int64_t j = thread; j < n_new; j += stride) {
+      const int64_t row = n_rows + j;
+      a.w[row] = initial(a.row_keys ? a.row_keys[row] : a.keys[first[j]], D);
+      if (a.acc_w) a.acc_w[row] = 0.f;
+      if (a.acc2_w) a.acc2_w[row] = 0.f;
+    }
+  }
+}
+
+// Passes B and D for a batch of up to kSmallInsert entries, in one launch of a few large workgroups.  Each of them counts and numbers
+// all new rows by itself, from what the probe left and none of them changes (pending bits, slots' first occurrences, the row count
+// before the call), and fills its share; the first one also tells the slots and entries and moves the row count on.
+// (One workgroup that numbers and a launch that fills: 4.0 and 2.0 us where no entry is new.)
+template <bool kValues>
+__global__ __launch_bounds__(kSmallInsertBlock) void k_new_small(Slot *__restrict__ slots, int32_t *__restrict__ rows,
+                                                                  const uint32_t *__restrict__ slot_of,
+                                                                  const unsigned long long *__restrict__ pending_bits, int n,
+                                                                  Ctrl *__restrict__ ctrl, uint64_t *__restrict__ row_keys,
+                                                                  const NewRowArgs a) {
+  constexpr int kItems = kSmallInsert / kSmallInsertBlock, kWaves = kSmallInsertBlock / kWave;
+  static_assert(kWave % kItems == 0, "a thread's entries share a word of pending bits");
+  __shared__ uint32_t lds[kWaves];
+  __shared__ int32_t first[kSmallInsert];             // entry that opened the j-th new row
+  __shared__ uint64_t column_hash[kValues ? 1 : 256 + 1];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, base = threadIdx.x * kItems;
+  const bool publishes = blockIdx.x == 0;
+  const int status = ctrl->status;                    // the first workgroup may set "full" meanwhile, which the others find as well
+  const long long n_rows = ctrl->base_rows;
+  const uint32_t mine = base < n ? (uint32_t)(pending_bits[base / kWave] >> (base % kWave)) & ((1u << kItems) - 1u) : 0u;
+  if (!__syncthreads_or(mine != 0)) {
+    if (publishes && threadIdx.x == 0) ctrl->n_new = 0;
     return;
   }
-  if (n_new == 0) return;                             // uniform over the grid
-  const auto initial = [&](uint64_t key, int c) {
-    const uint64_t h = mix64(key ^ column_hash[c]);
-    const float u = (float)(h >> 40) * (1.0f / 16777216.0f);
-    return __fmul_rn(__fsub_rn(u, 0.5f), a.width);
-  };
-  for (int c = threadIdx.x; c <= D; c += kBlock) column_hash[c] = mix64(a.seed + (uint64_t)c);
+  uint32_t at[kItems], cnt = 0;
+  bool flag[kItems];
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) at[i] = mine >> i & 1u ? slot_of[base + i] : 0u;
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) {
+    flag[i] = (mine >> i & 1u) && slots[at[i]].first == (uint32_t)(base + i);
+    cnt += flag[i] ? 1u : 0u;
+  }
+  const uint32_t inc = wave_incl_scan_u32(cnt);
+  if (lane == kWave - 1) lds[wave] = inc;
   __syncthreads();
-  const int shift = 31 - __clz(D / 4);                // D is a power of two
-  for (int64_t i = thread; i < n_new << shift; i += stride) {
-    const int64_t row = n_rows + (i >> shift);
-    const int c = (int)(i & (D / 4 - 1)) * 4;
-    const uint64_t key = a.row_keys[row];
-    *reinterpret_cast<float4 *>(&a.emb[row * D + c]) = make_float4(initial(key, c), initial(key, c + 1), initial(key, c + 2), initial(key, c + 3));
-    if (a.acc_emb) *reinterpret_cast<float4 *>(&a.acc_emb[row * D + c]) = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (a.acc2_emb) *reinterpret_cast<float4 *>(&a.acc2_emb[row * D + c]) = make_float4(0.f, 0.f, 0.f, 0.f);
+  uint32_t rank = inc - cnt, total = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    const uint32_t x = lds[w];
+    if (w < wave) rank += x;
+    total += x;
   }
-  for (int64_t row = n_rows + thread; row < n_rows + n_new; row += stride) {
-    a.w[row] = initial(a.row_keys[row], D);
-    if (a.acc_w) a.acc_w[row] = 0.f;
-    if (a.acc2_w) a.acc2_w[row] = 0.f;
+  const bool full = n_rows + (long long)total > a.capacity;
+  if (publishes && threadIdx.x == 0) {
+    ctrl->n_new = total;
+    if (full) set_status(ctrl, DES_ERR_FULL);
+    else if (status == 0) ctrl->n_rows = n_rows + (long long)total;
   }
+  const bool grow = !full && status == 0;
+  if (grow) {
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+      if (flag[i]) {
+        first[rank] = base + i;
+        if (publishes) {
+          const long long row = n_rows + rank;
+          slots[at[i]].row = (int32_t)row;
+          row_keys[row] = a.keys[base + i];
+        }
+        ++rank;
+      }
+    }
+  }
+  __syncthreads();                                    // the list is complete, the slots know their rows
+  if (publishes) {
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+      if (!(mine >> i & 1u)) continue;
+      const int32_t row = __hip_atomic_load(&slots[at[i]].row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      rows[base + i] = row >= 0 ? row : kRowAbsent;   // negative only after a failed call
+    }
+  }
+  if (grow) fill_new_rows<kValues>(a, n_rows, total, first, column_hash);
+}
+
+// Last pass of a larger batch.  Entries that saw a pending key read the row from the slot they remembered (tiles without such
+// entries are skipped), and the rows created by this call are filled.
+template <bool kValues>
+__global__ __launch_bounds__(kBlock) void k_finish(const Slot *__restrict__ slots, int64_t n, int32_t *__restrict__ rows,
+                                                    const uint32_t *__restrict__ slot_of,
+                                                    const uint32_t *__restrict__ tile_sums,
+                                                    const Ctrl *__restrict__ ctrl, const int32_t *__restrict__ first_idx,
+                                                    const NewRowArgs a) {
+  __shared__ uint64_t column_hash[kValues ? 1 : 256 + 1];
+  const int64_t nb = (n + kFlagTile - 1) / kFlagTile;
+  for (int64_t t = blockIdx.x; t < nb; t += gridDim.x) {
+    if (!(tile_sums[t] & kPendingBit)) continue;      // uniform
+    int32_t r[kFlagItems];
+    const int64_t base = t * kFlagTile + threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < kFlagItems; ++i) r[i] = base + i * kBlock < n ? rows[base + i * kBlock] : kRowAbsent;
+#pragma unroll
+    for (int i = 0; i < kFlagItems; ++i) {
+      if (r[i] > kRowPending) continue;               // neither pending nor kRowOpens
+      const int32_t row = slots[slot_of[base + i * kBlock]].row;
+      rows[base + i * kBlock] = row >= 0 ? row : kRowAbsent;       // negative only after a failed call
+    }
+  }
+  if (ctrl->status != 0) return;
+  const long long n_new = ctrl->n_new, n_rows = ctrl->base_rows;
+  if (n_rows + n_new > a.capacity || n_new == 0) return;           // uniform over the grid
+  fill_new_rows<kValues>(a, n_rows, n_new, first_idx, column_hash);
 }
 
 __global__ __launch_bounds__(kBlock) void k_fill_u64x2(uint4 *__restrict__ p, int64_t n16, uint4 v) {
@@ -493,18 +516,53 @@ __global__ __launch_bounds__(kBlock) void k_fm_finalize(const float *__restrict_
 
 // The three aggregations of one forward pass and the FM substitution operator in one launch: eight lanes
 // per sample sum the K shards' partials of their columns in double, square the sums for fm2 before they
-// are rounded, and lane 0 adds the two scalars.  Any of the LR and FM groups may be absent.
+// are rounded, and lanes 0 and 1 add the two scalars.  Any of the LR and FM groups may be absent.
+// Bound by the round trips of its loads while few partials are there, by HBM beyond.  kAhead, for the former: the scalars' partials are
+// requested with the first columns', eight shards at a time, instead of after them: 48 samples of 8 x 16 4.2 -> 2.6 us, 16384 of
+// 16 x 32 13.4 -> 8.4, where each lane's requests no longer matter beside the bytes 12.7 -> 14.6 (65536 of 8 x 16).
+constexpr int64_t kAheadSamples = 16384;          // two workgroups per CU
+template <bool kAhead>
 __global__ __launch_bounds__(kBlock) void k_aggregate_forward(const float *__restrict__ P_lr,
                                                                const float *__restrict__ P_sum,
                                                                const float *__restrict__ P_sq, int K, int64_t B, int D,
                                                                float *__restrict__ A_lr, float *__restrict__ A_sum,
                                                                float *__restrict__ A_sq, float *__restrict__ fm2) {
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t b = gid / 8;
+  const int64_t b = gid / 8, at = min(b, B - 1);
   const int sub = (int)(gid % 8);
-  double q = 0.0;
+  const float *scalars = sub == 1 ? P_lr : P_sq;          // what the lane adds up; lanes 2..7 read what their sample's lane 0 reads
+  if (!P_lr || !P_sum) scalars = P_lr ? P_lr : P_sq;
+  double q = 0.0, scalar = 0.0;
+  if (kAhead) {
+    constexpr int U = 8;
+    const int64_t col = at * D + sub * 4;
+    const bool columns = P_sum && sub < D / 4;
+    const float *p0 = columns ? P_sum + col : scalars;    // no columns: any partials, left out below
+    const int64_t pitch = columns ? B * D : 0;
+    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+    for (int s0 = 0; s0 < K; s0 += U) {
+      float4 p[U];
+      float sc[U];
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const int s = min(s0 + k, K - 1);
+        if (P_sum) p[k] = *reinterpret_cast<const float4 *>(p0 + s * pitch);
+        sc[k] = scalars[(int64_t)s * B + at];
+      }
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        if (s0 + k >= K) break;
+        if (P_sum) { a0 += (double)p[k].x; a1 += (double)p[k].y; a2 += (double)p[k].z; a3 += (double)p[k].w; }
+        scalar += (double)sc[k];
+      }
+    }
+    if (columns && b < B) {
+      *reinterpret_cast<float4 *>(A_sum + col) = make_float4((float)a0, (float)a1, (float)a2, (float)a3);
+      q += a0 * a0 + a1 * a1 + a2 * a2 + a3 * a3;
+    }
+  }
   if (b < B && P_sum)
-    for (int d4 = sub; d4 < D / 4; d4 += 8) {
+    for (int d4 = kAhead ? sub + 8 : sub; d4 < D / 4; d4 += 8) {
       double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
 #pragma unroll 8
       for (int s = 0; s < K; ++s) {                       // the shards' loads are independent: several in flight
@@ -517,21 +575,16 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_forward(const float *__res
   q += __shfl_xor(q, 1, 8);
   q += __shfl_xor(q, 2, 8);
   q += __shfl_xor(q, 4, 8);
-  if (b < B && sub == 0) {
-    if (P_sum) {
-      double sq = 0.0;
+  if (b >= B || sub > 1) return;
+  if (!kAhead) {
 #pragma unroll 8
-      for (int s = 0; s < K; ++s) sq += (double)P_sq[(int64_t)s * B + b];
-      A_sq[b] = (float)sq;
-      if (fm2) fm2[b] = (float)(0.5 * (q - sq));
-    }
-    if (P_lr) {
-      double l = 0.0;
-#pragma unroll 8
-      for (int s = 0; s < K; ++s) l += (double)P_lr[(int64_t)s * B + b];
-      A_lr[b] = (float)l;
-    }
+    for (int s = 0; s < K; ++s) scalar += (double)scalars[(int64_t)s * B + b];
   }
+  if (sub == 0 && P_sum) {
+    A_sq[b] = (float)scalar;
+    if (fm2) fm2[b] = (float)(0.5 * (q - scalar));
+  }
+  if (sub == 1 && P_lr) A_lr[b] = (float)scalar;
 }
 
 inline unsigned grid_for(int64_t n, int per_block = kBlock, int64_t cap = 1 << 20) {
@@ -755,38 +808,36 @@ static des_status_t insert_impl(des_table_t *t, const uint64_t *keys, int64_t n,
   {
     ProfScope ps(KID_PROBE, s);
     hipLaunchKernelGGL(k_probe<true>, dim3(grid_for(n)), dim3(kBlock), 0, s, t->slots, t->n_slots - 1, keys, n, rows, t->ctrl,
-                       slot_of, small ? (unsigned long long *)nullptr : pending_bits);
+                       slot_of, pending_bits);
+  }
+  NewRowArgs a;
+  a.D = c.dim; a.seed = c.init_seed; a.width = t->init_width; a.keys = keys; a.row_keys = small ? nullptr : c.row_keys;
+  a.values = values; a.emb = c.emb; a.w = c.w; a.acc_emb = c.acc_emb; a.acc_w = c.acc_w;
+  a.acc2_emb = c.acc2_emb; a.acc2_w = c.acc2_w; a.capacity = c.capacity_rows;
+  if (small) {
+    ProfScope ps(KID_ASSIGN, s);
+    const dim3 grid(grid_for(n * (values ? c.dim + 1 : c.dim / 4 + 1), kSmallInsertBlock, 64)), block(kSmallInsertBlock);
+    if (values) hipLaunchKernelGGL(k_new_small<true>, grid, block, 0, s, t->slots, rows, slot_of, pending_bits, (int)n, t->ctrl, c.row_keys, a);
+    else hipLaunchKernelGGL(k_new_small<false>, grid, block, 0, s, t->slots, rows, slot_of, pending_bits, (int)n, t->ctrl, c.row_keys, a);
+    return hipGetLastError() == hipSuccess ? DES_OK : DES_ERR_DEVICE;
   }
   {
     ProfScope ps(KID_ASSIGN, s);
-    if (small) {
-      hipLaunchKernelGGL(k_new_small, dim3(1), dim3(kSmallInsertBlock), 0, s, t->slots, rows, slot_of, keys, (int)n, t->ctrl,
-                         c.row_keys, first_idx, c.capacity_rows);
+    hipLaunchKernelGGL(k_new_count, dim3((unsigned)nb), dim3(kBlock), 0, s, t->slots, rows, slot_of, n, pending_bits, tile_sums);
+    if (nb > kSelfPrefixTiles) {
+      hipLaunchKernelGGL(k_new_sums, dim3(1), dim3(kBlock), 0, s, tile_sums, nb, t->ctrl, c.capacity_rows);
+      hipLaunchKernelGGL(k_new_assign<false>, dim3((unsigned)nb), dim3(kBlock), 0, s, t->slots, rows, slot_of, keys, n,
+                         tile_sums, t->ctrl, c.row_keys, first_idx, c.capacity_rows);
     } else {
-      hipLaunchKernelGGL(k_new_count, dim3((unsigned)nb), dim3(kBlock), 0, s, t->slots, rows, slot_of, n, pending_bits, tile_sums,
-                         t->ctrl);
-      if (nb > kSelfPrefixTiles) {
-        hipLaunchKernelGGL(k_new_sums, dim3(1), dim3(kBlock), 0, s, tile_sums, nb, t->ctrl, c.capacity_rows);
-        hipLaunchKernelGGL(k_new_assign<false>, dim3((unsigned)nb), dim3(kBlock), 0, s, t->slots, rows, slot_of, keys, n,
-                           tile_sums, t->ctrl, c.row_keys, first_idx, c.capacity_rows);
-      } else {
-        hipLaunchKernelGGL(k_new_assign<true>, dim3((unsigned)nb), dim3(kBlock), 0, s, t->slots, rows, slot_of, keys, n,
-                           tile_sums, t->ctrl, c.row_keys, first_idx, c.capacity_rows);
-      }
+      hipLaunchKernelGGL(k_new_assign<true>, dim3((unsigned)nb), dim3(kBlock), 0, s, t->slots, rows, slot_of, keys, n,
+                         tile_sums, t->ctrl, c.row_keys, first_idx, c.capacity_rows);
     }
   }
   {
     ProfScope ps(KID_FINISH_ROWS, s);
-    NewRowArgs a;
-    a.D = c.dim; a.seed = c.init_seed; a.width = t->init_width; a.row_keys = c.row_keys; a.values = values;
-    a.first_idx = first_idx; a.emb = c.emb; a.w = c.w; a.acc_emb = c.acc_emb; a.acc_w = c.acc_w;
-    a.acc2_emb = c.acc2_emb; a.acc2_w = c.acc2_w; a.capacity = c.capacity_rows;
     const dim3 grid(grid_for(n * (values ? c.dim + 1 : c.dim / 4 + 1), kBlock, 2048)), block(kBlock);
-#define DES_FINISH(PATCH, VALUES) \
-  hipLaunchKernelGGL((k_finish<PATCH, VALUES>), grid, block, 0, s, t->slots, n, rows, slot_of, tile_sums, t->ctrl, a)
-    if (small) { if (values) DES_FINISH(false, true); else DES_FINISH(false, false); }
-    else       { if (values) DES_FINISH(true, true);  else DES_FINISH(true, false); }
-#undef DES_FINISH
+    if (values) hipLaunchKernelGGL(k_finish<true>, grid, block, 0, s, t->slots, n, rows, slot_of, tile_sums, t->ctrl, first_idx, a);
+    else hipLaunchKernelGGL(k_finish<false>, grid, block, 0, s, t->slots, n, rows, slot_of, tile_sums, t->ctrl, first_idx, a);
   }
   return hipGetLastError() == hipSuccess ? DES_OK : DES_ERR_DEVICE;
 }
@@ -867,8 +918,9 @@ des_status_t des_aggregate_forward(const float *P_lr, const float *P_sum, const 
   if (P_sum && (!aligned16(P_sum) || !aligned16(A_sum))) return DES_ERR_INVALID_ARG;
   hipStream_t s = (hipStream_t)stream;
   ProfScope ps(KID_AGGREGATE, s);
-  hipLaunchKernelGGL(k_aggregate_forward, dim3(grid_for(B * 8, kBlock, 1ll << 30)), dim3(kBlock), 0, s, P_lr, P_sum, P_sq,
-                     K, B, D, A_lr, A_sum, A_sq, fm2);
+  const dim3 grid(grid_for(B * 8, kBlock, 1ll << 30)), block(kBlock);
+  if (B <= kAheadSamples) hipLaunchKernelGGL(k_aggregate_forward<true>, grid, block, 0, s, P_lr, P_sum, P_sq, K, B, D, A_lr, A_sum, A_sq, fm2);
+  else hipLaunchKernelGGL(k_aggregate_forward<false>, grid, block, 0, s, P_lr, P_sum, P_sq, K, B, D, A_lr, A_sum, A_sq, fm2);
   return hipGetLastError() == hipSuccess ? DES_OK : DES_ERR_DEVICE;
 }
 
