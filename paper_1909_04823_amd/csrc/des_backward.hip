@@ -368,10 +368,13 @@ __device__ inline uint32_t small_excl_scan(uint32_t v, uint32_t *lds, uint32_t &
   __syncthreads();
   uint32_t base = 0, tot = 0;
 #pragma unroll
-  for (int w = 0; w < kSmallWaves; ++w) {
-    const uint32_t x = lds[w];
-    if (w < wave) base = op(base, x);
-    tot = op(tot, x);
+  for (int w = 0; w < kSmallWaves; w += 4) {                // 16-byte reads: every wave reads every sum
+    const uint4 x = *reinterpret_cast<const uint4 *>(lds + w);
+    base = op(base, w < wave ? x.x : 0u);
+    base = op(base, w + 1 < wave ? x.y : 0u);
+    base = op(base, w + 2 < wave ? x.z : 0u);
+    base = op(base, w + 3 < wave ? x.w : 0u);
+    tot = op(op(tot, x.x), op(op(x.y, x.z), x.w));
   }
   __syncthreads();
   total = tot;
@@ -380,65 +383,94 @@ __device__ inline uint32_t small_excl_scan(uint32_t v, uint32_t *lds, uint32_t &
 
 template <bool kHasVals>
 __global__ __launch_bounds__(kSmallBlock) void k_sort_small(const BwdArgs a, uint32_t *__restrict__ pay_out, int bits) {
-  __shared__ uint32_t skey[kSmallSort + 1], spay[kSmallSort];
+  __shared__ __align__(16) uint32_t skey[kSmallSort + 4], spay[kSmallSort];
   __shared__ uint32_t cnt[kSmallWaves][1 << kSmallBits];
-  __shared__ uint32_t scan_lds[kSmallWaves];
-  __shared__ uint32_t n_long, n_chunks, n_multi;
+  __shared__ __align__(16) uint32_t scan_lds[kSmallWaves];
+  __shared__ uint32_t n_long;
   const int n = (int)a.n;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const auto sum = [](uint32_t x, uint32_t y) { return x + y; };
   const auto largest = [](uint32_t x, uint32_t y) { return x > y ? x : y; };
   uint32_t total;
-  if (tid == 0) n_long = n_chunks = n_multi = 0;
+  if (tid == 0) n_long = 0;
 
-  // (1) every bag that has entries leaves its number (plus one) at its first entry; the largest one up to an entry is its bag
-  for (int i = tid; i < kSmallSort; i += kSmallBlock) spay[i] = 0;
+  // (1) every bag that has entries leaves its number (plus one) at its first entry; the largest one up to an entry is its bag.
+  // The rows and kSmallItems offsets per thread are requested together.
+  int32_t row[kSmallItems];
+#pragma unroll
+  for (int j = 0; j < kSmallItems; ++j) row[j] = a.rows[min(tid * kSmallItems + j, n - 1)];
+  static_assert(kSmallItems == 4, "a thread's items are one 16-byte LDS access");
+  uint4 *const key4 = reinterpret_cast<uint4 *>(skey) + tid, *const pay4 = reinterpret_cast<uint4 *>(spay) + tid;
+  *pay4 = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
-  for (int b = tid; b < (int)a.nbags; b += kSmallBlock) {
-    const int e0 = a.offsets[b], e1 = a.offsets[b + 1];
-    if (e0 < e1) spay[e0] = (uint32_t)b + 1u;
+  for (int b0 = 0; b0 < (int)a.nbags; b0 += kSmallItems * kSmallBlock) {
+    int e0[kSmallItems], e1[kSmallItems];
+#pragma unroll
+    for (int j = 0; j < kSmallItems; ++j) {
+      const int b = min(b0 + j * kSmallBlock + tid, (int)a.nbags - 1);
+      e0[j] = a.offsets[b];
+      e1[j] = a.offsets[b + 1];
+    }
+#pragma unroll
+    for (int j = 0; j < kSmallItems; ++j) {
+      const int b = b0 + j * kSmallBlock + tid;
+      if (b < (int)a.nbags && e0[j] < e1[j]) spay[e0[j]] = (uint32_t)b + 1u;
+    }
   }
   __syncthreads();
   {
-    uint32_t bag[kSmallItems], run = 0;
+    const uint4 starts = *pay4;
+    uint32_t bag[kSmallItems] = {starts.x, starts.y, starts.z, starts.w};
 #pragma unroll
-    for (int j = 0; j < kSmallItems; ++j) { run = largest(run, spay[tid * kSmallItems + j]); bag[j] = run; }
-    const uint32_t before = small_excl_scan(run, scan_lds, total, largest);
+    for (int j = 1; j < kSmallItems; ++j) bag[j] = largest(bag[j], bag[j - 1]);
+    const uint32_t before = small_excl_scan(bag[kSmallItems - 1], scan_lds, total, largest);
+    uint32_t key[kSmallItems], pay[kSmallItems];
 #pragma unroll
     for (int j = 0; j < kSmallItems; ++j) {
       const int e = tid * kSmallItems + j;
       bag[j] = largest(bag[j], before) - 1u;
-      if (e < n) {
-        const int r = a.rows[e];
-        skey[e] = r >= 0 ? (uint32_t)r : a.missing;
-        spay[e] = kHasVals ? (uint32_t)e : bag[j];
-        if (kHasVals) a.bag_of[e] = (int32_t)bag[j];
-      }
+      key[j] = row[j] >= 0 ? (uint32_t)row[j] : a.missing;
+      pay[j] = kHasVals ? (uint32_t)e : bag[j];
+      if (kHasVals && e < n) a.bag_of[e] = (int32_t)bag[j];
     }
+    *key4 = make_uint4(key[0], key[1], key[2], key[3]);
+    *pay4 = make_uint4(pay[0], pay[1], pay[2], pay[3]);
   }
 
-  // (2) a wave owns kSmallItems * 64 consecutive items and walks them in rounds of 64
+  // (2) a wave owns `rounds` * 64 consecutive items and walks them in rounds of 64.  All sixteen waves share one CU, where an
+  // instruction of each costs sixteen cycles, so the number of instructions is what counts: no more rounds than the batch needs,
+  // four instructions per digit bit, digit counts read and written once, 16-byte LDS accesses (2560 entries, 14-bit rows: 13.7 -> 12.3 us,
+  // of which some 5.5 are the two passes, 2.8 the bags, 2.2 the heads).
   const unsigned long long lane_lt = (1ull << lane) - 1ull;
   const int npass = (bits + kSmallBits - 1) / kSmallBits, per = (bits + npass - 1) / npass;
+  const int rounds = (n + kSmallBlock - 1) / kSmallBlock, first = wave * rounds * kWave + lane;
   for (int p = 0; p < npass; ++p) {
     const int shift = p * per, b = min(per, bits - shift);
     const uint32_t radix = 1u << b, mask = radix - 1u;
-    for (int i = tid; i < kSmallWaves << kSmallBits; i += kSmallBlock) (&cnt[0][0])[i] = 0;
+    for (int i = tid; i < kSmallWaves << (kSmallBits - 2); i += kSmallBlock)
+      reinterpret_cast<uint4 *>(&cnt[0][0])[i] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();                                 // the items are in place, the counters clear
     uint32_t key[kSmallItems], pay[kSmallItems], rank[kSmallItems];
 #pragma unroll
     for (int r = 0; r < kSmallItems; ++r) {
-      const int i = (wave * kSmallItems + r) * kWave + lane;
-      const bool live = i < n;
-      key[r] = live ? skey[i] : 0u;
-      pay[r] = live ? spay[i] : 0u;
+      const int i = min(first + r * kWave, kSmallSort - 1);
+      key[r] = skey[i];
+      pay[r] = spay[i];
+    }
+#pragma unroll
+    for (int r = 0; r < kSmallItems; ++r) {
+      if (r >= rounds) break;
+      const bool live = first + r * kWave < n;
       const uint32_t d = (key[r] >> shift) & mask;
-      unsigned long long peers = __ballot(live);
+      const unsigned long long alive = __ballot(live);
+      uint32_t lo = (uint32_t)alive, hi = (uint32_t)(alive >> 32);
       for (int bit = 0; bit < b; ++bit) {
-        const bool one = (d >> bit) & 1u;
-        const unsigned long long bal = __ballot(one);
-        peers &= one ? bal : ~bal;
+        const uint32_t mine = (uint32_t)((int32_t)(d << (31 - bit)) >> 31);     // all ones where the bit is set
+        const unsigned long long set = __ballot(mine != 0u);
+        lo = __builtin_amdgcn_bitop3_b32(lo, mine, (uint32_t)set, 0x90);        // lo & ~(mine ^ set)
+        hi = __builtin_amdgcn_bitop3_b32(hi, mine, (uint32_t)(set >> 32), 0x90);
       }
+      const unsigned long long peers = (unsigned long long)hi << 32 | lo;
       const uint32_t earlier = (uint32_t)__popcll(peers & lane_lt);
       uint32_t prev = 0;
       if (live) prev = cnt[wave][d];
@@ -448,25 +480,27 @@ __global__ __launch_bounds__(kSmallBlock) void k_sort_small(const BwdArgs a, uin
       rank[r] = prev + earlier;
     }
     __syncthreads();
-    uint32_t of_digit = 0;                           // thread d: the digit's items; its counters become starts inside the digit
+    uint32_t of_digit = 0, of_wave[kSmallWaves];     // thread d: the digit's items; its counters become starts in the sorted order
     if (tid < (int)radix) {
 #pragma unroll
       for (int w = 0; w < kSmallWaves; ++w) {
-        const uint32_t c = cnt[w][tid];
-        cnt[w][tid] = of_digit;
-        of_digit += c;
+        of_wave[w] = cnt[w][tid];
+        of_digit += of_wave[w];
       }
     }
-    const uint32_t start = small_excl_scan(of_digit, scan_lds, total, sum);
+    uint32_t start = small_excl_scan(of_digit, scan_lds, total, sum);
     if (tid < (int)radix) {
 #pragma unroll
-      for (int w = 0; w < kSmallWaves; ++w) cnt[w][tid] += start;
+      for (int w = 0; w < kSmallWaves; ++w) {
+        cnt[w][tid] = start;
+        start += of_wave[w];
+      }
     }
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < kSmallItems; ++r) {
-      const int i = (wave * kSmallItems + r) * kWave + lane;
-      if (i < n) {
+      const int i = first + r * kWave;
+      if (r < rounds && i < n) {
         const uint32_t at = cnt[wave][(key[r] >> shift) & mask] + rank[r];
         skey[at] = key[r];
         spay[at] = pay[r];
@@ -476,14 +510,17 @@ __global__ __launch_bounds__(kSmallBlock) void k_sort_small(const BwdArgs a, uin
   }
 
   // (3) segment heads, in the order of the items
-  for (int i = tid; i < n; i += kSmallBlock) pay_out[i] = spay[i];
-  uint32_t key[kSmallItems], heads = 0;
+  uint32_t heads = 0;
   const int i0 = tid * kSmallItems;
-  uint32_t prev = i0 > 0 && i0 <= n ? skey[i0 - 1] : 0xFFFFFFFFu;
+  const uint4 k4 = *key4, p4 = *pay4;
+  uint32_t key[kSmallItems] = {k4.x, k4.y, k4.z, k4.w};
+  const uint32_t pay[kSmallItems] = {p4.x, p4.y, p4.z, p4.w};
+  uint32_t prev = i0 > 0 ? skey[i0 - 1] : 0xFFFFFFFFu;
   const uint32_t first_prev = prev;
 #pragma unroll
   for (int j = 0; j < kSmallItems; ++j) {
-    key[j] = i0 + j < n ? skey[i0 + j] : a.missing;
+    if (i0 + j < n) pay_out[i0 + j] = pay[j];
+    else key[j] = a.missing;
     heads += (key[j] != a.missing && (i0 + j == 0 || key[j] != prev)) ? 1u : 0u;
     prev = key[j];
   }
@@ -496,7 +533,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_sort_small(const BwdArgs a, uin
     if (i < n) {
       if (key[j] != a.missing && (i == 0 || key[j] != prev)) {
         a.uniq_rows[u] = (int32_t)key[j];
-        a.first_pay[u] = spay[i];
+        a.first_pay[u] = pay[j];
         a.seg_off[u] = i;
         skey[u] = (uint32_t)i;                       // and for the split below
         ++u;
@@ -513,24 +550,13 @@ __global__ __launch_bounds__(kSmallBlock) void k_sort_small(const BwdArgs a, uin
   }
   __syncthreads();
 
-  // long segments and their chunks; their order is irrelevant to the results
-  for (uint32_t v = tid; v < U; v += kSmallBlock) {
-    const uint32_t len = skey[v + 1] - skey[v];
-    if (len <= (uint32_t)kShortMax) continue;
-    const uint32_t nch = (uint32_t)chunks_of(a, (int)len);
-    const uint32_t j = atomicAdd(&n_long, 1u), c0 = atomicAdd(&n_chunks, nch);
-    a.long_seg[j] = (int32_t)v;
-    a.long_c0[j] = c0;
-    if (nch > 1) a.multi_seg[atomicAdd(&n_multi, 1u)] = (int32_t)j;
-    for (uint32_t c = 0; c < nch; ++c) a.chunk_owner[c0 + c] = (int32_t)j;
-  }
-  static_assert((kSmallSort >> kFewChunkShift) <= kMidFan, "no segment here has enough chunks for pre-summed groups");
+  // long segments; their order is irrelevant to the results
+  for (uint32_t v = tid; v < U; v += kSmallBlock)
+    if (skey[v + 1] - skey[v] > (uint32_t)kShortMax) a.long_seg[atomicAdd(&n_long, 1u)] = (int32_t)v;
   __syncthreads();
   if (tid == 0) {
     heads_bookkeeping(a, U);
     a.ctrl->n_long = n_long;
-    a.ctrl->n_chunks = n_chunks;
-    a.ctrl->n_multi = n_multi;
   }
 }
 
@@ -816,69 +842,47 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kSecond 
   }
 }
 
-// Which chunk of its segment wave `c` takes, where the segment has the waves c0 .. c0 + nch - 1: the waves of one die (workgroups
-// go round the eight dies) take consecutive chunks.  A row's entries come in batch order, so a die then sees an eighth of the
-// samples of every row with eight workgroups or more, and that eighth of A_sum stays in its L2: 8.0e6 entries of 64 floats
-// 359 -> 346 us, 1.05e8 of 64 2.62 -> 2.51 ms, 8.2e6 of 32 150 -> 141 us.
-__device__ inline uint32_t chunk_of_wave(uint32_t c, uint32_t c0, uint32_t nch) {
-  constexpr uint32_t kDies = 8, kRound = kDies * kWavesPerBlock;
-  const auto before = [](uint32_t w, uint32_t die) {          // waves of the die below w
-    const int in = (int)(w % kRound) - (int)(die * kWavesPerBlock);
-    return w / kRound * kWavesPerBlock + (uint32_t)min(max(in, 0), kWavesPerBlock);
-  };
-  const uint32_t mine = c / kWavesPerBlock % kDies;
-  uint32_t k = before(c, mine) - before(c0, mine);
-  for (uint32_t die = 0; die < mine; ++die) k += before(c0 + nch, die) - before(c0, die);
-  return k;
-}
+// What one wave needs to walk a stretch of a long segment: the lane groups take equal runs of a batch of kBatch entries.
+template <int D>
+struct Walk {
+  static constexpr int G = D / 4, NG = kWave / G;
+  static constexpr int U = 4;                                 // gradient rows in flight per lane
+  static constexpr int kBatch = NG * (G > U ? G : U), kLoads = kBatch / kWave;
+  uint2 bag[kBatch];                                          // (bag, sample) of a batch's entries
+  float2 x[kBatch];                                           // their (value, g_fm)
+};
 
-// (4b) one wave per chunk of a long segment: the wave walks the chunk in batches, its lane groups take equal runs of a
-// batch, the groups' sums are combined with cross-lane shuffles, and the wave writes
-// partials[c] = (s1[D], s2, gw, 0, 0) in double -- or, when the segment has no other chunk (33 .. 512 or 128
-// entries, most long segments), updates the row at once.
-// Bound by the gradient rows and A_sum rows that come through the fabric (2.7 GB at 7 TB/s for 8.0e6 entries of 64 floats); in
-// smaller batches by the round trips.  A lane loads, divides and adds up what an entry needs once (bag, sample, value, g_fm,
+// Sums over the sorted entries [lo, hi) (at least one), the same in every lane group.
+// A lane loads, divides and adds up what an entry needs once (bag, sample, value, g_fm,
 // g_lr) and leaves the rest to read in LDS; no gather is under a condition, so a step of U entries is waited for once: 8.2e6
 // entries of 32 floats 165 -> 150 us, 3.7e5 of 32 with values 17.3 -> 14.4, 8.0e6 of 64 366 -> 359.  U = 2 / 8 (150 / 162,
 // 15.2 / 14.9, 358 / 365) and six waves per SIMD (169, 20.8, 380) are no better.
 template <int D, bool kHasVals>
-__global__ __launch_bounds__(kBlock, 5) void k_long_partial(const BwdArgs a) {
-  constexpr int G = D / 4;
-  constexpr int NG = kWave / G;
-  constexpr int U = 4;                                        // gradient rows in flight per lane
-  constexpr int kBatch = NG * (G > U ? G : U), kLoads = kBatch / kWave;
-  __shared__ uint2 l_bag[kWavesPerBlock][kBatch];             // (bag, sample) of a batch's entries
-  __shared__ float2 l_x[kWavesPerBlock][kBatch];              // their (value, value * g_fm) factors
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const uint32_t wave_no = blockIdx.x * kWavesPerBlock + wave;
-  if (wave_no >= a.ctrl->n_chunks) return;                    // uniform per wave
-  const int g = lane / G, sub = lane % G;
-  const int j = a.chunk_owner[wave_no];
-  const int u = a.long_seg[j];
-  const int seg_lo = a.seg_off[u], seg_hi = a.seg_off[u + 1];
-  const uint32_t c0 = a.long_c0[j], k_seg = chunk_of_wave(wave_no, c0, (uint32_t)chunks_of(a, seg_hi - seg_lo));
-  const int c_lo = seg_lo + (int)(k_seg << a.chunk_shift);
-  const int c_hi = min(c_lo + (1 << a.chunk_shift), seg_hi);
+__device__ inline Acc walk_entries(const BwdArgs &a, int lo, int hi, Walk<D> &lds) {
+  constexpr int G = Walk<D>::G, NG = Walk<D>::NG, U = Walk<D>::U, kBatch = Walk<D>::kBatch, kLoads = Walk<D>::kLoads;
+  uint2 (&l_bag)[kBatch] = lds.bag;
+  float2 (&l_x)[kBatch] = lds.x;
+  const int lane = threadIdx.x & (kWave - 1), g = lane / G, sub = lane % G;
   Acc acc = acc_zero();
   // payloads of the lane's entries of the first batch and of the one after (an index past the end reads the last entry)
   uint32_t bag[kLoads], pay_n[kLoads];
   float x[kLoads];
 #pragma unroll
   for (int q = 0; q < kLoads; ++q) {
-    bag[q] = a.pay_sorted[min(c_lo + q * kWave + lane, c_hi - 1)];
-    pay_n[q] = a.pay_sorted[min(c_lo + kBatch + q * kWave + lane, c_hi - 1)];
+    bag[q] = a.pay_sorted[min(lo + q * kWave + lane, hi - 1)];
+    pay_n[q] = a.pay_sorted[min(lo + kBatch + q * kWave + lane, hi - 1)];
     x[q] = 1.f;
   }
   if (kHasVals) {
 #pragma unroll
     for (int q = 0; q < kLoads; ++q) { x[q] = a.vals[bag[q]]; bag[q] = (uint32_t)a.bag_of[bag[q]]; }
   }
-  for (int base = c_lo; base < c_hi; base += kBatch) {
+  for (int base = lo; base < hi; base += kBatch) {
     float gf[kLoads], gl[kLoads], xc[kLoads];
 #pragma unroll
     for (int q = 0; q < kLoads; ++q) {
       const uint32_t b = bag[q] / (uint32_t)a.F;
-      l_bag[wave][q * kWave + lane] = make_uint2(bag[q] & a.take_pool.mask, b & a.take_sum.mask);
+      l_bag[q * kWave + lane] = make_uint2(bag[q] & a.take_pool.mask, b & a.take_sum.mask);
       gf[q] = a.take_fm.base[b & a.take_fm.mask];
       gl[q] = a.take_lr.base[b & a.take_lr.mask];
       xc[q] = x[q];
@@ -888,15 +892,15 @@ __global__ __launch_bounds__(kBlock, 5) void k_long_partial(const BwdArgs a) {
     for (int q = 0; q < kLoads; ++q) {
       bag[q] = pay_n[q];
       if (kHasVals) { x[q] = a.vals[pay_n[q]]; bag[q] = (uint32_t)a.bag_of[pay_n[q]]; }
-      pay_n[q] = a.pay_sorted[min(base + 2 * kBatch + q * kWave + lane, c_hi - 1)];
+      pay_n[q] = a.pay_sorted[min(base + 2 * kBatch + q * kWave + lane, hi - 1)];
     }
-    const int cnt = min(kBatch, c_hi - base), per = (cnt + NG - 1) / NG;
+    const int cnt = min(kBatch, hi - base), per = (cnt + NG - 1) / NG;
     const int mine = g * per, upto = min(mine + per, cnt);    // this lane group's run of the batch
     for (int k0 = 0; k0 < per; k0 += U) {
       float4 gp[U], as[U];
 #pragma unroll
       for (int k = 0; k < U; ++k) {
-        const uint2 id = l_bag[wave][min(mine + k0 + k, cnt - 1)];
+        const uint2 id = l_bag[min(mine + k0 + k, cnt - 1)];
         gp[k] = ld4(a.take_pool.base + (int64_t)id.x * D + sub * 4);
         as[k] = ld4(a.take_sum.base + (int64_t)id.y * D + sub * 4);
       }
@@ -914,12 +918,12 @@ __global__ __launch_bounds__(kBlock, 5) void k_long_partial(const BwdArgs a) {
             acc.s2 += xd * (xd * (double)gf[q]);
             acc.gw += xd * (double)gl[q];
           }
-          l_x[wave][q * kWave + lane] = make_float2(xc[q], gf[q]);
+          l_x[q * kWave + lane] = make_float2(xc[q], gf[q]);
         }
       }
       float2 f[U];
 #pragma unroll
-      for (int k = 0; k < U; ++k) f[k] = l_x[wave][min(mine + k0 + k, cnt - 1)];
+      for (int k = 0; k < U; ++k) f[k] = l_x[min(mine + k0 + k, cnt - 1)];
 #pragma unroll
       for (int k = 0; k < U; ++k) {
         if (mine + k0 + k >= upto) continue;
@@ -943,6 +947,45 @@ __global__ __launch_bounds__(kBlock, 5) void k_long_partial(const BwdArgs a) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) acc.v[k] += __shfl_xor(acc.v[k], m, kWave);
   }
+  return acc;
+}
+
+// Which chunk of its segment wave `c` takes, where the segment has the waves c0 .. c0 + nch - 1: the waves of one die (workgroups
+// go round the eight dies) take consecutive chunks.  A row's entries come in batch order, so a die then sees an eighth of the
+// samples of every row with eight workgroups or more, and that eighth of A_sum stays in its L2: 8.0e6 entries of 64 floats
+// 359 -> 346 us, 1.05e8 of 64 2.62 -> 2.51 ms, 8.2e6 of 32 150 -> 141 us.
+__device__ inline uint32_t chunk_of_wave(uint32_t c, uint32_t c0, uint32_t nch) {
+  constexpr uint32_t kDies = 8, kRound = kDies * kWavesPerBlock;
+  const auto before = [](uint32_t w, uint32_t die) {          // waves of the die below w
+    const int in = (int)(w % kRound) - (int)(die * kWavesPerBlock);
+    return w / kRound * kWavesPerBlock + (uint32_t)min(max(in, 0), kWavesPerBlock);
+  };
+  const uint32_t mine = c / kWavesPerBlock % kDies;
+  uint32_t k = before(c, mine) - before(c0, mine);
+  for (uint32_t die = 0; die < mine; ++die) k += before(c0 + nch, die) - before(c0, die);
+  return k;
+}
+
+// (4b) one wave per chunk of a long segment: the wave walks the chunk in batches, its lane groups take equal runs of a
+// batch, the groups' sums are combined with cross-lane shuffles, and the wave writes
+// partials[c] = (s1[D], s2, gw, 0, 0) in double -- or, when the segment has no other chunk (33 .. 512 or 128
+// entries, most long segments), updates the row at once.
+// Bound by the gradient rows and A_sum rows that come through the fabric (2.7 GB at 7 TB/s for 8.0e6 entries of 64 floats); in
+// smaller batches by the round trips.
+template <int D, bool kHasVals>
+__global__ __launch_bounds__(kBlock, D == 4 ? 4 : 5) void k_long_partial(const BwdArgs a) {
+  constexpr int G = D / 4;
+  __shared__ Walk<D> lds[kWavesPerBlock];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const uint32_t wave_no = blockIdx.x * kWavesPerBlock + wave;
+  if (wave_no >= a.ctrl->n_chunks) return;                    // uniform per wave
+  const int g = lane / G, sub = lane % G;
+  const int j = a.chunk_owner[wave_no];
+  const int u = a.long_seg[j];
+  const int seg_lo = a.seg_off[u], seg_hi = a.seg_off[u + 1];
+  const uint32_t c0 = a.long_c0[j], k_seg = chunk_of_wave(wave_no, c0, (uint32_t)chunks_of(a, seg_hi - seg_lo));
+  const int c_lo = seg_lo + (int)(k_seg << a.chunk_shift);
+  const Acc acc = walk_entries<D, kHasVals>(a, c_lo, min(c_lo + (1 << a.chunk_shift), seg_hi), lds[wave]);
   if (g == 0) {
     if (seg_hi - seg_lo <= (1 << a.chunk_shift)) {
       // the segment is this one chunk: the wave holds its whole sum and updates the row itself
@@ -955,6 +998,42 @@ __global__ __launch_bounds__(kBlock, 5) void k_long_partial(const BwdArgs a) {
       if (sub == 0) *reinterpret_cast<double2 *>(p + D) = make_double2(acc.s2, acc.gw);
     }
   }
+}
+
+// (4b, c) for a batch of up to kSmallSort entries: one workgroup per long segment, whose waves take equal stretches; their sums are
+// added in wave order: one launch instead of two (3.4 -> 1.6 us where no segment is long).
+template <int D>
+constexpr int kLongSmallWaves = D == 4 ? 8 : 16;              // the waves' batches fit the LDS
+template <int D, bool kHasVals>
+__global__ __launch_bounds__(kLongSmallWaves<D> * kWave) void k_long_small(const BwdArgs a) {
+  constexpr int G = D / 4, kWaves = kLongSmallWaves<D>;
+  __shared__ Walk<D> lds[kWaves];
+  __shared__ double red[kWaves][D + 2];
+  const int64_t j = blockIdx.x;
+  if (j >= a.ctrl->n_long) return;
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, sub = lane % G;
+  const int u = a.long_seg[j];
+  const int seg_lo = a.seg_off[u], seg_hi = a.seg_off[u + 1], per = (seg_hi - seg_lo + kWaves - 1) / kWaves;
+  const int lo = min(seg_lo + wave * per, seg_hi), hi = min(lo + per, seg_hi);
+  Acc acc = acc_zero();
+  if (lo < hi) acc = walk_entries<D, kHasVals>(a, lo, hi, lds[wave]);
+  if (lane < G) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) red[wave][sub * 4 + k] = acc.v[k];
+    if (sub == 0) { red[wave][D] = acc.s2; red[wave][D + 1] = acc.gw; }
+  }
+  __syncthreads();
+  if (threadIdx.x >= G) return;
+  acc = acc_zero();
+#pragma unroll 2
+  for (int w = 0; w < kWaves; ++w) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) acc.v[k] += red[w][sub * 4 + k];
+    acc.s2 += red[w][D];
+    acc.gw += red[w][D + 1];
+  }
+  const int row = a.uniq_rows[u];
+  apply_row<D>(a, u, row, sub, load_row<D>(a, row, sub), acc);
 }
 
 // (4b') Segments of more than kMidFan chunks (rows that take a sizeable share of a skewed batch): one wave per
@@ -1082,6 +1161,11 @@ void launch_update(const BwdArgs &a, hipStream_t s) {
     const dim3 grid(blocks_for(a.n * G, kShortGrid)), block(kBlock);
     if (second) hipLaunchKernelGGL((k_short_update<D, kHasVals, true>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((k_short_update<D, kHasVals, false>), grid, block, 0, s, a);
+  }
+  if (a.n <= kSmallSort) {
+    ProfScope ps(KID_LONG_PARTIAL, s);
+    hipLaunchKernelGGL((k_long_small<D, kHasVals>), dim3((unsigned)max_long), dim3(kLongSmallWaves<D> * kWave), 0, s, a);
+    return;
   }
   {
     ProfScope ps(KID_LONG_PARTIAL, s);

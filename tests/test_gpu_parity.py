@@ -867,6 +867,8 @@ def test_merge_finds_the_bags(oracle, des, n, nbags, with_vals):
     (20011, 8, [63, 64, 65, 127, 1025, 4999], True),         # of 128
     (20011, 128, [33, 34, 63, 64, 65, 129, 6017], False),    # of 64 for two lane groups
     (20011, 256, [33, 63, 64, 65, 191, 193, 4097], True),    # of 64 for one
+    (4096, 4, [33, 63, 1023, 2049], True),                   # one workgroup per segment: 8 waves, or 16
+    (4095, 256, [33, 34, 513, 1025], False),
     ((1 << 22) + 3, 8, [511, 513, 16385, 17000, 2000003], True),   # chunks of 512 on all dies: 33, 34 and 3907 of them
 ])
 def test_merge_walk_of_a_chunk(oracle, des, n, D, lens, with_vals):
