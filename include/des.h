@@ -444,6 +444,16 @@ des_status_t des_head(const float *A_lr, const float *fm2, const float *a, const
 des_status_t des_dense_update(float *theta, const float *grad, float *s1, float *s2, int64_t n,
                               const des_optimizer_t *optimizer, void *stream);
 
+/* The same for `count` arrays with one optimizer: one launch per 16 of them.  `params` is read before the call returns (host memory);
+ * the arrays do not overlap.  Nothing is launched unless all of them are valid. */
+typedef struct {
+  float *theta;
+  const float *grad;
+  float *s1, *s2;
+  int64_t n;
+} des_dense_param_t;
+des_status_t des_dense_update_many(const des_dense_param_t *params, int32_t count, const des_optimizer_t *optimizer, void *stream);
+
 /* Checks the part of the contract the other calls take on trust, for callers that cannot vouch for
  * their batches (the kernels index memory with these values; a broken batch makes them fault):
  * offsets[0] == 0, offsets non-decreasing, offsets[B*F] == nnz, and, when `rows` is given, every

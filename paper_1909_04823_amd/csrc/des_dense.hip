@@ -191,12 +191,22 @@ __global__ __launch_bounds__(kWave) void k_head_final(const double *__restrict__
   }
 }
 
-// One optimizer step on every coordinate of a dense array, in double, state and weight stored in fp32.
-__global__ __launch_bounds__(kBlock) void k_dense_update(float *__restrict__ theta, const float *__restrict__ grad,
-                                                          float *__restrict__ s1, float *__restrict__ s2, int64_t n,
-                                                          const des_optimizer_t o, double c1, double c2) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+// One optimizer step on every coordinate of several dense arrays, in double, state and weight stored in fp32.  A tower's arrays are a
+// few kB to a few MB, so a launch each was all they took: six arrays of 1.4e5 floats in all 14.9 -> 3.6 us, and five calls less from the host.
+constexpr int kManyArrays = 16;                   // per launch: their descriptions are kernel arguments
+struct DenseArrays {
+  des_dense_param_t p[kManyArrays];
+  uint32_t end[kManyArrays];                      // workgroups up to and with the array's
+};
+__global__ __launch_bounds__(kBlock) void k_dense_update(const DenseArrays arrays, const des_optimizer_t o, double c1, double c2) {
+  int k = 0;
+  while (blockIdx.x >= arrays.end[k]) ++k;        // the last array's `end` is the grid
+  float *__restrict__ theta = arrays.p[k].theta, *__restrict__ s1 = arrays.p[k].s1, *__restrict__ s2 = arrays.p[k].s2;
+  const float *__restrict__ grad = arrays.p[k].grad;
+  const int64_t n = arrays.p[k].n;
+  const uint32_t begin = k > 0 ? arrays.end[k - 1] : 0u;
+  const int64_t stride = (int64_t)(arrays.end[k] - begin) * blockDim.x;
+  for (int64_t i = (int64_t)(blockIdx.x - begin) * blockDim.x + threadIdx.x; i < n; i += stride) {
     const double G = (double)grad[i], w = (double)theta[i];
     if (o.opt_emb == DES_OPT_SGD) {
       theta[i] = (float)(w - (double)o.lr * G);
@@ -322,16 +332,22 @@ des_status_t des_head(const float *A_lr, const float *fm2, const float *a, const
   return DES_OK;
 }
 
-des_status_t des_dense_update(float *theta, const float *grad, float *s1, float *s2, int64_t n,
-                              const des_optimizer_t *optimizer, void *stream) {
-  if (n < 0 || !optimizer) return DES_ERR_INVALID_ARG;
+des_status_t des_dense_update_many(const des_dense_param_t *params, int32_t count, const des_optimizer_t *optimizer, void *stream) {
+  if (count < 0 || (count > 0 && !params) || !optimizer) return DES_ERR_INVALID_ARG;
   const des_optimizer_t &o = *optimizer;
   const int opt = o.opt_emb;
   if (opt != DES_OPT_SGD && opt != DES_OPT_ADAGRAD && opt != DES_OPT_ADAM && opt != DES_OPT_FTRL) return DES_ERR_INVALID_ARG;
-  if (n == 0) return DES_OK;
-  if (!theta || !grad) return DES_ERR_INVALID_ARG;
-  if (opt != DES_OPT_SGD && !s1) return DES_ERR_INVALID_ARG;
-  if ((opt == DES_OPT_ADAM || opt == DES_OPT_FTRL) && !s2) return DES_ERR_INVALID_ARG;
+  bool any = false;
+  for (int32_t i = 0; i < count; ++i) {
+    const des_dense_param_t &p = params[i];
+    if (p.n < 0) return DES_ERR_INVALID_ARG;
+    if (p.n == 0) continue;
+    any = true;
+    if (!p.theta || !p.grad) return DES_ERR_INVALID_ARG;
+    if (opt != DES_OPT_SGD && !p.s1) return DES_ERR_INVALID_ARG;
+    if ((opt == DES_OPT_ADAM || opt == DES_OPT_FTRL) && !p.s2) return DES_ERR_INVALID_ARG;
+  }
+  if (!any) return DES_OK;
   if (opt == DES_OPT_ADAM && o.step < 1) return DES_ERR_INVALID_ARG;
   if (opt == DES_OPT_FTRL && !(o.ftrl_alpha > 0.f)) return DES_ERR_INVALID_ARG;
   double c1 = 1.0, c2 = 1.0;
@@ -341,8 +357,29 @@ des_status_t des_dense_update(float *theta, const float *grad, float *s1, float 
   }
   hipStream_t s = (hipStream_t)stream;
   ProfScope ps(KID_DENSE_UPDATE, s);
-  hipLaunchKernelGGL(k_dense_update, dim3(blocks_for(n, 1 << 16)), dim3(kBlock), 0, s, theta, grad, s1, s2, n, o, c1, c2);
+  DenseArrays arrays{};
+  uint32_t grid = 0;
+  int used = 0;
+  for (int32_t i = 0; i < count; ++i) {
+    if (params[i].n > 0) {
+      arrays.p[used] = params[i];
+      grid += blocks_for(params[i].n, 1 << 16);
+      arrays.end[used++] = grid;
+    }
+    if (used == kManyArrays || (i == count - 1 && used > 0)) {
+      hipLaunchKernelGGL(k_dense_update, dim3(grid), dim3(kBlock), 0, s, arrays, o, c1, c2);
+      grid = 0;
+      used = 0;
+    }
+  }
   return hipGetLastError() == hipSuccess ? DES_OK : DES_ERR_DEVICE;
+}
+
+des_status_t des_dense_update(float *theta, const float *grad, float *s1, float *s2, int64_t n,
+                              const des_optimizer_t *optimizer, void *stream) {
+  if (n < 0) return DES_ERR_INVALID_ARG;
+  const des_dense_param_t p = {theta, grad, s1, s2, n};
+  return des_dense_update_many(&p, 1, optimizer, stream);
 }
 
 }  // extern "C"

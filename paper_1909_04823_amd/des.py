@@ -29,7 +29,7 @@ EXPORTS = [
     "des_backward_update_sgd", "des_backward_update_adagrad", "des_backward_update", "des_backward_merge", "des_backward_prepare",
     "des_dnn_partial_forward", "des_dnn_backward_bytes", "des_dnn_backward",
     "des_batch_validate", "des_table_migrate_bytes", "des_table_migrate", "des_table_compact", "des_table_mark_seen", "des_table_select_recent",
-    "des_aggregate_bias_act", "des_dense_workspace_bytes", "des_bias_act_backward", "des_bias_act_backward_static", "des_head", "des_dense_update",
+    "des_aggregate_bias_act", "des_dense_workspace_bytes", "des_bias_act_backward", "des_bias_act_backward_static", "des_head", "des_dense_update", "des_dense_update_many",
     "des_cross_partial", "des_cross_apply", "des_cross_backward_bytes", "des_cross_backward", "des_cross_partial_backward",
     "des_cross_net_bytes", "des_cross_net_partial", "des_cross_net_forward", "des_cross_net_backward",
     "des_ceiling_gather_bytes", "des_ceiling_gather", "des_ceiling_update",
@@ -49,6 +49,10 @@ class TableConfig(C.Structure):
 class BatchDesc(C.Structure):
     _fields_ = [("B", C.c_int64), ("F", C.c_int32), ("nnz", C.c_int64), ("keys", C.c_void_p),
                 ("offsets", C.c_void_p), ("vals", C.c_void_p)]
+
+
+class DenseParam(C.Structure):
+    _fields_ = [("theta", C.c_void_p), ("grad", C.c_void_p), ("s1", C.c_void_p), ("s2", C.c_void_p), ("n", C.c_int64)]
 
 
 class BackwardIO(C.Structure):
@@ -100,6 +104,7 @@ _sig = {
     "des_bias_act_backward_static": [vp, vp, i64, i32, i32, vp, vp, vp],
     "des_head": [vp, vp, vp, vp, vp, vp, i64, i32, vp, vp, vp, vp, vp, vp, vp, vp, C.c_size_t, vp],
     "des_dense_update": [vp, vp, vp, vp, i64, C.POINTER(Optimizer), vp],
+    "des_dense_update_many": [C.POINTER(DenseParam), i32, C.POINTER(Optimizer), vp],
     "des_batch_validate": [vp, C.POINTER(BatchDesc), vp, C.POINTER(i64), vp],
     "des_table_migrate_bytes": [i64, C.POINTER(C.c_size_t)],
     "des_table_migrate": [vp, vp, vp, vp, vp, C.POINTER(i64), vp],
@@ -578,6 +583,13 @@ def head(labels: torch.Tensor, g_logit: torch.Tensor, workspace: torch.Tensor, A
 def dense_update(theta: torch.Tensor, grad: torch.Tensor, optimizer: Optimizer, s1=None, s2=None):
     _check(_lib.des_dense_update(_ptr(theta), _ptr(grad), _ptr(s1), _ptr(s2), theta.numel(), C.byref(optimizer),
                                  _stream()), "des_dense_update")
+
+
+def dense_update_many(params, optimizer: Optimizer):
+    """One optimizer step on several arrays that do not overlap: (theta, grad, s1, s2) each, s1 and s2 None where the optimizer keeps
+    no such state (des_dense_update_many: one launch per 16)."""
+    descs = (DenseParam * len(params))(*[(_ptr(p), _ptr(g), _ptr(s1), _ptr(s2), p.numel()) for p, g, s1, s2 in params])
+    _check(_lib.des_dense_update_many(descs, len(params), C.byref(optimizer), _stream()), "des_dense_update_many")
 
 
 def ceiling_gather(emb: torch.Tensor, rows: torch.Tensor, sink: Optional[torch.Tensor] = None,

@@ -193,8 +193,7 @@ class Model:
                                g_pool=self.g_pool if self.dnn else None,
                                dbg=dbg if dbg is not None else {"n_uniq": self.n_uniq})
         dn = des.Optimizer(**dict(self.opt_dense, step=self.step_no))
-        for k in self.params:
-            des.dense_update(self.params[k], g[k], dn, self.s1[k], self.s2[k])
+        des.dense_update_many([(p, g[k], self.s1[k], self.s2[k]) for k, p in self.params.items()], dn)
 
     def train_step(self, batch: des.Batch, labels: torch.Tensor, insert: bool = True, overlap: bool = True):
         """find -> forward -> backward -> updates.  With `overlap` the row-sorting half of the sparse backward

@@ -249,3 +249,24 @@ def test_dnn_weight_gradient_has_no_drift(des):
     _, dW = _gradients(des, torch, pool, W, dY)
     ref = pool.reshape(40003, 64).astype(np.float64).T @ dY.astype(np.float64)
     assert abs((dW - ref).mean()) < 3e-8 * np.sqrt((ref * ref).mean())
+
+
+@pytest.mark.parametrize("opt", ["OPT_SGD", "OPT_ADAGRAD", "OPT_ADAM", "OPT_FTRL"])
+def test_dense_update_of_many_arrays(des, opt):
+    """The same bits as one call per array, over more arrays than a launch takes: empty ones, single values, edges of workgroups."""
+    import torch
+    sizes = [1, 0, 255, 256, 257, 1000, 3, 70000, 1, 511, 512, 513, 2, 4096, 4097, 65, 64, 0, 12345, 7]
+    gen = torch.Generator(device="cuda").manual_seed(3)
+
+    def arrays():
+        gen.manual_seed(3)
+        return [tuple(torch.rand(n, generator=gen, device="cuda") + 0.1 for _ in range(4)) for n in sizes]
+
+    o = des.Optimizer(opt_emb=getattr(des, opt), lr=0.05, eps=1e-8, beta1=0.9, beta2=0.999, step=3, ftrl_alpha=0.05, ftrl_beta=1.0,
+                      ftrl_l1=0.01, ftrl_l2=0.1)
+    one, many = arrays(), arrays()
+    for theta, g, s1, s2 in one:
+        des.dense_update(theta, g, o, s1, s2)
+    des.dense_update_many(many, o)
+    for a, b in zip(one, many):
+        assert all(torch.equal(x, y) for x, y in zip(a, b))
