@@ -189,7 +189,7 @@ __global__ __launch_bounds__(kBlock) void k_slot_bounds(const Slot *__restrict__
 }
 
 // One workgroup: turns the tiles' counts into exclusive sums, sets the table's row count and leaves for the host what it decides
-// by: {rows kept, first dropped row (n if none), slot tiles without an empty slot}.
+// by: {rows kept, first dropped row (n if none), whether a slot tile has no empty slot}.
 constexpr int kTellBlock = 1024;
 __global__ __launch_bounds__(kTellBlock) void k_keep_tell(Ctrl *ctrl, const uint8_t *__restrict__ keep, int64_t n,
                                                            uint32_t *__restrict__ counts, const uint32_t *__restrict__ first_empty,
@@ -200,25 +200,53 @@ __global__ __launch_bounds__(kTellBlock) void k_keep_tell(Ctrl *ctrl, const uint
   const int64_t nb = (n + kKeepTile - 1) / kKeepTile;
   if (threadIdx.x == 0) { first_tile = 0xFFFFFFFFu; full_tiles = 0; first_row = kKeepTile; }
   __syncthreads();
-  uint32_t carry = 0;                                         // rows are fewer than 2^31
-  for (int64_t base = 0; base < nb; base += kTellBlock) {
-    const int64_t i = base + threadIdx.x;
-    const uint32_t c = i < nb ? counts[i] : 0u;
-    uint32_t total;
-    const uint32_t before = block_sum_before(c, lds, total);
-    if (i < nb) {
-      counts[i] = carry + before;
-      if (c < (uint32_t)min((int64_t)kKeepTile, n - i * kKeepTile)) atomicMin(&first_tile, (unsigned int)i);
-    }
-    carry += total;
+  // Each thread takes consecutive tiles, whose counts it adds up, and, once it knows what lies before, replaces; rows are fewer than
+  // 2^31.  All loads of a step are requested together.
+  constexpr int U = 4, UB = 8;
+  const int64_t per = (nb + kTellBlock - 1) / kTellBlock, i0 = min(threadIdx.x * per, nb), i1 = min(i0 + per, nb);
+  uint32_t sum = 0, carry;
+  for (int64_t i = i0; i < i1; i += U) {
+    uint32_t c[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) c[j] = counts[min(i + j, i1 - 1)];
+#pragma unroll
+    for (int j = 0; j < U; ++j) sum += i + j < i1 ? c[j] : 0u;
   }
-  for (int64_t t = threadIdx.x; t < ntiles; t += kTellBlock)
-    if (first_empty[t] >= kSlotTile) atomicAdd(&full_tiles, 1u);
+  bool full = false;
+  for (int64_t t = threadIdx.x; t < ntiles; t += UB * kTellBlock) {
+    uint32_t e[UB];
+#pragma unroll
+    for (int j = 0; j < UB; ++j) e[j] = first_empty[min(t + j * kTellBlock, ntiles - 1)];
+#pragma unroll
+    for (int j = 0; j < UB; ++j) full |= e[j] >= kSlotTile;
+  }
+  if (full) full_tiles = 1;
+  uint32_t before = block_sum_before(sum, lds, carry), dropped = 0xFFFFFFFFu;   // the thread's first tile with a dropped row
+  for (int64_t i = i0; i < i1; i += U) {
+    uint32_t c[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) c[j] = counts[min(i + j, i1 - 1)];
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      if (i + j >= i1) break;
+      counts[i + j] = before;
+      before += c[j];
+      if (c[j] < (uint32_t)min((int64_t)kKeepTile, n - (i + j) * kKeepTile)) dropped = min(dropped, (uint32_t)(i + j));
+    }
+  }
+  // Of a wave only the lowest lane that found one says so: LDS atomics on one address run one after the other (a tile's 2048 dropped
+  // rows and 600 tiles with dropped ones: 17.9 -> 5.4 us).
+  const auto lowest = [](bool found) {
+    const unsigned long long lanes = __ballot(found);
+    return found && (int)(threadIdx.x % kWave) == __ffsll(lanes) - 1;
+  };
+  if (lowest(dropped != 0xFFFFFFFFu)) atomicMin(&first_tile, dropped);
   __syncthreads();
   if (first_tile != 0xFFFFFFFFu) {                            // uniform
     const int64_t r0 = (int64_t)first_tile * kKeepTile;
+    static_assert(kKeepTile % kTellBlock == 0, "whole waves");
     for (int i = threadIdx.x; i < kKeepTile; i += kTellBlock)
-      if (r0 + i < n && !keep[r0 + i]) atomicMin(&first_row, i);
+      if (lowest(r0 + i < n && !keep[r0 + i])) atomicMin(&first_row, i);
   }
   __syncthreads();
   if (threadIdx.x == 0) {
