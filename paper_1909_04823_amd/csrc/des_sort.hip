@@ -295,6 +295,7 @@ __device__ inline unsigned long long same_digit(uint32_t d, int bits, unsigned l
 // per lane, with the last start before each of them.  Without the pass that wrote (row, bag) pairs first the kernels up to here
 // take, at 3.7e5 / 1.0e6 / 8.2e6 / 1.05e8 entries, 33 -> 29, 48 -> 37, 169 -> 145 and 2204 -> 1863 us.  (Three waves per SIMD instead
 // of four, which spill 16 bytes: 46 against 43 us at 8.0e6.)
+constexpr uint32_t kWideTile = 16;       // bags per entry of a tile from which a binary search per entry takes no longer than walking them
 template <typename KeyT, bool kHasPayload, int kItems, int kBits, bool kCsr>
 __global__ __launch_bounds__(kBlock, kItems == kSortItems ? 4 : 8) void k_radix_scatter(const KeyT *__restrict__ keys_in,
                                                            const uint32_t *__restrict__ pay_in,
@@ -353,11 +354,23 @@ __global__ __launch_bounds__(kBlock, kItems == kSortItems ? 4 : 8) void k_radix_
   if (kCsr) {
     first_bag = csr.tile_bag[tile_no];
     const uint32_t last_bag = min(csr.tile_bag[tile_no + 1], (uint32_t)csr.nbags - 1u);
-    for (uint32_t b = first_bag + 1 + threadIdx.x; b <= last_bag; b += kBlock) {
-      const int64_t at = csr.offsets[b] - tile;
-      if (at >= 0 && at < tile_n && csr.offsets[b + 1] - tile > at) {
+    if (last_bag - first_bag > kWideTile * kTile) {     // a long run of empty bags lies between: every entry looks its own bag up
+      for (int at = threadIdx.x; at < tile_n; at += kBlock) {
+        uint32_t lo = first_bag, hi = last_bag + 1;
+        while (hi - lo > 1) {
+          const uint32_t mid = (lo + hi) >> 1;
+          if (csr.offsets[mid] <= tile + at) lo = mid; else hi = mid;
+        }
         atomicOr(&starts[at >> 5], 1u << (at & 31));
-        bag_at[at] = b;
+        bag_at[at] = lo;
+      }
+    } else {
+      for (uint32_t b = first_bag + 1 + threadIdx.x; b <= last_bag; b += kBlock) {
+        const int64_t at = csr.offsets[b] - tile;
+        if (at >= 0 && at < tile_n && csr.offsets[b + 1] - tile > at) {
+          atomicOr(&starts[at >> 5], 1u << (at & 31));
+          bag_at[at] = b;
+        }
       }
     }
   }

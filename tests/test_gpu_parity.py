@@ -838,6 +838,7 @@ def test_merge_chunk_length_limits(oracle, des, n, D, lens, with_vals):
     (1 << 20, 300000, True),                # the last size with tiles of 1024
     ((1 << 20) + 1, 2000000, False),        # the first with tiles of 4096, most bags empty
     ((1 << 20) + 4095, 64, True),           # bags over several of them
+    (60000, 240000, True),                  # all but 4000 bags in one empty run in the middle of a tile
 ])
 def test_merge_finds_the_bags(oracle, des, n, nbags, with_vals):
     """Merged sums and counts where the bags' sizes differ most from the usual ones: empty ones and ones longer than a tile."""
@@ -846,6 +847,8 @@ def test_merge_finds_the_bags(oracle, des, n, nbags, with_vals):
     F, D = 4, 4
     keys = synth.scramble64(rng.zipf(1.3, n).astype(np.uint64) % np.uint64(5000) + np.uint64(1))
     cuts = np.sort(rng.integers(0, n + 1, size=nbags - 1))
+    if nbags == 240000:
+        cuts[:2000], cuts[2000:-2000], cuts[-2000:] = cuts[:2000] % (n // 2), n // 2, n // 2 + cuts[-2000:] % (n // 2)
     cuts[:2], cuts[-1] = 0, n                               # empty ones at both ends
     offsets = np.concatenate([[0], np.sort(cuts), [n]]).astype(np.int32)
     vals = rng.uniform(0.25, 2.0, n).astype(np.float32) if with_vals else None
