@@ -1,0 +1,18 @@
+// Index arithmetic of kernels whose lanes also read what they do not use, where every index has to be one that the caller's array
+// has.  Plain C++, so that a host program can walk through it.
+#pragma once
+#include <stdint.h>
+
+#ifdef __HIPCC__
+#define DES_INDEX __host__ __device__ inline
+#else
+#define DES_INDEX inline
+#endif
+
+namespace des {
+
+// Aggregation of the shards' partials P_sum[K][B][D] with eight lanes per sample: first of the four columns that lane `sub` of sample
+// `b` requests of the first shard.  A lane without columns requests its sample's first ones, which are there and aligned as P_sum is.
+DES_INDEX int64_t ahead_column(int64_t b, int D, int sub) { return b * D + (sub < D / 4 ? sub * 4 : 0); }
+
+}  // namespace des

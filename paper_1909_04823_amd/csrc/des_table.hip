@@ -15,6 +15,7 @@
 #include <mutex>
 #include <new>
 #include <vector>
+#include "des_index.h"
 #include "des_internal.h"
 
 using namespace des;
@@ -535,10 +536,8 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_forward(const float *__res
   double q = 0.0, scalar = 0.0;
   if (kAhead) {
     constexpr int U = 8;
-    const int64_t col = at * D + sub * 4;
-    const bool columns = P_sum && sub < D / 4;
-    const float *p0 = columns ? P_sum + col : scalars;    // no columns: any partials, left out below
-    const int64_t pitch = columns ? B * D : 0;
+    const int64_t col = ahead_column(at, D, sub), pitch = B * D;
+    const bool columns = P_sum && sub < D / 4;            // lanes without read some of their sample's, left out below
     double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
     for (int s0 = 0; s0 < K; s0 += U) {
       float4 p[U];
@@ -546,7 +545,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_forward(const float *__res
 #pragma unroll
       for (int k = 0; k < U; ++k) {
         const int s = min(s0 + k, K - 1);
-        if (P_sum) p[k] = *reinterpret_cast<const float4 *>(p0 + s * pitch);
+        if (P_sum) p[k] = *reinterpret_cast<const float4 *>(P_sum + s * pitch + col);
         sc[k] = scalars[(int64_t)s * B + at];
       }
 #pragma unroll

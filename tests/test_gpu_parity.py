@@ -879,6 +879,43 @@ def test_merge_walk_of_a_chunk(oracle, des, n, D, lens, with_vals):
     test_merge_chunk_length_limits(oracle, des, n, D, lens, with_vals)
 
 
+# ------------------------------------------------- aggregation of few partials --------------------
+@pytest.mark.parametrize("K,B", [(1, 1), (2, 1), (3, 1), (1, 2), (1, 3), (4, 1), (2, 7), (9, 5), (17, 33), (3, 16384), (3, 16385)])
+@pytest.mark.parametrize("D", [4, 8, 12, 16, 32, 36, 64, 100])
+def test_aggregate_forward_of_few_partials(des, K, B, D):
+    """Down to one partial, the scalars' arrays of exactly K*B floats at an odd address: sums in double in shard order, rounded once,
+    hence the same bits; fm2 differs by the order in which its squares are added (the bound of the other comparisons)."""
+    import torch
+    rng = np.random.default_rng(K * 1000 + B + D)
+    P_sum, P_sq, P_lr = (rng.standard_normal(s).astype(np.float32) for s in ((K, B, D), (K, B), (K, B)))
+
+    def odd(a):
+        return torch.cat([torch.zeros(1), torch.from_numpy(a).reshape(-1)]).cuda()[1:].reshape(a.shape)
+
+    def want(a):
+        total = np.zeros(a.shape[1:])
+        for part in a:
+            total += part
+        return total
+
+    d_sum, d_sq, d_lr = torch.from_numpy(P_sum).cuda(), odd(P_sq), odd(P_lr)
+    assert d_sq.data_ptr() % 16 == 4 and d_sum.data_ptr() % 16 == 0
+    f32 = lambda a: a.astype(np.float32)
+    for lr, fm in ((True, True), (True, False), (False, True)):
+        z = lambda *s: torch.full(s, float("nan"), device="cuda")
+        A_lr, A_sum, A_sq, fm2 = z(B), z(B, D), z(B), z(B)
+        des.aggregate_forward(d_lr if lr else None, d_sum if fm else None, d_sq if fm else None, A_lr if lr else None,
+                              A_sum if fm else None, A_sq if fm else None, fm2 if fm else None)
+        torch.cuda.synchronize()
+        if lr:
+            assert_equal(A_lr.cpu().numpy(), f32(want(P_lr)), "A_lr")
+        if fm:
+            s = want(P_sum)
+            assert_equal(A_sum.cpu().numpy(), f32(s), "A_sum")
+            assert_equal(A_sq.cpu().numpy(), f32(want(P_sq)), "A_sq")
+            assert_close(fm2.cpu().numpy(), f32(0.5 * ((s * s).sum(1) - want(P_sq))), "fm2")
+
+
 # ------------------------------------------------- one-workgroup sort and its neighbours ---------
 @pytest.mark.parametrize("n,B,F,capacity,vals", [
     (1, 1, 1, 1, False), (33, 3, 5, 300, True), (513, 40, 3, 1 << 16, False), (4095, 7, 9, 20000, True),
