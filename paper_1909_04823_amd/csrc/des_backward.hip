@@ -16,6 +16,7 @@
 //   d/dv += x*(g_fm[b]*A_sum[b,:] + g_pool[b,f,:]) - v * (x*x*g_fm[b])
 // i.e. the row's own vector v enters only through one scalar per segment, so v is read once.
 #include <math.h>
+#include "des_index.h"
 #include "des_internal.h"
 
 namespace des {
@@ -82,7 +83,7 @@ struct BwdArgs {
   int64_t *n_uniq_out;
 };
 
-__device__ inline int chunks_of(const BwdArgs &a, int len) { return (len + (1 << a.chunk_shift) - 1) >> a.chunk_shift; }
+__device__ inline int chunks_of(const BwdArgs &a, uint32_t len) { return (int)((len + (1u << a.chunk_shift) - 1u) >> a.chunk_shift); }
 
 __device__ inline float4 ld4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
 __device__ inline void st4(float *p, float4 v) { *reinterpret_cast<float4 *>(p) = v; }
@@ -116,16 +117,16 @@ __global__ __launch_bounds__(kBlock) void k_expand(const BwdArgs a, uint32_t *__
     __syncthreads();
     for (int i = threadIdx.x; i <= nb; i += kBlock) offs[i] = a.offsets[bag0 + i];
     __syncthreads();
-    const int e0 = offs[0], e1 = offs[nb];
-    for (int e = e0 + threadIdx.x; e < e1; e += kBlock) {
+    const uint32_t e0 = offs[0], e1 = offs[nb];
+    for (uint32_t e = e0 + threadIdx.x; e < e1; e += kBlock) {
       int lo = 0, hi = nb;                              // largest i with offs[i] <= e
       while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
-        if (offs[mid] <= e) lo = mid; else hi = mid;
+        if ((uint32_t)offs[mid] <= e) lo = mid; else hi = mid;
       }
       const int r = a.rows[e];
       key_out[e] = r >= 0 ? (uint32_t)r : a.missing;
-      pay_out[e] = kHasVals ? (uint32_t)e : (uint32_t)(bag0 + lo);
+      pay_out[e] = kHasVals ? e : (uint32_t)(bag0 + lo);
       if (kHasVals) a.bag_of[e] = (int32_t)(bag0 + lo);
     }
   }
@@ -629,10 +630,10 @@ __device__ inline void accumulate_batch(const BwdArgs &a, const uint32_t (&bag)[
 
 // Bags (and values) of the sorted entries i .. i+U-1, clipped at i1.
 template <bool kHasVals, int U>
-__device__ inline void load_batch_meta(const BwdArgs &a, int i, int i1, uint32_t (&bag)[U], bool (&live)[U], float (&x)[U]) {
+__device__ inline void load_batch_meta(const BwdArgs &a, uint32_t i, uint32_t i1, uint32_t (&bag)[U], bool (&live)[U], float (&x)[U]) {
 #pragma unroll
   for (int k = 0; k < U; ++k) {
-    live[k] = i + k < i1;
+    live[k] = i + k < i1;                                     // unsigned, as where it is called from: see entry_ahead
     uint32_t p = live[k] ? a.pay_sorted[i + k] : 0u;
     x[k] = 1.f;
     if (kHasVals) {
@@ -646,12 +647,12 @@ __device__ inline void load_batch_meta(const BwdArgs &a, int i, int i1, uint32_t
 // Sums over the sorted entries [i0, i1), U at a time; the payloads of the next U entries are requested
 // before the gradient rows of the current ones, so a batch costs one memory round trip, not two.
 template <int D, bool kHasVals, int U>
-__device__ inline void reduce_entries(const BwdArgs &a, int i0, int i1, int sub, Acc &acc) {
+__device__ inline void reduce_entries(const BwdArgs &a, uint32_t i0, uint32_t i1, int sub, Acc &acc) {
   uint32_t nbag[U];
   bool nlive[U];
   float nx[U];
   if (i0 < i1) load_batch_meta<kHasVals, U>(a, i0, i1, nbag, nlive, nx);
-  for (int i = i0; i < i1; i += U) {
+  for (uint32_t i = i0; i < i1; i += U) {
     uint32_t bag[U];
     bool live[U];
     float x[U];
@@ -798,7 +799,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kSecond 
     const int rest = i1 - 1;                               // the segment's last entry: what a dead lane or entry reads
     // The payloads of the next G entries are fetched lane by lane in the same round trip as the row state and
     // the first entry's gradients, so a segment of up to G+1 entries costs 2 + ceil((len-1)/U) round trips.
-    uint32_t mine = G >= U ? a.pay_sorted[min(i0 + 1 + sub, rest)] : 0u;
+    uint32_t mine = G >= U ? a.pay_sorted[entry_ahead(i0, 1 + sub, rest)] : 0u;
     RowState st = load_row<D, kSecond>(a, row, sub);
     float x0 = 1.f;
     uint32_t bag0 = p0;
@@ -816,7 +817,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kSecond 
       float myx = 1.f;
       const int glane = (int)(threadIdx.x & (kWave - 1)) - sub;       // first lane of this group in the wave
       for (int base = 1; base < len; base += G) {
-        if (base > 1) mine = a.pay_sorted[min(i0 + base + sub, rest)];
+        if (base > 1) mine = a.pay_sorted[entry_ahead(i0, base + sub, rest)];
         if (kHasVals) {
           myx = a.vals[mine];
           mine = (uint32_t)a.bag_of[mine];
@@ -858,7 +859,7 @@ struct Walk {
 // entries of 32 floats 165 -> 150 us, 3.7e5 of 32 with values 17.3 -> 14.4, 8.0e6 of 64 366 -> 359.  U = 2 / 8 (150 / 162,
 // 15.2 / 14.9, 358 / 365) and six waves per SIMD (169, 20.8, 380) are no better.
 template <int D, bool kHasVals>
-__device__ inline Acc walk_entries(const BwdArgs &a, int lo, int hi, Walk<D> &lds) {
+__device__ inline Acc walk_entries(const BwdArgs &a, uint32_t lo, uint32_t hi, Walk<D> &lds) {
   constexpr int G = Walk<D>::G, NG = Walk<D>::NG, U = Walk<D>::U, kBatch = Walk<D>::kBatch, kLoads = Walk<D>::kLoads;
   uint2 (&l_bag)[kBatch] = lds.bag;
   float2 (&l_x)[kBatch] = lds.x;
@@ -869,15 +870,15 @@ __device__ inline Acc walk_entries(const BwdArgs &a, int lo, int hi, Walk<D> &ld
   float x[kLoads];
 #pragma unroll
   for (int q = 0; q < kLoads; ++q) {
-    bag[q] = a.pay_sorted[min(lo + q * kWave + lane, hi - 1)];
-    pay_n[q] = a.pay_sorted[min(lo + kBatch + q * kWave + lane, hi - 1)];
+    bag[q] = a.pay_sorted[entry_ahead(lo, q * kWave + lane, hi - 1)];
+    pay_n[q] = a.pay_sorted[entry_ahead(lo, kBatch + q * kWave + lane, hi - 1)];
     x[q] = 1.f;
   }
   if (kHasVals) {
 #pragma unroll
     for (int q = 0; q < kLoads; ++q) { x[q] = a.vals[bag[q]]; bag[q] = (uint32_t)a.bag_of[bag[q]]; }
   }
-  for (int base = lo; base < hi; base += kBatch) {
+  for (uint32_t base = lo; base < hi; base += kBatch) {
     float gf[kLoads], gl[kLoads], xc[kLoads];
 #pragma unroll
     for (int q = 0; q < kLoads; ++q) {
@@ -892,9 +893,9 @@ __device__ inline Acc walk_entries(const BwdArgs &a, int lo, int hi, Walk<D> &ld
     for (int q = 0; q < kLoads; ++q) {
       bag[q] = pay_n[q];
       if (kHasVals) { x[q] = a.vals[pay_n[q]]; bag[q] = (uint32_t)a.bag_of[pay_n[q]]; }
-      pay_n[q] = a.pay_sorted[min(base + 2 * kBatch + q * kWave + lane, hi - 1)];
+      pay_n[q] = a.pay_sorted[entry_ahead(base, 2 * kBatch + q * kWave + lane, hi - 1)];
     }
-    const int cnt = min(kBatch, hi - base), per = (cnt + NG - 1) / NG;
+    const int cnt = min(kBatch, (int)(hi - base)), per = (cnt + NG - 1) / NG;
     const int mine = g * per, upto = min(mine + per, cnt);    // this lane group's run of the batch
     for (int k0 = 0; k0 < per; k0 += U) {
       float4 gp[U], as[U];
@@ -984,8 +985,8 @@ __global__ __launch_bounds__(kBlock, D == 4 ? 4 : 5) void k_long_partial(const B
   const int u = a.long_seg[j];
   const int seg_lo = a.seg_off[u], seg_hi = a.seg_off[u + 1];
   const uint32_t c0 = a.long_c0[j], k_seg = chunk_of_wave(wave_no, c0, (uint32_t)chunks_of(a, seg_hi - seg_lo));
-  const int c_lo = seg_lo + (int)(k_seg << a.chunk_shift);
-  const Acc acc = walk_entries<D, kHasVals>(a, c_lo, min(c_lo + (1 << a.chunk_shift), seg_hi), lds[wave]);
+  const uint32_t c_lo = seg_lo + (k_seg << a.chunk_shift);
+  const Acc acc = walk_entries<D, kHasVals>(a, c_lo, entry_ahead(c_lo, 1u << a.chunk_shift, seg_hi), lds[wave]);
   if (g == 0) {
     if (seg_hi - seg_lo <= (1 << a.chunk_shift)) {
       // the segment is this one chunk: the wave holds its whole sum and updates the row itself
