@@ -385,8 +385,10 @@ __device__ inline uint32_t small_excl_scan(uint32_t v, uint32_t *lds, uint32_t &
 template <bool kHasVals>
 __global__ __launch_bounds__(kSmallBlock) void k_sort_small(const BwdArgs a, uint32_t *__restrict__ pay_out, int bits) {
   __shared__ __align__(16) uint32_t skey[kSmallSort + 4], spay[kSmallSort];
-  __shared__ uint32_t cnt[kSmallWaves][1 << kSmallBits];
+  __shared__ __align__(16) uint32_t cnt[kSmallWaves][1 << kSmallBits];
   __shared__ __align__(16) uint32_t scan_lds[kSmallWaves];
+  static_assert(__alignof__(skey) >= 16 && __alignof__(spay) >= 16 && __alignof__(cnt) >= 16 && __alignof__(scan_lds) >= 16,
+                "accessed 16 bytes at a time");
   __shared__ uint32_t n_long;
   const int n = (int)a.n;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
