@@ -520,7 +520,9 @@ __global__ __launch_bounds__(kBlock) void k_fm_finalize(const float *__restrict_
 // are rounded, and lanes 0 and 1 add the two scalars.  Any of the LR and FM groups may be absent.
 // Bound by the round trips of its loads while few partials are there, by HBM beyond.  kAhead, for the former: the scalars' partials are
 // requested with the first columns', eight shards at a time, instead of after them: 48 samples of 8 x 16 4.2 -> 2.6 us, 16384 of
-// 16 x 32 13.4 -> 8.4, where each lane's requests no longer matter beside the bytes 12.7 -> 14.6 (65536 of 8 x 16).
+// 16 x 32 13.4 -> 8.4, where each lane's requests no longer matter beside the bytes 12.7 -> 14.6 (65536 of 8 x 16).  It needs columns
+// and several shards: the first-order sums alone are one round trip either way and took 1.9 -> 2.3 us (4096 samples of 2 shards),
+// 2.9 -> 5.5 (48 of 64), one shard has nothing to overlap (16384 of 32 columns 3.2 -> 3.5); two gain (2.6 -> 2.3, 48 of 16 columns).
 constexpr int64_t kAheadSamples = 16384;          // two workgroups per CU
 template <bool kAhead>
 __global__ __launch_bounds__(kBlock) void k_aggregate_forward(const float *__restrict__ P_lr,
@@ -918,7 +920,7 @@ des_status_t des_aggregate_forward(const float *P_lr, const float *P_sum, const 
   hipStream_t s = (hipStream_t)stream;
   ProfScope ps(KID_AGGREGATE, s);
   const dim3 grid(grid_for(B * 8, kBlock, 1ll << 30)), block(kBlock);
-  if (B <= kAheadSamples) hipLaunchKernelGGL(k_aggregate_forward<true>, grid, block, 0, s, P_lr, P_sum, P_sq, K, B, D, A_lr, A_sum, A_sq, fm2);
+  if (P_sum && K > 1 && B <= kAheadSamples) hipLaunchKernelGGL(k_aggregate_forward<true>, grid, block, 0, s, P_lr, P_sum, P_sq, K, B, D, A_lr, A_sum, A_sq, fm2);
   else hipLaunchKernelGGL(k_aggregate_forward<false>, grid, block, 0, s, P_lr, P_sum, P_sq, K, B, D, A_lr, A_sum, A_sq, fm2);
   return hipGetLastError() == hipSuccess ? DES_OK : DES_ERR_DEVICE;
 }
