@@ -98,13 +98,19 @@ __device__ inline void st4_stream(float *p, float4 v) {
   v4f r; r.x = v.x; r.y = v.y; r.z = v.z; r.w = v.w;
   __builtin_nontemporal_store(r, reinterpret_cast<v4f *>(p));
 }
-constexpr int64_t kBagsPerEntry = 4;
 __device__ inline float4 f4zero() { return make_float4(0.f, 0.f, 0.f, 0.f); }
 __device__ inline float4 f4add(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
 
-// (1) The first sorting pass takes rows and offsets as they are, as long as there are at most kBagsPerEntry bags per entry: its workgroups
-// walk the bags of a tile of entries (some 16 steps each at that ratio), which without a bound could be all of an almost empty
-// batch's.  Beyond that this kernel writes the pairs: sort key = row (or `missing`), payload = bag (or entry index with vals).  A workgroup takes
+// (1) The first sorting pass takes rows and offsets as they are where bags are not many more than entries: its workgroups walk the bags
+// of a tile of entries one step per 256 of them, which without a bound could be all of an almost empty batch's.  Row sort, segment
+// heads and split with pairs written first / from the batch, at 0.5, 1, 2 and 4 bags per entry: 2e4 entries 46/44, 46/46, 45/47, 46/51 us;
+// 1.0e6 70/64, 71/66, 72/69, 76/75; with the larger tiles 1.1e6 89/85, 88/91, 88/104, 92/132, 4.0e6 121/115, 126/122, 134/138, 151/171,
+// 1.6e7 364/330, 388/362, 438/428, 527/590.  So up to one bag per entry, and three quarters of one while there are few large tiles.
+inline bool bags_by_sort(int64_t n, int64_t nbags) {
+  return n > kFewSort && n <= 4 * kFewSort ? nbags <= n - n / 4 : nbags <= n;
+}
+
+// Beyond that this kernel writes the pairs: sort key = row (or `missing`), payload = bag (or entry index with vals).  A workgroup takes
 // kBlock consecutive bags, i.e. one contiguous range of entries, stages their offsets in LDS and
 // walks the entries with consecutive threads (coalesced reads and writes); the bag of an entry
 // is found by binary search in the staged offsets.
@@ -1248,7 +1254,7 @@ int sort_stage(des_table *t, BwdArgs &a, const Layout &L, hipStream_t s) {
     return 0;
   }
   const SortCsr csr{a.rows, a.offsets, a.nbags, a.missing, (uint32_t *)(ws + L.first_pay), a.vals ? a.bag_of : nullptr};
-  const bool from_csr = a.nbags <= kBagsPerEntry * n;
+  const bool from_csr = bags_by_sort(n, a.nbags);
   if (!from_csr) {
     ProfScope ps(KID_EXPAND, s);
     const dim3 grid(blocks_for(a.nbags, 1 << 20)), block(kBlock);     // one workgroup per kBlock bags

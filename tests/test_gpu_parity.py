@@ -833,12 +833,23 @@ def test_merge_chunk_length_limits(oracle, des, n, D, lens, with_vals):
 
 @pytest.mark.parametrize("n,nbags,with_vals", [
     (4097, 4, False),                       # bags over several tiles of 1024 entries, one entry in the last tile
-    (5120, 20480, True),                    # four bags per entry: the last ratio whose bags the sort finds itself
-    (5120, 20484, True),                    # one bag of every field more: pairs are written first
+    (5120, 20480, True),                    # pairs are written first, most bags empty
+    (5120, 20484, True),
+    (5120, 5120, True),                     # a bag per entry: the last ratio whose bags the sort finds itself
+    (5120, 5124, True),                     # one bag of every field more: pairs are written first
     (1 << 20, 300000, True),                # the last size with tiles of 1024
-    ((1 << 20) + 1, 2000000, False),        # the first with tiles of 4096, most bags empty
+    (1 << 20, 1 << 20, False),              # ... and ratio
+    ((1 << 20) + 1, 2000000, False),        # the first with tiles of 4096, pairs written first
+    ((1 << 20) + 1, 786432, True),          # ... the sort finds the bags, up to three quarters of a bag per entry
+    ((1 << 20) + 1, 786436, True),
     ((1 << 20) + 4095, 64, True),           # bags over several of them
-    (60000, 240000, True),                  # all but 4000 bags in one empty run in the middle of a tile
+    (1 << 22, 3 << 20, False),              # the last size with that ratio
+    ((1 << 22) + 1, 1 << 22, True),         # the first of a bag per entry again
+    (60000, 240000, True),                  # all but 4000 bags in one empty run in the middle of a tile, pairs written first
+    (60000, 60000, True),                   # the same for the sort to find: each entry of the tile searches
+    (61440, 60000, False),                  # the run on the border of two tiles
+    ((1 << 20) + 8002, 700000, True),       # the same in tiles of 4096: the middle of one
+    ((1 << 20) + 8192, 700000, False),      # ... and a border
 ])
 def test_merge_finds_the_bags(oracle, des, n, nbags, with_vals):
     """Merged sums and counts where the bags' sizes differ most from the usual ones: empty ones and ones longer than a tile."""
@@ -847,7 +858,7 @@ def test_merge_finds_the_bags(oracle, des, n, nbags, with_vals):
     F, D = 4, 4
     keys = synth.scramble64(rng.zipf(1.3, n).astype(np.uint64) % np.uint64(5000) + np.uint64(1))
     cuts = np.sort(rng.integers(0, n + 1, size=nbags - 1))
-    if nbags == 240000:
+    if nbags in (60000, 240000, 700000):
         cuts[:2000], cuts[2000:-2000], cuts[-2000:] = cuts[:2000] % (n // 2), n // 2, n // 2 + cuts[-2000:] % (n // 2)
     cuts[:2], cuts[-1] = 0, n                               # empty ones at both ends
     offsets = np.concatenate([[0], np.sort(cuts), [n]]).astype(np.int32)
