@@ -1207,7 +1207,7 @@ Layout layout_for(int D, int64_t n) {
   auto take = [&](size_t bytes) { size_t at = o; o += align_up(bytes, 256); return at; };
   L.key_a = take(m * 4); L.key_b = take(m * 4); L.pay_a = take(m * 4); L.pay_b = take(m * 4);
   L.bag_of = take(m * 4);
-  L.seg_off = take((m + 1) * 4); L.uniq_rows = take(m * 4); L.first_pay = take(m * 4);
+  L.seg_off = take((m + 1) * 4); L.uniq_rows = take(m * 4); L.first_pay = take(m * 4 > csr_scratch_bytes(n) ? m * 4 : csr_scratch_bytes(n));
   L.head_sums = take(((m + kHeadTile - 1) / kHeadTile + 1) * 4);
   L.long_seg = take(max_long * 4); L.long_c0 = take(max_long * 4);
   L.chunk_owner = take(max_chunks * 4);
@@ -1253,6 +1253,7 @@ int sort_stage(des_table *t, BwdArgs &a, const Layout &L, hipStream_t s) {
     else hipLaunchKernelGGL(k_sort_small<false>, dim3(1), dim3(kSmallBlock), 0, s, a, pay_a, bits);
     return 0;
   }
+  // the tiles' first bags lie where the segments' first payloads come later
   const SortCsr csr{a.rows, a.offsets, a.nbags, a.missing, (uint32_t *)(ws + L.first_pay), a.vals ? a.bag_of : nullptr};
   const bool from_csr = bags_by_sort(n, a.nbags);
   if (!from_csr) {
