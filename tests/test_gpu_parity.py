@@ -1061,3 +1061,68 @@ def test_forward_of_small_batches_adds_in_the_order_of_the_waves(des, F, policy)
             assert (P_sum == want).all() and (P_lr == want).all()
     finally:
         t.close()
+
+
+def short_bags(rng, B, F, D, shape):
+    """A batch of short bags: 'mixed' lengths 0 to 20, 'runs' of up to a hundred empty bags between them, or (a number) that many
+    entries in all.  A tenth of the IDs is not in the table when those below 3000 are."""
+    n_bags = B * F
+    if shape == "mixed":
+        lens = rng.choice([0, 0, 0, 1, 1, 2, 3, 20], n_bags)
+    elif shape == "runs":
+        lens = np.zeros(n_bags, np.int64)
+        at = np.cumsum(rng.integers(1, 100, n_bags // 20))
+        lens[at[at < n_bags]] = rng.integers(1, 12, int((at < n_bags).sum()))
+    else:
+        lens = np.full(n_bags, shape // n_bags)
+        lens[rng.integers(0, n_bags)] += shape - int(lens.sum())
+    offsets = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    n = int(offsets[-1])
+    return synth.Batch(B, F, synth.scramble64(rng.integers(1, 3300, n).astype(np.uint64)), offsets)
+
+
+def forward_of_short_bags(oracle, des, B, F, D, K, policy, shape):
+    rng = np.random.default_rng(B + F + D)
+    batch = short_bags(rng, B, F, D, shape)
+    p = Pair(oracle, des, D, 4000, K, policy, des.OPT_SGD, seed=2, max_n=max(batch.nnz, 1 << 12))
+    try:
+        known = synth.Batch(1, 1, synth.scramble64(np.arange(1, 3000, dtype=np.uint64)), np.array([0, 2999], np.int32))
+        p.find(known, insert=True)
+        assert (p.find(batch, insert=False) < 0).any()
+        p.forward(batch)
+        p.forward(batch, separate_calls=True)
+        batch.vals = rng.uniform(0.25, 2, batch.nnz).astype(np.float32)
+        p.find(batch, insert=False)
+        p.forward(batch, separate_calls=True)
+        p.forward(batch)
+    finally:
+        p.close()
+
+
+@pytest.mark.parametrize("policy", [0, 1])
+@pytest.mark.parametrize("B,F,D,K", [
+    (131073, 1, 4, 3),                                       # a lane per sample; the last workgroup takes one of 256
+    (65665, 2, 4, 4), (65537, 1, 8, 3),                      # two
+    (32769, 4, 4, 5), (32833, 2, 8, 7), (32770, 1, 16, 2),   # four
+    (16385, 8, 4, 5), (16390, 4, 8, 9), (16411, 1, 32, 4),   # eight
+    (8193, 13, 4, 8), (8200, 3, 16, 8), (8195, 1, 64, 4),    # sixteen
+    (4097, 32, 4, 8), (4099, 5, 16, 8), (4100, 4, 32, 8), (4103, 1, 128, 4),    # thirty-two: two samples per wave
+    (4095, 4, 32, 8),                                        # too few for it
+])
+def test_forward_of_several_samples_per_wave(oracle, des, B, F, D, K, policy):
+    """Few fields: part of a wave per sample, down to one lane; every output together and by itself, with absent rows and values."""
+    forward_of_short_bags(oracle, des, B, F, D, K, policy, "mixed")
+
+
+@pytest.mark.parametrize("policy", [0, 1])
+@pytest.mark.parametrize("B,F,D,K,shape", [
+    (700, 60, 4, 8, "mixed"), (700, 60, 8, 8, "mixed"), (513, 150, 4, 3, "runs"), (515, 300, 8, 5, "runs"), (600, 200, 16, 5, "runs"),
+    (300, 200, 32, 5, "runs"), (200, 300, 64, 4, "runs"), (100, 300, 128, 4, "runs"), (64, 300, 256, 2, "runs"),
+    (600, 4, 32, 8, 600 * 96), (600, 4, 32, 8, 600 * 96 + 1),       # twelve entries per lane group, and one more
+    (600, 3, 64, 8, 600 * 48), (600, 3, 64, 8, 600 * 48 + 1),
+    (600, 2, 128, 8, 600 * 24), (600, 2, 128, 8, 600 * 24 + 1),
+    (600, 1, 256, 8, 600 * 12), (600, 1, 256, 8, 600 * 12 + 1),
+])
+def test_forward_of_short_bags(oracle, des, B, F, D, K, policy, shape):
+    """Lane groups of few entries, of bags that end at different steps, and of runs of empty bags at either end of a group's range."""
+    forward_of_short_bags(oracle, des, B, F, D, K, policy, shape)
