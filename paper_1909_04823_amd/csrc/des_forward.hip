@@ -201,8 +201,9 @@ __global__ __launch_bounds__(kBlock, D == 32 && !kHasVals ? 6 : 4) void k_forwar
       const int end_l = my < e1 && at + 1 == end ? bag_l * D : -1;
       // read back with one broadcast LDS read per entry; same wave, program order: no barrier needed
       if (!kQuad) meta[lane] = make_int4(row_l, acc_l, end_l, __float_as_int(x_l));
-      // The first-order weight of this lane's own entry: one gather per chunk for the whole group.
-      float w_l = w_base[max(r_l, 0)];
+      // The first-order weight of this lane's own entry: one gather per chunk for the whole group (without first-order terms of one
+      // and the same element: without that a gather by row for nothing, 35 -> 29 us for the pooled sums alone of 4.3e6 entries of 4 floats).
+      float w_l = w_base[need_lr ? max(r_l, 0) : 0];
       double q_l = 0.0;                                   // sum of squares of this lane's own entry
       const int cnt = min(G, e1 - e);
 #pragma unroll
