@@ -139,6 +139,7 @@ __global__ __launch_bounds__(kBlock, D == 32 && !kHasVals ? 6 : 4) void k_forwar
     double bag_sq = 0.0;                                  // field partition: this lane's share of the bag's sum of squares
     int cur = f0;                                         // a bag that no entry to come lies before
     int cur_end = offs[min(f0 + 1, F)];                   // kQuad: where it ends
+    int cur_sh = kQuad && !kByKey ? f0 % K : 0;           // ... and its shard
 
     // metadata of entry e0 + sub of the first chunk; later chunks are fetched one chunk ahead
     int r_n = -1;
@@ -168,7 +169,11 @@ __global__ __launch_bounds__(kBlock, D == 32 && !kHasVals ? 6 : 4) void k_forwar
       if (kQuad) {
         end = cur_end;
         if (my < e1 && end <= at)
-          do { ++lo; end = offs[lo + 1]; } while (end <= at);
+          do {
+            ++lo;
+            end = offs[lo + 1];
+            if (!kByKey) cur_sh = cur_sh + 1 == K ? 0 : cur_sh + 1;
+          } while (end <= at);
         cur_end = end;
       } else {
         int ahead = 0;
@@ -193,11 +198,11 @@ __global__ __launch_bounds__(kBlock, D == 32 && !kHasVals ? 6 : 4) void k_forwar
       }
       const int bag_l = my < e1 ? lo : cur;
       cur = kQuad ? bag_l : __shfl(bag_l, lane - sub + min(G, e1 - e) - 1, kWave);
-      const int sh_l = !need_fm && !need_lr ? 0 : kByKey ? (int)((uint32_t)(mix64(key_l) >> 32) % (uint32_t)K) : bag_l % K;
-      // what the group needs of this lane's entry: row (0 if absent), its shard's accumulators (-1: absent), its bag's pooled
-      // row if it is the bag's last entry (-1: it is not), its value
+      const int sh_l = !need_fm && !need_lr ? 0 : kByKey ? (int)((uint32_t)(mix64(key_l) >> 32) % (uint32_t)K) : kQuad ? cur_sh : bag_l % K;
+      // what the group needs of this lane's entry: row (0 if absent), its shard's accumulators (negative: absent; by field their
+      // complement, for the bag that ends there), its bag's pooled row if it is the bag's last entry (-1: it is not), its value
       const int row_l = max(r_l, 0) & row_mask;
-      const int acc_l = r_l >= 0 ? sh_l * P : -1;
+      const int acc_l = r_l >= 0 ? sh_l * P : kByKey ? -1 : ~(sh_l * P);
       const int end_l = my < e1 && at + 1 == end ? bag_l * D : -1;
       // read back with one broadcast LDS read per entry; same wave, program order: no barrier needed
       if (!kQuad) meta[lane] = make_int4(row_l, acc_l, end_l, __float_as_int(x_l));
@@ -254,12 +259,11 @@ __global__ __launch_bounds__(kBlock, D == 32 && !kHasVals ? 6 : 4) void k_forwar
             if (md[i].z >= 0) {                            // the bag ends: pooled sum out, and to its shard under the field partition
               if (need_pool) st4(pool + (md[i].z + sub * 4), make_float4((float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3]));
               if (!kByKey && need_fm) {
-                const int s = (md[i].z / D) % K;
-                double *dst = sum + s * P + sub;
+                double *const shard = sum + (md[i].y ^ (md[i].y >> 31)), *const dst = shard + sub;
 #pragma unroll
                 for (int k = 0; k < 4; ++k) atomicAdd(dst + k * G, acc[k]);
                 const double q = group_sum<G>(bag_sq);
-                if (sub == 0) atomicAdd(sum + s * P + D, q);
+                if (sub == 0) atomicAdd(shard + D, q);
                 bag_sq = 0.0;
               }
               acc[0] = acc[1] = acc[2] = acc[3] = 0.0;
