@@ -99,6 +99,10 @@ __global__ __launch_bounds__(kBlock, D == 32 && !kHasVals ? 6 : 4) void k_forwar
   extern __shared__ __align__(16) double lds[];
   constexpr int G = D / 4;                 // lanes per row = entries per chunk
   constexpr int U = G < 8 ? G : D == 32 && !kHasVals ? 4 : 8;         // row gathers in flight per lane (4 / 8: D = 64 625 -> 598 us, D = 32 with values 21.9 -> 21.4, without 218 -> 219)
+  // Rows of one or two lanes: a wave's groups end their bags at up to 64 different steps, and stores among the steps are waited for with
+  // the next gathers (loads and stores complete in order).  So the pooled stores of a group's last bag and of bags without entries
+  // come behind its steps: 2.0e6 bags of 0 to 4 entries, 26 a sample, D = 4 / 8 125 / 114 -> 96 / 107 us, 60 a sample 126 -> 98 at D = 4.
+  constexpr bool kBehind = G <= 2;
   constexpr bool kQuad = G <= 4;           // a group lies inside a quad: its lanes' metadata comes by DPP instead of through LDS
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int g = lane / G, sub = lane % G;
@@ -132,7 +136,7 @@ __global__ __launch_bounds__(kBlock, D == 32 && !kHasVals ? 6 : 4) void k_forwar
     const uint64_t *keys = a.keys + first;
     const float *vals = kHasVals ? a.vals + first : nullptr;
     float *pool = a.pool + (b * F) * (int64_t)D;
-    if (need_pool)                                        // bags without entries; the others are stored at their last entry
+    if (need_pool && !kBehind)                            // bags without entries; the others are stored at their last entry
       for (int f = f0; f < f1; ++f)
         if (offs[f] == offs[f + 1]) st4(pool + (f * D + sub * 4), make_float4(0.f, 0.f, 0.f, 0.f));
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
@@ -203,7 +207,7 @@ __global__ __launch_bounds__(kBlock, D == 32 && !kHasVals ? 6 : 4) void k_forwar
       // complement, for the bag that ends there), its bag's pooled row if it is the bag's last entry (-1: it is not), its value
       const int row_l = max(r_l, 0) & row_mask;
       const int acc_l = r_l >= 0 ? sh_l * P : kByKey ? -1 : ~(sh_l * P);
-      const int end_l = my < e1 && at + 1 == end ? bag_l * D : -1;
+      const int end_l = my < (kBehind ? e1 - 1 : e1) && at + 1 == end ? bag_l * D : -1;
       // read back with one broadcast LDS read per entry; same wave, program order: no barrier needed
       if (!kQuad) meta[lane] = make_int4(row_l, acc_l, end_l, __float_as_int(x_l));
       // The first-order weight of this lane's own entry: one gather per chunk for the whole group (without first-order terms of one
@@ -285,6 +289,27 @@ __global__ __launch_bounds__(kBlock, D == 32 && !kHasVals ? 6 : 4) void k_forwar
         } else if (need_lr) {
           atomicAdd(dst + 1, l_l);
         }
+      }
+    }
+    if constexpr (kBehind) {
+      if (need_pool || (!kByKey && need_fm)) {
+        if (e0 < e1) {
+          const int last = group_lane<G>(cur, (e1 - e0 - 1) & (G - 1));   // bag of the range's last entry
+          if (need_pool) st4(pool + (last * D + sub * 4), make_float4((float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3]));
+          if (!kByKey && need_fm) {
+            double *const shard = sum + group_lane<G>(cur_sh, (e1 - e0 - 1) & (G - 1)) * P, *const dst = shard + sub;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) atomicAdd(dst + k * G, acc[k]);
+            const double q = group_sum<G>(bag_sq);
+            if (sub == 0) atomicAdd(shard + D, q);
+          }
+        }
+        if (need_pool)
+          for (int f = f0, start = offs[f0]; f < f1; ++f) {
+            const int next = offs[f + 1];
+            if (start == next) st4(pool + (f * D + sub * 4), make_float4(0.f, 0.f, 0.f, 0.f));
+            start = next;
+          }
       }
     }
   }
