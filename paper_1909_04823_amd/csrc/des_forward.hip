@@ -94,11 +94,15 @@ __device__ inline int group_lane(int v, int src) {
 // entry).  Otherwise the field partition of Section 5: a bag belongs to shard f mod K as a whole, so its sums
 // are formed in registers and the shard's accumulators take one update per bag.
 // kHasVals: the batch carries feature values; without them every x is 1 and the products with x are left out.
-template <int D, bool kByKey, bool kHasVals>
+// kFew: few entries per lane group, so that most of a batch of gathers would be of entries that are not there.  They are requested and
+// waited for all the same, hence fewer at a time (and fewer registers): 2.0e5 samples of 10 one-entry bags, D = 64 (1.0e5) / 32 204 / 251 ->
+// 159 / 225 us, 12 and more entries per group of D = 64 69 -> 72.
+constexpr int64_t kFewEntries = 12;
+template <int D, bool kByKey, bool kHasVals, bool kFew>
 __global__ __launch_bounds__(kBlock, D == 32 && !kHasVals ? 6 : 4) void k_forward(const FwdArgs a) {
   extern __shared__ __align__(16) double lds[];
   constexpr int G = D / 4;                 // lanes per row = entries per chunk
-  constexpr int U = G < 8 ? G : D == 32 && !kHasVals ? 4 : 8;         // row gathers in flight per lane (4 / 8: D = 64 625 -> 598 us, D = 32 with values 21.9 -> 21.4, without 218 -> 219)
+  constexpr int U = kFew ? (D >= 128 ? 4 : 2) : G < 8 ? G : D == 32 && !kHasVals ? 4 : 8;         // row gathers in flight per lane (4 / 8: D = 64 625 -> 598 us, D = 32 with values 21.9 -> 21.4, without 218 -> 219)
   // Rows of one or two lanes: a wave's groups end their bags at up to 64 different steps, and stores among the steps are waited for with
   // the next gathers (loads and stores complete in order).  So the pooled stores of a group's last bag and of bags without entries
   // come behind its steps: 2.0e6 bags of 0 to 4 entries, 26 a sample, D = 4 / 8 125 / 114 -> 96 / 107 us, 60 a sample 126 -> 98 at D = 4.
@@ -372,15 +376,22 @@ __global__ __launch_bounds__(kBlock) void k_pool_dense(const FwdArgs a, float *_
   }
 }
 
-template <int D>
+template <int D, bool kFew>
 void launch_forward(bool by_key, bool has_vals, dim3 grid, dim3 block, size_t shmem, hipStream_t s, const FwdArgs &a) {
   if (by_key) {
-    if (has_vals) hipLaunchKernelGGL((k_forward<D, true, true>), grid, block, shmem, s, a);
-    else hipLaunchKernelGGL((k_forward<D, true, false>), grid, block, shmem, s, a);
+    if (has_vals) hipLaunchKernelGGL((k_forward<D, true, true, kFew>), grid, block, shmem, s, a);
+    else hipLaunchKernelGGL((k_forward<D, true, false, kFew>), grid, block, shmem, s, a);
   } else {
-    if (has_vals) hipLaunchKernelGGL((k_forward<D, false, true>), grid, block, shmem, s, a);
-    else hipLaunchKernelGGL((k_forward<D, false, false>), grid, block, shmem, s, a);
+    if (has_vals) hipLaunchKernelGGL((k_forward<D, false, true, kFew>), grid, block, shmem, s, a);
+    else hipLaunchKernelGGL((k_forward<D, false, false, kFew>), grid, block, shmem, s, a);
   }
+}
+template <int D>
+void launch_forward(bool few, bool by_key, bool has_vals, dim3 grid, dim3 block, size_t shmem, hipStream_t s, const FwdArgs &a) {
+  if constexpr (D >= 32) {
+    if (few) return launch_forward<D, true>(by_key, has_vals, grid, block, shmem, s, a);
+  }
+  launch_forward<D, false>(by_key, has_vals, grid, block, shmem, s, a);
 }
 
 FwdArgs make_args(des_table *t, const des_batch_t *b, const int32_t *rows) {
@@ -434,15 +445,16 @@ des_status_t forward_launch(des_table *t, const des_batch_t *b, const int32_t *r
   const dim3 grid((unsigned)((b->B + spb - 1) / spb)), block(kBlock);
   const size_t shmem = 16 * (size_t)kBlock + (size_t)a.lds_per_sample * 8 * spb;
   const bool by_key = a.policy == DES_SHARD_KEY_HASH;
+  const bool few = b->nnz <= kFewEntries * b->B * (threads / (D / 4));
   ProfScope ps(KID_FORWARD, s);
   switch (D) {
-    case 4: launch_forward<4>(by_key, a.vals != nullptr, grid, block, shmem, s, a); break;
-    case 8: launch_forward<8>(by_key, a.vals != nullptr, grid, block, shmem, s, a); break;
-    case 16: launch_forward<16>(by_key, a.vals != nullptr, grid, block, shmem, s, a); break;
-    case 32: launch_forward<32>(by_key, a.vals != nullptr, grid, block, shmem, s, a); break;
-    case 64: launch_forward<64>(by_key, a.vals != nullptr, grid, block, shmem, s, a); break;
-    case 128: launch_forward<128>(by_key, a.vals != nullptr, grid, block, shmem, s, a); break;
-    case 256: launch_forward<256>(by_key, a.vals != nullptr, grid, block, shmem, s, a); break;
+    case 4: launch_forward<4>(few, by_key, a.vals != nullptr, grid, block, shmem, s, a); break;
+    case 8: launch_forward<8>(few, by_key, a.vals != nullptr, grid, block, shmem, s, a); break;
+    case 16: launch_forward<16>(few, by_key, a.vals != nullptr, grid, block, shmem, s, a); break;
+    case 32: launch_forward<32>(few, by_key, a.vals != nullptr, grid, block, shmem, s, a); break;
+    case 64: launch_forward<64>(few, by_key, a.vals != nullptr, grid, block, shmem, s, a); break;
+    case 128: launch_forward<128>(few, by_key, a.vals != nullptr, grid, block, shmem, s, a); break;
+    case 256: launch_forward<256>(few, by_key, a.vals != nullptr, grid, block, shmem, s, a); break;
     default: return DES_ERR_INVALID_ARG;
   }
   return hipGetLastError() == hipSuccess ? DES_OK : DES_ERR_DEVICE;
