@@ -97,12 +97,17 @@ __device__ inline int group_lane(int v, int src) {
 // kFew: few entries per lane group, so that most of a batch of gathers would be of entries that are not there.  They are requested and
 // waited for all the same, hence fewer at a time (and fewer registers): 2.0e5 samples of 10 one-entry bags, D = 64 (1.0e5) / 32 204 / 251 ->
 // 159 / 225 us, 12 and more entries per group of D = 64 69 -> 72.
+// Where accumulators leave LDS for no more than four workgroups per CU, registers saved are none gained and a batch of the usual size
+// is one round trip less: there only while a batch of these few takes all entries (D = 64, K = 32 / 60,
+// 24 / 50 bags a sample 119 / 114 -> 114 / 109 us, with the former kernel 110 / 105; D = 32 134 / 131 -> 131 / 128, 129 / 128).
 constexpr int64_t kFewEntries = 12;
+constexpr size_t kFewLds = 32 * 1024;
+constexpr int few_gathers(int D) { return D >= 128 ? 4 : 2; }
 template <int D, bool kByKey, bool kHasVals, bool kFew>
 __global__ __launch_bounds__(kBlock, D == 32 && !kHasVals ? 6 : 4) void k_forward(const FwdArgs a) {
   extern __shared__ __align__(16) double lds[];
   constexpr int G = D / 4;                 // lanes per row = entries per chunk
-  constexpr int U = kFew ? (D >= 128 ? 4 : 2) : G < 8 ? G : D == 32 && !kHasVals ? 4 : 8;         // row gathers in flight per lane (4 / 8: D = 64 625 -> 598 us, D = 32 with values 21.9 -> 21.4, without 218 -> 219)
+  constexpr int U = kFew ? few_gathers(D) : G < 8 ? G : D == 32 && !kHasVals ? 4 : 8;         // row gathers in flight per lane (4 / 8: D = 64 625 -> 598 us, D = 32 with values 21.9 -> 21.4, without 218 -> 219)
   // Rows of one or two lanes: a wave's groups end their bags at up to 64 different steps, and stores among the steps are waited for with
   // the next gathers (loads and stores complete in order).  So the pooled stores of a group's last bag and of bags without entries
   // come behind its steps: 2.0e6 bags of 0 to 4 entries, 26 a sample, D = 4 / 8 125 / 114 -> 96 / 107 us, 60 a sample 126 -> 98 at D = 4.
@@ -445,7 +450,7 @@ des_status_t forward_launch(des_table *t, const des_batch_t *b, const int32_t *r
   const dim3 grid((unsigned)((b->B + spb - 1) / spb)), block(kBlock);
   const size_t shmem = 16 * (size_t)kBlock + (size_t)a.lds_per_sample * 8 * spb;
   const bool by_key = a.policy == DES_SHARD_KEY_HASH;
-  const bool few = b->nnz <= kFewEntries * b->B * (threads / (D / 4));
+  const bool few = b->nnz <= (shmem > kFewLds ? few_gathers(D) : kFewEntries) * b->B * (threads / (D / 4));
   ProfScope ps(KID_FORWARD, s);
   switch (D) {
     case 4: launch_forward<4>(few, by_key, a.vals != nullptr, grid, block, shmem, s, a); break;

@@ -1122,6 +1122,9 @@ def test_forward_of_several_samples_per_wave(oracle, des, B, F, D, K, policy):
     (600, 3, 64, 8, 600 * 48), (600, 3, 64, 8, 600 * 48 + 1),
     (600, 2, 128, 8, 600 * 24), (600, 2, 128, 8, 600 * 24 + 1),
     (600, 1, 256, 8, 600 * 12), (600, 1, 256, 8, 600 * 12 + 1),
+    (2100, 4, 32, 32, 2100 * 16), (2100, 4, 32, 32, 2100 * 16 + 1), # two or four, where accumulators take much of the LDS
+    (600, 4, 64, 32, 600 * 16), (600, 4, 64, 32, 600 * 16 + 1),
+    (600, 2, 256, 8, 600 * 8), (600, 2, 256, 8, 600 * 8 + 1),
 ])
 def test_forward_of_short_bags(oracle, des, B, F, D, K, policy, shape):
     """Lane groups of few entries, of bags that end at different steps, and of runs of empty bags at either end of a group's range."""
