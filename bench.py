@@ -15,8 +15,10 @@ oracle, single-threaded, on a bounded sample of the same workload.
 from __future__ import annotations
 
 import argparse
+import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -66,17 +68,37 @@ def algorithmic_bytes(w, nnz, st, sort_passes, state_mult):
 PROFILE_TAG = {0: "tiny_lr_fm", 1: "dlrm_pooled", 2: "deepfm", 3: "streaming", 4: "large_table"}
 
 
+KERNEL_SOURCE = {"table": "des_table.hip", "aggregate": "des_table.hip", "forward": "des_forward.hip", "sort": "des_sort.hip",
+                 "backward": "des_backward.hip"}        # by the first word of a kernel's label
+
+
+def source_digest(name: str):
+    """Digest of a kernel source and the headers it is compiled with, without comments and white space."""
+    csrc = os.path.join(ROOT, "paper_1909_04823_amd", "csrc")
+    h = hashlib.sha256()
+    for part in (name, "des_internal.h", "des_index.h"):
+        with open(os.path.join(csrc, part)) as f:
+            code = re.sub(r"//[^\n]*|/\*.*?\*/", "", f.read(), flags=re.S)
+        h.update(re.sub(r"\s+", "", code).encode())
+    return h.hexdigest()[:16]
+
+
 def measured_traffic(index: int, label: str):
     """(HBM bytes per launch of kernel `label`, commit the counters were collected at) from the committed
-    rocprofv3 counter summary of this workload (profiles/<tag>_hbm_traffic.md: columns fetch MB / write MB, and a
-    line "Measured at commit: <id>"), or (None, None)."""
+    rocprofv3 counter summary of this workload (profiles/<tag>_hbm_traffic.md: columns fetch MB / write MB, a
+    line "Measured at commit: <id>" and lines "Source <file>: <digest>"), or (None, None).  Bytes of another state of the
+    kernel's source say nothing about the present kernel's time: then they are None."""
     path = os.path.join(ROOT, "profiles", f"{PROFILE_TAG[index]}_hbm_traffic.md")
     if not os.path.exists(path):
         return None, None
-    total, seen, commit = 0.0, False, None
+    source = KERNEL_SOURCE.get(label.split("_")[0])
+    total, seen, present, commit = 0.0, False, False, None
     for line in open(path):
+        line = line.strip()
         if line.lower().startswith("measured at commit:"):
             commit = line.split(":", 1)[1].strip().strip("`")
+        if source and line.replace("`", "").startswith(f"Source {source}:"):
+            present = line.split(":", 1)[1].strip().strip("`") == source_digest(source)
         cells = [c.strip() for c in line.split("|")]
         if len(cells) >= 6 and cells[2] == label:
             try:
@@ -84,7 +106,7 @@ def measured_traffic(index: int, label: str):
                 seen = True
             except ValueError:
                 pass
-    return (int(total), commit) if seen else (None, commit)
+    return (int(total), commit) if seen and present else (None, commit)
 
 
 def cpu_baseline(w, batch, sample_B, opt_code):
