@@ -769,7 +769,8 @@ __device__ inline void apply_row(const BwdArgs &a, int64_t u, int row, int sub, 
 // All gathers are unconditional and waited for once per step, ahead of the row's stores: with a condition around each (an
 // array the caller did not pass, an entry past the end) a step of two entries waited four times, and a segment's first
 // accesses behind the previous one's stores.  8.0e6 entries of 64 floats, 1.0e6 short segments 387 -> 341 us (their 1.6 GB at
-// 4.7 TB/s), 1.05e8 of 64 12.9 -> 11.5 ms, 8.2e6 of 32 128 -> 117 us, 3.7e5 of 32 with values and Adam 39.4 -> 28.5.
+// 4.7 TB/s), 1.05e8 of 64 12.9 -> 11.5 ms, 8.2e6 of 32 128 -> 117 us, 3.7e5 of 32 with values and Adam 39.4 -> 28.5.  (Those 1.05e8 on a
+// table of 6e7 rows; on one of 3e8 15.05 -> 14.86 ms: 104 GB then go through the fabric, at 7.0 TB/s, whatever waits for what.)
 // Compiled for five waves per SIMD (up to 88 of 96 vector registers), two entries at a time: with six 395 us and 12.1 ms
 // at those sizes, with four entries at a time 403 us and 13.1 ms, with four entries and four waves 341 us and 11.7 ms.
 // The second state array's registers do
@@ -979,8 +980,9 @@ __device__ inline uint32_t chunk_of_wave(uint32_t c, uint32_t c0, uint32_t nch) 
 // batch, the groups' sums are combined with cross-lane shuffles, and the wave writes
 // partials[c] = (s1[D], s2, gw, 0, 0) in double -- or, when the segment has no other chunk (33 .. 512 or 128
 // entries, most long segments), updates the row at once.
-// Bound by the gradient rows and A_sum rows that come through the fabric (2.7 GB at 7 TB/s for 8.0e6 entries of 64 floats); in
-// smaller batches by the round trips.
+// Bound by the gradient rows and A_sum rows that come through the fabric: with consecutive chunks on one die 2.65 GB at 7.0 TB/s for 8.0e6
+// entries of 64 floats (2.72 GB before), 15.8 GB at 6.8 for 1.05e8 (17.1), 0.91 GB at 6.3 for 8.2e6 of 32 (1.07); in smaller batches by
+// the round trips.
 template <int D, bool kHasVals>
 __global__ __launch_bounds__(kBlock, D == 4 ? 4 : 5) void k_long_partial(const BwdArgs a) {
   constexpr int G = D / 4;

@@ -18,15 +18,16 @@
 // stored column-permuted (column 4*sub+k at k*G+sub) with a row pitch of D+2 doubles, so that the
 // 64 lanes of one atomic instruction spread over the LDS banks instead of piling onto a few.
 //
-// What bounds it: at D = 32 the LDS pipe (78 % busy, about 14 cycles per wave of double additions, a quarter of it bank
-// conflicts) and the vector ALU (62 %); at D = 64 dependent accesses beside them (57 % of the waves' time is waiting).
+// What bounds it (8e6 entries): at D = 32 the LDS pipe (71 % busy, a quarter of it bank conflicts; double additions for the most part) and
+// the vector ALU (80 %); at D = 64 dependent accesses beside them (the waves wait for 58 % of their time, vector ALU 63 %, LDS 38 %).
 // Vector memory operations complete in order and a wait can only be counted along straight code: with a gather under a
 // condition, or the bag's store between a batch's gathers and their uses, each was waited for alone.  Gathers without
 // conditions, all waited for at once ahead of the stores: 8.0e6 entries of 64 floats 694 -> 598 us, 1.05e8 of 64 7.50 -> 6.35 ms,
 // 8.2e6 of 32 236 -> 218 us.
 // Registers: U gathers of four floats each.  Four waves per SIMD need 128 registers (without the bound 131 at D = 128 with values:
 // 91 -> 81 us for 8.1e5 entries); D = 32 without values fits six waves with four gathers in flight (8.2e6 entries 217 -> 207 us, with
-// the scalars' additions below).
+// the scalars' additions below).  Narrower rows need no bound for six (at most 72 registers without values).  At D = 64 it depends on
+// where the rows come from: 1.7e6 entries by Zipf's law 76.5 -> 72.4 us with six waves and four gathers, uniform 105 -> 110, so it stays.
 //
 // Accumulation is in double, inputs and outputs are fp32: a sample's sum of several hundred
 // signed terms cancels, and fp32 accumulation alone would exceed the 1e-5 relative bound

@@ -119,7 +119,8 @@ __global__ __launch_bounds__(kBlock) void k_compact_store(T *__restrict__ arr, i
   arr[(first + i) * upr + u] = staging[i * upr + u];
 }
 
-// Compaction, first look at the keep flags: rows kept per tile of kKeepTile rows, 16 flags per load where they are aligned.
+// Compaction, first look at the keep flags: rows kept per tile of kKeepTile rows, a thread's eight flags by one load where they
+// are aligned.
 constexpr int kKeepTile = 2048;
 constexpr int kKeepItems = kKeepTile / kBlock;
 

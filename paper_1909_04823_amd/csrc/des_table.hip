@@ -25,7 +25,7 @@ namespace {
 constexpr int kFlagItems = 8;                       // entries per thread in the numbering kernels
 constexpr int kFlagTile = kBlock * kFlagItems;
 constexpr uint32_t kPendingBit = 0x80000000u;       // in a tile's count: the tile has entries whose row is not known yet
-constexpr int kSmallInsert = 4096;                  // up to this many entries one workgroup numbers the new rows
+constexpr int kSmallInsert = 4096;                  // up to this many entries every workgroup of one launch numbers the new rows by itself
 constexpr int kSmallInsertBlock = 1024;
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int64_t kSelfPrefixTiles = 4096;          // up to this many tiles the numbering kernel sums the tile counts itself
