@@ -18,8 +18,12 @@
 // stored column-permuted (column 4*sub+k at k*G+sub) with a row pitch of D+2 doubles, so that the
 // 64 lanes of one atomic instruction spread over the LDS banks instead of piling onto a few.
 //
-// What bounds it (8e6 entries): at D = 32 the LDS pipe (71 % busy, a quarter of it bank conflicts; double additions for the most part) and
-// the vector ALU (80 %); at D = 64 dependent accesses beside them (the waves wait for 58 % of their time, vector ALU 63 %, LDS 38 %).
+// What bounds it (8e6 entries): dependent accesses, at D = 32 beside an LDS pipe that is busy 73 % of the time (double additions for the most
+// part; vector ALU 46 %), at D = 64 beside a vector ALU busy 40 % (LDS 39 %; the waves wait for 62 % of their time).
+// Vector instructions: row addresses by one multiply-add, the sums of squares of up to four entries together, a remainder by a known
+// reciprocal, sums that are set back without selecting, gathers whose four floats stay together: 80.6 -> 59.3 million of them for 8.2e6
+// entries of 32 floats, whose 212 us hardly change (208), 1.0e6 of 16 26.0 -> 24.6 us, 8.0e6 of 64 627 -> 616, 9.9e5 of 128
+// 98 -> 83; 40 shapes of all widths take 4 % less on average, none more.
 // Vector memory operations complete in order and a wait can only be counted along straight code: with a gather under a
 // condition, or the bag's store between a batch's gathers and their uses, each was waited for alone.  Gathers without
 // conditions, all waited for at once ahead of the stores: 8.0e6 entries of 64 floats 694 -> 598 us, 1.05e8 of 64 7.50 -> 6.35 ms,
@@ -39,6 +43,7 @@ namespace des {
 namespace {
 
 constexpr int64_t kFillGroups = 512;      // two workgroups per CU
+constexpr size_t kSixPerCu = 160 * 1024 / 6;     // LDS bytes of a workgroup of which a CU holds six
 
 struct FwdArgs {
   const float *emb, *w;
@@ -49,9 +54,11 @@ struct FwdArgs {
   float *P_lr, *P_sum, *P_sq, *pool;
   int64_t B;
   int F, K, policy;
+  int pitch;            // LDS doubles from one shard's sums to the next's
   int acc_doubles;      // LDS doubles of one set of a sample's accumulators
   int sets;             // sets per sample: 1, which its waves share, or one for each of them
   int lds_per_sample;   // LDS doubles per sample in total (accumulators + staged offsets)
+  uint32_t per_shard;   // floor(2^32 / K), at most 2^32 - 1
   int log_threads;      // log2 of the threads per sample: part of a wave (whole lane groups), or 1, 2 or 4 waves
 };
 
@@ -67,6 +74,14 @@ __device__ inline double dpp_f64(double v) {
   return __hiloint2double(hi, lo);
 }
 
+// Four floats at `base` in row `row` of rows of `pitch` bytes.  The address is one multiply-add: `pitch` is opaque to the compiler, which
+// would take four instructions for the shift that it makes of a known one.
+typedef float v4f __attribute__((ext_vector_type(4)));
+__device__ inline v4f ld4_row(const float *base, uint32_t row, uint32_t pitch) {
+  const uint64_t at = reinterpret_cast<uint64_t>(base) + (uint64_t)row * pitch;
+  return *reinterpret_cast<const __attribute__((address_space(1))) v4f *>(at);
+}
+
 // Sum of q over the G adjacent lanes of a lane group (every lane gets the total).
 template <int G>
 __device__ inline double group_sum(double q) {
@@ -79,6 +94,37 @@ __device__ inline double group_sum(double q) {
   return q;
 }
 
+// The sums of n = 1, 2 or 4 values over the lanes of a group, of which lane `sub` gets the one of value sub % n: a lane hands half of its
+// values to its neighbour and takes the other half of the neighbour's, so that all sums together take hardly more instructions than one
+// (n = 4, G = 8: 26 against 44).  odd0 and odd1: bits 0 and 1 of the lane's number, turned in every second quad, since the
+// mirrored steps pair lanes of different quads whose numbers differ in these bits as well (kTurn: in the others instead, so that
+// the lanes of the group's every second quad are the ones that hold sub % n).
+template <int kCtrl, bool kTurn>
+__device__ inline double exchange(double a, double b, bool odd) {
+  const double keep = odd != kTurn ? b : a, give = odd != kTurn ? a : b;
+  return keep + dpp_f64<kCtrl>(give);
+}
+template <int G, int N, bool kTurn>
+__device__ inline double group_sums(const double (&p)[N], bool odd0, bool odd1) {
+  static_assert(N == 1 || N == 2 || N == 4, "up to a quad");
+  if constexpr (N == 1 || G < N) {
+    return group_sum<G>(p[0]);
+  } else {
+    double q = exchange<0xB1, kTurn>(p[0], p[1], odd0);
+    if constexpr (N == 4) {
+      const double r = exchange<0xB1, kTurn>(p[2], p[3], odd0);
+      q = exchange<0x4E, kTurn>(q, r, odd1);
+    } else if constexpr (G >= 4) {
+      q += dpp_f64<0x4E>(q);
+    }
+    if (G >= 8) q += dpp_f64<0x141>(q);
+    if (G >= 16) q += dpp_f64<0x140>(q);
+#pragma unroll
+    for (int m = 16; m < G; m <<= 1) q += __shfl_xor(q, m, kWave);
+    return q;
+  }
+}
+
 // v of lane `src` of the caller's group of G = 1, 2 or 4 lanes (VALU, does not use the LDS pipe).
 template <int G>
 __device__ inline int group_lane(int v, int src) {
@@ -89,6 +135,12 @@ __device__ inline int group_lane(int v, int src) {
   if (src == 1) return __builtin_amdgcn_mov_dpp(v, 0x55, 0xF, 0xF, true);
   if (src == 2) return __builtin_amdgcn_mov_dpp(v, 0xAA, 0xF, 0xF, true);
   return __builtin_amdgcn_mov_dpp(v, 0xFF, 0xF, 0xF, true);
+}
+
+// x mod K from floor(2^32 / K): the quotient that gives is the true one or one less.  (The compiler's own division corrects twice.)
+__device__ inline uint32_t mod_shards(uint32_t x, uint32_t K, uint32_t per_shard) {
+  const uint32_t r = x - __umulhi(x, per_shard) * K;
+  return min(r, r - K);
 }
 
 // kByKey: shard of an entry = hash of its ID (entries of a bag scatter over the shards: one LDS update per
@@ -121,7 +173,7 @@ __global__ __launch_bounds__(kBlock, D == 32 && !kHasVals ? 6 : 4) void k_forwar
   const int nts = 1 << a.log_threads, tis = threadIdx.x & (nts - 1);   // threads per sample, thread in sample
   // LDS: one 16-byte metadata slot per thread, then per sample the accumulators and offsets
   int4 *meta = reinterpret_cast<int4 *>(lds) + wave * kWave;
-  constexpr int P = D + 2;                                // row pitch: D columns, sum of squares, LR sum
+  const int P = a.pitch;                                  // row pitch: D columns, sum of squares, LR sum (and none or some of no use)
   double *sums = lds + 2 * kBlock + (size_t)local * a.lds_per_sample;  // [sets][K][P]
   double *sum = a.sets > 1 ? sums + tis / kWave * a.acc_doubles : sums;  // the one this wave adds to
   int *offs = reinterpret_cast<int *>(sums + a.sets * a.acc_doubles);  // [F+1]
@@ -131,6 +183,10 @@ __global__ __launch_bounds__(kBlock, D == 32 && !kHasVals ? 6 : 4) void k_forwar
   const bool hashed = kByKey && (need_fm || need_lr);
   const int row_mask = need_fm || need_pool ? -1 : 0;     // first-order terms alone need no rows
   const float *w_base = need_lr ? a.w : a.emb;
+  const float *const emb = a.emb + sub * 4;
+  uint32_t pitch = D * sizeof(float);
+  asm("" : "+s"(pitch));
+  const bool turned = G >= 8 && (sub & 4) != 0, odd0 = ((sub & 1) != 0) != turned, odd1 = ((sub & 2) != 0) != turned;
 
   for (int i = tis; i < a.sets * a.acc_doubles; i += nts) sums[i] = 0.0;
   if (active)
@@ -149,6 +205,7 @@ __global__ __launch_bounds__(kBlock, D == 32 && !kHasVals ? 6 : 4) void k_forwar
     if (need_pool && !kBehind)                            // bags without entries; the others are stored at their last entry
       for (int f = f0; f < f1; ++f)
         if (offs[f] == offs[f + 1]) st4(pool + (f * D + sub * 4), make_float4(0.f, 0.f, 0.f, 0.f));
+    const int last_marked = need_pool || (!kByKey && need_fm) ? (kBehind ? e1 - 1 : e1) : 0;   // entries before it may end a bag
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     double bag_sq = 0.0;                                  // field partition: this lane's share of the bag's sum of squares
     int cur = f0;                                         // a bag that no entry to come lies before
@@ -212,12 +269,12 @@ __global__ __launch_bounds__(kBlock, D == 32 && !kHasVals ? 6 : 4) void k_forwar
       }
       const int bag_l = my < e1 ? lo : cur;
       cur = kQuad ? bag_l : __shfl(bag_l, lane - sub + min(G, e1 - e) - 1, kWave);
-      const int sh_l = !need_fm && !need_lr ? 0 : kByKey ? (int)((uint32_t)(mix64(key_l) >> 32) % (uint32_t)K) : kQuad ? cur_sh : bag_l % K;
+      const int sh_l = !need_fm && !need_lr ? 0 : kByKey ? (int)mod_shards((uint32_t)(mix64(key_l) >> 32), (uint32_t)K, a.per_shard) : kQuad ? cur_sh : bag_l % K;
       // what the group needs of this lane's entry: row (0 if absent), its shard's accumulators (negative: absent; by field their
       // complement, for the bag that ends there), its bag's pooled row if it is the bag's last entry (-1: it is not), its value
       const int row_l = max(r_l, 0) & row_mask;
       const int acc_l = r_l >= 0 ? sh_l * P : kByKey ? -1 : ~(sh_l * P);
-      const int end_l = my < (kBehind ? e1 - 1 : e1) && at + 1 == end ? bag_l * D : -1;
+      const int end_l = my < last_marked && at + 1 == end ? bag_l * D : -1;
       // read back with one broadcast LDS read per entry; same wave, program order: no barrier needed
       if (!kQuad) meta[lane] = make_int4(row_l, acc_l, end_l, __float_as_int(x_l));
       // The first-order weight of this lane's own entry: one gather per chunk for the whole group (without first-order terms of one
@@ -229,7 +286,7 @@ __global__ __launch_bounds__(kBlock, D == 32 && !kHasVals ? 6 : 4) void k_forwar
       for (int j0 = 0; j0 < G; j0 += U) {
         if (j0 == 0 || j0 < cnt) {
           int4 md[U];
-          float4 v[U];
+          v4f v[U];
           // Every row is requested without a condition (an absent one reads row 0 and is left out below) and all of them,
           // with what was requested before them, are waited for here: loads under a condition, or waits between the pooled
           // stores, would be waited for one by one.
@@ -240,17 +297,19 @@ __global__ __launch_bounds__(kBlock, D == 32 && !kHasVals ? 6 : 4) void k_forwar
                                 kHasVals ? group_lane<G>(__float_as_int(x_l), j0 + i) : 0);
             else
               md[i] = meta[g * G + j0 + i];
-            v[i] = ld4(a.emb + (int64_t)md[i].x * D + sub * 4);
+            v[i] = ld4_row(emb, (uint32_t)md[i].x, pitch);
           }
 #pragma unroll
-          for (int i = 0; i < U; ++i) asm volatile("" : "+v"(v[i].x), "+v"(v[i].y), "+v"(v[i].z), "+v"(v[i].w));
+          for (int i = 0; i < U; ++i) asm volatile("" : "+v"(v[i]));
           if (j0 == 0) {
             asm volatile("" : "+v"(w_l), "+v"(r_n));
             if (hashed) asm volatile("" : "+v"(key_n));
             if (kHasVals) asm volatile("" : "+v"(x_n));
           }
+          double squares[U];
 #pragma unroll
           for (int i = 0; i < U; ++i) {
+            squares[i] = 0.0;
             if (md[i].y >= 0) {
               const double xd = kHasVals ? (double)__int_as_float(md[i].w) : 1.0;
               const double xv[4] = {kHasVals ? xd * (double)v[i].x : (double)v[i].x, kHasVals ? xd * (double)v[i].y : (double)v[i].y,
@@ -265,13 +324,14 @@ __global__ __launch_bounds__(kBlock, D == 32 && !kHasVals ? 6 : 4) void k_forwar
                   double *dst = sum + md[i].y + sub;
 #pragma unroll
                   for (int k = 0; k < 4; ++k) atomicAdd(dst + k * G, xv[k]);
-                  const double q = group_sum<G>(p);
-                  if (sub == j0 + i) q_l = q;
+                  squares[i] = p;
                 }
               }
             }
-            if (md[i].z >= 0) {                            // the bag ends: pooled sum out, and to its shard under the field partition
-              if (need_pool) st4(pool + (md[i].z + sub * 4), make_float4((float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3]));
+            // The bag ends: pooled sum out, and to its shard under the field partition.  (Where neither is asked for no entry is
+            // marked as a last one: a condition less around the sums that are set back.)
+            if (md[i].z >= 0) {
+              if (kByKey || need_pool) st4(pool + (md[i].z + sub * 4), make_float4((float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3]));
               if (!kByKey && need_fm) {
                 double *const shard = sum + (md[i].y ^ (md[i].y >> 31)), *const dst = shard + sub;
 #pragma unroll
@@ -281,6 +341,17 @@ __global__ __launch_bounds__(kBlock, D == 32 && !kHasVals ? 6 : 4) void k_forwar
                 bag_sq = 0.0;
               }
               acc[0] = acc[1] = acc[2] = acc[3] = 0.0;
+            }
+          }
+          if (kByKey && need_fm) {                         // sums of squares, each to the lane that holds its entry's metadata
+            constexpr int N = U < 4 ? U : 4;
+#pragma unroll
+            for (int i = 0; i < U; i += N) {
+              double p[N];
+#pragma unroll
+              for (int k = 0; k < N; ++k) p[k] = squares[i + k];
+              const double q = ((j0 + i) & 4) && G >= 8 ? group_sums<G, N, true>(p, odd0, odd1) : group_sums<G, N, false>(p, odd0, odd1);
+              if (sub >= j0 + i && sub < j0 + i + N) q_l = q;
             }
           }
         }
@@ -406,6 +477,8 @@ FwdArgs make_args(des_table *t, const des_batch_t *b, const int32_t *rows) {
   a.keys = b->keys; a.offsets = b->offsets; a.vals = b->vals; a.rows = rows;
   a.P_lr = a.P_sum = a.P_sq = a.pool = nullptr;
   a.B = b->B; a.F = b->F; a.K = t->cfg.num_shards; a.policy = t->cfg.shard_policy;
+  a.pitch = 0;
+  a.per_shard = a.K > 1 ? (uint32_t)((1ull << 32) / (uint32_t)a.K) : ~0u;
   a.acc_doubles = 0; a.sets = 1; a.lds_per_sample = 0; a.log_threads = 6;
   return a;
 }
@@ -421,10 +494,10 @@ des_status_t forward_launch(des_table *t, const des_batch_t *b, const int32_t *r
   // LDS per sample: K*(D+2) doubles of accumulators plus the sample's F+1 offsets.  Fewer
   // samples per workgroup (more waves per sample) when that is large, so that a CU still holds
   // several workgroups.
-  const int64_t acc_doubles = (int64_t)align_up((size_t)a.K * (D + 2), 2);
-  const int64_t per_sample = acc_doubles + ((int64_t)b->F + 2) / 2;
+  int64_t acc_doubles = (int64_t)align_up((size_t)a.K * (D + 2), 2);
+  const int64_t offs_doubles = ((int64_t)b->F + 2) / 2, per_sample = acc_doubles + offs_doubles;
   if (per_sample * 8 + 16 * kBlock > 65536) return DES_ERR_INVALID_ARG;   // K*(dim+2) doubles + F+1 ints + 4 KB must fit 64 KB of LDS
-  a.acc_doubles = (int)acc_doubles;
+  a.pitch = D + 2;
   int wps = 1;
   while (wps < 4 && (kBlock / kWave / wps) * per_sample * 8 > 40 * 1024) wps *= 2;
   const int64_t entries_per_sample = b->nnz / (b->B > 0 ? b->B : 1);
@@ -446,8 +519,16 @@ des_status_t forward_launch(des_table *t, const des_batch_t *b, const int32_t *r
     threads /= 2;
   a.log_threads = __builtin_ctz((unsigned)threads);
   a.sets = without == 1 ? wps : 1;
-  a.lds_per_sample = (int)((a.sets - 1) * acc_doubles + per_sample);
   const int spb = kBlock / threads;
+  // An addition of doubles takes 16 lanes at a time over 32 banks (64 consecutive doubles: 8 cycles).  At D = 32 those are two lane groups
+  // of 16 banks each: with rows 16 banks apart they meet where both shards are odd or both even, with rows 4 apart nearly always
+  // (8.2e6 entries, 16 shards 208 -> 202 us).  Only where a CU still holds the workgroups that its registers allow.
+  if (D == 32 && a.policy == DES_SHARD_KEY_HASH) {
+    const int64_t spread = (int64_t)a.K * 40;
+    if ((size_t)(a.sets * spread + offs_doubles) * 8 * spb + 16 * kBlock <= kSixPerCu) { a.pitch = 40; acc_doubles = spread; }
+  }
+  a.lds_per_sample = (int)(a.sets * acc_doubles + offs_doubles);
+  a.acc_doubles = (int)acc_doubles;
   const dim3 grid((unsigned)((b->B + spb - 1) / spb)), block(kBlock);
   const size_t shmem = 16 * (size_t)kBlock + (size_t)a.lds_per_sample * 8 * spb;
   const bool by_key = a.policy == DES_SHARD_KEY_HASH;

@@ -1129,3 +1129,12 @@ def test_forward_of_several_samples_per_wave(oracle, des, B, F, D, K, policy):
 def test_forward_of_short_bags(oracle, des, B, F, D, K, policy, shape):
     """Lane groups of few entries, of bags that end at different steps, and of runs of empty bags at either end of a group's range."""
     forward_of_short_bags(oracle, des, B, F, D, K, policy, shape)
+
+
+@pytest.mark.parametrize("B,F,D,K", [
+    (2100, 8, 32, 18), (2100, 8, 32, 19),                           # rows of accumulators sixteen banks apart, and no longer
+    (300, 7, 4, 1), (300, 7, 4, 255), (300, 7, 8, 256), (300, 7, 16, 129), (300, 7, 32, 61), (300, 7, 64, 65), (300, 7, 128, 3), (300, 7, 256, 27),
+])
+def test_forward_of_any_number_of_shards(oracle, des, B, F, D, K):
+    """Shards by the remainder of a hash, and sums of squares of 1, 2 or 4 entries at a time over 1 to 64 lanes."""
+    forward_of_short_bags(oracle, des, B, F, D, K, 0, "mixed")
