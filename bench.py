@@ -48,7 +48,7 @@ def algorithmic_bytes(w, nnz, st, sort_passes, state_mult):
     R = D + 1
     n, U = nnz, st["U"]
     gp = 4.0 * B * F * D                      # g_pool, each bag row once
-    return {
+    by = {
         "table_probe": 8 * n + 4 * n + 16 * U,
         "forward_gather_pool": 8 * n + 4 * n + 4 * (B * F + 1) + 4 * R * U + 4 * K * B * (D + 2) + 4 * B * F * D,
         "aggregate_partials": 4 * (K + 1) * B * (D + 2),
@@ -63,6 +63,8 @@ def algorithmic_bytes(w, nnz, st, sort_passes, state_mult):
                                  + 8 * (D + 4) * st["n_chunks"],
         "backward_long_final": 8 * (D + 4) * st["n_chunks"] + 2 * state_mult * 4 * R * st["U_long"],
     }
+    by["backward_update"] = by["backward_short_update"] + by["backward_long_partial"]      # both in one launch
+    return by
 
 
 PROFILE_TAG = {0: "tiny_lr_fm", 1: "dlrm_pooled", 2: "deepfm", 3: "streaming", 4: "large_table"}
@@ -624,7 +626,8 @@ def run_workload(args, index, cpu):
         if "forward_gather_pool" in kernels:
             ceil_res["forward_gather_pool_ms"] = kernels["forward_gather_pool"]["ms_per_step"]
             ceil_res["gather_ceiling_over_forward"] = round(g_ms / kernels["forward_gather_pool"]["ms_per_step"], 3)
-        upd = sum(kernels[k]["ms_per_step"] for k in ("backward_short_update", "backward_long_partial", "backward_long_final") if k in kernels)
+        upd = sum(kernels[k]["ms_per_step"] for k in ("backward_update", "backward_short_update", "backward_long_partial", "backward_long_final")
+                  if k in kernels)
         if upd > 0:
             ceil_res["merge_and_update_ms"] = round(upd, 4)
             ceil_res["update_ceiling_over_merge_and_update"] = round(u_ms / upd, 3)

@@ -780,13 +780,12 @@ __device__ inline void apply_row(const BwdArgs &a, int64_t u, int row, int sub, 
 // Adagrad, D = 16, same sizes: 54.7 -> 45.5, 110 -> 87, 270 -> 217 us (two at a time: 48.7, 90, 232; at D = 32 four lose).
 // kSecond: an optimizer with a second state array (Adam, FTRL) may be in use.
 template <int D, bool kHasVals, bool kSecond>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kSecond ? 4 : 5, kSecond ? 4 : 5))) void k_short_update(
-    const BwdArgs a) {
+__device__ inline void update_short(const BwdArgs &a, uint32_t block, uint32_t blocks) {
   constexpr int G = D / 4;
   constexpr int U = kSecond && (D == 8 || D == 16) ? 4 : 2;
-  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t gid = (int64_t)block * kBlock + threadIdx.x;
   const int sub = (int)(gid % G);
-  const int64_t ngroups = (int64_t)gridDim.x * blockDim.x / G;
+  const int64_t ngroups = (int64_t)blocks * kBlock / G;
   const int64_t n_uniq = a.ctrl->n_uniq;
   // grid-stride over the segments: the grid is sized on the host for the chip, not for the (device-side) segment count.
   // The bounds, row and first payload of the lane group's next segment are requested while the current one is being
@@ -983,12 +982,11 @@ __device__ inline uint32_t chunk_of_wave(uint32_t c, uint32_t c0, uint32_t nch) 
 // Bound by the gradient rows and A_sum rows that come through the fabric: with consecutive chunks on one die 2.65 GB at 7.0 TB/s for 8.0e6
 // entries of 64 floats (2.72 GB before), 15.8 GB at 6.8 for 1.05e8 (17.1), 0.91 GB at 6.3 for 8.2e6 of 32 (1.07); in smaller batches by
 // the round trips.
-template <int D, bool kHasVals>
-__global__ __launch_bounds__(kBlock, D == 4 ? 4 : 5) void k_long_partial(const BwdArgs a) {
+template <int D, bool kHasVals, bool kSecond>
+__device__ inline void update_chunk(const BwdArgs &a, uint32_t block, Walk<D> (&lds)[kWavesPerBlock]) {
   constexpr int G = D / 4;
-  __shared__ Walk<D> lds[kWavesPerBlock];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const uint32_t wave_no = blockIdx.x * kWavesPerBlock + wave;
+  const uint32_t wave_no = block * kWavesPerBlock + wave;
   if (wave_no >= a.ctrl->n_chunks) return;                    // uniform per wave
   const int g = lane / G, sub = lane % G;
   const int j = a.chunk_owner[wave_no];
@@ -1001,7 +999,7 @@ __global__ __launch_bounds__(kBlock, D == 4 ? 4 : 5) void k_long_partial(const B
     if (seg_hi - seg_lo <= (1 << a.chunk_shift)) {
       // the segment is this one chunk: the wave holds its whole sum and updates the row itself
       const int row = a.uniq_rows[u];
-      apply_row<D>(a, u, row, sub, load_row<D>(a, row, sub), acc);
+      apply_row<D, kSecond>(a, u, row, sub, load_row<D, kSecond>(a, row, sub), acc);
     } else {
       double *p = a.partials + (int64_t)(c0 + k_seg) * (D + 4);
       *reinterpret_cast<double2 *>(p + sub * 4) = make_double2(acc.v[0], acc.v[1]);
@@ -1009,6 +1007,38 @@ __global__ __launch_bounds__(kBlock, D == 4 ? 4 : 5) void k_long_partial(const B
       if (sub == 0) *reinterpret_cast<double2 *>(p + D) = make_double2(acc.s2, acc.gw);
     }
   }
+}
+
+// (4a) and (4b) in one launch: they touch different rows, and while either waits (a short segment for its round trips, a chunk for the
+// fabric) the other's waves find work, as long as neither fills the chip by itself.  Workgroups of chunks come first from D = 32 on;
+// of narrow rows, whose lane groups hold one to four lanes, the segments, whose longest then take longer than a chunk.  Both at
+// once / one after the other, whole backward pass: 8.0e3 to 1.3e5 entries of any width 62 / 70 us on average, 3.7e5 of 32 with values and
+// Adam 100 / 107, 1.0e6 of 16 123 / 125, 1.2e6 of 8 111 / 124, 2.7e6 of 4 173 / 203, 4.0e6 of 8 240 / 252, 8.0e6 412 / 412; above 2^20 nothing
+// from D = 16 on (3.7e6 of 16 240 / 231, 8.2e6 of 32 492 / 488, 8.0e6 of 64 917 / 917) nor with second state arrays, with which this is
+// compiled for a wave per SIMD less than chunks alone (1.7e6 with Adam 205 / 199).
+inline bool update_at_once(int D, int64_t n, bool second) { return n <= kFewSort || (D <= 8 && !second && n <= kFewEntries); }
+template <int D, bool kHasVals, bool kSecond>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kSecond || D == 4 ? 4 : 5, kSecond || D == 4 ? 4 : 5))) void k_update(
+    const BwdArgs a, uint32_t n_short, uint32_t n_chunk) {
+  __shared__ Walk<D> lds[kWavesPerBlock];
+  if constexpr (D <= 16) {
+    if (blockIdx.x < n_short) update_short<D, kHasVals, kSecond>(a, blockIdx.x, n_short);
+    else update_chunk<D, kHasVals, kSecond>(a, blockIdx.x - n_short, lds);
+  } else {
+    if (blockIdx.x < n_chunk) update_chunk<D, kHasVals, kSecond>(a, blockIdx.x, lds);
+    else update_short<D, kHasVals, kSecond>(a, blockIdx.x - n_chunk, n_short);
+  }
+}
+
+template <int D, bool kHasVals, bool kSecond>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kSecond ? 4 : 5, kSecond ? 4 : 5))) void k_short_update(const BwdArgs a) {
+  update_short<D, kHasVals, kSecond>(a, blockIdx.x, gridDim.x);
+}
+
+template <int D, bool kHasVals>
+__global__ __launch_bounds__(kBlock, D == 4 ? 4 : 5) void k_long_partial(const BwdArgs a) {
+  __shared__ Walk<D> lds[kWavesPerBlock];
+  update_chunk<D, kHasVals, true>(a, blockIdx.x, lds);
 }
 
 // (4b, c) for a batch of up to kSmallSort entries: one workgroup per long segment, whose waves take equal stretches; their sums are
@@ -1166,21 +1196,27 @@ void launch_update(const BwdArgs &a, hipStream_t s) {
   constexpr int G = D / 4;
   const int64_t max_long = a.n / (kShortMax + 1) + 1;
   const int64_t max_chunks = (a.n >> a.chunk_shift) + max_long + 1;
-  {
-    ProfScope ps(KID_SHORT_UPDATE, s);
-    const bool second = a.opt_emb == DES_OPT_ADAM || a.opt_w == DES_OPT_ADAM || a.opt_w == DES_OPT_FTRL;
-    const dim3 grid(blocks_for(a.n * G, kShortGrid)), block(kBlock);
-    if (second) hipLaunchKernelGGL((k_short_update<D, kHasVals, true>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_short_update<D, kHasVals, false>), grid, block, 0, s, a);
-  }
-  if (a.n <= kSmallSort) {
+  const bool second = a.opt_emb == DES_OPT_ADAM || a.opt_w == DES_OPT_ADAM || a.opt_w == DES_OPT_FTRL;
+  // multiples of eight: consecutive workgroups go round the dies, on which chunk_of_wave counts
+  const auto eights = [](unsigned blocks) { return (blocks + 7) / 8 * 8; };
+  const unsigned n_short = eights(blocks_for(a.n * G, kShortGrid)), n_chunk = eights(blocks_for(max_chunks * kWave));
+  const dim3 block(kBlock);
+  if (a.n > kSmallSort && update_at_once(D, a.n, second)) {
+    ProfScope ps(KID_UPDATE, s);
+    if (second) hipLaunchKernelGGL((k_update<D, kHasVals, true>), dim3(n_short + n_chunk), block, 0, s, a, n_short, n_chunk);
+    else hipLaunchKernelGGL((k_update<D, kHasVals, false>), dim3(n_short + n_chunk), block, 0, s, a, n_short, n_chunk);
+  } else {
+    {
+      ProfScope ps(KID_SHORT_UPDATE, s);
+      if (second) hipLaunchKernelGGL((k_short_update<D, kHasVals, true>), dim3(n_short), block, 0, s, a);
+      else hipLaunchKernelGGL((k_short_update<D, kHasVals, false>), dim3(n_short), block, 0, s, a);
+    }
     ProfScope ps(KID_LONG_PARTIAL, s);
-    hipLaunchKernelGGL((k_long_small<D, kHasVals>), dim3((unsigned)max_long), dim3(kLongSmallWaves<D> * kWave), 0, s, a);
-    return;
-  }
-  {
-    ProfScope ps(KID_LONG_PARTIAL, s);
-    hipLaunchKernelGGL((k_long_partial<D, kHasVals>), dim3(blocks_for(max_chunks * kWave)), dim3(kBlock), 0, s, a);
+    if (a.n <= kSmallSort) {
+      hipLaunchKernelGGL((k_long_small<D, kHasVals>), dim3((unsigned)max_long), dim3(kLongSmallWaves<D> * kWave), 0, s, a);
+      return;
+    }
+    hipLaunchKernelGGL((k_long_partial<D, kHasVals>), dim3(n_chunk), block, 0, s, a);
   }
   {
     ProfScope ps(KID_LONG_FINAL, s);

@@ -890,6 +890,16 @@ def test_merge_walk_of_a_chunk(oracle, des, n, D, lens, with_vals):
     test_merge_chunk_length_limits(oracle, des, n, D, lens, with_vals)
 
 
+@pytest.mark.parametrize("n,D,lens,with_vals", [
+    (1 << 20, 16, [32, 33, 128, 129, 70001], True),          # the last size at which short and long segments share a launch
+    ((1 << 20) + 1, 16, [32, 33, 128, 129, 70001], True),    # ... from D = 16 on, the first at which they do not
+    ((1 << 20) + 1, 8, [32, 33, 128, 129, 70001], False),    # narrow rows: up to 2^22 without second state arrays
+    (50021, 64, [31, 32, 33, 128, 129], False),              # wide rows: chunks first
+])
+def test_merge_of_short_and_long_segments_together(oracle, des, n, D, lens, with_vals):
+    test_merge_chunk_length_limits(oracle, des, n, D, lens, with_vals)
+
+
 # ------------------------------------------------- aggregation of few partials --------------------
 @pytest.mark.parametrize("K,B", [(1, 1), (2, 1), (3, 1), (1, 2), (1, 3), (4, 1), (2, 7), (9, 5), (17, 33), (3, 16384), (3, 16385)])
 @pytest.mark.parametrize("D", [4, 8, 12, 16, 32, 36, 64, 100])
