@@ -8,32 +8,45 @@
 // pooled embeddings) and of its own weight rows (V_s dY).
 //
 // This is the one dense contraction of the path, so it runs on the matrix cores.  128x128 output tile per workgroup (64x64
-// where that leaves CUs idle), four waves in a 2x2 arrangement of 64x64 (32x32).  Two kernels:
+// where that leaves CUs idle), four waves in a 2x2 arrangement of 64x64 (32x32).  Three kernels:
 //
 // k_gemm_f32, the forward product: the fp32 matrix instruction (32x32x2, 64 cycles), 16 or 32 products deep per LDS tile, the
 // next tile in registers meanwhile.  Bound by the matrix pipe, and by its writes where the shards are shallow.  The sum of an
 // output element is one chain in ascending k (above 1024 products: of chains of forward_run products) whatever the tile,
-// so results do not depend on the tile size.  It keeps the fp32 chain because a ReLU follows it: with the split (223 against
+// so results do not depend on the tile size.  It keeps the fp32 chain because a ReLU follows it: with a split (223 against
 // 271 us at 16384 x 3200 x 256) a unit within 1e-8 of zero changes sides in one of six training steps at 4096 x 256 units, and
 // its gradient with it.  A shard's fields are walked as one range (a field of 20 columns costs no padding).
 //
-// k_gemm_split, the two gradient products: fp32 accuracy from the bf16 instruction (32x32x16, 32 cycles).  Every operand
-// element is cut into three bf16 parts, a = hi + mid + lo, each the rounded rest of what the parts before it left (the cut is
-// exact: 3 x 8 significant bits), and a product is six bf16 products accumulated in fp32:
+// k_gemm_halves, the two gradient products: fp32 accuracy from the fp16 instruction (32x32x16, 32 cycles).  Every operand element,
+// times a power of two that its row of the tile has, is cut into two fp16 parts, a = hi + lo, each the nearest to what is left (11 + 12
+// significant bits with lo's sign: the cut is exact but for the last bit of every fourth element), and a product is three:
+//   hi*hi + hi*lo + lo*hi
+// so 16 products of depth take 3 x 32 instead of 8 x 64 cycles.  lo is kept times 2^11, in hi's range, and the last two terms in sums
+// of their own: with one sum for all, lo would leave fp16's range 2^10 below the row's largest; so an element is cut in full
+// down to 2^-14 of the row's unit and to the nearest multiple of 2^-36 below.  The unit is the power of two at or below the
+// largest of the row's first 32 products, which leaves 2^16 above it; a later element beyond that, or a row whose first 32
+// products are zeros and whose largest is then below 2^-10 of the unit it was given instead (the tile's), is computed again with
+// the fp32 instruction, as is a sum that is not finite.
+// A single product is off by 7e-8 on average (fp32 3e-8), but the sum is rounded once per 16 products instead of once per product, so that
+// sums of 64 and more are closer than in fp32 or from three bf16 parts.  Error against 64 bits, 2-norm, fp32 / thirds / halves: sums of 64
+// 1.45 / 1.1 / 0.97 e-7, 128 - / 1.6 / 1.1, 256 2.9 / 2.4 / 1.3, 512 - / 3.4 / 1.7; of 1648 in slices 1.8 (thirds) and 1.7.  Deep sums
+// (above 1024) are taken 512 products at a time, which are added to the result in memory: registers for a second level are not left.
+// Bound by the vector instructions of the cut (5 per element and tile) beside a matrix pipe busy a quarter of the time.  32 products per
+// step in two LDS buffers; the next tile travels in registers, both its halves requested together, so that lines of 128 bytes
+// along k are used when they come (16 per step: g_pool 152, dW 213 us).  16384 x 3200 x 256, thirds / halves: g_pool 181 / 138 us,
+// dW 162 / 147; both 346 / 273; 131072 x 320 x 64 614 / 354; 65536 x 416 x 256 371 / 265; 4096 x 416 x 256 40 / 32.
+//
+// k_gemm_split, sums of fewer than 64 products: three bf16 parts, a = hi + mid + lo (the cut is exact: 3 x 8 significant bits), and
+// six products:
 //   hi*hi + hi*mid + mid*hi + hi*lo + lo*hi + mid*mid
-// so 16 products of depth take 6 x 32 instead of 8 x 64 cycles.  What is left out is at most 2^-24 of a*b (mid is up to 2^-8 of
-// a, lo up to 2^-17): a single product can be off by 2^-23 where the fp32 instruction is by 2^-24, a sum is closer from three
-// products on.  Error against 64 bits, 2-norm, split / fp32: sums of 1, 2, 3, 16 and 64 products 3.5 / 2.5, 3.3 / 3.1, 3.2 / 3.6, 3.4 /
-// 7.3 and 10.9 / 14.4 e-8; 16384 x 3200 x 256 2.4e-7 / 2.9e-7.
-// Bound by the matrix pipe and, nearly as long, the vector instructions of the cut (5 per element, once per element and tile, on
-// the way into LDS): two LDS buffers of 16 products, so that a wave cuts the next tile between the matrix instructions of
-// the current one, and two tiles under way in registers.  16384 x 3200 x 256, fp32 / split: 242 / 174 us, 235 / 154 us; 131072 x
-// 12800 x 256: g_pool 7.31 / 5.47 ms (157 TFLOP/s), dW 7.07 / 4.90 ms; a library's plain bf16 product of 8192^3 reaches 1.1
-// PFLOP/s here, one sixth of which is 183.
-// The bf16 instruction drops the bits of its sum that do not fit, towards minus infinity; over many runs that adds up (a mean
+// What is left out is at most 2^-24 of a*b (mid is up to 2^-8 of a, lo up to 2^-17): a single product can be off by 2^-23 where the
+// fp32 instruction is by 2^-24, a sum is closer from three products on.  Error, split / fp32: sums of 1, 2, 3, 16 products
+// 3.5 / 2.5, 3.3 / 3.1, 3.2 / 3.6, 3.4 / 7.3 e-8.  Two LDS buffers of 16 products, and two tiles under way in registers.
+//
+// The 16-bit instructions drop the bits of their sum that do not fit, towards minus infinity; over many runs that adds up (a mean
 // of -3e-7 of the results' root mean square at 124623 samples), so every second run of kRun products is accumulated with the
 // opposite sign.  A single run, or a last one without a partner, keeps its part: tiles and slices begin with alternating
-// signs, so that it has both signs in what a row of the table adds up over the samples and in a slice sum (mean error /
+// signs, so that it has both signs in what a row of the table adds up over the samples and in a slice sum (of thirds, mean error /
 // root mean square, all beginning with plus and so: g_pool of 128 hidden units, 4096 samples, -9.4e-9 and -2e-11; dW of 2048
 // samples -2.9e-8 and 3e-10.  Signs by rows instead of tiles cost g_pool 4 %).
 //
@@ -49,9 +62,12 @@ namespace {
 
 constexpr int kRun = 128;                    // products per first-level run of a two-level sum
 constexpr long long kTwoLevelDepth = 1024;
+constexpr long long kHalvesDepth = 64;       // products from which a sum of fp16 halves is no less exact than one of bf16 thirds
+constexpr int kDeepRun = 512;                // products of a deep sum of halves that are summed before they are added to the result
 constexpr int kMinSlice = 16;                // samples a slice of dW has at least; slices are multiples of it
 constexpr int kForwardGroup = 16;           // row tiles of the forward product whose shards are done together
 constexpr int kShallowDepth = 64;           // products of the largest shard up to which the forward product is bound by its writes
+constexpr long long kStreamBytes = 128ll << 20;
 constexpr int kXcds = 8;                     // dies; consecutive workgroups are handed to them in turn
 constexpr uint32_t kGridRow = 1u << 23;      // workgroups per row of a grid; a launch takes fewer than 2^32 threads along x
 
@@ -59,6 +75,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
 struct GemmArgs {
   const float *A, *B;
@@ -75,6 +93,7 @@ struct GemmArgs {
   bool in_turn = false;               // the dies take the n tiles of one row tile and slice each, in turn; else each an eighth of all tiles
   uint32_t die_run = 0;               // tiles in succession that a die takes, accordingly
   int run;                            // products per first-level run of a two-level sum with the fp32 instruction
+  bool stream;                        // the result is larger than what caches keep for who reads it next
 };
 
 __device__ inline float4 ld4g(const float *p) { return *reinterpret_cast<const float4 *>(p); }
@@ -95,6 +114,15 @@ __device__ inline void split2(float a0, float a1, uint32_t &hi, uint32_t &mid, u
   const float l0 = r0 - __uint_as_float(mid << 16), l1 = r1 - __uint_as_float(mid & 0xFFFF0000u);
   lo = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){l0, l1}, bf16x2));
   odd |= __float_as_uint(l0) | __float_as_uint(l1);
+}
+
+// Two floats times `scale`, a power of two, to two fp16 parts: the nearest, and 2^11 times the nearest to the rest.
+__device__ inline void halve2(float a0, float a1, float scale, uint32_t &hi, uint32_t &lo) {
+  const f16x2 h = __builtin_convertvector((f32x2){a0 * scale, a1 * scale}, f16x2);
+  const float up = scale * 2048.f;
+  const float l0 = __builtin_fmaf((float)h.x, -2048.f, a0 * up), l1 = __builtin_fmaf((float)h.y, -2048.f, a1 * up);   // exact
+  hi = __builtin_bit_cast(uint32_t, h);
+  lo = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){l0, l1}, f16x2));
 }
 
 // The part of a T x BK operand tile that a thread stages, and its way there.
@@ -155,6 +183,44 @@ struct Operand {
 #pragma unroll
     for (int i = 0; i < kVecs; ++i)
       if (k0 + k_in + (kKContig ? 0 : i) >= klen) v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  static constexpr int kRows = kKContig ? kUnits : 4;      // rows of which a thread stages products
+  // largest magnitude of the staged values of each of the thread's rows, and so far
+  __device__ inline void largest(const float4 (&v)[kVecs], float (&top)[kRows]) const {
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) {
+      const float x0 = kKContig ? v[i].x : reinterpret_cast<const float *>(&v[0])[i], x1 = kKContig ? v[i].y : reinterpret_cast<const float *>(&v[1])[i];
+      const float x2 = kKContig ? v[i].z : reinterpret_cast<const float *>(&v[2])[i], x3 = kKContig ? v[i].w : reinterpret_cast<const float *>(&v[3])[i];
+      top[i] = fmaxf(fmaxf(top[i], fabsf(x0)), fabsf(x1));
+      top[i] = fmaxf(fmaxf(top[i], fabsf(x2)), fabsf(x3));
+      asm volatile("" : "+v"(top[i]));             // now: done later, it would keep the values in registers that the next tile is loaded to
+    }
+  }
+  // largest of each row over the BK/4 lanes that its products are spread over
+  __device__ inline void row_tops(const float (&top)[kRows], float (&of_row)[kRows]) const {
+    constexpr int kNext = kKContig ? 1 : kWave / (BK / 4);
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) {
+      of_row[i] = top[i];
+#pragma unroll
+      for (int m = kNext; m < kNext * (BK / 4); m <<= 1) of_row[i] = fmaxf(of_row[i], __shfl_xor(of_row[i], m, kWave));
+    }
+  }
+  __device__ inline int tile_row(int i) const { return kKContig ? x0 + i * kRowStep : x0 + i; }
+  // the staged values times their rows' scales as fp16 parts into the two planes at `plane`
+  __device__ inline void store_halves(const float4 (&v)[kVecs], char *plane, const float (&scale)[kRows]) const {
+    static_assert(BK == 16, "two chunks per row");
+    if (T != 128 && !active) return;
+    const float *f = reinterpret_cast<const float *>(v);
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) {
+      uint2 p[2];
+      halve2(f[kKContig ? i * 4 : i], f[kKContig ? i * 4 + 1 : 4 + i], scale[i], p[0].x, p[1].x);
+      halve2(f[kKContig ? i * 4 + 2 : 8 + i], f[kKContig ? i * 4 + 3 : 12 + i], scale[i], p[0].y, p[1].y);
+      const int at = lds_offset(tile_row(i), k_in / 8) + (k_in & 4) * 2;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) *reinterpret_cast<uint2 *>(plane + q * (T * 32) + at) = p[q];
+    }
   }
   // cuts the staged values into the three planes at `plane` (T rows each), their signs flipped if `flip` is the sign bit
   template <bool kFlip>
@@ -296,12 +362,6 @@ struct Sums {
 #pragma unroll
         for (int r = 0; r < 16; ++r) { acc[i][j][r] = 0.f; total[i][j][r] = 0.f; }
   }
-  __device__ inline void negate_total() {
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-#pragma unroll
-      for (int j = 0; j < NB; ++j) total[i][j] = 0.f - total[i][j];
-  }
   __device__ inline void flush() {
 #pragma unroll
     for (int i = 0; i < NB; ++i)
@@ -316,12 +376,11 @@ struct Sums {
 #pragma unroll
     for (int i = 0; i < NB; ++i)
 #pragma unroll
-      for (int j = 0; j < NB; ++j) acc[i][j] = 0.f - acc[i][j];
-  }
-  // End of a run of a sum whose every second run is accumulated with the opposite sign (`odd`: this was one).
-  __device__ inline void turn(bool odd) {
-    if (!kTwoLevel || odd) negate();               // the next run, or the total, wants the other sign
-    if (kTwoLevel) flush();
+      for (int j = 0; j < NB; ++j) {
+        // opaque, so that it stays where it is: the compiler would negate ahead of the branch around it, every other step
+        asm volatile("" : "+v"(acc[i][j]));
+        acc[i][j] = 0.f - acc[i][j];
+      }
   }
   // The finished sum; flush() first if there are two levels.
   __device__ inline float value(int i, int j, int r) const { return kTwoLevel ? total[i][j][r] : acc[i][j][r]; }
@@ -335,18 +394,56 @@ struct Sums {
         for (int r = 0; r < 16; ++r) any = __builtin_fmaf(value(i, j, r), 0.f, any);
     return any == 0.f;
   }
+  // adds what store() left in the matrix, a block's sixteen values at a time
+  __device__ inline void add_stored(const GemmArgs &g, int z, int m_wave, int n_wave) {
+    const int lane = threadIdx.x & (kWave - 1);
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        int row0 = m_wave + i * 32 + (lane >> 5) * 4;
+        asm volatile("" : "+v"(row0));             // the addresses are made here: ahead of the loop around this they would all be kept
+        const float *C = g.C + (long long)z * g.c_slice + min(n_wave + j * 32 + (lane & 31), g.N - 1);
+        float old[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) old[r] = C[(long long)min(row0 + (r >> 2) * 8 + (r & 3), g.M - 1) * g.c_rs];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] += old[r];
+      }
+  }
   // element r of a 32x32 block sits at row (r/4)*8 + (lane/32)*4 + r%4, column lane%32
   __device__ inline void store(const GemmArgs &g, int z, int m_wave, int n_wave) const {
     const int lane = threadIdx.x & (kWave - 1);
     float *C = g.C + (long long)z * g.c_slice;
+    // a block inside the matrix: no comparisons, addresses by addition
+    const auto inside = [&](auto put) {
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        float *row = C + (long long)(m_wave + i * 32 + (lane >> 5) * 4) * g.c_rs + n_wave + (lane & 31);
+        asm volatile("" : "+v"(row));              // see add_stored
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+#pragma unroll
+          for (int j = 0; j < NB; ++j) put(row + j * 32, value(i, j, r));
+          row += (r & 3) == 3 ? 5 * g.c_rs : g.c_rs;
+        }
+      }
+    };
+    if (m_wave + NB * 32 <= g.M && n_wave + NB * 32 <= g.N) {     // uniform per wave
+      if (g.stream) inside([](float *p, float v) { __builtin_nontemporal_store(v, p); });
+      else inside([](float *p, float v) { *p = v; });
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < NB; ++i)
 #pragma unroll
       for (int j = 0; j < NB; ++j) {
         const int col = n_wave + j * 32 + (lane & 31);
+        int row0 = m_wave + i * 32 + (lane >> 5) * 4;
+        asm volatile("" : "+v"(row0));             // see add_stored
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int row = m_wave + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+          const int row = row0 + (r >> 2) * 8 + (r & 3);
           if (row < g.M && col < g.N) C[(long long)row * g.c_rs + col] = value(i, j, r);
         }
       }
@@ -437,23 +534,22 @@ struct SplitStage {
   OpB ob;
   float4 va[2][OpA::kVecs], vb[2][OpB::kVecs];    // two tiles under way
   char *to;
-  uint32_t flips, flip;                           // the sign bit for threads that stage A; what the current run flips
+  uint32_t flip;                                  // the sign bit for threads that stage A, in every second tile
   __device__ inline void start(const GemmArgs &g, const Place<T> &at, char *lds) {
     const float *A = g.A + (unsigned long long)at.first * g.a_ks, *B = g.B + (unsigned long long)at.first * g.b_ks;
     if constexpr (kShared) {
       constexpr int n = Operand<T, BK, false>::kTotal;
       const bool second = threadIdx.x / n == 1;   // threads past the second operand's units: idle
       to = lds + (second ? kOperandBytes : 0);
-      flips = second ? 0u : 0x80000000u;
+      flip = second || !at.sign ? 0u : 0x80000000u;
       oa.start(second ? B : A, 1, second ? g.b_ks : g.a_ks, second ? at.n0 : at.m0, second ? g.N : g.M,
                second ? threadIdx.x - n : threadIdx.x, at.klen, g);
     } else {
       to = lds;
-      flips = 0x80000000u;
+      flip = at.sign ? 0x80000000u : 0u;
       oa.start(A, g.a_xs, g.a_ks, at.m0, g.M, threadIdx.x, at.klen, g);
       ob.start(B, g.b_xs, g.b_ks, at.n0, g.N, threadIdx.x ^ (kBlock / 2), at.klen, g);
     }
-    flip = at.sign ? 0u : flips;                  // the first run turns it
   }
   template <int kSet>
   __device__ inline void load(uint32_t whole, uint32_t rest, const GemmArgs &g) {
@@ -466,16 +562,14 @@ struct SplitStage {
     oa.blank(va[kSet], k0, klen);
     if constexpr (!kShared) ob.blank(vb[kSet], k0, klen);
   }
-  // k0: the tile's first product, in order; A is negated in every second run, in the first one if at.sign is 1
   template <int kSet>
-  __device__ inline void store(int buf, int k0, uint32_t &odd) {
-    if (k0 % kRun == 0) flip ^= flips;            // uniform
+  __device__ inline void store(int buf, uint32_t &odd) {
     oa.template store_split<true>(va[kSet], to + buf, flip, odd);
     if constexpr (!kShared) ob.template store_split<false>(vb[kSet], to + buf + kOperandBytes, 0u, odd);
   }
 };
 
-template <int T, bool kAKContig, bool kBKContig, bool kTwoLevel>
+template <int T, bool kAKContig, bool kBKContig>
 __global__ __launch_bounds__(kBlock, 2) void k_gemm_split(const GemmArgs g) {
   constexpr int NB = T / 64, BK = 16;
   constexpr int kPlane = T * 32, kBuffer = 6 * kPlane;      // bytes: one bf16 plane of one operand; both operands' planes
@@ -488,7 +582,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_split(const GemmArgs g) {
   const int ra = lds_offset(m_wave + (lane & 31), lane >> 5), rb = 3 * kPlane + lds_offset(n_wave + (lane & 31), lane >> 5);
   const uint32_t whole = BK / g.blk_len, rest = BK - whole * g.blk_len;
   const int klen = at.klen;
-  Sums<NB, kTwoLevel> sums;
+  Sums<NB, false> sums;
   sums.clear();
   uint32_t odd = 0;
   if (klen > 0) {
@@ -497,7 +591,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_split(const GemmArgs g) {
     stage.template load<0>(whole, rest, g);
     stage.template load<1>(whole, rest, g);
     stage.template blank<0>(0, klen);
-    stage.template store<0>(0, 0, odd);
+    stage.template store<0>(0, odd);
     stage.template load<0>(whole, rest, g);
     // multiplies the tile at k0 out of buffer kBuf and, unless it is the last, cuts the next one into the other buffer and requests
     // the third one on
@@ -514,7 +608,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_split(const GemmArgs g) {
           a[q][i] = *reinterpret_cast<const bf16x8 *>(lds + kBuf * kBuffer + q * kPlane + i * 1024 + ra);
           b[q][i] = *reinterpret_cast<const bf16x8 *>(lds + kBuf * kBuffer + q * kPlane + i * 1024 + rb);
         }
-      if constexpr (!kLast) stage.template store<kNext>(kNext * kBuffer, k0 + BK, odd);
+      if constexpr (!kLast) stage.template store<kNext>(kNext * kBuffer, odd);
       // smallest terms first
       constexpr int qa[6] = {2, 0, 1, 1, 0, 0}, qb[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
@@ -525,7 +619,6 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_split(const GemmArgs g) {
           for (int j = 0; j < NB; ++j)
             sums.acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[qa[p]][i], b[qb[p]][j], sums.acc[i][j], 0, 0, 0);
       if constexpr (!kLast) stage.template load<kNext>(whole, rest, g);
-      if ((k0 + BK) % kRun == 0) sums.turn((k0 / kRun & 1) != 0);
     };
     const std::integral_constant<int, 0> even{};
     const std::integral_constant<int, 1> uneven{};
@@ -547,30 +640,279 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_split(const GemmArgs g) {
         step(even, std::true_type{}, k0);
       }
     }
-    // the run the loop ended in, if it is not complete (a complete one has been turned), and the sign of the whole
-    const int tiles = (klen + BK - 1) / BK;
-    const bool odd_run = (tiles % (kRun / BK) != 0 || !kTwoLevel) && (tiles / (kRun / BK) & 1);
-    if (kTwoLevel) {
-      if (odd_run) sums.negate();
-      sums.flush();
-      if (at.sign) sums.negate_total();
-    } else if (odd_run != (at.sign != 0)) {
-      sums.negate();
-    }
+    if (at.sign) sums.negate();
   }
   // An infinity or NaN among the operands (times a zero part it makes a NaN of what should stay infinite), a product or sum past
   // fp32's range (its parts' products can be infinities of both signs, a NaN again): either leaves a sum that is not
   // finite.  Then, or if an operand was too small for three bf16 parts, the tile is computed again with the fp32 instruction.
   if (__syncthreads_or((odd & 0xFFFFu) != 0 || !sums.finite()))
-    multiply_f32<T, kPlainBK, kAKContig, kBKContig, kTwoLevel>(g, at, reinterpret_cast<float *>(lds), sums);
+    multiply_f32<T, kPlainBK, kAKContig, kBKContig, false>(g, at, reinterpret_cast<float *>(lds), sums);
   sums.store(g, at.z, at.m0 + m_wave, at.n0 + n_wave);
+}
+
+// Largest of a wave's values, none of them negative, in its last lane.
+__device__ inline float wave_max(float v) {
+  const auto step = [&](auto ctrl) {                 // lanes that a step does not reach take a zero
+    v = fmaxf(v, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), decltype(ctrl)::value, 0xF, 0xF, true)));
+  };
+  step(std::integral_constant<int, 0x111>{});        // row_shr 1, 2, 4, 8: the last lane of every 16
+  step(std::integral_constant<int, 0x112>{});
+  step(std::integral_constant<int, 0x114>{});
+  step(std::integral_constant<int, 0x118>{});
+  step(std::integral_constant<int, 0x142>{});        // row_bcast 15 and 31
+  step(std::integral_constant<int, 0x143>{});
+  return v;
+}
+
+// Staging of both operands' tiles as planes of fp16 parts, and their rows' scales.
+template <int T, int BK, bool kAKContig, bool kBKContig>
+struct HalfStage {
+  static constexpr int kOperandBytes = 2 * T * 32;
+  static constexpr bool kShared = !kAKContig && !kBKContig;
+  using OpA = Operand<T, BK, kAKContig>;
+  using OpB = Operand<T, BK, kBKContig>;
+  OpA oa;
+  OpB ob;
+  float4 va[2][OpA::kVecs], vb[2][OpB::kVecs];    // the two halves of the tile under way
+  float top_a[OpA::kRows], top_b[OpB::kRows];
+  char *to;
+  float scale_a[OpA::kRows], scale_b[OpB::kRows]; // of the rows that the thread stages; A's take the sign of the current run
+  bool second;                                    // kShared: the thread stages B
+  // the products from k0 on, `len` of them
+  __device__ inline void start(const GemmArgs &g, const Place<T> &at, char *lds, int k0, int len) {
+    const float *A = g.A + (unsigned long long)(at.first + k0) * g.a_ks, *B = g.B + (unsigned long long)(at.first + k0) * g.b_ks;
+    if constexpr (kShared) {
+      constexpr int n = Operand<T, BK, false>::kTotal;
+      second = threadIdx.x / n == 1;              // threads past the second operand's units: idle
+      to = lds + (second ? kOperandBytes : 0);
+      oa.start(second ? B : A, 1, second ? g.b_ks : g.a_ks, second ? at.n0 : at.m0, second ? g.N : g.M,
+               second ? threadIdx.x - n : threadIdx.x, len, g);
+    } else {
+      second = false;
+      to = lds;
+      oa.start(A, g.a_xs, g.a_ks, at.m0, g.M, threadIdx.x, len, g);
+      ob.start(B, g.b_xs, g.b_ks, at.n0, g.N, threadIdx.x ^ (kBlock / 2), len, g);
+    }
+  }
+  __device__ inline void clear() {
+#pragma unroll
+    for (int i = 0; i < OpA::kRows; ++i) top_a[i] = 0.f;
+#pragma unroll
+    for (int i = 0; i < OpB::kRows; ++i) top_b[i] = 0.f;
+  }
+  // The rows' scales from the magnitudes of the first tile: a row's largest is brought to 1 .. 2, a row of zeros is taken for one with
+  // the tile's largest.  `tops`: LDS, a float per wave and operand; `inverse`: LDS, where each operand's T rows leave 1 / scale.
+  __device__ inline void set_scales(float (*tops)[kBlock / kWave], float (*inverse)[T], bool negative) {
+    float row_a[OpA::kRows], row_b[OpB::kRows], ta = 0.f, tb = 0.f;
+    oa.largest(va[0], top_a);
+    oa.largest(va[1], top_a);
+    oa.row_tops(top_a, row_a);
+#pragma unroll
+    for (int i = 0; i < OpA::kRows; ++i) ta = fmaxf(ta, row_a[i]);
+    if constexpr (!kShared) {
+      ob.largest(vb[0], top_b);
+      ob.largest(vb[1], top_b);
+      ob.row_tops(top_b, row_b);
+#pragma unroll
+      for (int i = 0; i < OpB::kRows; ++i) tb = fmaxf(tb, row_b[i]);
+    } else {
+      tb = second ? ta : 0.f;
+      ta = second ? 0.f : ta;
+    }
+    ta = wave_max(ta);
+    tb = wave_max(tb);
+    const int wave = threadIdx.x / kWave;
+    if ((threadIdx.x & (kWave - 1)) == kWave - 1) { tops[0][wave] = ta; tops[1][wave] = tb; }
+    __syncthreads();
+    ta = tb = 0.f;
+#pragma unroll
+    for (int w = 0; w < kBlock / kWave; ++w) { ta = fmaxf(ta, tops[0][w]); tb = fmaxf(tb, tops[1][w]); }
+    const auto exponent = [](float row, float tile) { // of a power of two within 2^-60 .. 2^60, so that the product of two is one as well
+      const float t = row == 0.f ? tile : row;
+      return t == 0.f ? 0 : min(max(127 - (int)(__float_as_uint(t) >> 23), -60), 60);
+    };
+    const auto power = [](int e) { return __uint_as_float((uint32_t)(127 + e) << 23); };
+    const bool flip = negative && !(kShared && second);
+#pragma unroll
+    for (int i = 0; i < OpA::kRows; ++i) {
+      const int e = exponent(row_a[i], kShared && second ? tb : ta);
+      scale_a[i] = flip ? -power(e) : power(e);
+      if (oa.k_in == 0 && (T == 128 || oa.active)) inverse[kShared && second ? 1 : 0][oa.tile_row(i)] = power(-e);
+    }
+    if constexpr (!kShared) {
+#pragma unroll
+      for (int i = 0; i < OpB::kRows; ++i) {
+        const int e = exponent(row_b[i], tb);
+        scale_b[i] = power(e);
+        if (ob.k_in == 0 && (T == 128 || ob.active)) inverse[1][ob.tile_row(i)] = power(-e);
+      }
+    }
+  }
+  template <int kSet>
+  __device__ inline void load(uint32_t whole, uint32_t rest, const GemmArgs &g) {
+    oa.load(va[kSet], whole, rest, g);
+    if constexpr (!kShared) ob.load(vb[kSet], whole, rest, g);
+  }
+  template <int kSet>
+  __device__ inline void blank(int k0, int klen) {
+    if (k0 + BK <= klen) return;                  // uniform
+    oa.blank(va[kSet], k0, klen);
+    if constexpr (!kShared) ob.blank(vb[kSet], k0, klen);
+  }
+  __device__ inline void turn() {                 // A's sign is the other one from here on
+#pragma unroll
+    for (int i = 0; i < OpA::kRows; ++i)
+      if (!(kShared && second)) scale_a[i] = -scale_a[i];
+  }
+  template <int kSet>
+  __device__ inline void store(int buf) {
+    oa.largest(va[kSet], top_a);
+    oa.store_halves(va[kSet], to + buf, scale_a);
+    if constexpr (!kShared) {
+      ob.largest(vb[kSet], top_b);
+      ob.store_halves(vb[kSet], to + buf + kOperandBytes, scale_b);
+    }
+  }
+  // Is one of the thread's rows, whose first products were zeros, so small that its parts hold less than fp32 does?
+  __device__ inline bool too_small() const {
+    float row_a[OpA::kRows];
+    oa.row_tops(top_a, row_a);
+    bool small = false;
+#pragma unroll
+    for (int i = 0; i < OpA::kRows; ++i) small |= row_a[i] != 0.f && row_a[i] * fabsf(scale_a[i]) < 0x1p-10f;
+    small &= T == 128 || oa.active;
+    if constexpr (!kShared) {
+      float row_b[OpB::kRows];
+      ob.row_tops(top_b, row_b);
+      bool small_b = false;
+#pragma unroll
+      for (int i = 0; i < OpB::kRows; ++i) small_b |= row_b[i] != 0.f && row_b[i] * scale_b[i] < 0x1p-10f;
+      small |= small_b && (T == 128 || ob.active);
+    }
+    return small;
+  }
+};
+
+template <int T, bool kAKContig, bool kBKContig, bool kDeep>
+__global__ __launch_bounds__(kBlock, 2) void k_gemm_halves(const GemmArgs g) {
+  constexpr int NB = T / 64, BK = 16, kStep = 2 * BK;
+  constexpr int kPlane = T * 32, kHalf = 4 * kPlane, kBuffer = 2 * kHalf;   // bytes: one part of one operand's half tile; both operands'; both halves
+  constexpr int kPlainBytes = plain_floats<T, kPlainBK, kAKContig, kBKContig>() * 4;
+  __shared__ __align__(16) char lds[2 * kBuffer > kPlainBytes ? 2 * kBuffer : kPlainBytes];
+  __shared__ float tops[2][kBlock / kWave];
+  __shared__ __align__(16) float inverse[2][T];
+  const Place<T> at(g, std::false_type{});
+  if (!at.ok) return;                             // uniform per workgroup
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int m_wave = (wave >> 1) * (T / 2), n_wave = (wave & 1) * (T / 2);
+  const int ra = lds_offset(m_wave + (lane & 31), lane >> 5), rb = 2 * kPlane + lds_offset(n_wave + (lane & 31), lane >> 5);
+  const uint32_t whole = BK / g.blk_len, rest = BK - whole * g.blk_len;
+  Sums<NB, false> sums, cross;                    // of the products of leading parts, and of those with one rest, times 2^11
+  sums.clear();
+  cross.clear();
+  bool again = false;
+  HalfStage<T, BK, kAKContig, kBKContig> stage;
+  stage.clear();
+  for (int done = 0; done < at.klen; done += kDeepRun) {       // once, unless kDeep
+    const int len = kDeep ? min(at.klen - done, kDeepRun) : at.klen;
+    stage.start(g, at, lds, done, len);
+    const auto load = [&]() {
+      stage.template load<0>(whole, rest, g);
+      stage.template load<1>(whole, rest, g);
+    };
+    load();
+    stage.template blank<0>(0, len);
+    stage.template blank<1>(BK, len);
+    if (done == 0) stage.set_scales(tops, inverse, at.sign != 0);
+    else __syncthreads();                         // the last tile has been read
+    stage.template store<0>(0);
+    stage.template store<1>(kHalf);
+    load();
+    // multiplies a half of the tile in buffer `buf` and, unless it is the last tile, cuts that half of the next one into the other buffer
+    auto half = [&](auto half_c, auto last_c, int buf) {
+      constexpr int kSet = decltype(half_c)::value;
+      f16x8 a[2][NB], b[2][NB];
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+          a[q][i] = *reinterpret_cast<const f16x8 *>(lds + buf + (kSet * kHalf + q * kPlane + i * 1024) + ra);
+          b[q][i] = *reinterpret_cast<const f16x8 *>(lds + buf + (kSet * kHalf + q * kPlane + i * 1024) + rb);
+        }
+      if constexpr (!decltype(last_c)::value) stage.template store<kSet>((buf ^ kBuffer) + kSet * kHalf);
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+          cross.acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[1][i], b[0][j], cross.acc[i][j], 0, 0, 0);
+          sums.acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0][i], b[0][j], sums.acc[i][j], 0, 0, 0);
+        }
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+          cross.acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0][i], b[1][j], cross.acc[i][j], 0, 0, 0);
+    };
+    const std::integral_constant<int, 0> first{};
+    const std::integral_constant<int, 1> second{};
+    int k0 = 0, buf = 0;
+    for (; k0 + kStep < len; k0 += kStep, buf ^= kBuffer) {
+      stage.template blank<0>(k0 + kStep, len);
+      stage.template blank<1>(k0 + kStep + BK, len);
+      __syncthreads();                            // the current tile is written, the other buffer fully read
+      const bool turn = (k0 + kStep) % kRun == 0;
+      if (turn) stage.turn();
+      half(first, std::false_type{}, buf);
+      half(second, std::false_type{}, buf);
+      load();
+      if (turn) { sums.negate(); cross.negate(); }
+    }
+    __syncthreads();
+    half(first, std::true_type{}, buf);
+    if (k0 + BK < len) half(second, std::true_type{}, buf);
+    // both sums to one, in the operands' own scale and with their sign
+    const bool odd = ((len - 1) / kRun & 1) != 0;
+    if (kDeep && odd) stage.turn();
+    const float sign = odd != (at.sign != 0) ? -1.f : 1.f;
+    float of_col[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) of_col[j] = sign * inverse[1][n_wave + j * 32 + (lane & 31)];
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float4 of_row = *reinterpret_cast<const float4 *>(&inverse[0][m_wave + i * 32 + q * 8 + (lane >> 5) * 4]);
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {           // (adding zero: a sum of zeros is +0)
+            const float v = __builtin_fmaf(cross.acc[i][j][q * 4 + r], 0x1p-11f, sums.acc[i][j][q * 4 + r]);
+            sums.acc[i][j][q * 4 + r] = __builtin_fmaf(v, reinterpret_cast<const float *>(&of_row)[r] * of_col[j], 0.f);
+          }
+      }
+    if (!kDeep) break;
+    if (done > 0) sums.add_stored(g, at.z, at.m0 + m_wave, at.n0 + n_wave);
+    if (done + len < at.klen) {
+      sums.store(g, at.z, at.m0 + m_wave, at.n0 + n_wave);
+      sums.clear();
+      cross.clear();
+    }
+  }
+  again = at.klen > 0 && stage.too_small();
+  if (__syncthreads_or(again || !sums.finite())) {
+    Sums<NB, kDeep> plain;
+    multiply_f32<T, kPlainBK, kAKContig, kBKContig, kDeep>(g, at, reinterpret_cast<float *>(lds), plain);
+    plain.store(g, at.z, at.m0 + m_wave, at.n0 + n_wave);
+  } else {
+    sums.store(g, at.z, at.m0 + m_wave, at.n0 + n_wave);
+  }
 }
 
 inline long long tiles_of(long long n, int T) { return (n + T - 1) / T; }
 
 // Tile edge.  The large tile reads and cuts each operand element half as often; the small one gives four times as many
 // workgroups and less padding.  Measured, large / small tile:
-//   split, 16384 x 3200 x 256: 172 / 242 us (g_pool), 159 / 313 us (dW); 5003 x 540 x 300, 200 and 240 large tiles: 24.1 / 26.5 us
+//   thirds, 16384 x 3200 x 256: 172 / 242 us (g_pool), 159 / 313 us (dW); 5003 x 540 x 300, 200 and 240 large tiles: 24.1 / 26.5 us
 //   and 24.0 / 26.6 us; 4096 x 416 x 256, 128 large tiles: 34.9 / 32.6 us for the two g_pool of a model step
 //   fp32 (results do not depend on the choice), 16384 x 3200 x 256, 16 shards: 311 / 321 us; 5003 x 540 x 300 with 7 shards, where
 //   the large tile multiplies 21 % more padding: 36 / 30 us
@@ -607,6 +949,10 @@ des_status_t launch(GemmArgs g, int slices, long long depth, int kid, hipStream_
   const dim3 grid((unsigned)(blocks < (long long)kGridRow ? blocks : kGridRow), (unsigned)((blocks + kGridRow - 1) / kGridRow));
   const dim3 block(kBlock);
   const bool two = depth > kTwoLevelDepth;
+  // Results that the caches cannot keep until they are read are stored past them, so that they do not take the place of the operands: forward /
+  // g_pool of 16384 x 3200 x 256 (268 and 210 MB) 272 / 147 -> 261 / 131 us, 131072 x 320 x 64 (537 and 168 MB) 137 / 54 -> 118 / 53.
+  // Smaller ones are slower to read afterwards: a layer of 4096 x 416 x 256 (33 MB of partials) 52 -> 54 us in all.
+  g.stream = (long long)g.M * g.N * slices * 4 > kStreamBytes;
   ProfScope ps(kid, s);
   // k tiles of the fp32 product: 16 deep for large tiles of one level, so that four workgroups fit a CU (116 registers; 32 deep
   // 137 and three; 65536 x 416 x 256: 118 / 142 us), and shards whose depth is no multiple of 32 have no half tile of padding
@@ -615,7 +961,10 @@ des_status_t launch(GemmArgs g, int slices, long long depth, int kid, hipStream_
 #define DES_GEMM(EDGE, TWO)                                                                                               \
   do {                                                                                                                    \
     constexpr int kBK = EDGE == 128 && !TWO ? 16 : kPlainBK;                                                              \
-    if constexpr (kSplit) hipLaunchKernelGGL((k_gemm_split<EDGE, kAKContig, kBKContig, TWO>), grid, block, 0, s, g);       \
+    if constexpr (kSplit) {                                                                                               \
+      if (depth >= kHalvesDepth) hipLaunchKernelGGL((k_gemm_halves<EDGE, kAKContig, kBKContig, TWO>), grid, block, 0, s, g); \
+      else if constexpr (!TWO) hipLaunchKernelGGL((k_gemm_split<EDGE, kAKContig, kBKContig>), grid, block, 0, s, g);        \
+    }                                                                                                                     \
     else hipLaunchKernelGGL((k_gemm_f32<EDGE, kBK, kAKContig, kBKContig, TWO>), grid, block, 0, s, g);                     \
   } while (0)
   if (T == 128) { if (two) DES_GEMM(128, true); else DES_GEMM(128, false); }

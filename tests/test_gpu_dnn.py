@@ -206,6 +206,34 @@ def test_dnn_gradients_of_operands_with_subnormal_parts(des, exponent):
         assert np.linalg.norm(got.astype(np.float64) * 2.0 ** (-40 - exponent) - ref) <= bound * np.linalg.norm(ref)
 
 
+@pytest.mark.parametrize("B,F,D,H", [
+    (300, 7, 8, 60), (300, 7, 8, 64), (300, 7, 8, 68), (300, 7, 8, 96),            # g_pool: thirds, halves, a last half tile, none
+    (300, 7, 8, 1024), (300, 7, 8, 1028), (300, 7, 8, 1536),                       # ... one stretch, several of 512 and a short one, whole ones
+    (2000, 130, 16, 132), (2000, 130, 16, 1060),                                   # large tiles
+    (1024, 7, 8, 36), (16400, 3, 4, 36), (17000, 30, 64, 260),                     # dW: slices of 64, 1040 and 1072 samples or more
+])
+def test_dnn_gradients_of_rows_of_any_magnitude(des, B, F, D, H):
+    """Operand rows from 1 down to 2^-90 of each other, in both products; rows that begin with zeros, and go on small; single elements
+    that are 2^20 times their row's others.  Bound, for each output by the sum of its products' magnitudes: a product from halves is off by
+    up to 3 * 2^-24 (two cuts and the term left out), one in fp32 by 2^-24, and each of at most min(k, 1024) roundings of a partial sum,
+    which is no larger than that sum, by 2^-24 (to nearest; the 16-bit instruction's by 2^-23, one per 16 products); taken as independent,
+    six standard deviations.  Without the rests of a cut it would be 2^-12 per product."""
+    rng = np.random.default_rng(B + H)
+    pool, W, dY = synth.dnn_layer_inputs(B + H, B, F, D, H)
+    pool = pool.reshape(B, F * D)
+    dY *= np.exp2(-rng.integers(0, 30, (B, 1)) * rng.integers(0, 4, (B, 1))).astype(np.float32)   # a sample's gradients
+    pool *= np.exp2(-rng.integers(0, 20, (1, F * D))).astype(np.float32)                          # a column's embeddings
+    W *= np.exp2(-rng.integers(0, 20, (F * D, 1))).astype(np.float32)
+    dY[5, :40], pool[:40, 3], W[2, :40] = 0, 0, 0
+    dY[6, 34], W[4, 35] = dY[6, 34] * np.float32(2 ** 20), W[4, 35] * np.float32(2 ** 20)
+    dY[7, :40] = 0
+    dY[7, 40:] = rng.standard_normal(H - 40).astype(np.float32) * np.float32(2.0 ** -80) if H > 40 else 0     # (products stay normal)
+    x, w, g = pool.astype(np.float64), W.astype(np.float64), dY.astype(np.float64)
+    g_pool, dW = _gradients(des, __import__("torch"), pool.reshape(B, F, D), W, dY)
+    for got, ref, mag, k, what in ((g_pool, g @ w.T, np.abs(g) @ np.abs(w.T), H, "g_pool"), (dW, x.T @ g, np.abs(x.T) @ np.abs(g), B, "dW")):
+        assert np.all(np.abs(got - ref) <= 6 * 2.0 ** -24 * np.sqrt(9 + min(k, 1024)) * mag), what
+
+
 @pytest.mark.parametrize("B", [1, 2, 3])
 def test_dnn_weight_gradient_of_a_few_samples(des, B):
     """One product is rounded once, to nearest; the sum of two or three loses no more than fp32 arithmetic does (2-norm errors 3.1e-8
