@@ -45,8 +45,8 @@
 //
 // The 16-bit instructions drop the bits of their sum that do not fit, towards minus infinity; over many runs that adds up (a mean
 // of -3e-7 of the results' root mean square at 124623 samples), so every second run of kRun products is accumulated with the
-// opposite sign.  A single run, or a last one without a partner, keeps its part: tiles and slices begin with alternating
-// signs, so that it has both signs in what a row of the table adds up over the samples and in a slice sum (of thirds, mean error /
+// opposite sign.  A single run, or a last one without a partner, keeps its part: tiles (in k_gemm_halves blocks of 64 x 64 outputs) and
+// slices begin with alternating signs, so that it has both signs in what a row of the table adds up over the samples and in a slice sum (of thirds, mean error /
 // root mean square, all beginning with plus and so: g_pool of 128 hidden units, 4096 samples, -9.4e-9 and -2e-11; dW of 2048
 // samples -2.9e-8 and 3e-10.  Signs by rows instead of tiles cost g_pool 4 %).
 //
@@ -322,12 +322,11 @@ struct Place {
   bool ok;
   // kInTurn: g.in_turn may be set (the division tells in short products)
   template <bool kInTurn>
-  __device__ inline Place(const GemmArgs &g, std::integral_constant<bool, kInTurn>) {
+  __device__ inline Place(const GemmArgs &g, uint32_t block, std::integral_constant<bool, kInTurn>) {
     // Every die takes contiguous runs of tiles.  They are numbered n first, then m inside a group of m_group tiles, then
     // the slice, then the group: tiles that read the same rows of A follow each other, a slice's part of B is used by a
     // whole group, and the slices of a group (in the forward product: the shards' columns of the same rows of A) are
     // done together, before the next rows.
-    const uint32_t block = kInTurn ? blockIdx.y * kGridRow + blockIdx.x : blockIdx.x;
     const uint32_t total = (uint32_t)g.tiles_m * g.tiles_n * g.slices, turn = block / kXcds;
     uint32_t round = 0;
     if (kInTurn && g.in_turn) round = turn / g.die_run;
@@ -514,7 +513,7 @@ __device__ inline void multiply_f32(const GemmArgs &g, const Place<T> &at, float
 template <int T, int BK, bool kAKContig, bool kBKContig, bool kTwoLevel>
 __global__ __launch_bounds__(kBlock, 2) void k_gemm_f32(const GemmArgs g) {
   __shared__ __align__(16) float lds[plain_floats<T, BK, kAKContig, kBKContig>()];
-  const Place<T> at(g, std::true_type{});
+  const Place<T> at(g, blockIdx.y * kGridRow + blockIdx.x, std::true_type{});
   if (!at.ok) return;                             // uniform per workgroup
   Sums<T / 64, kTwoLevel> sums;
   multiply_f32<T, BK, kAKContig, kBKContig, kTwoLevel>(g, at, lds, sums);
@@ -569,13 +568,14 @@ struct SplitStage {
   }
 };
 
+constexpr int at_least(int bytes, int other) { return bytes > other ? bytes : other; }
 template <int T, bool kAKContig, bool kBKContig>
-__global__ __launch_bounds__(kBlock, 2) void k_gemm_split(const GemmArgs g) {
+constexpr int split_bytes() { return at_least(2 * 6 * T * 32, plain_floats<T, kPlainBK, kAKContig, kBKContig>() * 4); }
+template <int T, bool kAKContig, bool kBKContig>
+__device__ inline void multiply_split(const GemmArgs &g, uint32_t block, char *lds) {
   constexpr int NB = T / 64, BK = 16;
   constexpr int kPlane = T * 32, kBuffer = 6 * kPlane;      // bytes: one bf16 plane of one operand; both operands' planes
-  constexpr int kPlainBytes = plain_floats<T, kPlainBK, kAKContig, kBKContig>() * 4;
-  __shared__ __align__(16) char lds[2 * kBuffer > kPlainBytes ? 2 * kBuffer : kPlainBytes];
-  const Place<T> at(g, std::false_type{});
+  const Place<T> at(g, block, std::false_type{});
   if (!at.ok) return;                             // uniform per workgroup
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int m_wave = (wave >> 1) * (T / 2), n_wave = (wave & 1) * (T / 2);
@@ -701,8 +701,9 @@ struct HalfStage {
     for (int i = 0; i < OpB::kRows; ++i) top_b[i] = 0.f;
   }
   // The rows' scales from the magnitudes of the first tile: a row's largest is brought to 1 .. 2, a row of zeros is taken for one with
-  // the tile's largest.  `tops`: LDS, a float per wave and operand; `inverse`: LDS, where each operand's T rows leave 1 / scale.
-  __device__ inline void set_scales(float (*tops)[kBlock / kWave], float (*inverse)[T], bool negative) {
+  // the tile's largest.  Every second 64 rows (and slice of A) take the other sign, so that a result does not depend on the tile's size.
+  // `tops`: LDS, a float per wave and operand; `inverse`: LDS, where each operand's T rows leave 1 / scale.
+  __device__ inline void set_scales(float (*tops)[kBlock / kWave], float (*inverse)[T], const Place<T> &at) {
     float row_a[OpA::kRows], row_b[OpB::kRows], ta = 0.f, tb = 0.f;
     oa.largest(va[0], top_a);
     oa.largest(va[1], top_a);
@@ -731,20 +732,21 @@ struct HalfStage {
       const float t = row == 0.f ? tile : row;
       return t == 0.f ? 0 : min(max(127 - (int)(__float_as_uint(t) >> 23), -60), 60);
     };
-    const auto power = [](int e) { return __uint_as_float((uint32_t)(127 + e) << 23); };
-    const bool flip = negative && !(kShared && second);
+    const auto power = [](int e, int sign) { return __uint_as_float((uint32_t)(127 + e) << 23 | (uint32_t)sign << 31); };
+    const bool b_too = kShared && second;
 #pragma unroll
     for (int i = 0; i < OpA::kRows; ++i) {
-      const int e = exponent(row_a[i], kShared && second ? tb : ta);
-      scale_a[i] = flip ? -power(e) : power(e);
-      if (oa.k_in == 0 && (T == 128 || oa.active)) inverse[kShared && second ? 1 : 0][oa.tile_row(i)] = power(-e);
+      const int e = exponent(row_a[i], b_too ? tb : ta), row = oa.tile_row(i);
+      const int sign = ((b_too ? (at.n0 + row) >> 6 : (at.m0 + row) >> 6 ^ at.z) & 1);
+      scale_a[i] = power(e, sign);
+      if (oa.k_in == 0 && (T == 128 || oa.active)) inverse[b_too ? 1 : 0][row] = power(-e, sign);
     }
     if constexpr (!kShared) {
 #pragma unroll
       for (int i = 0; i < OpB::kRows; ++i) {
-        const int e = exponent(row_b[i], tb);
-        scale_b[i] = power(e);
-        if (ob.k_in == 0 && (T == 128 || ob.active)) inverse[1][ob.tile_row(i)] = power(-e);
+        const int e = exponent(row_b[i], tb), row = ob.tile_row(i), sign = (at.n0 + row) >> 6 & 1;
+        scale_b[i] = power(e, sign);
+        if (ob.k_in == 0 && (T == 128 || ob.active)) inverse[1][row] = power(-e, sign);
       }
     }
   }
@@ -786,22 +788,23 @@ struct HalfStage {
       ob.row_tops(top_b, row_b);
       bool small_b = false;
 #pragma unroll
-      for (int i = 0; i < OpB::kRows; ++i) small_b |= row_b[i] != 0.f && row_b[i] * scale_b[i] < 0x1p-10f;
+      for (int i = 0; i < OpB::kRows; ++i) small_b |= row_b[i] != 0.f && row_b[i] * fabsf(scale_b[i]) < 0x1p-10f;
       small |= small_b && (T == 128 || ob.active);
     }
     return small;
   }
 };
 
+template <int T, bool kAKContig, bool kBKContig>
+constexpr int halves_bytes() { return at_least(2 * 8 * T * 32, plain_floats<T, kPlainBK, kAKContig, kBKContig>() * 4) + 2 * T * 4 + 2 * (kBlock / kWave) * 4; }
 template <int T, bool kAKContig, bool kBKContig, bool kDeep>
-__global__ __launch_bounds__(kBlock, 2) void k_gemm_halves(const GemmArgs g) {
+__device__ inline void multiply_halves(const GemmArgs &g, uint32_t block, char *lds) {
   constexpr int NB = T / 64, BK = 16, kStep = 2 * BK;
   constexpr int kPlane = T * 32, kHalf = 4 * kPlane, kBuffer = 2 * kHalf;   // bytes: one part of one operand's half tile; both operands'; both halves
-  constexpr int kPlainBytes = plain_floats<T, kPlainBK, kAKContig, kBKContig>() * 4;
-  __shared__ __align__(16) char lds[2 * kBuffer > kPlainBytes ? 2 * kBuffer : kPlainBytes];
-  __shared__ float tops[2][kBlock / kWave];
-  __shared__ __align__(16) float inverse[2][T];
-  const Place<T> at(g, std::false_type{});
+  char *const behind = lds + at_least(2 * kBuffer, plain_floats<T, kPlainBK, kAKContig, kBKContig>() * 4);
+  float(*const inverse)[T] = reinterpret_cast<float(*)[T]>(behind);
+  float(*const tops)[kBlock / kWave] = reinterpret_cast<float(*)[kBlock / kWave]>(behind + 2 * T * 4);
+  const Place<T> at(g, block, std::false_type{});
   if (!at.ok) return;                             // uniform per workgroup
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int m_wave = (wave >> 1) * (T / 2), n_wave = (wave & 1) * (T / 2);
@@ -823,7 +826,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_halves(const GemmArgs g) {
     load();
     stage.template blank<0>(0, len);
     stage.template blank<1>(BK, len);
-    if (done == 0) stage.set_scales(tops, inverse, at.sign != 0);
+    if (done == 0) stage.set_scales(tops, inverse, at);
     else __syncthreads();                         // the last tile has been read
     stage.template store<0>(0);
     stage.template store<1>(kHalf);
@@ -873,7 +876,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_halves(const GemmArgs g) {
     // both sums to one, in the operands' own scale and with their sign
     const bool odd = ((len - 1) / kRun & 1) != 0;
     if (kDeep && odd) stage.turn();
-    const float sign = odd != (at.sign != 0) ? -1.f : 1.f;
+    const float sign = odd ? -1.f : 1.f;
     float of_col[NB];
 #pragma unroll
     for (int j = 0; j < NB; ++j) of_col[j] = sign * inverse[1][n_wave + j * 32 + (lane & 31)];
@@ -908,6 +911,34 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_halves(const GemmArgs g) {
   }
 }
 
+template <int T, bool kAKContig, bool kBKContig>
+__global__ __launch_bounds__(kBlock, 2) void k_gemm_split(const GemmArgs g) {
+  __shared__ __align__(16) char lds[split_bytes<T, kAKContig, kBKContig>()];
+  multiply_split<T, kAKContig, kBKContig>(g, blockIdx.x, lds);
+}
+
+template <int T, bool kAKContig, bool kBKContig, bool kDeep>
+__global__ __launch_bounds__(kBlock, 2) void k_gemm_halves(const GemmArgs g) {
+  __shared__ __align__(16) char lds[halves_bytes<T, kAKContig, kBKContig>()];
+  multiply_halves<T, kAKContig, kBKContig, kDeep>(g, blockIdx.x, lds);
+}
+
+// Both gradient products in one launch, where each by itself leaves most of the chip idle: the first n_w workgroups take dW's tiles,
+// the others g_pool's.  kWHalves, kGHalves: from fp16 halves, else from bf16 thirds.
+template <int T, bool kWHalves, bool kGHalves, bool kWDeep = false>
+__global__ __launch_bounds__(kBlock, 2) void k_gemm_both(const GemmArgs w, const GemmArgs g, uint32_t n_w) {
+  constexpr int kWBytes = kWHalves ? halves_bytes<T, false, false>() : split_bytes<T, false, false>();
+  constexpr int kGBytes = kGHalves ? halves_bytes<T, true, true>() : split_bytes<T, true, true>();
+  __shared__ __align__(16) char lds[at_least(kWBytes, kGBytes)];
+  if (blockIdx.x < n_w) {
+    if constexpr (kWHalves) multiply_halves<T, false, false, kWDeep>(w, blockIdx.x, lds);
+    else multiply_split<T, false, false>(w, blockIdx.x, lds);
+  } else {
+    if constexpr (kGHalves) multiply_halves<T, true, true, false>(g, blockIdx.x - n_w, lds);
+    else multiply_split<T, true, true>(g, blockIdx.x - n_w, lds);
+  }
+}
+
 inline long long tiles_of(long long n, int T) { return (n + T - 1) / T; }
 
 // Tile edge.  The large tile reads and cuts each operand element half as often; the small one gives four times as many
@@ -916,10 +947,11 @@ inline long long tiles_of(long long n, int T) { return (n + T - 1) / T; }
 //   and 24.0 / 26.6 us; 4096 x 416 x 256, 128 large tiles: 34.9 / 32.6 us for the two g_pool of a model step
 //   fp32 (results do not depend on the choice), 16384 x 3200 x 256, 16 shards: 311 / 321 us; 5003 x 540 x 300 with 7 shards, where
 //   the large tile multiplies 21 % more padding: 36 / 30 us
+constexpr long long kFewLarge = 192;
 template <bool kSplit>
 inline int tile_edge(long long M, long long N, long long slices) {
   const long long large = tiles_of(M, 128) * tiles_of(N, 128) * slices, small = tiles_of(M, 64) * tiles_of(N, 64) * slices;
-  if (kSplit) return large >= 192 ? 128 : 64;
+  if (kSplit) return large >= kFewLarge ? 128 : 64;
   return large >= 384 && large * 40 <= small * 11 ? 128 : 64;    // at most 10 % more area
 }
 
@@ -933,9 +965,15 @@ inline int forward_run(int D) {
 }
 
 // `depth`: products summed per output element of one slice; above kTwoLevelDepth the two-level kernel runs.
-template <bool kSplit, bool kAKContig, bool kBKContig>
-des_status_t launch(GemmArgs g, int slices, long long depth, int kid, hipStream_t s) {
-  const int T = tile_edge<kSplit>(g.M, g.N, slices);
+struct Product {
+  GemmArgs g;
+  int T;                              // tile edge
+  long long blocks, depth;
+  bool two;
+};
+template <bool kSplit>
+des_status_t plan(GemmArgs g, int slices, long long depth, Product &p, int T = 0) {
+  if (T == 0) T = tile_edge<kSplit>(g.M, g.N, slices);
   g.tiles_m = (int)tiles_of(g.M, T); g.tiles_n = (int)tiles_of(g.N, T); g.slices = slices;
   if (g.m_group <= 0 || g.m_group > g.tiles_m) g.m_group = g.tiles_m;
   const long long total = (long long)g.tiles_m * g.tiles_n * slices;
@@ -946,13 +984,19 @@ des_status_t launch(GemmArgs g, int slices, long long depth, int kid, hipStream_
   // A product whose operands and result fit the card has fewer than 2^23 large tiles; only the forward product, whose tiles
   // are small where it has few columns and whose shards come on top, may need further rows.
   if (kSplit && blocks > (long long)kGridRow) return DES_ERR_INVALID_ARG;
-  const dim3 grid((unsigned)(blocks < (long long)kGridRow ? blocks : kGridRow), (unsigned)((blocks + kGridRow - 1) / kGridRow));
-  const dim3 block(kBlock);
-  const bool two = depth > kTwoLevelDepth;
   // Results that the caches cannot keep until they are read are stored past them, so that they do not take the place of the operands: forward /
   // g_pool of 16384 x 3200 x 256 (268 and 210 MB) 272 / 147 -> 261 / 131 us, 131072 x 320 x 64 (537 and 168 MB) 137 / 54 -> 118 / 53.
   // Smaller ones are slower to read afterwards: a layer of 4096 x 416 x 256 (33 MB of partials) 52 -> 54 us in all.
   g.stream = (long long)g.M * g.N * slices * 4 > kStreamBytes;
+  p = Product{g, T, blocks, depth, depth > kTwoLevelDepth};
+  return DES_OK;
+}
+
+template <bool kSplit, bool kAKContig, bool kBKContig>
+des_status_t launch(const Product &p, int kid, hipStream_t s) {
+  const GemmArgs &g = p.g;
+  const dim3 grid((unsigned)(p.blocks < (long long)kGridRow ? p.blocks : kGridRow), (unsigned)((p.blocks + kGridRow - 1) / kGridRow));
+  const dim3 block(kBlock);
   ProfScope ps(kid, s);
   // k tiles of the fp32 product: 16 deep for large tiles of one level, so that four workgroups fit a CU (116 registers; 32 deep
   // 137 and three; 65536 x 416 x 256: 118 / 142 us), and shards whose depth is no multiple of 32 have no half tile of padding
@@ -962,15 +1006,45 @@ des_status_t launch(GemmArgs g, int slices, long long depth, int kid, hipStream_
   do {                                                                                                                    \
     constexpr int kBK = EDGE == 128 && !TWO ? 16 : kPlainBK;                                                              \
     if constexpr (kSplit) {                                                                                               \
-      if (depth >= kHalvesDepth) hipLaunchKernelGGL((k_gemm_halves<EDGE, kAKContig, kBKContig, TWO>), grid, block, 0, s, g); \
+      if (p.depth >= kHalvesDepth) hipLaunchKernelGGL((k_gemm_halves<EDGE, kAKContig, kBKContig, TWO>), grid, block, 0, s, g); \
       else if constexpr (!TWO) hipLaunchKernelGGL((k_gemm_split<EDGE, kAKContig, kBKContig>), grid, block, 0, s, g);        \
     }                                                                                                                     \
     else hipLaunchKernelGGL((k_gemm_f32<EDGE, kBK, kAKContig, kBKContig, TWO>), grid, block, 0, s, g);                     \
   } while (0)
-  if (T == 128) { if (two) DES_GEMM(128, true); else DES_GEMM(128, false); }
-  else          { if (two) DES_GEMM(64, true);  else DES_GEMM(64, false); }
+  if (p.T == 128) { if (p.two) DES_GEMM(128, true); else DES_GEMM(128, false); }
+  else            { if (p.two) DES_GEMM(64, true);  else DES_GEMM(64, false); }
 #undef DES_GEMM
   return hipGetLastError() == hipSuccess ? DES_OK : DES_ERR_DEVICE;
+}
+
+// Both gradient products at once: they share operands, and neither fills the chip's last round by itself.  Their tiles have to be alike;
+// where the rule above chose differently for each, it is asked for both together.  Both at once / one after the other, 5003 x 540 x 300
+// 32 / 45 us, 109 x 816 x 300 15 / 19, 64 x 32 x 16 6.2 / 9.7, 4096 x 416 x 256 25 / 32, 2048 x 6400 x 256 80 / 85, 9000 x 540 x 300 54 / 55;
+// dW of several stretches per slice, whose few workgroups run long: 16384 x 3200 x 256 245 / 273, 65536 x 416 x 256 221 / 265.  Not with a tile that
+// doubles one's padding: 131072 x 320 x 64 with large tiles for dW too 438 / 354.
+bool launch_both(Product &w, Product &g, hipStream_t s) {
+  if (g.two) return false;
+  const bool wh = w.depth >= kHalvesDepth, gh = g.depth >= kHalvesDepth;
+  if (w.T != g.T) {
+    if (!wh || !gh) return false;
+    const auto tiles = [](const Product &p, int T) { return tiles_of(p.g.M, T) * tiles_of(p.g.N, T) * p.g.slices; };
+    const int T = tiles(w, 128) + tiles(g, 128) >= kFewLarge ? 128 : 64;
+    const Product &small = w.T < g.T ? w : g;
+    if (T == 128 && tiles(small, 128) * 4 > tiles(small, 64) * 5 / 4) return false;      // a quarter of padding more
+    if (plan<true>(w.g, w.g.slices, w.depth, w, T) != DES_OK || plan<true>(g.g, 1, g.depth, g, T) != DES_OK) return false;
+  }
+  if (((w.T == 128 || w.two) && !(wh && gh)) || w.blocks + g.blocks > (long long)kGridRow) return false;
+  const dim3 grid((unsigned)(w.blocks + g.blocks)), block(kBlock);
+  const uint32_t n_w = (uint32_t)w.blocks;
+  ProfScope ps(KID_DNN_BOTH, s);
+  if (w.two && w.T == 128) hipLaunchKernelGGL((k_gemm_both<128, true, true, true>), grid, block, 0, s, w.g, g.g, n_w);
+  else if (w.two) hipLaunchKernelGGL((k_gemm_both<64, true, true, true>), grid, block, 0, s, w.g, g.g, n_w);
+  else if (w.T == 128) hipLaunchKernelGGL((k_gemm_both<128, true, true>), grid, block, 0, s, w.g, g.g, n_w);
+  else if (wh && gh) hipLaunchKernelGGL((k_gemm_both<64, true, true>), grid, block, 0, s, w.g, g.g, n_w);
+  else if (wh) hipLaunchKernelGGL((k_gemm_both<64, true, false>), grid, block, 0, s, w.g, g.g, n_w);
+  else if (gh) hipLaunchKernelGGL((k_gemm_both<64, false, true>), grid, block, 0, s, w.g, g.g, n_w);
+  else hipLaunchKernelGGL((k_gemm_both<64, false, false>), grid, block, 0, s, w.g, g.g, n_w);
+  return true;
 }
 
 bool al16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
@@ -1004,7 +1078,9 @@ des_status_t des_dnn_partial_forward(const float *pool, const float *W, int64_t 
   g.in_turn = shallow;
   g.run = forward_run(D);
   g.k_shift = g.blk_len = D; g.blk_stride = (uint32_t)(K < F ? K : F) * D; g.k_limit = g.k_max = (uint32_t)F * D;
-  return launch<false, true, false>(g, K, depth, KID_DNN_FORWARD, (hipStream_t)stream);
+  Product p;
+  const des_status_t st = plan<false>(g, K, depth, p);
+  return st != DES_OK ? st : launch<false, true, false>(p, KID_DNN_FORWARD, (hipStream_t)stream);
 }
 
 des_status_t des_dnn_backward_bytes(int64_t B, int32_t F, int32_t D, int32_t H, size_t *workspace_bytes) {
@@ -1025,6 +1101,7 @@ des_status_t des_dnn_backward(const float *pool, const float *W, const float *dY
     return DES_ERR_INVALID_ARG;
   hipStream_t s = (hipStream_t)stream;
   const long long FD = (long long)F * D;
+  Product pg, pw;
   if (g_pool) {                                   // g_pool[B, F*D] = dY[B,H] x W^T: B(k=h, n=j) = W[j*H + h]
     GemmArgs g;
     g.A = dY; g.a_xs = H; g.a_ks = 1;
@@ -1033,8 +1110,9 @@ des_status_t des_dnn_backward(const float *pool, const float *W, const float *dY
     g.m_group = 0;
     g.run = kRun;
     g.k_shift = 0; g.blk_len = g.blk_stride = g.k_limit = g.k_max = H;
-    des_status_t st = launch<true, true, true>(g, 1, H, KID_DNN_GPOOL, s);
+    const des_status_t st = plan<true>(g, 1, H, pg);
     if (st != DES_OK) return st;
+    if (!dW) return launch<true, true, true>(pg, KID_DNN_GPOOL, s);
   }
   if (dW) {                                       // dW[F*D, H] = pool^T x dY, split over slices of samples
     const long long tiles = tiles_of(FD, 128) * tiles_of(H, 128);
@@ -1053,7 +1131,10 @@ des_status_t des_dnn_backward(const float *pool, const float *W, const float *dY
     }
     long long chunk = ((B + Z - 1) / Z + kMinSlice - 1) / kMinSlice * kMinSlice;
     Z = (int)((B + chunk - 1) / chunk);
-    if (Z > 1 && (!workspace || workspace_bytes < (size_t)Z * FD * H * sizeof(float))) return DES_ERR_WORKSPACE;
+    if (Z > 1 && (!workspace || workspace_bytes < (size_t)Z * FD * H * sizeof(float))) {
+      if (g_pool) (void)launch<true, true, true>(pg, KID_DNN_GPOOL, s);      // which needs none
+      return DES_ERR_WORKSPACE;
+    }
     GemmArgs g;
     g.A = pool; g.a_xs = 1; g.a_ks = (uint32_t)FD;          // A(m=j, k=b) = pool[b*FD + j]
     g.B = dY; g.b_xs = 1; g.b_ks = H;
@@ -1063,9 +1144,13 @@ des_status_t des_dnn_backward(const float *pool, const float *W, const float *dY
     g.k_shift = g.k_max = (uint32_t)chunk; g.blk_len = g.blk_stride = 1u << 31; g.k_limit = (uint32_t)B;
     // one or two samples: a single rounding is closer than the split's truncated sums (2-norm error 2.5e-8 against 3.5e-8 and
     // 3.1e-8 against 3.3e-8; from three samples on the split is, 3.2e-8 against 3.6e-8)
-    des_status_t st = B < 3 ? launch<false, false, false>(g, Z, chunk, KID_DNN_DW, s)
-                            : launch<true, false, false>(g, Z, chunk, KID_DNN_DW, s);
+    des_status_t st = B < 3 ? plan<false>(g, Z, chunk, pw) : plan<true>(g, Z, chunk, pw);
     if (st != DES_OK) return st;
+    if (!g_pool || B < 3 || !launch_both(pw, pg, s)) {
+      if (g_pool) st = launch<true, true, true>(pg, KID_DNN_GPOOL, s);
+      if (st == DES_OK) st = B < 3 ? launch<false, false, false>(pw, KID_DNN_DW, s) : launch<true, false, false>(pw, KID_DNN_DW, s);
+      if (st != DES_OK) return st;
+    }
     if (Z > 1) return des_aggregate_partials((const float *)workspace, Z, FD * H, dW, stream);
   }
   return DES_OK;

@@ -646,7 +646,7 @@ const char *kKernelNames[KID_COUNT] = {
     "backward_long_final", "backward_export", "fill",
     "dnn_forward", "dnn_grad_pool", "dnn_grad_weights",
     "aggregate_bias_act", "column_partials", "column_final", "output_unit", "dense_update", "table_migrate",
-    "cross_partial", "cross_apply", "cross_backward", "ceiling_gather", "ceiling_update", "backward_update"};
+    "cross_partial", "cross_apply", "cross_backward", "ceiling_gather", "ceiling_update", "backward_update", "dnn_gradients"};
 }  // namespace
 
 des_status_t blocking_status(des_table *t) {

@@ -234,6 +234,28 @@ def test_dnn_gradients_of_rows_of_any_magnitude(des, B, F, D, H):
         assert np.all(np.abs(got - ref) <= 6 * 2.0 ** -24 * np.sqrt(9 + min(k, 1024)) * mag), what
 
 
+@pytest.mark.parametrize("B,F,D,H", [
+    (64, 4, 8, 16), (64, 4, 8, 64), (1100, 4, 8, 32), (1100, 4, 8, 64),      # small tiles; thirds or halves for either product
+    (2000, 60, 16, 256),                                                    # large tiles for dW alone, small ones for g_pool alone
+    (5003, 27, 20, 300), (16640, 26, 16, 256), (20000, 50, 32, 256),        # large tiles; dW of several stretches per slice
+    (131072, 2, 16, 64), (1100, 100, 32, 16),                               # two launches
+    (2, 7, 8, 64),
+])
+def test_dnn_gradients_together_and_alone(des, B, F, D, H):
+    """Both gradients from one launch have the bits that each has from a launch of its own."""
+    import torch
+    pool, W, dY = (dev(a, torch) for a in synth.dnn_layer_inputs(B, B, F, D, H))
+    ws = torch.empty(des.dnn_backward_bytes(B, F, D, H), dtype=torch.uint8, device="cuda")
+    out = [torch.full((B, F, D), float("nan"), device="cuda") for _ in range(2)], [torch.full((F * D, H), float("nan"), device="cuda") for _ in range(2)]
+    des.dnn_backward(pool, W, dY, out[0][0], out[1][0], ws)
+    des.dnn_backward(pool, W, dY, out[0][1], None, None)
+    des.dnn_backward(pool, W, dY, None, out[1][1], ws)
+    assert torch.equal(out[0][0], out[0][1]) and torch.equal(out[1][0], out[1][1])
+    rows = slice(0, 500)
+    assert_close(out[0][0].view(B, -1)[rows].cpu().numpy(), (dY[rows].double() @ W.double().t()).cpu().numpy(), "g_pool")
+    assert_close(out[1][0][rows].cpu().numpy(), (pool.view(B, -1)[:, rows].double().t() @ dY.double()).cpu().numpy(), "dW")
+
+
 @pytest.mark.parametrize("B", [1, 2, 3])
 def test_dnn_weight_gradient_of_a_few_samples(des, B):
     """One product is rounded once, to nearest; the sum of two or three loses no more than fp32 arithmetic does (2-norm errors 3.1e-8
