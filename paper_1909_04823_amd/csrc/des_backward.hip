@@ -208,7 +208,6 @@ __device__ inline void heads_bookkeeping(const BwdArgs &a, uint32_t n_uniq) {
   a.ctrl->n_chunks = 0;
   a.ctrl->n_multi = 0;
   a.ctrl->n_groups = 0;
-  if (a.n_uniq_out) *a.n_uniq_out = n_uniq;
 }
 
 __global__ void k_heads_finish(const BwdArgs a, const uint32_t *total) { heads_bookkeeping(a, *total); }
@@ -787,6 +786,7 @@ __device__ inline void update_short(const BwdArgs &a, uint32_t block, uint32_t b
   const int sub = (int)(gid % G);
   const int64_t ngroups = (int64_t)blocks * kBlock / G;
   const int64_t n_uniq = a.ctrl->n_uniq;
+  if (gid == 0 && a.n_uniq_out) *a.n_uniq_out = n_uniq;
   // grid-stride over the segments: the grid is sized on the host for the chip, not for the (device-side) segment count.
   // The bounds, row and first payload of the lane group's next segment are requested while the current one is being
   // worked on, which takes one of the two dependent round trips per segment off the critical path.
@@ -1348,8 +1348,6 @@ void batch_args(des_table *t, const des_batch_t *b, const int32_t *rows, const L
   a.chunk_owner = (int32_t *)(ws + L.chunk_owner); a.partials = (double *)(ws + L.partials);
 }
 
-__global__ void k_report_n_uniq(const Ctrl *ctrl, int64_t *out) { *out = ctrl->n_uniq; }
-
 }  // namespace
 
 size_t backward_ws_bytes(int D, int64_t max_n) { return layout_for(D, max_n).total; }
@@ -1397,7 +1395,6 @@ des_status_t backward_launch(des_table *t, const des_batch_t *b, const int32_t *
   if (prepared) {
     set_sorted_keys(a, (uint32_t *)(ws + (t->prep.side ? L.key_b : L.key_a)));
     a.pay_sorted = (uint32_t *)(ws + (t->prep.side ? L.pay_b : L.pay_a));
-    if (io->n_uniq_out) hipLaunchKernelGGL(k_report_n_uniq, dim3(1), dim3(1), 0, s, t->ctrl, io->n_uniq_out);
   } else {
     sort_stage(t, a, L, s);
   }

@@ -295,8 +295,12 @@ __device__ inline unsigned long long same_digit(uint32_t d, int bits, unsigned l
 // per lane, with the last start before each of them.  Without the pass that wrote (row, bag) pairs first the kernels up to here
 // take, at 3.7e5 / 1.0e6 / 8.2e6 / 1.05e8 entries, 33 -> 29, 48 -> 37, 169 -> 145 and 2204 -> 1863 us.  (Three waves per SIMD instead
 // of four, which spill 16 bytes: 46 against 43 us at 8.0e6.)
+// kCounts: `offsets` holds the tiles' counts as they are and every workgroup adds up what it needs of them by itself, which while they
+// are few is shorter than the launch of a scan: backward pass of 1.6e4 entries, three passes of 8 bits 68 -> 60 us, two of 9 and 8 61 -> 53;
+// 6.4e4 (63 tiles) 70 -> 65 and, of 9 and 8, 61 -> 62; 1.3e5 81 -> 81 and 64 -> 71.
+constexpr int kCountsAdded = 16384, kCountFlight = 16;   // counts; tiles whose counts a thread requests together
 constexpr uint32_t kWideTile = 16;       // bags per entry of a tile from which a binary search per entry takes no longer than walking them
-template <typename KeyT, bool kHasPayload, int kItems, int kBits, bool kCsr>
+template <typename KeyT, bool kHasPayload, int kItems, int kBits, bool kCsr, bool kCounts>
 __global__ __launch_bounds__(kBlock, kItems == kSortItems ? 4 : 8) void k_radix_scatter(const KeyT *__restrict__ keys_in,
                                                            const uint32_t *__restrict__ pay_in,
                                                            KeyT *__restrict__ keys_out, uint32_t *__restrict__ pay_out,
@@ -334,6 +338,38 @@ __global__ __launch_bounds__(kBlock, kItems == kSortItems ? 4 : 8) void k_radix_
     if (kHasPayload && !kCsr) pay[r] = live ? pay_in[idx] : 0u;
   }
   if (kCsr && threadIdx.x < kWords * 2) starts[threadIdx.x] = 0u;
+  // kCounts: the sums over the tiles before this one and over all of them, of two digits per thread and as many tiles at a time as there are
+  // threads for
+  uint32_t *const before = dig_base, *const all = gofs;   // written in earnest only behind the ranking
+  if (kCounts) {
+    const int pairs = radix / 2 > 0 ? radix / 2 : 1, groups = kBlock / pairs, grp = threadIdx.x / pairs, d = (int)(threadIdx.x % pairs) * 2;
+    for (int i = threadIdx.x; i < radix; i += kBlock) before[i] = all[i] = 0u;
+    uint32_t sum[2] = {0u, 0u}, lower[2] = {0u, 0u};
+    const auto row = [&](int t) { return *reinterpret_cast<const uint2 *>(offsets + (size_t)t * radix + d); };
+    if (grp < groups) {
+      for (int t0 = grp; t0 < (int)gridDim.x; t0 += groups * kCountFlight) {
+        uint2 c[kCountFlight];
+#pragma unroll
+        for (int j = 0; j < kCountFlight; ++j) c[j] = row(min(t0 + j * groups, (int)gridDim.x - 1));
+#pragma unroll
+        for (int j = 0; j < kCountFlight; ++j) {
+          const int t = t0 + j * groups;
+          if (t >= (int)gridDim.x) c[j] = make_uint2(0u, 0u);
+          sum[0] += c[j].x; sum[1] += c[j].y;
+          if (t < (int)tile_no) { lower[0] += c[j].x; lower[1] += c[j].y; }
+        }
+      }
+    }
+    __syncthreads();
+    if (grp < groups) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        atomicAdd(&before[d + j], lower[j]);
+        atomicAdd(&all[d + j], sum[j]);
+      }
+    }
+    __syncthreads();
+  }
   // two digits per thread (kMaxRadix <= 2 * kBlock): the tile's offset inside the digit and the digit's total
   static_assert(kMaxRadix <= 2 * kBlock, "two digits per thread");
   uint32_t in_digit[2] = {0u, 0u};
@@ -342,8 +378,8 @@ __global__ __launch_bounds__(kBlock, kItems == kSortItems ? 4 : 8) void k_radix_
   for (int j = 0; j < 2; ++j) {
     const int d = threadIdx.x * 2 + j;
     if (d < radix) {
-      in_digit[j] = offsets[(size_t)tile_no * radix + d];
-      tot[j] = (unsigned long long)totals[d] << 32;
+      in_digit[j] = kCounts ? before[d] : offsets[(size_t)tile_no * radix + d];
+      tot[j] = (unsigned long long)(kCounts ? all[d] : totals[d]) << 32;
 #pragma unroll
       for (int w = 0; w < kWavesPerBlock; ++w) cnt[w][d] = 0;
     }
@@ -512,7 +548,8 @@ int radix_sort(SortBuffers buf, int64_t n, int bits, uint32_t *hist, uint32_t *s
       if (from_csr) hipLaunchKernelGGL((k_radix_hist<KeyT, kItems, true>), dim3(nblocks), dim3(kBlock), 0, s, kin, n, shift, b, hist, *csr);
       else hipLaunchKernelGGL((k_radix_hist<KeyT, kItems, false>), dim3(nblocks), dim3(kBlock), 0, s, kin, n, shift, b, hist, SortCsr{});
     }
-    {
+    const bool counts = kItems == kFewSortItems && nblocks <= kCountsAdded >> b;
+    if (!counts) {
       ProfScope ps(kid_scan, s);
       const dim3 grid(((1 << b) + kScanDigits - 1) / kScanDigits, (nblocks + kScanStretch - 1) / kScanStretch);
       if (grid.y > 1)
@@ -525,14 +562,19 @@ int radix_sort(SortBuffers buf, int64_t n, int bits, uint32_t *hist, uint32_t *s
         hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(kBlock), 0, s, kin, pin, kout, pout, n, shift, b, hist, totals,
                            from_csr ? *csr : SortCsr{});
       };
-      const auto of_width = [&](auto first) {
-        constexpr bool kCsr = decltype(first)::value;
-        if (b == 9) scatter(k_radix_scatter<KeyT, kHasPayload, kItems, 9, kCsr>);
-        else if (b == 8) scatter(k_radix_scatter<KeyT, kHasPayload, kItems, 8, kCsr>);
-        else if (b == 7) scatter(k_radix_scatter<KeyT, kHasPayload, kItems, 7, kCsr>);
-        else scatter(k_radix_scatter<KeyT, kHasPayload, kItems, 0, kCsr>);
+      const auto of_width = [&](auto first, auto raw) {
+        constexpr bool kCsr = decltype(first)::value, kCounts = decltype(raw)::value;
+        if (b == 9) scatter(k_radix_scatter<KeyT, kHasPayload, kItems, 9, kCsr, kCounts>);
+        else if (b == 8) scatter(k_radix_scatter<KeyT, kHasPayload, kItems, 8, kCsr, kCounts>);
+        else if (b == 7) scatter(k_radix_scatter<KeyT, kHasPayload, kItems, 7, kCsr, kCounts>);
+        else scatter(k_radix_scatter<KeyT, kHasPayload, kItems, 0, kCsr, kCounts>);
       };
-      if (from_csr) of_width(std::true_type{}); else of_width(std::false_type{});
+      const auto of_first = [&](auto raw) { if (from_csr) of_width(std::true_type{}, raw); else of_width(std::false_type{}, raw); };
+      if constexpr (kItems == kFewSortItems) {
+        if (counts) of_first(std::true_type{}); else of_first(std::false_type{});
+      } else {
+        of_first(std::false_type{});
+      }
     }
     KeyT *tk = kin; kin = kout; kout = tk;
     uint32_t *tp = pin; pin = pout; pout = tp;

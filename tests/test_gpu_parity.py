@@ -976,6 +976,16 @@ def test_row_sort_at_its_size_limits(oracle, des, n, B, F, capacity, vals):
         p.close()
 
 
+@pytest.mark.parametrize("n,capacity,vals", [
+    (32768, 200000, True), (32769, 200000, False),      # two passes of 9 bits: 32 tiles, whose counts the scatter adds up, and 33
+    (65536, 60000, False), (65537, 60000, True),        # two of 8: 64 tiles and 65
+    (131072, 120, True), (131073, 120, False),          # one of 7: 128 tiles and 129
+    (40000, 1, True), (40000, 100000, False),           # one bit; passes of 9 and 8, of which the second adds up
+])
+def test_row_sort_at_the_limits_of_its_counts(oracle, des, n, capacity, vals):
+    test_row_sort_at_its_size_limits(oracle, des, n, 300, 5, capacity, vals)
+
+
 @pytest.mark.parametrize("n", [1, 63, 65, 1025, 4096, 4097, 6145, 300000])     # one workgroup numbers up to 4096 entries
 @pytest.mark.parametrize("with_values", [False, True])
 def test_insert_numbers_new_rows_at_its_size_limits(oracle, des, n, with_values):
