@@ -348,6 +348,104 @@ __global__ __launch_bounds__(kBlock) void k_chunk_owner(const BwdArgs a) {
   }
 }
 
+// Step (3) and the split for up to kFewHeads sorted entries in one workgroup, whose waves see all of it in LDS: one launch instead of
+// four.  What it does is bound by a few dependent accesses; the passes over tiles, by the 2 to 4 us that each launch takes.  A thread's
+// stretch of entries is consecutive for the count; the heads are then written with consecutive threads, eight loads in flight each
+// (one at a time, 16 in a row would take what the launches took).  Backward pass with the four launches / this one: of 5e3 entries
+// 49 / 39 us (1e5 rows, D = 16) and 58 / 45 (3e6, 32), of 9e3 52 / 43 and 59 / 50, of 1.6e4 53 / 45 and 59 / 52, with all entries on
+// 40 rows 45 / 31.  The starts of twice the entries would not fit a workgroup's static 64 KB with the rest.
+constexpr int64_t kFewHeads = 16384;
+constexpr int kFewHeadsBlock = 1024, kFewHeadsItems = kFewHeads / kFewHeadsBlock;
+__global__ __launch_bounds__(kFewHeadsBlock) void k_heads_few(const BwdArgs a) {
+  constexpr int kWaves = kFewHeadsBlock / kWave, kItems = kFewHeadsItems;
+  static_assert(kFewHeads <= 1 << 16, "positions in 16 bits");
+  __shared__ uint16_t start[kFewHeads];
+  __shared__ uint32_t sums[kWaves];
+  __shared__ uint32_t n_long, n_chunks, n_multi, n_groups, end;
+  const int n = (int)a.n, base = threadIdx.x * kItems, lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  uint32_t key[kItems];
+  if (base + kItems <= n) {
+#pragma unroll
+    for (int q = 0; q < kItems / 4; ++q) {
+      const uint4 v = *reinterpret_cast<const uint4 *>(a.key_sorted + base + q * 4);
+      key[q * 4] = v.x; key[q * 4 + 1] = v.y; key[q * 4 + 2] = v.z; key[q * 4 + 3] = v.w;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) key[i] = base + i < n ? a.key_sorted[base + i] : a.missing;
+  }
+  uint32_t prev = base > 0 && base < n ? a.key_sorted[base - 1] : 0xFFFFFFFFu;
+  if (threadIdx.x == 0) { n_long = n_chunks = n_multi = n_groups = 0; end = (uint32_t)n; }
+  uint32_t heads = 0, with_row = 0;
+  bool flag[kItems];
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) {                       // entries past the end read as without a row
+    flag[i] = key[i] != a.missing && (base + i == 0 || key[i] != prev);
+    heads += flag[i] ? 1u : 0u;
+    with_row += key[i] != a.missing ? 1u : 0u;
+    prev = key[i];
+  }
+  const uint32_t inc = wave_incl_scan_u32(heads);
+  if (lane == kWave - 1) sums[wave] = inc;
+  __syncthreads();
+  uint32_t u = inc - heads, U = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    const uint32_t x = sums[w];
+    if (w < wave) u += x;
+    U += x;
+  }
+#pragma unroll
+  for (int i = 0; i < kItems; ++i)
+    if (flag[i]) start[u++] = (uint16_t)(base + i);
+  if (with_row < kItems && base < n) atomicMin(&end, (uint32_t)(base + with_row));   // entries without a row sort last
+  __syncthreads();
+  const uint32_t stop = end;
+  constexpr int kAtOnce = 8;                               // heads whose loads a thread has in flight
+  for (uint32_t j0 = threadIdx.x; j0 < U; j0 += kAtOnce * kFewHeadsBlock) {
+    uint32_t at[kAtOnce], row[kAtOnce], pay[kAtOnce];
+#pragma unroll
+    for (int i = 0; i < kAtOnce; ++i) {
+      const uint32_t j = j0 + i * kFewHeadsBlock;
+      at[i] = start[j < U ? j : 0];
+      row[i] = a.key_sorted[at[i]];
+      pay[i] = a.pay_sorted[at[i]];
+    }
+#pragma unroll
+    for (int i = 0; i < kAtOnce; ++i) {
+      const uint32_t j = j0 + i * kFewHeadsBlock;
+      if (j < U) {
+        a.uniq_rows[j] = (int32_t)row[i];
+        a.seg_off[j] = (int32_t)at[i];
+        a.first_pay[j] = pay[i];
+      }
+    }
+  }
+  if (threadIdx.x == 0) a.seg_off[U] = (int32_t)stop;
+  __syncthreads();                                         // the keys have been read: the lists below take their place
+  for (uint32_t j = threadIdx.x; j < U; j += kFewHeadsBlock) {
+    const uint32_t len = (j + 1 < U ? start[j + 1] : stop) - start[j];
+    if (len <= (uint32_t)kShortMax) continue;
+    const uint32_t nch = (uint32_t)chunks_of(a, len), l = atomicAdd(&n_long, 1u), c0 = atomicAdd(&n_chunks, nch);
+    a.long_seg[l] = (int32_t)j;
+    a.long_c0[l] = c0;
+    if (nch > 1) a.multi_seg[atomicAdd(&n_multi, 1u)] = (int32_t)l;
+    if (nch > kMidFan) {
+      uint32_t gi = atomicAdd(&n_groups, (nch + kMidFan - 1) / kMidFan);
+      for (uint32_t k = 0; k < nch; k += kMidFan) { a.group_seg[gi] = (int32_t)l; a.group_c[gi] = c0 + k; ++gi; }
+    }
+    for (uint32_t k = 0; k < nch; ++k) a.chunk_owner[c0 + k] = (int32_t)l;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    a.ctrl->n_uniq = U;
+    a.ctrl->n_long = n_long;
+    a.ctrl->n_chunks = n_chunks;
+    a.ctrl->n_multi = n_multi;
+    a.ctrl->n_groups = n_groups;
+  }
+}
+
 // Steps (1)-(3) and the split of long segments for a batch of up to kSmallSort entries, all in the LDS of one workgroup: such a
 // batch is bound by launches (14 of them at 2560 entries, about 3.5 us each), not by work.  The sort is the same stable
 // radix sort, eight bits a pass.
@@ -1308,6 +1406,11 @@ int sort_stage(des_table *t, BwdArgs &a, const Layout &L, hipStream_t s) {
                                         from_csr ? &csr : nullptr, s);
   set_sorted_keys(a, (uint32_t *)(ws + (side ? L.key_b : L.key_a)));
   a.pay_sorted = (uint32_t *)(ws + (side ? L.pay_b : L.pay_a));
+  if (n <= kFewHeads) {
+    ProfScope ps(KID_HEADS, s);
+    hipLaunchKernelGGL(k_heads_few, dim3(1), dim3(kFewHeadsBlock), 0, s, a);
+    return side;
+  }
   {
     ProfScope ps(KID_HEADS, s);
     const int64_t nb = (n + kHeadTile - 1) / kHeadTile;

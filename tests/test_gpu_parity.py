@@ -900,6 +900,17 @@ def test_merge_of_short_and_long_segments_together(oracle, des, n, D, lens, with
     test_merge_chunk_length_limits(oracle, des, n, D, lens, with_vals)
 
 
+@pytest.mark.parametrize("n,D,lens,with_vals", [
+    (16383, 8, [32, 33, 128, 129, 8193], True),              # the last stretch of the one workgroup that finds the segments is cut short
+    (16384, 16, [32, 33, 128, 129, 8192, 8193 - 500], False),   # the largest batch of that workgroup, chunks summed in groups
+    (16385, 16, [32, 33, 128, 129, 8193], False),            # one entry more: passes over tiles
+    (4099, 32, [1, 2, 3], True),
+    (16384, 4, [], False),                                   # no long segment
+])
+def test_segments_of_few_entries(oracle, des, n, D, lens, with_vals):
+    test_merge_chunk_length_limits(oracle, des, n, D, lens, with_vals)
+
+
 # ------------------------------------------------- aggregation of few partials --------------------
 @pytest.mark.parametrize("K,B", [(1, 1), (2, 1), (3, 1), (1, 2), (1, 3), (4, 1), (2, 7), (9, 5), (17, 33), (3, 16384), (3, 16385)])
 @pytest.mark.parametrize("D", [4, 8, 12, 16, 32, 36, 64, 100])
