@@ -350,8 +350,8 @@ __global__ __launch_bounds__(kBlock) void k_chunk_owner(const BwdArgs a) {
 
 // Step (3) and the split for up to kFewHeads sorted entries in one workgroup, whose waves see all of it in LDS: one launch instead of
 // four.  What it does is bound by a few dependent accesses; the passes over tiles, by the 2 to 4 us that each launch takes.  A thread's
-// stretch of entries is consecutive for the count; the heads are then written with consecutive threads, eight loads in flight each
-// (one at a time, 16 in a row would take what the launches took).  Backward pass with the four launches / this one: of 5e3 entries
+// stretch of entries is consecutive for the count; the heads are then written with consecutive threads, eight of them in flight each,
+// since up to 16 round trips in a row would be longer than the launches.  Backward pass with the four launches / this one: of 5e3 entries
 // 49 / 39 us (1e5 rows, D = 16) and 58 / 45 (3e6, 32), of 9e3 52 / 43 and 59 / 50, of 1.6e4 53 / 45 and 59 / 52, with all entries on
 // 40 rows 45 / 31.  The starts of twice the entries would not fit a workgroup's static 64 KB with the rest.
 constexpr int64_t kFewHeads = 16384;
