@@ -299,7 +299,8 @@ def run_dnn_layer(args, index):
         per = total_ms / reps
         e = {"launches_per_pass": launches / reps, "ms_per_pass": round(per, 4)}
         if name.startswith("dnn_") and per > 0:
-            e["TFLOPs"] = round(flops / (per * 1e-3) / 1e12, 2)
+            products = 2 if name == "dnn_gradients" else 1      # both gradients in one launch
+            e["TFLOPs"] = round(products * flops / (per * 1e-3) / 1e12, 2)
             e["frac_of_fp32_mfma_peak"] = round(e["TFLOPs"] / FP32_MFMA_PEAK_TFLOPS, 4)
         kernels[name] = e
     assert bool(torch.isfinite(Y).all()) and bool(torch.isfinite(dW).all())
